@@ -1013,6 +1013,13 @@ bool attn_decode_mfma_supported(const Dims &dm, int g_max) {
     return dm.bf16 && dm.D == kD && dm.Bk == kBk && g_max >= 1 && g_max <= 80;
 }
 
+// Tokens one prefill workgroup can walk: its block ids take what the KV ring leaves of the CU's 160 KB of LDS.  (The
+// ring already limits a CU to one workgroup, so the ids cost no occupancy; bounded by the 16384 tokens of a decode
+// piece, a 512-row chunk over a 32000-token prefix fell to the vector kernel and took 860 ms instead of 1.67 ms.)
+constexpr size_t kPrefillRing = (size_t)2 * 4 * 16 * 64 * 16, kLdsBytes = (size_t)160 << 10;
+constexpr int kPrefillMaxCtx = (int)((kLdsBytes - kPrefillRing) / 4) * kBk;
+int attn_prefill_max_ctx() { return kPrefillMaxCtx; }
+
 int attn_prefill_group_queries() { return kPrefillWaves * kPrefillNT * 16; }  // stacked queries one prefill workgroup holds
 
 bool attn_prefill_mfma_supported(const Dims &dm, int g_max) {
@@ -1022,13 +1029,13 @@ bool attn_prefill_mfma_supported(const Dims &dm, int g_max) {
 hipError_t launch_attn_prefill_mfma(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
                                     const AttnPlan &pl, void *out, hipStream_t st) {
     if (pl.n_items <= 0) return hipSuccess;
-    if (!pl.causal || pl.chunk > kAttnMaxChunk) return hipErrorInvalidValue;
+    if (!pl.causal || pl.chunk > kPrefillMaxCtx) return hipErrorInvalidValue;
     constexpr int NT = kPrefillNT;
     float scale_log2 = kLog2e / sqrtf((float)dm.D) * (dm.kv8 ? dm.k_scale : 1.f);
-    size_t shm = (size_t)2 * 4 * 16 * 64 * 16 + (size_t)(kAttnMaxChunk / kBk) * 4;  // two ring stages + the block ids
+    const size_t shm = kPrefillRing + (size_t)((pl.chunk + kBk - 1) / kBk) * 4;  // two ring stages + the block ids
     auto launch = [&](auto kernel, bool &attr_set) -> hipError_t {
         if (!attr_set) {
-            hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+            hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
             if (e != hipSuccess) return e;
             attr_set = true;
         }

@@ -358,11 +358,12 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
     const icarus_layer_config &c = ctx->cfg;
     if (ctx->mode != 0) return;
     const int g = c.n_q_heads / c.n_kv_heads, Hkv = c.n_kv_heads;
-    int g_max = 0;
+    int g_max = 0, longest_ctx = 0;
     for (int s = 0; s < S; ++s) {
         if (seq_rows[s] > 0 && kv_lens[s] <= 0) return;  // empty context: generic kernel writes zeros
-        if (causal && kv_lens[s] > kAttnMaxChunk) return;
+        if (causal && kv_lens[s] > attn_prefill_max_ctx()) return;
         g_max = std::max(g_max, seq_rows[s] * g);
+        longest_ctx = std::max(longest_ctx, kv_lens[s]);
     }
     if (causal ? !attn_prefill_mfma_supported(ctx->dm, g_max) : (!attn_decode_mfma_supported(ctx->dm, g_max) || g_max > kAttnGMax)) return;
     const int32_t *d = dmeta + at;
@@ -405,7 +406,7 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
         pl->seq_rows = pl->seq_row0 + S;
         pl->seq_bt = pl->seq_rows + S;
         pl->n_items = (int)n_items;
-        pl->chunk = kAttnMaxChunk;
+        pl->chunk = longest_ctx;
         pl->g_max = g_max;
         pl->causal = 1;
         hp->ints = n_items + 4 * (size_t)S;

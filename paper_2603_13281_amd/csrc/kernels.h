@@ -142,6 +142,7 @@ hipError_t launch_merge_shrink(const Dims &dm, const float *part_o, const float 
 // Causal attention of prefill chunks: each plan sequence is a group of consecutive chunk tokens with at
 // most attn_prefill_group_queries() stacked queries (tokens x Hq/Hkv); never split, writes `out` directly.
 int attn_prefill_group_queries();
+int attn_prefill_max_ctx();  // longest context, in tokens, that a piece may cover
 bool attn_prefill_mfma_supported(const Dims &dm, int g_max);
 hipError_t launch_attn_prefill_mfma(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
                                     const AttnPlan &pl, void *out, hipStream_t st);

@@ -362,3 +362,25 @@ def test_prefill_causal_groups_and_boundaries(shape):
     got2 = layer.prefill_kv(dpool2, bt, pre, chunk, dev(x, True))
     torch.cuda.synchronize()
     assert_close(host(got2), want, 2e-2, "prefill x_out (generic kernels)")
+
+
+@pytest.mark.parametrize("pre,chunk", [([16379, 16384, 40001], [9, 33, 70]),          # around the longest decode piece, and beyond
+                                       ([131072 - 20], [20]), ([131072 - 19], [20])],  # the longest context a workgroup's LDS covers, one more
+                         ids=["beyond-16384", "longest", "past-longest"])
+def test_prefill_over_long_contexts(pre, chunk):
+    _say("case: prefill long contexts", pre, chunk)
+    shape = synth.LLAMA_SMALL
+    base = synth.make_base(shape, seed=17, norm_ones=False)
+    batch = synth.make_batch(shape, pre, [0] * len(pre), seed=17, headroom=max(chunk) + 16, pool_factor=1.0)
+    pool = filled_batch(shape, batch, seed=17)
+    mark_unwritten(shape, batch, pool, np.nan)
+    x = synth.make_hidden(shape, sum(chunk), seed=17, tag=5)
+    dpool = dev(pool_to_device_layout(pool), True)
+    orc = oracle.Oracle(oracle_config(shape, batch.num_blocks), base, None)
+    want, want_slots = orc.prefill(pool, batch.block_tables, pre, chunk, x)
+    layer = make_layer(shape, base, None, batch.num_blocks, max_position=1 << 18)
+    slots = torch.zeros(sum(chunk), dtype=torch.int64, device="cuda")
+    got = layer.prefill_kv(dpool, torch.from_numpy(batch.block_tables).cuda(), pre, chunk, dev(x, True), slot_out=slots)
+    torch.cuda.synchronize()
+    assert np.array_equal(slots.cpu().numpy(), want_slots)
+    assert_close(host(got), want, 2e-2, "prefill x_out")
