@@ -224,10 +224,10 @@ icarus_status icarus_attn_shared_kv_static(icarus_ctx *ctx, const void *q, const
  * where the shape allows, default), 1 = force the generic vector kernels. */
 icarus_status icarus_set_kernel_mode(icarus_ctx *ctx, int32_t mode);
 
-/* For tests and measurements: the longest piece, in tokens, that the decode attention's plan may give one
- * workgroup (rounded down to a multiple of 32, at least 32); 0 = automatic (default: up to 16384).  A small
- * limit cuts even short sequences into several pieces, which exercises the partial-result merge at sizes an
- * oracle finishes in seconds.  Changes the workspace a call needs: query icarus_workspace_bytes afterwards. */
+/* For tests and measurements: the longest piece, in tokens, that the attention's plan may give one workgroup
+ * (decode: rounded down to a multiple of 32, at least 32; prefill: to a multiple of 128, at least 128);
+ * 0 = automatic (default: up to 16384 and 131072).  A small limit cuts even short sequences into several pieces,
+ * which exercises the partial-result merge at sizes an oracle finishes in seconds.  Changes the workspace a call needs: query icarus_workspace_bytes afterwards. */
 icarus_status icarus_set_attn_piece_limit(icarus_ctx *ctx, int32_t tokens);
 
 /* Per-phase kernel timing for measurements.  While enabled, every kernel launch of the entry

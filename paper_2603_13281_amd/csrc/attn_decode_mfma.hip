@@ -860,9 +860,10 @@ __device__ __forceinline__ void load_half8(uint2 (&r)[8], int part, const uint8_
 // overlaps the softmax arithmetic of the other on the same SIMD).  ring: [2][4][16][64] x 16 B.
 template <int NT, bool KV8 = false>
 __device__ __forceinline__ void prefill_walk(State<NT> &st, const void *__restrict__ pool_v, const int *__restrict__ blds,
-                                             int n_blk, int n_tok, int n_clean, const int (&stag)[NT], int w, int c, int Hkv,
-                                             bf16x8 *__restrict__ ring, const bf16x8 (&qr)[NT][kKS], float scale_log2,
+                                             int n_blk, int n_tok, int left, int n_clean, const int (&stag)[NT], bool busy, int w, int c,
+                                             int Hkv, bf16x8 *__restrict__ ring, const bf16x8 (&qr)[NT][kKS], float scale_log2,
                                              int lane) {
+    // left: tokens of the sequence from this piece's first on (n_tok or more); busy: this wave holds queries
     const int n_grp = (n_tok + kGrp - 1) / kGrp;  // groups, the masked ones included
     const int n_round = (n_grp + 3) / 4;          // the same for every wave
     const int part = w & 1, gl = w >> 1;
@@ -890,6 +891,7 @@ __device__ __forceinline__ void prefill_walk(State<NT> &st, const void *__restri
         }
         if (mine + 4 < n_grp) load(mine + 4);
         __syncthreads();
+        if (!busy) continue;  // a wave of a partly filled group only helps to load
         // the round's unmasked groups, then its masked ones: two loops of one code path each (with both paths
         // in one loop body the accumulators are copied between the registers the two paths leave them in)
         const int n_here = min(4, n_grp - 4 * r), n_plain = max(0, min(n_here, n_clean - 4 * r));
@@ -898,7 +900,7 @@ __device__ __forceinline__ void prefill_walk(State<NT> &st, const void *__restri
             compute_group_lds<NT, false>(st, stage + (size_t)gi * 16 * 64 + lane, qr, kGrp, stag, scale_log2, lane);
 #pragma nounroll
         for (int gi = n_plain; gi < n_here; ++gi)
-            compute_group_lds<NT, true>(st, stage + (size_t)gi * 16 * 64 + lane, qr, n_tok - (4 * r + gi) * kGrp, stag, scale_log2, lane);
+            compute_group_lds<NT, true>(st, stage + (size_t)gi * 16 * 64 + lane, qr, left - (4 * r + gi) * kGrp, stag, scale_log2, lane);
     }
 }
 
@@ -906,21 +908,26 @@ constexpr int kPrefillWaves = 8, kPrefillNT = 2;  // 8 waves x 2 tiles x 16 = 25
 
 // Causal attention of a prefill chunk.  A workgroup owns one kv-head of one group of T consecutive
 // chunk tokens (T * g <= 256 stacked queries; token t attends to kv_len - (T-1-t) positions) and
-// walks the sequence's cache once for all of them; wave w holds query tiles [w NT, (w+1) NT).
+// walks the sequence's cache, or one piece of it, once for all of them; wave w holds query tiles
+// [w NT, (w+1) NT).  Bound by MFMA and softmax issue, so what counts is that every CU has a walk: with
+// whole walks only, 14 groups x 8 kv-heads of a round of agent turns (60-400 rows over 600-8192 cached
+// tokens each) took 240 us on 112 CUs, cut into pieces 109 us + 12.5 us for
+// the merge; 512 rows over 32000 tokens (16 groups) 990 us -> 574 + 12.5 us.
 template <int NT, bool KV8 = false>
 __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_t *__restrict__ qg, const void *__restrict__ pool,
                                                                      const int32_t *__restrict__ bt, int max_blocks, AttnPlan pl,
-                                                                     bf16_t *__restrict__ out, int Hq, int Hkv, float scale_log2,
+                                                                     bf16_t *__restrict__ out, float *__restrict__ part_o,
+                                                                     float *__restrict__ part_ml, int Hq, int Hkv, float scale_log2,
                                                                      float v_scale) {
     extern __shared__ float lds[];
     const int item = blockIdx.x / Hkv, c = blockIdx.x % Hkv;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int s = pl.item_seq[item];
-    const int n_tok = pl.seq_kvlen[s];  // a causal plan never splits a sequence
+    const int begin = pl.item_begin[item], n_tok = pl.item_len[item], left = pl.seq_kvlen[s] - begin;
     const int row0 = pl.seq_row0[s], T = pl.seq_rows[s];
     const int g = Hq / Hkv, G = T * g;
     const int m = lane & 15, q = lane >> 4;
-    const int32_t *btr = bt + (size_t)pl.seq_bt[s] * max_blocks;
+    const int32_t *btr = bt + (size_t)pl.seq_bt[s] * max_blocks + begin / kBk;
     // LDS: [KV ring, two stages of 64 KB] [block ids]; the wave's Q fragments (B operands) stay in registers
     bf16x8 *ring = (bf16x8 *)lds;
     bf16x8 qr[NT][kKS];
@@ -952,8 +959,9 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
         for (int dt = 0; dt < kDT; ++dt) st.o[dt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
         stag[qt] = T - 1 - min((16 * (w * NT + qt) + m) / g, T - 1);
     }
-    const int n_clean = max(0, n_tok - (T - 1)) / kGrp;  // groups valid for every query
-    prefill_walk<NT, KV8>(st, pool, blds, n_blk, n_tok, n_clean, stag, w, c, Hkv, ring, qr, scale_log2, lane);
+    const int n_clean = max(0, left - (T - 1)) / kGrp;  // groups valid for every query (further ones may be in later pieces)
+    const bool busy = __builtin_amdgcn_readfirstlane(16 * w * NT) < G;
+    prefill_walk<NT, KV8>(st, pool, blds, n_blk, n_tok, left, n_clean, stag, busy, w, c, Hkv, ring, qr, scale_log2, lane);
     if constexpr (KV8) {
 #pragma unroll
         for (int qt = 0; qt < NT; ++qt)
@@ -962,31 +970,53 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
                 st.o[dt][qt][0] *= v_scale; st.o[dt][qt][1] *= v_scale; st.o[dt][qt][2] *= v_scale; st.o[dt][qt][3] *= v_scale;
             }
     }
-    finish<NT>(st, w * NT, NT, G, g, row0, c, Hq, Hkv, 1, 0, 0, out, nullptr, nullptr, lane);
+    finish<NT>(st, w * NT, NT, G, g, row0, c, Hq, Hkv, pl.item_direct[item], pl.item_part[item], pl.g_max, out, part_o, part_ml, lane);
 }
 
-// Combine the partial results of sequences that were split into several chunks.
-// One block of 128 threads per (row, query head); thread d owns output element d.
-__global__ void __launch_bounds__(128) k_attn_merge(const float *__restrict__ part_o, const float *__restrict__ part_ml,
-                                                    AttnPlan pl, const int32_t *__restrict__ row_seq /* row -> plan sequence */,
-                                                    bf16_t *__restrict__ out, int Hq, int Hkv) {
-    const int row = blockIdx.y, h = blockIdx.x, d = threadIdx.x;
-    const int s = row_seq[row];
+// Combine the partial results of sequences that were split into several pieces.  32 threads per (row, query head),
+// four output elements each; four pieces' loads in flight (a piece past the last repeats it with weight zero).
+__global__ void __launch_bounds__(256) k_attn_merge(const float *__restrict__ part_o, const float *__restrict__ part_ml,
+                                                    AttnPlan pl, const int32_t *__restrict__ row_pseq /* row -> plan sequence */,
+                                                    bf16_t *__restrict__ out, int R, int Hq, int Hkv) {
+    const int idx = blockIdx.x * 8 + (threadIdx.x >> 5), d = (threadIdx.x & 31) * 4;
+    if (idx >= R * Hq) return;
+    const int row = idx / Hq, h = idx % Hq;
+    const int s = row_pseq[row];
     const int g = Hq / Hkv, c = h / g;
     const int np = pl.seq_nparts[s];
     if (np <= 1) return;  // written directly by the attention kernel
-    const int j = (row - pl.seq_row0[s]) * g + h % g;
-    const int p0 = pl.seq_part0[s];
+    const size_t pj0 = ((size_t)pl.seq_part0[s] * Hkv + c) * pl.g_max + (row - pl.seq_row0[s]) * g + h % g;
+    const size_t pstep = (size_t)Hkv * pl.g_max;  // between consecutive pieces
     float M = -INFINITY;
-    for (int p = 0; p < np; ++p) M = fmaxf(M, part_ml[(((size_t)(p0 + p) * Hkv + c) * pl.g_max + j) * 2]);
-    float num = 0.f, den = 0.f;
-    for (int p = 0; p < np; ++p) {
-        size_t pj = ((size_t)(p0 + p) * Hkv + c) * pl.g_max + j;
-        float wgt = __builtin_amdgcn_exp2f(part_ml[pj * 2] - M);
-        den += wgt * part_ml[pj * 2 + 1];
-        num += wgt * part_o[pj * kD + d];
+    for (int p = 0; p < np; p += 4) {
+        float m4[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) m4[u] = part_ml[(pj0 + min(p + u, np - 1) * pstep) * 2];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) M = fmaxf(M, m4[u]);
     }
-    out[((size_t)row * Hq + h) * kD + d] = f32_to_bf16(num / den);
+    float num[4] = {0.f, 0.f, 0.f, 0.f}, den = 0.f;
+    for (int p = 0; p < np; p += 4) {
+        float2 ml[4];
+        f32x4 o[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const size_t pj = pj0 + min(p + u, np - 1) * pstep;
+            ml[u] = *(const float2 *)(part_ml + pj * 2);
+            o[u] = *(const f32x4 *)(part_o + pj * kD + d);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {  // in piece order
+            const float wgt = p + u < np ? __builtin_amdgcn_exp2f(ml[u].x - M) : 0.f;
+            den += wgt * ml[u].y;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) num[i] += wgt * o[u][i];
+        }
+    }
+    uint2 pk;
+    pk.x = (uint32_t)f32_to_bf16(num[0] / den) | ((uint32_t)f32_to_bf16(num[1] / den) << 16);
+    pk.y = (uint32_t)f32_to_bf16(num[2] / den) | ((uint32_t)f32_to_bf16(num[3] / den) << 16);
+    *(uint2 *)(out + ((size_t)row * Hq + h) * kD + d) = pk;
 }
 
 template <int NA, int NB, bool KV8 = false>
@@ -1019,6 +1049,7 @@ bool attn_decode_mfma_supported(const Dims &dm, int g_max) {
 constexpr size_t kPrefillRing = (size_t)2 * 4 * 16 * 64 * 16, kLdsBytes = (size_t)160 << 10;
 constexpr int kPrefillMaxCtx = (int)((kLdsBytes - kPrefillRing) / 4) * kBk;
 int attn_prefill_max_ctx() { return kPrefillMaxCtx; }
+int attn_prefill_round() { return 4 * kGrp; }
 
 int attn_prefill_group_queries() { return kPrefillWaves * kPrefillNT * 16; }  // stacked queries one prefill workgroup holds
 
@@ -1027,7 +1058,7 @@ bool attn_prefill_mfma_supported(const Dims &dm, int g_max) {
 }
 
 hipError_t launch_attn_prefill_mfma(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
-                                    const AttnPlan &pl, void *out, hipStream_t st) {
+                                    const AttnPlan &pl, void *out, float *part_o, float *part_ml, hipStream_t st) {
     if (pl.n_items <= 0) return hipSuccess;
     if (!pl.causal || pl.chunk > kPrefillMaxCtx) return hipErrorInvalidValue;
     constexpr int NT = kPrefillNT;
@@ -1040,7 +1071,7 @@ hipError_t launch_attn_prefill_mfma(const Dims &dm, const void *q, const void *p
             attr_set = true;
         }
         hipLaunchKernelGGL(kernel, dim3(pl.n_items * dm.Hkv), dim3(64 * kPrefillWaves), shm, st, (const bf16_t *)q, pool, bt, max_blocks, pl,
-                           (bf16_t *)out, dm.Hq, dm.Hkv, scale_log2, dm.kv8 ? dm.v_scale : 1.f);
+                           (bf16_t *)out, part_o, part_ml, dm.Hq, dm.Hkv, scale_log2, dm.kv8 ? dm.v_scale : 1.f);
         return hipGetLastError();
     };
     static bool set_bf16 = false, set_fp8 = false;
@@ -1075,9 +1106,9 @@ hipError_t launch_attn_decode_mfma(const Dims &dm, const void *q, const void *po
 }
 
 hipError_t launch_attn_merge(const Dims &dm, const float *part_o, const float *part_ml, const AttnPlan &pl,
-                             const int32_t *row_seq, void *out, int R, hipStream_t st) {
+                             const int32_t *row_pseq, void *out, int R, hipStream_t st) {
     if (R <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_attn_merge, dim3(dm.Hq, R), dim3(128), 0, st, part_o, part_ml, pl, row_seq, (bf16_t *)out, dm.Hq, dm.Hkv);
+    hipLaunchKernelGGL(k_attn_merge, dim3((R * dm.Hq + 7) / 8), dim3(256), 0, st, part_o, part_ml, pl, row_pseq, (bf16_t *)out, R, dm.Hq, dm.Hkv);
     return hipGetLastError();
 }
 

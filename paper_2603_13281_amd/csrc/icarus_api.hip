@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -135,7 +136,7 @@ bool has_lora(const icarus_ctx *ctx, int p) {
 // ---- workspace layout ---------------------------------------------------------------
 struct WsLayout {
     size_t meta, xn, qkv, q, attn, z, h, f32a, f32b, t, part_o, part_ml, lora_t, xg, ag, yg, total;
-    size_t meta_ints, max_items, gemm_part, gemm_part_bytes;
+    size_t meta_ints, max_items, max_partial, gemm_part, gemm_part_bytes;
 };
 
 // Rows regrouped for decoders with private weights: group 0 = encoder rows, group 1 + j = rows of model j.
@@ -167,7 +168,8 @@ WsLayout ws_layout(const icarus_ctx *ctx, size_t rows, size_t seqs, size_t max_c
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     w.max_items = attn_max_items(ctx, seqs, max_ctx);
     // metadata: 4 row arrays and the attention plan (5 arrays per piece, the shares' first pieces, 6 arrays
-    // per plan sequence); a prefill call has up to `rows` plan sequences of one piece each
+    // per plan sequence); a prefill call has up to `rows` plan sequences, max_items pieces if any is cut, and an array
+    // of its rows' plan sequences (where a decode call keeps the regrouping of its rows)
     w.meta_ints = 4 * rows + 5 * std::max(rows, w.max_items) + (size_t)ctx->attn_wgs + 6 * std::max(rows, seqs) + 64 +
                   rows + seqs +  // + what a layer stack stages with the call: prompt tokens, last row of each sequence
                   2 * rows;      // + the regrouping of rows for decoders with private weights
@@ -175,7 +177,8 @@ WsLayout ws_layout(const icarus_ctx *ctx, size_t rows, size_t seqs, size_t max_c
     {
         size_t g = (size_t)c.n_q_heads / c.n_kv_heads;
         size_t g_bound = std::min<size_t>(kAttnGMax, rows * g);
-        size_t pj = w.max_items * c.n_kv_heads * g_bound;
+        w.max_partial = w.max_items * g_bound;
+        size_t pj = w.max_partial * c.n_kv_heads;
         w.part_o = take(pj * c.head_dim * 4);
         w.part_ml = take(pj * 2 * 4);
     }
@@ -345,11 +348,13 @@ struct HostPlan {
 // (a workgroup per kv-head), so that every workgroup finishes at about the same time whatever the
 // mix of context lengths; pieces are multiples of 32 tokens and at most kAttnMaxChunk long.
 // Prefill (causal): seq_bt gives the block-table row of each plan sequence (a group of consecutive
-// chunk tokens; row t attends to kv_len - (rows-1-t) tokens); never split, so the call is covered
-// only if every kv_len fits one piece.
+// chunk tokens; row t attends to kv_len - (rows-1-t) tokens).  A few groups over long contexts would
+// leave most of the chip idle: then each walk is cut into pieces, see below.
+// max_items: pieces the staging buffer and the workspace are sized for; max_partial: stacked queries
+// (per kv-head, over all pieces of cut walks) that the workspace's partial results hold.
 void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t *dmeta, int S, const int32_t *kv_lens,
                      const int32_t *seq_row0, const int32_t *seq_rows, const int32_t *seq_bt, bool causal, size_t max_items,
-                     HostPlan *hp) {
+                     size_t max_partial, HostPlan *hp) {
     AttnPlan *pl = &hp->pl;
     *pl = AttnPlan{};
     hp->valid = false;
@@ -358,28 +363,27 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
     const icarus_layer_config &c = ctx->cfg;
     if (ctx->mode != 0) return;
     const int g = c.n_q_heads / c.n_kv_heads, Hkv = c.n_kv_heads;
-    int g_max = 0, longest_ctx = 0;
+    int g_max = 0;
     for (int s = 0; s < S; ++s) {
         if (seq_rows[s] > 0 && kv_lens[s] <= 0) return;  // empty context: generic kernel writes zeros
-        if (causal && kv_lens[s] > attn_prefill_max_ctx()) return;
         g_max = std::max(g_max, seq_rows[s] * g);
-        longest_ctx = std::max(longest_ctx, kv_lens[s]);
     }
     if (causal ? !attn_prefill_mfma_supported(ctx->dm, g_max) : (!attn_decode_mfma_supported(ctx->dm, g_max) || g_max > kAttnGMax)) return;
     const int32_t *d = dmeta + at;
     if (causal) {
-        // One piece per token group (x kv-heads in the launch).  The launch maps kv-head c of piece i to workgroup
+        // Pieces of token groups (x kv-heads in the launch).  The launch maps kv-head c of piece i to workgroup
         // i * Hkv + c, so with Hkv = 8 every XCD runs one kv-head and takes the pieces in this order, about 32 at a
-        // time: the token groups of one sequence are kept next to each other, so that they walk the sequence's
-        // cached prefix at the same time and all but the first find it in that XCD's L2 (sorted by length alone,
-        // the groups of a sequence were rounds apart and each one fetched the prefix from HBM again).  Sequences
-        // with the longest contexts go first, and within a sequence the longest group.
+        // time: pieces of one sequence that walk the same part of its cached prefix are kept next to each other, so
+        // that all but the first find it in that XCD's L2 (sorted by length alone, the groups of a sequence were
+        // rounds apart and each one fetched the prefix from HBM again).  Sequences with the longest contexts go
+        // first, and within a sequence the longest group.
         std::vector<int32_t> order;
         int n_bt = 0;
         for (int s = 0; s < S; ++s) {
             if (seq_rows[s] > 0) order.push_back(s);
             n_bt = std::max(n_bt, (seq_bt ? seq_bt[s] : s) + 1);
         }
+        if (order.empty()) return;
         std::vector<int32_t> longest((size_t)n_bt, 0);  // per block-table row (= sequence of the call)
         for (int s : order) {
             int32_t &l = longest[seq_bt ? seq_bt[s] : s];
@@ -391,26 +395,132 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
             if (ra != rb) return ra < rb;
             return kv_lens[a] > kv_lens[b];
         });
-        const size_t n_items = order.size();
-        int32_t *item_seq = m + at, *seq_kvlen = item_seq + n_items, *row0 = seq_kvlen + S, *rows = row0 + S, *sbt = rows + S;
-        for (size_t i = 0; i < n_items; ++i) item_seq[i] = order[i];
+        // Cut every sequence's walk into parts of at most `most` tokens, whole rounds of the walk each: part p of a
+        // group is tokens [p len, (p + 1) len) with the same len for all groups of a sequence; a last part shorter
+        // than a round joins the one before it.
+        struct Cut { int32_t s, begin, len, n; };
+        std::vector<Cut> cuts;
+        const int round = attn_prefill_round(), max_piece = attn_prefill_max_ctx();
+        auto cut = [&](int most) {
+            cuts.clear();
+            for (size_t i = 0; i < order.size();) {
+                const int bt_row = seq_bt ? seq_bt[order[i]] : order[i];
+                size_t e = i;
+                while (e < order.size() && (seq_bt ? seq_bt[order[e]] : order[e]) == bt_row) ++e;
+                const int64_t top = longest[bt_row], k = (top + most - 1) / most;
+                const int len = (int)(((top + k - 1) / k + round - 1) / round * round);
+                for (int p = 0; p < k; ++p)
+                    for (size_t o = i; o < e; ++o) {
+                        const int s = order[o], kv = kv_lens[s];
+                        int n = std::max(1, (kv - (round - 1) + len - 1) / len);  // parts of this group
+                        if (kv - (n - 1) * len > max_piece) ++n;
+                        if (p < n) cuts.push_back({s, p * len, p + 1 < n ? len : kv - p * len, n});
+                    }
+                i = e;
+            }
+        };
+        // Model of a launch, in tokens walked by one workgroup: the kernel gives a CU one workgroup, so attn_wgs / Hkv
+        // pieces run at a time, each next one on the first CU that is free; a piece costs its tokens and
+        // kPieceTokens on top (prologue, Q loads, output), and if any group is cut, the partial results cost a merge
+        // launch and their way through memory.
+        const int cus = std::max(1, ctx->attn_wgs / Hkv);
+        auto cost = [&]() {
+            constexpr int64_t kPieceTokens = 160, kMergeTokens = 160, kSlotTokens = 8;
+            std::vector<int64_t> busy((size_t)cus, 0);  // min-heap of finishing times
+            int64_t end = 0;
+            size_t slots = 0;
+            for (const Cut &c : cuts) {
+                std::pop_heap(busy.begin(), busy.end(), std::greater<int64_t>());
+                busy.back() += c.len + kPieceTokens;
+                end = std::max(end, busy.back());
+                std::push_heap(busy.begin(), busy.end(), std::greater<int64_t>());
+                slots += c.n > 1;
+            }
+            return end + (slots ? kMergeTokens + kSlotTokens * (int64_t)slots : 0);
+        };
+        auto fits = [&]() {
+            size_t slots = 0;
+            for (const Cut &c : cuts) slots += c.n > 1;
+            return cuts.size() <= std::max(max_items, order.size()) && slots * (size_t)g_max <= max_partial;
+        };
+        int best_most = max_piece;
+        if (ctx->attn_chunk_override > 0) {
+            best_most = std::min(max_piece, std::max(round, ctx->attn_chunk_override / round * round));
+        } else {
+            cut(max_piece);
+            int64_t best = cost();
+            // Enough pieces for several per CU need no cutting: the last ones end within a piece of each other.
+            if (cuts.size() < (size_t)8 * cus) {
+                int64_t work = 0;
+                for (int s : order) work += kv_lens[s];
+                // one piece per CU, or up to five; lengths in between because a sequence's parts are of one length
+                for (int pct : {200, 150, 125, 105, 90, 78, 68, 60, 52, 45, 38, 32, 26, 20}) {
+                    const int most = (int)std::min<int64_t>(max_piece, std::max<int64_t>(2 * round, work * pct / (100 * (int64_t)cus)));
+                    cut(most);
+                    if (!fits()) continue;
+                    const int64_t c = cost();
+                    if (c < best) { best = c; best_most = most; }
+                    if (most == 2 * round) break;
+                }
+            }
+        }
+        cut(best_most);
+        if (!fits()) {
+            cut(max_piece);
+            if (!fits()) return;
+        }
+        const size_t n_items = cuts.size();
+        int32_t *item_seq = m + at, *item_begin = item_seq + n_items, *item_len = item_begin + n_items, *item_part = item_len + n_items,
+                *item_direct = item_part + n_items, *seq_kvlen = item_direct + n_items, *row0 = seq_kvlen + S, *rows = row0 + S,
+                *sbt = rows + S, *part0 = sbt + S, *nparts = part0 + S, *pseq = nparts + S;
+        int n_rows = 0;
         for (int s = 0; s < S; ++s) {
             seq_kvlen[s] = kv_lens[s];
             row0[s] = seq_row0[s];
             rows[s] = seq_rows[s];
             sbt[s] = seq_bt ? seq_bt[s] : s;
+            part0[s] = 0;
+            nparts[s] = 0;
+            for (int t = 0; t < seq_rows[s]; ++t) pseq[seq_row0[s] + t] = s;
+            n_rows = std::max(n_rows, seq_row0[s] + seq_rows[s]);
+        }
+        // partial results of a group are consecutive, in token order
+        for (const Cut &c : cuts) nparts[c.s] = c.n;
+        int slot = 0;
+        for (int s : order) {
+            part0[s] = slot;
+            if (nparts[s] > 1) slot += nparts[s];
+        }
+        std::vector<int32_t> used((size_t)S, 0);
+        int max_len = 0;
+        for (size_t i = 0; i < n_items; ++i) {
+            const Cut &c = cuts[i];
+            item_seq[i] = c.s;
+            item_begin[i] = c.begin;
+            item_len[i] = c.len;
+            item_direct[i] = c.n == 1;
+            item_part[i] = part0[c.s] + used[c.s]++;
+            max_len = std::max(max_len, (int)c.len);
         }
         pl->item_seq = d;
-        pl->seq_kvlen = d + n_items;
+        pl->item_begin = d + n_items;
+        pl->item_len = d + 2 * n_items;
+        pl->item_part = d + 3 * n_items;
+        pl->item_direct = d + 4 * n_items;
+        pl->seq_kvlen = d + 5 * n_items;
         pl->seq_row0 = pl->seq_kvlen + S;
         pl->seq_rows = pl->seq_row0 + S;
         pl->seq_bt = pl->seq_rows + S;
+        pl->seq_part0 = pl->seq_bt + S;
+        pl->seq_nparts = pl->seq_part0 + S;
+        pl->row_pseq = pl->seq_nparts + S;
         pl->n_items = (int)n_items;
-        pl->chunk = longest_ctx;
+        pl->chunk = max_len;
         pl->g_max = g_max;
         pl->causal = 1;
-        hp->ints = n_items + 4 * (size_t)S;
-        hp->valid = n_items > 0;
+        hp->has_split = slot > 0;
+        hp->ints = 5 * n_items + 6 * (size_t)S + (size_t)n_rows;
+        hp->valid = true;
         return;
     }
     // ---- decode: equal shares of the weighted work line
@@ -528,11 +638,13 @@ icarus_status run_decode_attention(icarus_ctx *ctx, char *ws, const WsLayout &L,
         PHASE(ctx, st, ICARUS_PH_ATTN, launch_attn_generic(ctx->dm, q, pool, bt, max_blocks, rm, out, R, st));
         return ICARUS_OK;
     }
+    float *part_o = (float *)(ws + L.part_o), *part_ml = (float *)(ws + L.part_ml);
     if (hp->pl.causal) {
-        PHASE(ctx, st, ICARUS_PH_ATTN, launch_attn_prefill_mfma(ctx->dm, q, pool, bt, max_blocks, hp->pl, out, st));
+        PHASE(ctx, st, ICARUS_PH_ATTN, launch_attn_prefill_mfma(ctx->dm, q, pool, bt, max_blocks, hp->pl, out, part_o, part_ml, st));
+        if (hp->has_split)
+            PHASE(ctx, st, ICARUS_PH_ATTN_MERGE, launch_attn_merge(ctx->dm, part_o, part_ml, hp->pl, hp->pl.row_pseq, out, R, st));
         return ICARUS_OK;
     }
-    float *part_o = (float *)(ws + L.part_o), *part_ml = (float *)(ws + L.part_ml);
     PHASE(ctx, st, ICARUS_PH_ATTN, launch_attn_decode_mfma(ctx->dm, q, pool, bt, max_blocks, hp->pl, out, part_o, part_ml, st));
     if (hp->has_split && merge_left) {  // the caller merges the partials in its next row kernel
         *merge_left = true;
@@ -858,7 +970,7 @@ icarus_status prepare_decode(icarus_ctx *ctx, const void *kv_pool, const int32_t
     for (int s = 0; s < S; ++s) kvl[s] = ctx_lens[s] + 1;
     char *ws = (char *)workspace;
     const int32_t *dmeta = (const int32_t *)(ws + L.meta);
-    build_attn_plan(ctx, m, (size_t)4 * R, dmeta, S, kvl.data(), row0.data(), rows.data(), nullptr, false, L.max_items, &pr->hp);
+    build_attn_plan(ctx, m, (size_t)4 * R, dmeta, S, kvl.data(), row0.data(), rows.data(), nullptr, false, L.max_items, L.max_partial, &pr->hp);
     size_t used = (size_t)4 * R + pr->hp.ints;
     if (n_extra) {
         memcpy(m + used, extra, n_extra * 4);
@@ -952,7 +1064,7 @@ icarus_status prepare_prefill(icarus_ctx *ctx, const void *kv_pool, const int32_
             row += chunk_lens[s];
         }
         build_attn_plan(ctx, m, (size_t)4 * R, dmeta, (int)vkv.size(), vkv.data(), vrow0.data(), vrows.data(), vbt.data(), true,
-                        L.max_items, &pr->hp);
+                        L.max_items, L.max_partial, &pr->hp);
     }
     size_t used = (size_t)4 * R + pr->hp.ints;
     if (n_extra) {
@@ -1311,7 +1423,7 @@ static icarus_status attn_shared_kv_impl(icarus_ctx *ctx, const void *q, const v
     if (use_static) L.meta = 0;  // the static scratch starts with the metadata
     const int32_t *dmeta = (const int32_t *)(ws + L.meta);
     HostPlan hp;
-    build_attn_plan(ctx, m, (size_t)4 * R, dmeta, S, kv_lens, row0.data(), rows.data(), nullptr, false, L.max_items, &hp);
+    build_attn_plan(ctx, m, (size_t)4 * R, dmeta, S, kv_lens, row0.data(), rows.data(), nullptr, false, L.max_items, L.max_partial, &hp);
     const size_t used = (size_t)4 * R + hp.ints;
     if (use_static) {
         // what THIS call needs, from its own plan: metadata, then the partial results of its pieces

@@ -67,20 +67,22 @@ hipError_t launch_bench_mfma(float *out, int waves, int iters, hipStream_t st);
 // the pieces [wg_first[b], wg_first[b+1]), a piece being a token range of one sequence.  Piece
 // boundaries are multiples of 32 tokens.  A sequence cut into several pieces leaves one partial
 // result per piece and kv-head.
-// Prefill (causal = 1): one piece per token group (x kv-heads in the launch), never split.
+// Prefill (causal = 1): one workgroup per piece and kv-head; a piece is the whole walk of a token group, or a part of
+// it that leaves a partial result (launch_attn_merge combines them).  Inner boundaries on whole rounds of the walk.
 struct AttnPlan {
     const int32_t *item_seq;     // [n_items] plan sequence of the piece
-    const int32_t *item_begin;   // [n_items] first token of the piece (decode)
-    const int32_t *item_len;     // [n_items] tokens of the piece (decode)
-    const int32_t *item_part;    // [n_items] partial-result slot of the piece (decode)
-    const int32_t *item_direct;  // [n_items] 1: the piece is its whole sequence: write the final output (decode)
+    const int32_t *item_begin;   // [n_items] first token of the piece
+    const int32_t *item_len;     // [n_items] tokens of the piece
+    const int32_t *item_part;    // [n_items] partial-result slot of the piece
+    const int32_t *item_direct;  // [n_items] 1: the piece is its whole sequence: write the final output
     const int32_t *wg_first;     // [n_wgs + 1] first piece of each share (decode)
     const int32_t *seq_kvlen;    // [S] tokens to attend to
     const int32_t *seq_row0;     // [S] first row of the sequence
     const int32_t *seq_rows;     // [S] rows (stacked streams) of the sequence
-    const int32_t *seq_part0;    // [S] first partial slot (decode)
-    const int32_t *seq_nparts;   // [S] number of pieces (decode)
+    const int32_t *seq_part0;    // [S] first partial slot
+    const int32_t *seq_nparts;   // [S] number of pieces
     const int32_t *seq_bt;       // [S] row of the block table the sequence reads
+    const int32_t *row_pseq;     // [R] plan sequence of each row (prefill; at decode RowMeta::row_seq says it)
     int n_items, n_wgs, chunk, g_max;  // n_wgs: shares; chunk: longest piece; g_max: largest stacked group (rows * Hq/Hkv)
     int causal;                  // 1: row t of a sequence attends to kv_len - (rows - 1 - t) tokens (prefill)
 };
@@ -140,17 +142,19 @@ hipError_t launch_merge_shrink(const Dims &dm, const float *part_o, const float 
                                const int32_t *row_pseq, void *attn, int R, const void *A0, const int32_t *row_model, void *T,
                                hipStream_t st);
 // Causal attention of prefill chunks: each plan sequence is a group of consecutive chunk tokens with at
-// most attn_prefill_group_queries() stacked queries (tokens x Hq/Hkv); never split, writes `out` directly.
+// most attn_prefill_group_queries() stacked queries (tokens x Hq/Hkv).  Whole walks write `out`, pieces of cut ones
+// part_o / part_ml (as launch_attn_decode_mfma).
 int attn_prefill_group_queries();
-int attn_prefill_max_ctx();  // longest context, in tokens, that a piece may cover
+int attn_prefill_max_ctx();  // longest piece, in tokens
+int attn_prefill_round();    // tokens of a round of the walk: pieces are cut between rounds
 bool attn_prefill_mfma_supported(const Dims &dm, int g_max);
 hipError_t launch_attn_prefill_mfma(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
-                                    const AttnPlan &pl, void *out, hipStream_t st);
+                                    const AttnPlan &pl, void *out, float *part_o, float *part_ml, hipStream_t st);
 // part_o: fp32 [slots, Hkv, g_max, D]; part_ml: fp32 [slots, Hkv, g_max, 2] (max in log2 units, sum)
 hipError_t launch_attn_decode_mfma(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
                                    const AttnPlan &pl, void *out, float *part_o, float *part_ml, hipStream_t st);
 hipError_t launch_attn_merge(const Dims &dm, const float *part_o, const float *part_ml, const AttnPlan &pl,
-                             const int32_t *row_seq, void *out, int R, hipStream_t st);
+                             const int32_t *row_pseq, void *out, int R, hipStream_t st);
 
 // ---- layer stack helpers (index work) ----------------------------------------------------------
 // x[row, :] = embed[tok[idx ? idx[row] : row], :]   (rows of row_bytes bytes, a multiple of 16)

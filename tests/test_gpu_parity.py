@@ -3,6 +3,8 @@ seeded inputs.  Tolerances (per output tensor): max|g-o|/max|o| <= 2e-2 for bf16
 plus an elementwise rtol/atol gate (helpers.assert_close); cache entries within one storage ulp plus the slack that
 the bf16 rounding of the normed row causes (helpers.CACHE_SLACK_BF16, measured in tests/test_cache_gate_model.py);
 slots, and everything the call must not touch, bit-exact."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -10,7 +12,7 @@ import torch
 import oracle
 from paper_2603_13281_amd import synth
 from helpers import assert_cache_close, assert_close, fill_pool, filled_batch, mark_unwritten, oracle_config, read_pool
-from gpu_util import bf16_ulp, dev, host, make_layer, pool_from_device_layout, pool_to_device_layout
+from gpu_util import bf16_ulp, dev, fp8_pool_to_float, host, make_layer, pool_from_device_layout, pool_to_device_layout
 
 pytestmark = pytest.mark.gpu
 
@@ -383,4 +385,40 @@ def test_prefill_over_long_contexts(pre, chunk):
     got = layer.prefill_kv(dpool, torch.from_numpy(batch.block_tables).cuda(), pre, chunk, dev(x, True), slot_out=slots)
     torch.cuda.synchronize()
     assert np.array_equal(slots.cpu().numpy(), want_slots)
+    assert_close(host(got), want, 2e-2, "prefill x_out")
+
+
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
+@pytest.mark.parametrize("limit", [0, 128, 384])
+def test_prefill_walks_cut_into_pieces(limit, fp8):
+    # the walks of a few token groups are cut into pieces (128-token rounds) and their partial results merged: last
+    # pieces of one token, of just under a round (joined to the one before) and of a whole round; a piece that some
+    # of a group's queries do not reach at all; whole and cut walks in one call; groups that fill one wave or all
+    _say("case: prefill pieces, limit", limit, "fp8", fp8)
+    shape = synth.QWEN_SMALL                        # g = 8: 32 chunk tokens per group
+    pre = [0, 127, 128, 255, 380, 1000, 2303, 5]
+    chunk = [129, 2, 128, 1, 133, 40, 33, 31]
+    ks, vs = 0.02, 0.013
+    base = synth.make_base(shape, seed=19, norm_ones=False)
+    batch = synth.make_batch(shape, pre, [0] * len(pre), seed=19, headroom=140)
+    x = synth.make_hidden(shape, sum(chunk), seed=19, tag=5)
+    cfg = oracle_config(shape, batch.num_blocks)
+    if fp8:
+        layer = make_layer(shape, base, None, batch.num_blocks, kv_fp8=True, k_scale=ks, v_scale=vs)
+        gen = torch.Generator(device="cuda:0")
+        gen.manual_seed(19)
+        dpool = torch.randint(0, 256, layer.cfg.pool_shape(), generator=gen, device="cuda:0", dtype=torch.uint8)
+        dpool[(dpool & 0x7f) == 0x7f] = 0x38        # no NaN codes inside the contexts
+        dpool[(dpool & 0x78) == 0x78] &= 0xbf
+        pool = pool_from_device_layout(fp8_pool_to_float(dpool, ks, vs), shape.block_size, shape.head_dim)
+        cfg = dataclasses.replace(cfg, kv_fp8=True, k_scale=ks, v_scale=vs)
+    else:
+        layer = make_layer(shape, base, None, batch.num_blocks)
+        pool = filled_batch(shape, batch, seed=19)
+        mark_unwritten(shape, batch, pool, np.nan)
+        dpool = dev(pool_to_device_layout(pool), True)
+    want, _ = oracle.Oracle(cfg, base, None).prefill(pool, batch.block_tables, pre, chunk, x)
+    layer.set_attn_piece_limit(limit)
+    got = layer.prefill_kv(dpool, torch.from_numpy(batch.block_tables).cuda(), pre, chunk, dev(x, True))
+    torch.cuda.synchronize()
     assert_close(host(got), want, 2e-2, "prefill x_out")
