@@ -15,10 +15,10 @@
 // Tile: 4 waves (one per SIMD, so each may hold 512 registers) as 2 x 2 over 192 rows x 256 weight rows; a wave
 // owns 96 x 128 = 3 x 4 MFMA tiles of 32x32x16 (192 accumulator registers).  Per 16-wide K step the CU reads
 // 4 x (96 + 128) x 32 B = 28 KB of fragments for 48 MFMAs; the square-ish wave tile is what keeps the LDS below
-// the matrix pipe.  Rows beyond 192 go to further row blocks: the row blocks of one column tile sit next to each
-// other on one XCD, so the second reads the weights from that XCD's L2.  Batches of at most 160 rows take a
-// 160 x 256 tile instead, the four waves side by side with 160 x 64 = 5 x 2 MFMA tiles each: the same 28 KB of
-// fragments for 40 MFMAs, fewer of them on rows that do not exist.
+// the matrix pipe.  Rows beyond 192 go to further row blocks: the row blocks of a panel of tiles run next to each
+// other on one XCD, so the second reads the weights from that XCD's L2.  The other shape is a 160 x 256 tile, the four
+// waves side by side with 160 x 64 = 5 x 2 MFMA tiles each: the same 28 KB of fragments for 40 MFMAs, for row counts
+// of which it leaves fewer MFMAs on rows that do not exist (gemm_plan decides).
 //
 // Loads return in order, so everything a wave has in flight is kept at one distance (D = 2 slabs: the loads
 // issued while slab i is multiplied are parked while slab i + D is), and every load is unconditional (past the
@@ -97,13 +97,8 @@ __global__ void __launch_bounds__(256) k_gemm_decode(GemmArgs g) {
     const int wr = w / WVN, wc = w % WVN;
     const int cl = lane & 31, half = lane >> 5;
     int tile_n, row_blk;
-    {   // consecutive workgroups of one XCD: the row blocks of one column tile
-        const int id = blockIdx.x, s = id >> 3;
-        row_blk = s % g.m_tiles;
-        tile_n = (s / g.m_tiles) * 8 + (id & 7);
-        if (tile_n >= g.n_tiles) return;
-    }
-    const int kz = blockIdx.y;
+    int kz;
+    if (!tile_of_workgroup(g, blockIdx.x, &row_blk, &tile_n, &kz)) return;
     const int row0 = row_blk * BM;
     const bool dual = g.mode == GEMM_DUAL;
 
@@ -371,12 +366,11 @@ hipError_t launch_gd(GemmArgs g, hipStream_t st) {
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    dim3 grid((g.n_tiles + 7) / 8 * 8 * g.m_tiles, g.splits);
+    gemm_set_panels(&g, BM, BN, 1);
+    dim3 grid(gemm_grid(g));
     hipLaunchKernelGGL((k_gemm_decode<TM, TN>), grid, dim3(256), shm, st, g);
     return hipGetLastError();
 }
-
-constexpr int kGdBM = 192, kGdBN = 256, kGdBMSmall = 160;  // row tile; the smaller one where it covers every row
 
 }  // namespace
 
@@ -393,21 +387,10 @@ bool gemm_decode_supported(const GemmArgs &g) {
     return true;
 }
 
-// Workgroups of one K slice.
-int gemm_decode_tiles(const GemmArgs &g) {
-    const int m_tiles = (g.R + kGdBM - 1) / kGdBM;
-    if (g.mode == GEMM_DUAL) return m_tiles * ((g.n_seg[0] + kGdBN / 2 - 1) / (kGdBN / 2));
-    int n = 0;
-    for (int s = 0; s < g.nseg; ++s) n += (g.n_seg[s] + kGdBN - 1) / kGdBN;
-    return m_tiles * n;
-}
-
-int gemm_decode_slabs(const GemmArgs &g) { return g.K / kBK + ((g.T ? g.ldt : 0) + kBK - 1) / kBK; }
-
 hipError_t launch_gemm_decode(GemmArgs g, hipStream_t st) {
     if (!gemm_decode_supported(g)) return hipErrorInvalidValue;
     if (!g.T || !(g.B[0] || g.B[1])) { g.T = nullptr; g.ldt = 0; }
-    return g.R <= kGdBMSmall ? launch_gd<5, 2>(g, st) : launch_gd<3, 4>(g, st);
+    return g.tile == TILE_REG_160x256 ? launch_gd<5, 2>(g, st) : launch_gd<3, 4>(g, st);
 }
 
 }  // namespace icarus

@@ -121,23 +121,13 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) k_gemm_mfma(GemmArgs g
     const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)smem;
 
     // XCD-aware tile order.  The 8 XCDs take workgroups round-robin and each runs about 32 of them
-    // at a time (one per CU).  The tile grid is cut into panels of panel_m x panel_n <= run tiles
-    // (run = 32 for a grid that fills the chip, less for small ones so that every XCD gets work);
-    // `run` consecutive workgroups of one XCD work on one panel, so that what they stream through
-    // that XCD's L2 at any moment is panel_m slabs of X and panel_n slabs of W instead of run + 1.
-    // Consecutive panels (on different XCDs at the same time) walk down the rows first, sharing
-    // their weight columns in the memory-side cache.
-    const int Mt = g.m_tiles, Nt = g.n_tiles;
-    int tile_m, tile_n;
-    {
-        const int bid = blockIdx.x, xcd = bid & 7, s = bid >> 3;
-        const int panel = (s / g.run) * 8 + xcd, within = s % g.run;
-        if (panel >= g.n_panels || within >= g.panel_m * g.panel_n) return;
-        tile_m = (panel % g.panels_m) * g.panel_m + within % g.panel_m;
-        tile_n = (panel / g.panels_m) * g.panel_n + within / g.panel_m;
-        if (tile_m >= Mt || tile_n >= Nt) return;
-    }
-    const int kz = blockIdx.y;  // split-K slice
+    // at a time (one per CU).  The tile grid of every K slice is cut into panels of panel_m x panel_n
+    // <= 32 tiles; consecutive workgroups of one XCD work on one panel, so that what they stream
+    // through that XCD's L2 at any moment is panel_m slabs of X and panel_n slabs of W instead of one
+    // of each per tile.  Consecutive panels (on different XCDs at the same time) walk down the rows
+    // first, sharing their weight columns in the memory-side cache, then the slices.
+    int tile_m, tile_n, kz;
+    if (!tile_of_workgroup(g, blockIdx.x, &tile_m, &tile_n, &kz)) return;
     const int k_begin = kz * g.k_per_split;
     const int k_end = min(g.K_ext, k_begin + g.k_per_split);
     const int nk = (k_end - k_begin + BK - 1) / BK;
@@ -457,12 +447,8 @@ hipError_t launch_cfg(GemmArgs g, hipStream_t st) {
             g.n_tiles += g.tiles_seg[s];
         }
     }
-    g.run = std::max(1, std::min(32, g.m_tiles * g.n_tiles / 8));
-    g.panel_m = std::min({g.m_tiles, 8, g.run});
-    g.panel_n = g.run / g.panel_m;
-    g.panels_m = (g.m_tiles + g.panel_m - 1) / g.panel_m;
-    g.n_panels = g.panels_m * ((g.n_tiles + g.panel_n - 1) / g.panel_n);
-    size_t shm = (size_t)NS * (BM + BN) * BK * sizeof(bf16_t);
+    constexpr size_t shm = (size_t)NS * (BM + BN) * BK * sizeof(bf16_t);
+    gemm_set_panels(&g, BM, BN, (int)(((size_t)160 << 10) / shm));
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void *)k_gemm_mfma<BM, BN, BK, NS, WAVES_M, WAVES_N>,
@@ -470,23 +456,27 @@ hipError_t launch_cfg(GemmArgs g, hipStream_t st) {
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    dim3 grid((g.n_panels + 7) / 8 * 8 * g.run, g.splits);
+    dim3 grid(gemm_grid(g));
     hipLaunchKernelGGL((k_gemm_mfma<BM, BN, BK, NS, WAVES_M, WAVES_N>), grid, dim3(64 * WAVES_M * WAVES_N), shm, st, g);
     return hipGetLastError();
 }
 
-// Tile shapes (rows x weight rows x K slab, ring stages, waves).  What bounds a tile is the bytes it
-// pulls through the CU's vector memory path per MFMA cycle, 4096 (1/BM + 1/BN): 64 for 128 x 128
-// (the path's peak), 32 for 256 x 256.  Many rows (prefill): 256 x 256.  Few rows (decode): every
-// weight is used once, straight from HBM, and what counts is how the weight rows are fetched: 64-wide
-// K slabs ask for whole 128-byte lines (32-wide slabs ask for every line twice, half each time, and
-// stream at about 60% of the rate), the grid must fill 256 CUs, so tiles stay 128 wide in N and K is
-// split, and the row tile is the smallest that covers the stacked rows in one or two tiles (64, 128,
-// 192 rows), which keeps the activation re-reads and the ring small enough for two workgroups per CU.
-enum TileKind { TILE_AUTO = 0, TILE_128, TILE_256x128, TILE_256x256_K64, TILE_192x128_N3, TILE_192x128_N2, TILE_64x128, TILE_192x256_W8, TILE_KINDS };
-struct TileShape { int bm, bn, bk; };
-constexpr TileShape kTileShape[TILE_KINDS] = {{0, 0, 0},      {128, 128, 64}, {256, 128, 32}, {256, 256, 64},
-                                              {192, 128, 64}, {192, 128, 64}, {64, 128, 64}, {192, 256, 64}};
+// Tile shapes: rows x weight rows of a workgroup, all with 64-wide K slabs (32-wide slabs ask for every 128-byte line of
+// a weight row twice, half each time, and stream at about 60 % of the rate).  The first four are k_gemm_mfma, the last
+// two k_gemm_decode.  first_us: what a workgroup takes apart from its slabs (start, first slab, epilogue); slab_us: a slab
+// with every CU busy, two workgroups to a CU in the second figure where two fit.  The figures are a fit to 5000 timings on
+// this GPU (65-4337 rows x the projections of a Llama-3-8B- and a Qwen3-32B-shaped layer x every tile x 1-12 slices; the
+// fit is 7-11 % off on average), see gemm_plan.
+struct TileShape { int bm, bn, per_cu; float first_us, slab_us, slab2_us; };
+constexpr TileShape kTileShape[TILE_KINDS] = {
+    {0, 0, 0, 0.f, 0.f, 0.f},
+    {64, 128, 2, 2.0f, 0.48f, 0.77f},
+    {128, 128, 1, 3.8f, 0.60f, 0.f},
+    {192, 128, 1, 4.7f, 0.77f, 0.f},
+    {256, 256, 1, 7.8f, 1.65f, 0.f},
+    {192, 256, 1, 10.2f, 1.26f, 0.f},
+    {160, 256, 1, 9.3f, 1.13f, 0.f},
+};
 
 int n_tiles_for(const GemmArgs &g, int bm, int bn) {
     int m_tiles = (g.R + bm - 1) / bm, n_tiles = 0;
@@ -495,27 +485,57 @@ int n_tiles_for(const GemmArgs &g, int bm, int bn) {
     return m_tiles * n_tiles;
 }
 
-int pick_tile_unchecked(const GemmArgs &g) {
-    if (g.tile > 0 && g.tile < TILE_KINDS) return g.tile;
-    if (g.R >= 1024 && n_tiles_for(g, 256, 256) >= 192) return TILE_256x256_K64;  // enough large tiles for 256 CUs
-    if (g.R <= 64) return TILE_64x128;
-    if (g.R <= 128) return TILE_128;
-    if (g.mode == GEMM_DUAL && g.R > 192 && g.R <= 256) return TILE_256x128;
-    if (g.R <= 384) {
-        if (g.mode != GEMM_DUAL) return TILE_192x128_N3;
-        // The fused gate/up GEMM cannot split K.  Two 192 x 128 workgroups per CU, or, when that still fills the chip,
-        // one 192 x 256 workgroup of 8 waves: the activation slab is written to LDS once for both halves (4 % faster).
-        return n_tiles_for(g, 192, 256) >= 192 ? TILE_192x256_W8 : TILE_192x128_N2;
-    }
-    return TILE_128;
+bool is_register_staged(int kind) { return kind >= TILE_REG_192x256; }
+
+int k_ext_of(const GemmArgs &g) {
+    if (g.mode == GEMM_DUAL) return g.K + (g.T ? 2 * g.M_models * g.r : 0);
+    return g.K + ((g.T && g.B[0]) ? g.M_models * g.r : 0);
 }
 
-int pick_tile(const GemmArgs &g) {
-    int kind = pick_tile_unchecked(g);
-    return g.K % kTileShape[kind].bk ? TILE_128 : kind;  // K is a multiple of 64 at least
+// Modelled time of a launch, in us: rounds of workgroups over the 256 CUs; a round that leaves CUs idle has faster slabs.
+float model_us(const GemmArgs &g, int kind, int splits) {
+    const TileShape &t = kTileShape[kind];
+    const int slabs = (k_ext_of(g) + kKAlign - 1) / kKAlign, per_slice = (slabs + splits - 1) / splits;
+    const int64_t wgs = (int64_t)n_tiles_for(g, t.bm, t.bn) * splits;
+    auto round = [&](int64_t n) {
+        if (n == 0) return 0.f;
+        const float per = (float)n / 256.f;
+        return t.first_us + (float)per_slice * (per > 1.f ? t.slab2_us : t.slab_us) * (0.75f + 0.25f * std::min(1.f, per));
+    };
+    return (float)(wgs / (256 * t.per_cu)) * round(256 * t.per_cu) + round(wgs % (256 * t.per_cu));
 }
 
 }  // namespace
+
+// Panels of the XCD-aware tile order (see k_gemm_mfma) for bm x bn tiles, per_cu workgroups to a CU.  The panels of all
+// K slices are dealt to the 8 XCDs in turn, so what an XCD gets is a whole number of panels: the shape is the one that
+// keeps the fullest XCD's workgroups within the fewest rounds of its 32 CUs, and among those the one that streams the
+// fewest bytes per tile through the XCD's L2.  (With panels always as large as the grid allows, 20 column tiles in 12
+// slices made 10 panels, two for two of the XCDs and one for the others; 9 row tiles made panels of 8 and 1 rows, which
+// alternate over the XCDs: 144 rows, 25600 -> 5120 in 160 x 256 tiles 102 us -> 70 us; 2100 rows, gate/up
+// 14336 x 2 in 256 x 256 tiles 579 -> 442 us.)
+void gemm_set_panels(GemmArgs *g, int bm, int bn, int per_cu) {
+    const int Mt = g->m_tiles, Nt = g->n_tiles, splits = std::max(1, g->splits), cap = 32 * per_cu;
+    float best = 0.f;
+    g->panel_m = 0;
+    for (int m = 1; m <= std::min(Mt, 8); ++m) {
+        const int pms = (Mt + m - 1) / m, pm = (Mt + pms - 1) / pms;
+        if (pm != m) continue;  // the same height is reached with a smaller m
+        for (int n = 1; n <= std::min(Nt, 32 / m); ++n) {
+            const int pns = (Nt + n - 1) / n, pn = (Nt + pns - 1) / pns;
+            if (pn != n) continue;
+            const int64_t fullest = ((int64_t)pms * pns * splits + 7) / 8 * (pm * pn);
+            const float load = (float)fullest / (float)cap;  // a last round that is only partly filled is also a faster one
+            const float rounds = fullest <= cap ? load : 0.5f * (load + (float)((fullest + cap - 1) / cap));
+            const float bytes = (float)(pm * bm + pn * bn) / (float)((bm + bn) * pm * pn);  // of a tile on its own
+            const float score = rounds * (1.f + 0.5f * bytes);
+            if (!g->panel_m || score < best) {
+                best = score;
+                g->panel_m = pm; g->panel_n = pn; g->panels_m = pms; g->n_panels = pms * pns;
+            }
+        }
+    }
+}
 
 bool gemm_mfma_supported(const Dims &dm, int K) {
     bool r_ok = dm.r == 0 || (dm.r >= 8 && (dm.r & (dm.r - 1)) == 0);  // adapter rank: a power of two >= 8
@@ -524,45 +544,63 @@ bool gemm_mfma_supported(const Dims &dm, int K) {
     return dm.bf16 && K % kKAlign == 0 && r_ok && n_ok;
 }
 
-// Batches of a few hundred rows against a wide weight matrix (enough 192 x 256 tiles to fill the chip without
-// splitting K: the fused gate/up projection, an LM head) take the register-staged decode kernel.  Narrow
-// projections stay on the smaller LDS-direct tiles of this file: with 192 x 128 tiles they need half as many
-// split-K slices, and the slices' fp32 partial sums are what their epilogues spend their time writing.
-bool gemm_uses_decode(const GemmArgs &g) {
-    return g.R > 128 && g.R < 1024 && g.tile == 0 && gemm_decode_supported(g) && gemm_decode_tiles(g) >= 160;
-}
-
-int gemm_mfma_max_splits(const GemmArgs &g) {
-    if (gemm_uses_decode(g)) return std::max(1, gemm_decode_slabs(g) / 8);
-    int k_ext = g.K + ((g.T && g.B[0]) ? g.M_models * g.r : 0);
-    return std::max(1, k_ext / 256);
-}
-
-int gemm_mfma_tiles(const GemmArgs &g) {
-    if (gemm_uses_decode(g)) return gemm_decode_tiles(g);
-    int t = pick_tile(g);
-    return n_tiles_for(g, kTileShape[t].bm, kTileShape[t].bn);
+// Tile and number of K slices of a GEMM.
+//
+// Up to 64 rows the weights' way from HBM is what counts: one row tile, and so many slices that about one workgroup per
+// CU streams them (more slices were measured: their partial sums cost more than the depth in flight brings).
+//
+// Beyond that the choice is the smallest modelled time over the tiles and slice counts (model_us + the partial sums'
+// way through memory and, where no later kernel takes the slices as they are, a launch).  Over the 96 shapes of the
+// timings the choice is within 0.8 % of the fastest on average, 10 % at worst; one tile for each range of row counts
+// was 17 % off on average, and up to 62 % between 400 and 2000 rows, where it had 128 x 128 tiles (512 rows,
+// 25600 -> 5120: 233 us, now 144 us in 256 x 256 tiles and 6 slices; 753 rows, 14336 -> 4096: 134 -> 97 us; 4337 rows,
+// 14336 -> 4096, whose 272 tiles of 256 x 256 need two rounds of 256 CUs: 616 -> 486 us in 160 x 256 tiles).
+GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices) {
+    int n_total = 0;
+    for (int s = 0; s < g.nseg; ++s) n_total += g.n_seg[s];
+    const int slabs = (k_ext_of(g) + kKAlign - 1) / kKAlign;
+    if (g.R <= 64) {
+        const int tiles = n_tiles_for(g, kTileShape[TILE_64x128].bm, kTileShape[TILE_64x128].bn);
+        int splits = tiles < 160 ? std::min({max_splits, 256 / tiles, slabs / 4}) : 1;
+        return {TILE_64x128, std::max(1, splits)};
+    }
+    GemmPlan best{TILE_128, 1};
+    float best_us = -1.f;
+    const bool reg_ok = gemm_decode_supported(g);
+    for (int kind = 1; kind < TILE_KINDS; ++kind) {
+        if (is_register_staged(kind) && !reg_ok) continue;
+        if (kind == TILE_64x128 && g.R > 3 * 64) continue;  // weights from HBM: re-read for every row tile (the timings had them cached)
+        for (int splits = 1; splits <= max_splits; ++splits) {
+            if (splits > 1) {
+                const int per = (slabs + splits - 1) / splits;
+                if (per < 6) break;
+                if ((slabs + per - 1) / per != splits) continue;  // the last slice would be empty
+            }
+            float us = model_us(g, kind, splits);
+            if (splits > 1) {
+                const float mb = (float)g.R * (float)n_total * 4e-6f;  // one slice
+                us += mb * splits * (0.11f + 0.2f) + (takes_slices ? 0.f : 4.f + mb * 0.2f);
+            }
+            if (best_us < 0.f || us < best_us) { best_us = us; best = {kind, splits}; }
+        }
+    }
+    return best;
 }
 
 hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st) {
     if (g.R <= 0) return hipSuccess;
-    if (gemm_uses_decode(g)) return launch_gemm_decode(g, st);
-    if (g.mode == GEMM_DUAL)
-        g.K_ext = g.K + (g.T ? 2 * g.M_models * g.r : 0);
-    else
-        g.K_ext = g.K + ((g.T && g.B[0]) ? g.M_models * g.r : 0);
+    if (g.K % kKAlign) return hipErrorInvalidValue;
     if (g.splits < 1) g.splits = 1;
-    const int kind = pick_tile(g), bk = kTileShape[kind].bk;
-    if (g.K % bk) return hipErrorInvalidValue;
-    g.k_per_split = ((g.K_ext + g.splits - 1) / g.splits + bk - 1) / bk * bk;
-    switch (kind) {
-    case TILE_256x128: return launch_cfg<256, 128, 32, 4, 2, 2>(g, st);
-    case TILE_256x256_K64: return launch_cfg<256, 256, 64, 2, 2, 4>(g, st);
-    case TILE_192x128_N3: return launch_cfg<192, 128, 64, 3, 2, 2>(g, st);
-    case TILE_192x128_N2: return launch_cfg<192, 128, 64, 2, 2, 2>(g, st);
+    if (g.tile == TILE_AUTO) g.tile = gemm_plan(g, 1, false).tile;
+    if (is_register_staged(g.tile)) return launch_gemm_decode(g, st);
+    g.K_ext = k_ext_of(g);
+    g.k_per_split = ((g.K_ext + g.splits - 1) / g.splits + kKAlign - 1) / kKAlign * kKAlign;
+    switch (g.tile) {
     case TILE_64x128: return launch_cfg<64, 128, 64, 3, 2, 2>(g, st);
-    case TILE_192x256_W8: return launch_cfg<192, 256, 64, 2, 2, 4>(g, st);
-    default: return launch_cfg<128, 128, 64, 4, 2, 2>(g, st);
+    case TILE_128: return launch_cfg<128, 128, 64, 4, 2, 2>(g, st);
+    case TILE_192x128: return launch_cfg<192, 128, 64, 3, 2, 2>(g, st);
+    case TILE_256x256: return launch_cfg<256, 256, 64, 2, 2, 4>(g, st);
+    default: return hipErrorInvalidValue;
     }
 }
 

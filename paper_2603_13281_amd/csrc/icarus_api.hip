@@ -664,18 +664,19 @@ bool layer_mfma_supported(const icarus_ctx *ctx) {
            gemm_mfma_supported(ctx->dm, c.d_ffn) && shrink_ok;
 }
 
-// One plain ICaRusLinear GEMM.  When its grid would leave most of the chip idle (few rows and a
+// One plain ICaRusLinear GEMM.  Where its grid would leave most of the chip idle (few rows and a
 // narrow output), K is split over several workgroups into fp32 partials [splits][R][N]; a second
 // small kernel sums them and applies the epilogue, unless the caller takes the slices as they are
 // (deferred_splits: set to the number of slices left in the workspace, 0 if the output is final).
 icarus_status run_gemm(icarus_ctx *ctx, char *ws, const WsLayout &L, int phase, GemmArgs g, hipStream_t st,
                        int *deferred_splits = nullptr) {
-    int tiles = gemm_mfma_tiles(g);
     int n_total = 0;
     for (int s = 0; s < g.nseg; ++s) n_total += g.n_seg[s];
-    int splits = 1;
-    if (tiles < 160) splits = std::max(1, std::min({kGemmMaxSplits, 256 / tiles, gemm_mfma_max_splits(g)}));
-    splits = (int)std::max<size_t>(1, std::min<size_t>(splits, L.gemm_part_bytes / ((size_t)g.R * n_total * 4)));
+    const bool takes_slices = deferred_splits && n_total == g.ldy;
+    const int max_splits = (int)std::max<size_t>(1, std::min<size_t>(kGemmMaxSplits, L.gemm_part_bytes / ((size_t)g.R * n_total * 4)));
+    const GemmPlan plan = gemm_plan(g, max_splits, takes_slices);
+    const int splits = plan.splits;
+    g.tile = plan.tile;
     if (deferred_splits) *deferred_splits = 0;
     if (splits == 1) {
         g.splits = 1;
@@ -685,7 +686,7 @@ icarus_status run_gemm(icarus_ctx *ctx, char *ws, const WsLayout &L, int phase, 
     GemmArgs p = g;
     p.epi = EPI_F32; p.Y = ws + L.gemm_part; p.ldy = n_total; p.splits = splits;
     PHASE(ctx, st, phase, launch_gemm_mfma(p, st));
-    if (deferred_splits && n_total == g.ldy) {  // the consumer sums the slices [splits][R][n_total] itself
+    if (takes_slices) {  // the consumer sums the slices [splits][R][n_total] itself
         *deferred_splits = splits;
         return ICARUS_OK;
     }

@@ -89,6 +89,7 @@ struct AttnPlan {
 // ICaRusLinear GEMM on matrix cores.  Y = X W^T (+ T Bcat^T), see gemm_mfma.hip.
 enum { GEMM_PLAIN = 0, GEMM_DUAL = 1 };          // DUAL: W[0] = gate, W[1] = up, Y = silu(gate) * up
 enum { EPI_F32 = 0, EPI_BF16_RESID = 1 };        // plain epilogues (DUAL always stores bf16)
+enum TileKind { TILE_AUTO = 0, TILE_64x128, TILE_128, TILE_192x128, TILE_256x256, TILE_REG_192x256, TILE_REG_160x256, TILE_KINDS };
 struct GemmArgs {
     const bf16_raw *X; int ldx; int R; int K;    // activations [R, K] (row stride ldx)
     const bf16_raw *W[3]; int n_seg[3]; int nseg; // weight segments stacked along N, each [n_seg, K]
@@ -98,22 +99,37 @@ struct GemmArgs {
     void *Y; int ldy;                            // EPI_F32: float [splits][R][ldy]; else bf16 [R][ldy]
     const bf16_raw *resid; int ldr;              // EPI_BF16_RESID: added to the result
     int splits;                                  // split-K slices (EPI_F32 without adapters only)
-    int tile;                                    // tile kind, 0 = chosen by the launcher
+    int tile;                                    // tile kind (TILE_AUTO: chosen by the launcher)
     // filled by the launcher
     int tiles_seg[3]; int m_tiles, n_tiles, K_ext, k_per_split;
-    int run, panel_m, panel_n, panels_m, n_panels;  // tile order: panels of panel_m x panel_n <= run tiles
+    int panel_m, panel_n, panels_m, n_panels;       // tile order: panels of panel_m x panel_n tiles (n_panels per K slice)
     int slabs_per_split;                            // decode kernel: 64-wide K slabs per split-K slice
 };
 bool gemm_mfma_supported(const Dims &dm, int K);
+// fills the tile order from m_tiles, n_tiles and splits, for bm x bn tiles and per_cu workgroups to a CU
+void gemm_set_panels(GemmArgs *g, int bm, int bn, int per_cu);
+// workgroups of the launch: whole panels for each of the 8 XCDs
+inline unsigned gemm_grid(const GemmArgs &g) {
+    return (unsigned)((g.n_panels * g.splits + 7) / 8 * 8 * (g.panel_m * g.panel_n));
+}
+// tile and K slice of workgroup `id`; false: none
+__device__ __forceinline__ bool tile_of_workgroup(const GemmArgs &g, int id, int *tile_m, int *tile_n, int *kz) {
+    const int area = g.panel_m * g.panel_n, s = id >> 3;
+    const int p = (s / area) * 8 + (id & 7), within = s % area;
+    *kz = p / g.n_panels;
+    const int panel = p % g.n_panels;
+    *tile_m = (panel % g.panels_m) * g.panel_m + within % g.panel_m;
+    *tile_n = (panel / g.panels_m) * g.panel_n + within / g.panel_m;
+    return *kz < g.splits && *tile_m < g.m_tiles && *tile_n < g.n_tiles;
+}
 hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st);
-int gemm_mfma_tiles(const GemmArgs &g);  // workgroups of one K slice
-int gemm_mfma_max_splits(const GemmArgs &g);  // most split-K slices worth launching (each keeps a pipeline's worth of K)
-// The same contraction for decode-sized batches (gemm_decode.hip): both operands loaded coalesced, parked in registers
-// two slabs ahead and staged through LDS by register stores; launch_gemm_mfma takes this path when gemm_uses_decode.
-bool gemm_uses_decode(const GemmArgs &g);
+// How a GEMM is run: tile kind and split-K slices, at most max_splits (1 where K cannot be split: DUAL).  takes_slices: a
+// later kernel of the caller reads the slices as they are, no reduction is launched for them.
+struct GemmPlan { int tile, splits; };
+GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices);
+// Tiles of gemm_decode.hip (TILE_REG_*): both operands loaded coalesced, parked in registers two slabs ahead and staged
+// through LDS by register stores; launch_gemm_mfma takes this path for them.
 bool gemm_decode_supported(const GemmArgs &g);
-int gemm_decode_tiles(const GemmArgs &g);
-int gemm_decode_slabs(const GemmArgs &g);
 hipError_t launch_gemm_decode(GemmArgs g, hipStream_t st);
 // Sum split-K partials P[splits][R][N] (fp32) and apply the epilogue `epi` into Y.
 hipError_t launch_splitk_reduce(const float *P, int splits, int R, int N, int epi, void *Y, int ldy, const void *resid,

@@ -422,3 +422,25 @@ def test_prefill_walks_cut_into_pieces(limit, fp8):
     got = layer.prefill_kv(dpool, torch.from_numpy(batch.block_tables).cuda(), pre, chunk, dev(x, True))
     torch.cuda.synchronize()
     assert_close(host(got), want, 2e-2, "prefill x_out")
+
+
+@pytest.mark.parametrize("rows", [65, 129, 161, 250, 321, 449, 577, 770, 1100])
+@pytest.mark.parametrize("d_ffn", [4096, 8256])
+def test_prefill_row_counts_over_the_gemm_tiles(rows, d_ffn):
+    # every tile kind and slice count that the GEMM plan reaches at these widths, plain, with residual and gate/up: row
+    # counts one past a tile edge or well inside, a ragged last column tile (8256 outputs), panels that do not divide
+    _say("case: prefill rows", rows, "d_ffn", d_ffn)
+    shape = synth.LLAMA_SMALL.replace(d_model=1024, d_ffn=d_ffn)
+    base = synth.make_base(shape, seed=23, norm_ones=False)
+    pre, chunk = [40, 0], [rows - 20, 20]
+    batch = synth.make_batch(shape, pre, [0, 0], seed=23, headroom=max(chunk))
+    pool = filled_batch(shape, batch, seed=23)
+    x = synth.make_hidden(shape, rows, seed=23, tag=5)
+    dpool = dev(pool_to_device_layout(pool), True)
+    want, _ = oracle.Oracle(oracle_config(shape, batch.num_blocks), base, None).prefill(pool, batch.block_tables, pre, chunk, x)
+    layer = make_layer(shape, base, None, batch.num_blocks)
+    got = layer.prefill_kv(dpool, torch.from_numpy(batch.block_tables).cuda(), pre, chunk, dev(x, True))
+    torch.cuda.synchronize()
+    assert_close(host(got), want, 2e-2, "prefill x_out")
+    got_pool = pool_from_device_layout(host(dpool), shape.block_size, shape.head_dim)
+    _cache_close(shape, got_pool, pool, "prefill cache")
