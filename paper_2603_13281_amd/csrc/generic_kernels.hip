@@ -307,14 +307,43 @@ hipError_t launch_rope_append(const Dims &dm, const float *qkv, int ldq, int spl
 }
 
 // ------------------------------------------------------------------ attention (one block per row and query head)
-// Online softmax over chunks of 1024 cached positions; thread d < D owns output element d.
+// four consecutive cache elements (aligned to four elements)
+template <typename KT> struct KVElem4;
+template <> struct KVElem4<float> {
+    static __device__ __forceinline__ void ld(const float *p, float, float (&f)[4]) {
+        const float4 v = *(const float4 *)p;
+        f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+    }
+};
+template <> struct KVElem4<bf16_t> {
+    static __device__ __forceinline__ void ld(const bf16_t *p, float, float (&f)[4]) {
+        const uint2 v = *(const uint2 *)p;
+        f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
+        f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
+    }
+};
+template <> struct KVElem4<fp8_t> {
+    static __device__ __forceinline__ void ld(const fp8_t *p, float scale, float (&f)[4]) {
+        const uint32_t v = *(const uint32_t *)p;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e] = fp8_to_f32((v >> (8 * e)) & 0xffu) * scale;
+    }
+};
+
+// Online softmax over chunks of 1024 cached positions.  Scores: a thread per position.  Output: thread (part, d) adds
+// every parts-th quad of positions to output element d; V^T rows hold a block's tokens side by side, so a quad is
+// one load, and 256 / D parts (D rounded up to a power of two) keep all threads on it.  Latency-bound at the sizes
+// this kernel is for: with one element and one position at a time, 128 positions x 64 dims took 20.5 us, now 8.6 us.
+// quads: D and Bk are multiples of 4 (else one element, one position at a time).
 template <typename T, typename KT>
 __global__ void __launch_bounds__(256) k_attn_generic(const T *__restrict__ q, const KT *__restrict__ pool,
                                                       const int32_t *__restrict__ bt, int max_blocks,
                                                       const int32_t *__restrict__ row_seq, const int32_t *__restrict__ row_kvlen,
                                                       T *__restrict__ out, int Hq, int Hkv, int D, int Bk, float scale,
-                                                      float k_scale, float v_scale) {
+                                                      float k_scale, float v_scale, int parts, int quads) {
     __shared__ float sc[1024];
+    __shared__ int sblk[1024];
+    __shared__ float sum[256];
     __shared__ float red[16];
     extern __shared__ float qs[];  // [D]
     int row = blockIdx.y, h = blockIdx.x;
@@ -323,16 +352,29 @@ __global__ void __launch_bounds__(256) k_attn_generic(const T *__restrict__ q, c
     const int32_t *btr = bt + (size_t)s * max_blocks;
     for (int i = threadIdx.x; i < D; i += 256) qs[i] = Elem<T>::ld(q + ((size_t)row * Hq + h) * D + i);
     __syncthreads();
+    const int width = 256 / parts, part = threadIdx.x / width, d = threadIdx.x % width;
     size_t head_stride = (size_t)2 * Bk * D, blk_stride = (size_t)Hkv * head_stride;
+    const KT *head = pool + (size_t)c * head_stride;
     float m = -INFINITY, l = 0.f, acc = 0.f;
     for (int c0 = 0; c0 < n; c0 += 1024) {
         int cnt = min(1024, n - c0);
         float lmax = -INFINITY;
         for (int t = threadIdx.x; t < cnt; t += 256) {
             int tok = c0 + t;
-            const KT *kr = pool + (size_t)btr[tok / Bk] * blk_stride + (size_t)c * head_stride + (size_t)(tok % Bk) * D;
+            const int blk = btr[tok / Bk];
+            sblk[t] = blk;
+            const KT *kr = head + (size_t)blk * blk_stride + (size_t)(tok % Bk) * D;
             float dot = 0.f;
-            for (int i = 0; i < D; ++i) dot += qs[i] * KVElem<KT>::ld(kr + i, k_scale);
+            if (quads) {
+                for (int i = 0; i < D; i += 4) {
+                    float kv[4];
+                    KVElem4<KT>::ld(kr + i, k_scale, kv);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) dot += qs[i + e] * kv[e];
+                }
+            } else {
+                for (int i = 0; i < D; ++i) dot += qs[i] * KVElem<KT>::ld(kr + i, k_scale);
+            }
             dot *= scale;
             sc[t] = dot;
             lmax = fmaxf(lmax, dot);
@@ -345,34 +387,49 @@ __global__ void __launch_bounds__(256) k_attn_generic(const T *__restrict__ q, c
             sc[t] = p;
             lsum += p;
         }
-        float csum = block_sum(lsum, red);  // barriers inside also publish sc[]
+        float csum = block_sum(lsum, red);  // barriers inside also publish sc[] and sblk[]
         float alpha = (m == -INFINITY) ? 0.f : __expf(m - m_new);
         l = l * alpha + csum;
-        if (threadIdx.x < D) {
+        if (d < D) {
             float a = acc * alpha;
-            int d = threadIdx.x;
-            for (int t = 0; t < cnt; ++t) {
-                int tok = c0 + t;
-                const KT *vr = pool + (size_t)btr[tok / Bk] * blk_stride + (size_t)c * head_stride + (size_t)Bk * D;
-                a += sc[t] * KVElem<KT>::ld(vr + (size_t)d * Bk + (tok % Bk), v_scale);
+            const KT *vd = head + (size_t)Bk * D + (size_t)d * Bk;
+            if (quads) {
+#pragma unroll 4
+                for (int t = 4 * part; t + 3 < cnt; t += 4 * parts) {
+                    float v[4];
+                    KVElem4<KT>::ld(vd + (size_t)sblk[t] * blk_stride + (c0 + t) % Bk, v_scale, v);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) a += sc[t + e] * v[e];
+                }
+                if (part == 0)  // the last, partial quad: what lies past the context may be anything
+                    for (int t = cnt & ~3; t < cnt; ++t) a += sc[t] * KVElem<KT>::ld(vd + (size_t)sblk[t] * blk_stride + (c0 + t) % Bk, v_scale);
+            } else {
+                for (int t = part; t < cnt; t += parts) a += sc[t] * KVElem<KT>::ld(vd + (size_t)sblk[t] * blk_stride + (c0 + t) % Bk, v_scale);
             }
             acc = a;
         }
         m = m_new;
         __syncthreads();
     }
-    if (threadIdx.x < D)
+    sum[threadIdx.x] = acc;
+    __syncthreads();
+    if (threadIdx.x < D) {
+        for (int p = 1; p < parts; ++p) acc += sum[p * width + threadIdx.x];
         Elem<T>::st(out + ((size_t)row * Hq + h) * D + threadIdx.x, l > 0.f ? acc / l : 0.f);
+    }
 }
 
 hipError_t launch_attn_generic(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
                                const RowMeta &rm, void *out, int R, hipStream_t st) {
     if (R <= 0) return hipSuccess;
     float scale = 1.0f / sqrtf((float)dm.D);
+    int parts = 1;
+    while (256 / (2 * parts) >= dm.D) parts *= 2;
+    const int quads = dm.D % 4 == 0 && dm.Bk % 4 == 0;
     dim3 grid(dm.Hq, R);
     DISPATCH_TK(dm.bf16, dm.kv8, hipLaunchKernelGGL((k_attn_generic<T, KT>), grid, dim3(256), sizeof(float) * dm.D, st, (const T *)q,
                                                     (const KT *)pool, bt, max_blocks, rm.row_seq, rm.row_kvlen, (T *)out, dm.Hq, dm.Hkv,
-                                                    dm.D, dm.Bk, scale, dm.k_scale, dm.v_scale));
+                                                    dm.D, dm.Bk, scale, dm.k_scale, dm.v_scale, parts, quads));
     return hipGetLastError();
 }
 

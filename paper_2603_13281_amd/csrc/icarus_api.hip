@@ -872,6 +872,58 @@ icarus_status run_layer_full(icarus_ctx *ctx, char *ws, const WsLayout &L, const
     return ICARUS_OK;
 }
 
+// ---- a handful of rows on the vector kernels ---------------------------------------------
+icarus_status run_layer_skinny(icarus_ctx *ctx, char *ws, const WsLayout &L, const RowMeta &rm, const HostPlan *hp, int R, bool use_lora,
+                               bool kv_only, int slot_by_row, void *pool, const int32_t *bt, int max_blocks, const void *x_in, void *x_out,
+                               int64_t *slot_out, hipStream_t st) {
+    const icarus_layer_config &c = ctx->cfg;
+    const Dims &dm = ctx->dm;
+    const int d = c.d_model, qd = c.n_q_heads * c.head_dim, kvd = c.n_kv_heads * c.head_dim, F = c.d_ffn, ldq = qd + 2 * kvd;
+    void *xn = ws + L.xn, *q = ws + L.q, *attn = ws + L.attn, *z = ws + L.z, *h = ws + L.h;
+    float *qkv = (float *)(ws + L.qkv), *t = (float *)(ws + L.t);
+    auto lo = [&](int p) { return use_lora && has_lora(ctx, p); };
+    auto A = [&](int p) { return lo(p) ? ctx->lora.A[p] : nullptr; };
+    auto B = [&](int p) { return lo(p) ? ctx->lora.B[p] : nullptr; };
+    auto gemm = [&](int phase, int mode, const void *X, int K, int p0, int n0, int p1, int n1, int p2, int n2, const void *resid, void *Y,
+                    int ldy) -> icarus_status {
+        SkinnyGemm g{};
+        g.X = X; g.ldx = K; g.R = R; g.K = K; g.mode = mode; g.resid = resid; g.Y = Y; g.ldy = ldy;
+        const int p[3] = {p0, p1, p2}, n[3] = {n0, n1, n2};
+        for (int s = 0; s < 3; ++s)
+            if (p[s] >= 0) { g.W[s] = ctx->base.w[p[s]]; g.n[s] = n[s]; }
+        g.B[0] = B(p0); g.B[1] = mode == SKINNY_DUAL ? B(p1) : nullptr; g.t = t; g.row_model = rm.row_model;
+        PHASE(ctx, st, phase, launch_gemm_skinny(dm, g, st));
+        return ICARUS_OK;
+    };
+    // norm + shrink of the projections that read the normalised rows: a target without an adapter leaves its half of t unused
+    auto row = [&](int phase, const void *x, int K, const void *wn, void *y, int p0, int p1) -> icarus_status {
+        const void *A0 = p0 >= 0 ? A(p0) : nullptr, *A1 = p1 >= 0 ? A(p1) : nullptr;
+        if (!A0 && A1) {  // the second target alone: its t is the second half
+            PHASE(ctx, st, phase, launch_row_generic(dm, x, K, K, wn, y, nullptr, nullptr, rm.row_model, t, R, st));
+            PHASE(ctx, st, ICARUS_PH_LORA, launch_row_generic(dm, y, K, K, nullptr, nullptr, A1, nullptr, rm.row_model, t + (size_t)R * dm.r, R, st));
+            return ICARUS_OK;
+        }
+        PHASE(ctx, st, phase, launch_row_generic(dm, x, K, K, wn, y, A0, A1, rm.row_model, t, R, st));
+        return ICARUS_OK;
+    };
+    LORA_TRY(row(ICARUS_PH_NORM, x_in, d, ctx->base.norm_attn, xn, kv_only ? -1 : ICARUS_PROJ_Q, -1));
+    if (kv_only)  // K and V carry no adapter
+        LORA_TRY(gemm(ICARUS_PH_GEMM_QKV, SKINNY_F32, xn, d, ICARUS_PROJ_K, kvd, ICARUS_PROJ_V, kvd, -1, 0, nullptr, qkv + qd, ldq));
+    else
+        LORA_TRY(gemm(ICARUS_PH_GEMM_QKV, SKINNY_F32, xn, d, ICARUS_PROJ_Q, qd, ICARUS_PROJ_K, kvd, ICARUS_PROJ_V, kvd, nullptr, qkv, ldq));
+    PHASE(ctx, st, ICARUS_PH_ROPE_APPEND, launch_rope_append(dm, qkv, ldq, 1, 0, rm, bt, max_blocks, pool, q, slot_out, slot_by_row,
+                                                             ctx->base.q_norm, ctx->base.k_norm, R, st));
+    if (kv_only) return ICARUS_OK;
+    LORA_TRY(run_decode_attention(ctx, ws, L, rm, hp, q, pool, bt, max_blocks, attn, R, st));
+    if (lo(ICARUS_PROJ_O)) LORA_TRY(row(ICARUS_PH_LORA, attn, qd, nullptr, nullptr, ICARUS_PROJ_O, -1));
+    LORA_TRY(gemm(ICARUS_PH_GEMM_O, SKINNY_RESID, attn, qd, ICARUS_PROJ_O, d, -1, 0, -1, 0, x_in, z, d));
+    LORA_TRY(row(ICARUS_PH_NORM, z, d, ctx->base.norm_ffn, xn, ICARUS_PROJ_GATE, ICARUS_PROJ_UP));
+    LORA_TRY(gemm(ICARUS_PH_GEMM_GATEUP, SKINNY_DUAL, xn, d, ICARUS_PROJ_GATE, F, ICARUS_PROJ_UP, F, -1, 0, nullptr, h, F));
+    if (lo(ICARUS_PROJ_DOWN)) LORA_TRY(row(ICARUS_PH_LORA, h, F, nullptr, nullptr, ICARUS_PROJ_DOWN, -1));
+    LORA_TRY(gemm(ICARUS_PH_GEMM_DOWN, SKINNY_RESID, h, F, ICARUS_PROJ_DOWN, d, -1, 0, -1, 0, z, x_out, d));
+    return ICARUS_OK;
+}
+
 // Whether run_layer would take rows that are still in pieces (split-K slices + residual) as its input: only the
 // matrix-core path forms its rows in its first row kernel.
 bool layer_takes_slices(icarus_ctx *ctx, bool use_lora) {
@@ -897,6 +949,8 @@ icarus_status run_layer(icarus_ctx *ctx, char *ws, const WsLayout &L, const RowM
                                   in_splits, out_splits);
     }
     if (in_splits > 0) return fail(ctx, ICARUS_ERR_UNSUPPORTED, "input rows in pieces need the matrix-core path");
+    if (R <= kSkinnyRows)
+        return run_layer_skinny(ctx, ws, L, rm, hp, R, use_lora, kv_only, slot_by_row, pool, bt, max_blocks, x_in, x_out, slot_out, st);
     const icarus_layer_config &c = ctx->cfg;
     const Dims &dm = ctx->dm;
     int d = c.d_model, qd = c.n_q_heads * c.head_dim, kvd = c.n_kv_heads * c.head_dim, F = c.d_ffn;
@@ -1163,7 +1217,14 @@ icarus_status run_stack(icarus_stack *st, char *ws, const StackLayout &SL, const
         STACK_TRY(launch_gemm_mfma(g, s));
     } else {
         STACK_TRY(launch_rmsnorm(dm, xh, st->final_norm, xn, n_head, dm.d, s));
-        STACK_TRY(launch_gemm_generic(dm, xn, dm.d, st->lm_head, n_head, st->vocab, dm.d, lg, st->vocab, s));
+        if (n_head <= kSkinnyRows) {
+            SkinnyGemm g{};
+            g.X = xn; g.ldx = dm.d; g.R = n_head; g.K = dm.d; g.W[0] = st->lm_head; g.n[0] = st->vocab;
+            g.Y = lg; g.ldy = st->vocab; g.mode = SKINNY_F32;
+            STACK_TRY(launch_gemm_skinny(dm, g, s));
+        } else {
+            STACK_TRY(launch_gemm_generic(dm, xn, dm.d, st->lm_head, n_head, st->vocab, dm.d, lg, st->vocab, s));
+        }
     }
     // the normed rows are dead once the logits exist: their buffer takes the argmax partials
     if (argmax_scratch_bytes(n_head) > (size_t)n_head * row_bytes) return stack_fail(st, ICARUS_ERR_UNSUPPORTED, "d_model too small for the argmax scratch");

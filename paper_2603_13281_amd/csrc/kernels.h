@@ -53,6 +53,22 @@ hipError_t launch_rope_append(const Dims &dm, const float *qkv, int ldq, int spl
 hipError_t launch_attn_generic(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
                                const RowMeta &rm, void *out, int R, hipStream_t st);
 
+// ---- the same for at most kSkinnyRows rows (skinny_kernels.hip) ---------------------------------
+constexpr int kSkinnyRows = 16;
+enum { SKINNY_F32 = 0, SKINNY_RESID = 1, SKINNY_DUAL = 2 };  // float out; storage out + residual; silu(gate) * up, storage out
+struct SkinnyGemm {
+    const void *X; int ldx, R, K;             // storage type
+    const void *W[3]; int n[3];               // up to three weight segments [n, K] stacked along the outputs; DUAL: gate, up (n[0] each)
+    const void *B[2]; const float *t;         // adapter B [M, n[0], r] of segment 0 (DUAL: gate, up), t [targets][R][r]; null: none
+    const int32_t *row_model;
+    const void *resid; void *Y; int ldy;      // SKINNY_RESID: resid has the stride of Y
+    int mode;
+};
+hipError_t launch_gemm_skinny(const Dims &dm, const SkinnyGemm &g, hipStream_t st);
+// y = rmsnorm(x) * wn (wn != null) and, with A0, t[target][row][0..r) = lora_scale * A_target[model(row)] (y or x)
+hipError_t launch_row_generic(const Dims &dm, const void *x, int ldx, int K, const void *wn, void *y, const void *A0, const void *A1,
+                              const int32_t *row_model, float *t, int R, hipStream_t st);
+
 // plain grid-stride copy of `bytes` bytes (multiple of 16), kernel k_bench_copy: profiler calibration
 hipError_t launch_bench_copy(const void *src, void *dst, size_t bytes, hipStream_t st);
 // streaming read of `bytes` bytes (whole 8 KB chunks) by kernel k_bench_read: the read rate HBM sustains; out: one word

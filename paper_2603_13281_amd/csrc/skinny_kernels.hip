@@ -1,0 +1,230 @@
+// Vector kernels of the layer step for a handful of rows: any shape, storage type float32 or bfloat16, fp32 accumulation.
+//
+// With up to kSkinnyRows rows a projection is a few mat-vecs, and what bounds it is latency, not bytes or arithmetic:
+// the 64 x 64 tiles of the many-row kernel put a 256-wide layer's projections on 4-11 workgroups, each of which walks K
+// sixteen at a time between two barriers (32-94 us a projection, 340 us a step of 3 rows).  Here a wave owns a few
+// output columns and all rows: its 64 lanes split K in 16-byte pieces, so a column of 1024 bytes is one load per lane,
+// and the sums meet in registers.  The adapter delta, the residual and the SwiGLU product are added where the sum
+// is, and one launch serves the projections that read the same rows: 9 launches for that step instead of 18, 4-5 us
+// each, which is what a dependent launch takes here (49 us a step).
+#include "device_util.h"
+#include "kernels.h"
+
+#include <type_traits>
+
+namespace icarus {
+
+namespace {
+
+// 16 bytes of storage elements as floats
+template <typename T> struct Vec16;
+template <> struct Vec16<float> {
+    static constexpr int N = 4;
+    static __device__ __forceinline__ void ld(const float *p, float (&f)[4]) {
+        const float4 v = *(const float4 *)p;
+        f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+    }
+};
+template <> struct Vec16<bf16_t> {
+    static constexpr int N = 8;
+    static __device__ __forceinline__ void ld(const bf16_t *p, float (&f)[8]) {
+        const uint4 v = *(const uint4 *)p;
+        f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
+        f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
+        f[4] = __uint_as_float(v.z << 16); f[5] = __uint_as_float(v.z & 0xffff0000u);
+        f[6] = __uint_as_float(v.w << 16); f[7] = __uint_as_float(v.w & 0xffff0000u);
+    }
+};
+// one element at a time: rows that are not whole 16-byte pieces
+template <typename T> struct Vec1 {
+    static constexpr int N = 1;
+    static __device__ __forceinline__ void ld(const T *p, float (&f)[1]) { f[0] = Elem<T>::ld(p); }
+};
+
+// One workgroup per row: y = rmsnorm(x) * wn (NORM), and for a decoder row t[target][row][0..r) = scale * A[model] y (or
+// x) for up to two targets; a wave takes every fourth of the targets * r outputs.
+template <typename T, typename V, bool NORM>
+__global__ void __launch_bounds__(256) k_row_generic(const T *__restrict__ x, int ldx, int K, const T *__restrict__ wn, float eps,
+                                                     T *__restrict__ y, const T *__restrict__ A0, const T *__restrict__ A1, int r,
+                                                     const int32_t *__restrict__ row_model, float scale, float *__restrict__ t, int R) {
+    __shared__ float red[16];
+    const int row = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const T *xr = x + (size_t)row * ldx;
+    if (NORM) {
+        float ss = 0.f;
+        for (int k = threadIdx.x * V::N; k < K; k += 256 * V::N) {
+            float f[V::N];
+            V::ld(xr + k, f);
+#pragma unroll
+            for (int e = 0; e < V::N; ++e) ss += f[e] * f[e];
+        }
+        ss = block_sum(ss, red);
+        const float inv = rsqrtf(ss / (float)K + eps);
+        T *yr = y + (size_t)row * K;
+        for (int k = threadIdx.x; k < K; k += 256) Elem<T>::st(yr + k, Elem<T>::ld(xr + k) * inv * Elem<T>::ld(wn + k));
+        __syncthreads();  // the shrink reads the row as stored, from this workgroup's own stores
+        xr = yr;
+    }
+    const int j = A0 ? row_model[row] : -1;
+    if (j < 0) return;
+    const int n_out = (A1 ? 2 : 1) * r;
+    for (int o = w; o < n_out; o += 4) {
+        const T *a = (o < r ? A0 : A1) + ((size_t)j * r + (o < r ? o : o - r)) * K;
+        float acc = 0.f;
+        for (int k = lane * V::N; k < K; k += 64 * V::N) {
+            float f[V::N], g[V::N];
+            V::ld(xr + k, f);
+            V::ld(a + k, g);
+#pragma unroll
+            for (int e = 0; e < V::N; ++e) acc += f[e] * g[e];
+        }
+        acc = wave_sum(acc);
+        if (lane == 0) t[((size_t)(o < r ? 0 : 1) * R + row) * r + (o < r ? o : o - r)] = acc * scale;
+    }
+}
+
+// Y[R, N] = X W^T (+ the rows' adapter deltas), RM >= R rows.  A wave takes kCols columns; DUAL: kCols / 2 columns of the
+// gate and of the up projection.
+constexpr int kCols = 4;
+struct SkinnyArgs {
+    const void *X; int ldx, R, K;
+    const void *W[3]; int n_end[3];          // weight segments: columns [n_end[s - 1], n_end[s]) are rows of W[s]; DUAL: gate, up
+    const void *B[2]; const float *t; int r; // adapter of the first segment (DUAL: gate, up), t from k_row_generic; null: none
+    const int32_t *row_model;
+    const void *resid; void *Y; int ldy;     // SKINNY_F32: float Y; else storage Y (SKINNY_RESID: + resid, same stride)
+};
+
+template <typename T, typename V, int RM, int MODE>
+__global__ void __launch_bounds__(256) k_gemm_skinny(SkinnyArgs a) {
+    constexpr bool dual = MODE == SKINNY_DUAL;
+    constexpr int NO = dual ? kCols / 2 : kCols;  // output columns of a wave
+    const int lane = threadIdx.x & 63, N = a.n_end[dual ? 0 : 2];
+    const int n0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * NO;
+    if (n0 >= N) return;
+    const T *wrow[kCols];
+#pragma unroll
+    for (int c = 0; c < kCols; ++c) {
+        const int n = min(n0 + c % NO, N - 1);  // columns past the last are computed on it and dropped
+        if (dual) {
+            wrow[c] = (const T *)a.W[c / NO] + (size_t)n * a.K;
+        } else {
+            const int s = n < a.n_end[0] ? 0 : n < a.n_end[1] ? 1 : 2;
+            wrow[c] = (const T *)a.W[s] + (size_t)(n - (s ? a.n_end[s - 1] : 0)) * a.K;
+        }
+    }
+    float acc[kCols][RM];
+#pragma unroll
+    for (int c = 0; c < kCols; ++c)
+#pragma unroll
+        for (int m = 0; m < RM; ++m) acc[c][m] = 0.f;
+    const T *X = (const T *)a.X;
+    for (int k = lane * V::N; k < a.K; k += 64 * V::N) {
+        float wv[kCols][V::N];
+#pragma unroll
+        for (int c = 0; c < kCols; ++c) V::ld(wrow[c] + k, wv[c]);
+#pragma unroll
+        for (int m = 0; m < RM; ++m) {
+            float xv[V::N];
+            V::ld(X + (size_t)min(m, a.R - 1) * a.ldx + k, xv);
+#pragma unroll
+            for (int c = 0; c < kCols; ++c)
+#pragma unroll
+                for (int e = 0; e < V::N; ++e) acc[c][m] += wv[c][e] * xv[e];
+        }
+    }
+    // lane c * RM + m keeps sum (column c, row m)
+    float mine = 0.f, up = 0.f;
+#pragma unroll
+    for (int c = 0; c < kCols; ++c)
+#pragma unroll
+        for (int m = 0; m < RM; ++m) {
+            const float s = wave_sum(acc[c][m]);
+            if (c < NO) { if (lane == c * RM + m) mine = s; }
+            else if (lane == (c - NO) * RM + m) up = s;
+        }
+    const int c = lane / RM, row = lane % RM, n = n0 + c;
+    if (c >= NO || row >= a.R || n >= N) return;
+    const int j = a.t ? a.row_model[row] : -1;
+    if (j >= 0 && n < a.n_end[0]) {
+#pragma unroll
+        for (int d = 0; d < (dual ? 2 : 1); ++d) {
+            const T *b = (const T *)a.B[d];
+            if (!b) continue;
+            b += ((size_t)j * a.n_end[0] + n) * a.r;
+            const float *tr = a.t + ((size_t)d * a.R + row) * a.r;
+            float v = 0.f;
+            for (int i = 0; i < a.r; ++i) v += Elem<T>::ld(b + i) * tr[i];
+            (d ? up : mine) += v;
+        }
+    }
+    if (MODE == SKINNY_F32) ((float *)a.Y)[(size_t)row * a.ldy + n] = mine;
+    else if (MODE == SKINNY_RESID) Elem<T>::st((T *)a.Y + (size_t)row * a.ldy + n, Elem<T>::ld((const T *)a.resid + (size_t)row * a.ldy + n) + mine);
+    else Elem<T>::st((T *)a.Y + (size_t)row * a.ldy + n, mine / (1.f + __expf(-mine)) * up);
+}
+
+template <typename F>
+hipError_t with_type(bool bf16, bool vec, F f) {
+    if (bf16) return vec ? f(bf16_t(), Vec16<bf16_t>()) : f(bf16_t(), Vec1<bf16_t>());
+    return vec ? f(float(), Vec16<float>()) : f(float(), Vec1<float>());
+}
+
+bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
+bool whole_pieces(const Dims &dm, int n) { return n % (dm.bf16 ? 8 : 4) == 0; }
+
+}  // namespace
+
+hipError_t launch_row_generic(const Dims &dm, const void *x, int ldx, int K, const void *wn, void *y, const void *A0, const void *A1,
+                              const int32_t *row_model, float *t, int R, hipStream_t st) {
+    if (R <= 0 || (!wn && !A0)) return hipSuccess;
+    const bool vec = whole_pieces(dm, K) && whole_pieces(dm, ldx) && aligned16(x);
+    return with_type(dm.bf16, vec, [&](auto tt, auto vv) {
+        typedef decltype(tt) T;
+        typedef decltype(vv) V;
+        if (wn)
+            hipLaunchKernelGGL((k_row_generic<T, V, true>), dim3(R), dim3(256), 0, st, (const T *)x, ldx, K, (const T *)wn, dm.eps, (T *)y,
+                               (const T *)A0, (const T *)A1, dm.r, row_model, dm.lora_scale, t, R);
+        else
+            hipLaunchKernelGGL((k_row_generic<T, V, false>), dim3(R), dim3(256), 0, st, (const T *)x, ldx, K, (const T *)nullptr, dm.eps,
+                               (T *)nullptr, (const T *)A0, (const T *)A1, dm.r, row_model, dm.lora_scale, t, R);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_gemm_skinny(const Dims &dm, const SkinnyGemm &g, hipStream_t st) {
+    if (g.R <= 0) return hipSuccess;
+    if (g.R > kSkinnyRows) return hipErrorInvalidValue;
+    SkinnyArgs a{};
+    a.X = g.X; a.ldx = g.ldx; a.R = g.R; a.K = g.K;
+    const bool dual = g.mode == SKINNY_DUAL;
+    bool vec = whole_pieces(dm, g.K) && whole_pieces(dm, g.ldx) && aligned16(g.X);
+    int end = 0;
+    for (int s = 0; s < 3; ++s) {
+        a.W[s] = g.W[s];
+        if (g.W[s]) vec = vec && aligned16(g.W[s]);
+        if (!dual) end += g.n[s];
+        a.n_end[s] = dual ? g.n[0] : end;
+    }
+    a.B[0] = g.B[0]; a.B[1] = g.B[1]; a.t = (g.B[0] || g.B[1]) ? g.t : nullptr; a.r = dm.r; a.row_model = g.row_model;
+    a.resid = g.resid; a.Y = g.Y; a.ldy = g.ldy;
+    const int N = a.n_end[dual ? 0 : 2], per_wg = 4 * (dual ? kCols / 2 : kCols);
+    if (N <= 0) return hipSuccess;
+    const dim3 grid((N + per_wg - 1) / per_wg);
+    return with_type(dm.bf16, vec, [&](auto tt, auto vv) {
+        typedef decltype(tt) T;
+        typedef decltype(vv) V;
+        auto rows = [&](auto rm) {
+            constexpr int RM = decltype(rm)::value;
+            switch (g.mode) {
+            case SKINNY_F32: hipLaunchKernelGGL((k_gemm_skinny<T, V, RM, SKINNY_F32>), grid, dim3(256), 0, st, a); break;
+            case SKINNY_RESID: hipLaunchKernelGGL((k_gemm_skinny<T, V, RM, SKINNY_RESID>), grid, dim3(256), 0, st, a); break;
+            default: hipLaunchKernelGGL((k_gemm_skinny<T, V, RM, SKINNY_DUAL>), grid, dim3(256), 0, st, a); break;
+            }
+            return hipGetLastError();
+        };
+        if (g.R <= 4) return rows(std::integral_constant<int, 4>());
+        if (g.R <= 8) return rows(std::integral_constant<int, 8>());
+        return rows(std::integral_constant<int, 16>());
+    });
+}
+
+}  // namespace icarus

@@ -444,3 +444,42 @@ def test_prefill_row_counts_over_the_gemm_tiles(rows, d_ffn):
     assert_close(host(got), want, 2e-2, "prefill x_out")
     got_pool = pool_from_device_layout(host(dpool), shape.block_size, shape.head_dim)
     _cache_close(shape, got_pool, pool, "prefill cache")
+
+
+SKINNY_SHAPES = {
+    # whole 16-byte pieces; rows and heads that are not (one element at a time, blocks of 6 tokens); bf16 outside the matrix cores
+    "fp32": synth.TINY.replace(n_models=8, lora_target_mask=synth.ALL_TARGETS),
+    "fp32-odd": synth.TINY.replace(d_model=90, n_q_heads=6, n_kv_heads=2, head_dim=18, d_ffn=70, lora_rank=3, n_models=8, block_size=6,
+                                   lora_target_mask=synth.ALL_TARGETS),
+    "fp32-gate-only": synth.TINY.replace(n_models=8, lora_target_mask=0b0010000, n_q_heads=8, n_kv_heads=2, head_dim=32),
+    "bf16-d64": synth.LLAMA_SMALL.replace(d_model=256, head_dim=64, d_ffn=200, n_models=8),
+    "bf16-up-only": synth.LLAMA_SMALL.replace(d_model=256, head_dim=96, d_ffn=344, n_models=8, lora_target_mask=0b0100001),
+}
+
+
+@pytest.mark.parametrize("shape", list(SKINNY_SHAPES.values()), ids=list(SKINNY_SHAPES))
+@pytest.mark.parametrize("ctx,n_active", [([128], [2]), ([0, 37], [0, 3]), ([5, 1023, 1030, 2050], [1, 3, 0, 8]), ([3, 40], [6, 8]), ([70, 11], [8, 7])],
+                         ids=["r3", "r5", "r16", "r16b", "r17"])
+def test_decode_of_a_few_rows_on_vector_kernels(shape, ctx, n_active):
+    _say("case: few rows", shape.name, "d", shape.d_model, "ctx", ctx, "active", n_active)
+    _check_decode(shape, ctx, n_active, seed=29, mode=0)
+
+
+@pytest.mark.parametrize("shape", list(SKINNY_SHAPES.values()), ids=list(SKINNY_SHAPES))
+def test_prefill_of_a_few_rows_on_vector_kernels(shape):
+    _say("case: few rows prefill", shape.name)
+    base = synth.make_base(shape, seed=31, norm_ones=False)
+    pre, chunk = [33, 0], [6, 9]
+    batch = synth.make_batch(shape, pre, [0, 0], seed=31, headroom=16)
+    pool = filled_batch(shape, batch, seed=31)
+    mark_unwritten(shape, batch, pool, np.nan)
+    x = synth.make_hidden(shape, sum(chunk), seed=31, tag=5)
+    dpool, dpool2 = (dev(pool_to_device_layout(pool), shape.bf16) for _ in range(2))
+    want, _ = oracle.Oracle(oracle_config(shape, batch.num_blocks), base, None).prefill(pool, batch.block_tables, pre, chunk, x)
+    layer = make_layer(shape, base, None, batch.num_blocks)
+    bt = torch.from_numpy(batch.block_tables).cuda()
+    got = layer.prefill_kv(dpool, bt, pre, chunk, dev(x, shape.bf16))
+    layer.prefill_kv(dpool2, bt, pre, chunk, dev(x, shape.bf16), want_out=False)   # cache only: the same bytes
+    torch.cuda.synchronize()
+    assert_close(host(got), want, TOL[shape.bf16], "prefill x_out")
+    assert np.array_equal(host(dpool).view(np.uint32), host(dpool2).view(np.uint32))
