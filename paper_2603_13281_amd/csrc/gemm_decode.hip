@@ -286,7 +286,7 @@ __global__ void __launch_bounds__(256) k_gemm_decode(GemmArgs g) {
     };
     const int n_rows = g.R, ldy = g.ldy, n_in = n_wave + c8, n_out = col_base + n_in;
     const bool f32_out = !dual && g.epi == EPI_F32;
-    float *const y32 = (float *)g.Y + (size_t)kz * n_rows * ldy + n_out;
+    float *const y32 = (float *)g.Y + (size_t)kz * g.slice_rows * ldy + n_out;
     bf16_t *const y16 = (bf16_t *)g.Y + n_out;
     const int wrow0 = row0 + wr * (BM / WVM);  // first row of this wave
     if (with_resid) load_resid(0, rres[0]);

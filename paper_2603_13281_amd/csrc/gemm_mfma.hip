@@ -47,13 +47,14 @@ struct BRow {
 // LDS B-row b of weight tile tile_n -> weight row.  DUAL: a tile covers BN/2 output columns; inside
 // each wave column of WN LDS rows the first WN/2 are gate rows and the next WN/2 the up rows of the
 // same WN/2 output columns.
+// W0, W1: weights of segment 0 (DUAL: gate, up), which in a grouped launch are the row group's.
 template <int BN, int WN>
-__device__ __forceinline__ BRow b_row(const GemmArgs &g, int tile_n, int b) {
+__device__ __forceinline__ BRow b_row(const GemmArgs &g, const bf16_t *W0, const bf16_t *W1, int tile_n, int b) {
     BRow o;
     if (g.mode == GEMM_DUAL) {
         int wn = b / WN, j = (b % WN) / (WN / 2), nn = b % (WN / 2);
         int n = min(tile_n * (BN / 2) + wn * (WN / 2) + nn, g.n_seg[0] - 1);
-        o.w = (j ? g.W[1] : g.W[0]) + (size_t)n * g.K;
+        o.w = (j ? W1 : W0) + (size_t)n * g.K;
         const bf16_t *B = j ? g.B[1] : g.B[0];
         o.kind = (g.T && B) ? 1 + j : 0;
         o.b = o.kind ? B + (size_t)n * g.r : o.w;
@@ -61,7 +62,7 @@ __device__ __forceinline__ BRow b_row(const GemmArgs &g, int tile_n, int b) {
     }
     // plain: up to three weight segments stacked along N; tiles never straddle segments
     int t = tile_n;
-    const bf16_t *W = g.W[0];
+    const bf16_t *W = W0;
     int n_seg = g.n_seg[0];
     bool first = true;
     if (g.nseg > 1 && t >= g.tiles_seg[0]) {
@@ -135,7 +136,18 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) k_gemm_mfma(GemmArgs g
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = w / WAVES_N, wn = w % WAVES_N;
-    const int row0 = tile_m * BM;
+    // rows [row0, row_end) of this tile, and the weights they are multiplied with
+    int row0 = tile_m * BM, row_end = g.R;
+    const bf16_t *W0 = g.W[0], *W1 = g.W[1];
+    if (g.row_tiles) {
+        row0 = g.row_tiles[3 * tile_m];
+        row_end = g.row_tiles[3 * tile_m + 1];
+        const int grp = g.row_tiles[3 * tile_m + 2];
+        if (grp > 0) {
+            W0 = g.Wg[0] + (size_t)(grp - 1) * g.wg_stride;
+            W1 = g.Wg[1] + (size_t)(grp - 1) * g.wg_stride;
+        }
+    }
 
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -159,13 +171,13 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) k_gemm_mfma(GemmArgs g
     BRow br[B_LD];
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) {
-        int row = min(row0 + (w + NW * i) * RPU + ru, g.R - 1);  // clamped rows feed outputs that are never stored
+        int row = min(row0 + (w + NW * i) * RPU + ru, row_end - 1);  // clamped rows feed outputs that are never stored
         pa[i] = g.X + (size_t)row * g.ldx + kc;
         pt[i] = g.T ? g.T + (size_t)row * g.ldt + kc : zero;
     }
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
-        br[i] = b_row<BN, WN>(g, tile_n, (w + NW * i) * RPU + ru);
+        br[i] = b_row<BN, WN>(g, W0, W1, tile_n, (w + NW * i) * RPU + ru);
         br[i].w += kc;
     }
     const int K_base = g.K, mr = g.M_models * g.r, lr = 31 - __clz(max(g.r, 1)), ldt = g.T ? g.ldt : 0;
@@ -329,7 +341,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) k_gemm_mfma(GemmArgs g
 #pragma unroll
         for (int p = 0; p < kPasses; ++p) {
             const int row = row0 + wm * WM + i * 32 + rr0 + p * rpp, n_in = n_wave + c8;
-            dst[p] = (row < g.R && n_in < n_lim) ? *(const uint4 *)(g.resid + (size_t)row * g.ldr + col_base + n_in) : make_uint4(0u, 0u, 0u, 0u);
+            dst[p] = (row < row_end && n_in < n_lim) ? *(const uint4 *)(g.resid + (size_t)row * g.ldr + col_base + n_in) : make_uint4(0u, 0u, 0u, 0u);
         }
     };
     if (with_resid) load_resid(0, rres[0]);
@@ -357,12 +369,12 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) k_gemm_mfma(GemmArgs g
             const int rr = rr0 + p * rpp;
             if (rr >= 32) break;  // the fused gate/up tile has half the output columns: half the passes
             const int row = row0 + wm * WM + i * 32 + rr, n_in = n_wave + c8;
-            if (row >= g.R || n_in >= n_lim) continue;  // output widths are multiples of 8
+            if (row >= row_end || n_in >= n_lim) continue;  // output widths are multiples of 8
             const float4 a = *(const float4 *)(scr + rr * kEs + c8), b = *(const float4 *)(scr + rr * kEs + c8 + 4);
             float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
             const int n = col_base + n_in;
             if (!dual && g.epi == EPI_F32) {
-                float *yp = (float *)g.Y + ((size_t)kz * g.R + row) * g.ldy + n;
+                float *yp = (float *)g.Y + ((size_t)kz * g.slice_rows + row) * g.ldy + n;
                 *(float4 *)yp = a;
                 *(float4 *)(yp + 4) = b;
                 continue;
@@ -437,7 +449,7 @@ __global__ void __launch_bounds__(256) k_bench_mfma(float *__restrict__ out, int
 
 template <int BM, int BN, int BK, int NS, int WAVES_M, int WAVES_N>
 hipError_t launch_cfg(GemmArgs g, hipStream_t st) {
-    g.m_tiles = (g.R + BM - 1) / BM;
+    g.m_tiles = g.row_tiles ? g.n_row_tiles : (g.R + BM - 1) / BM;
     g.n_tiles = 0;
     if (g.mode == GEMM_DUAL) {
         g.n_tiles = (g.n_seg[0] + BN / 2 - 1) / (BN / 2);
@@ -587,10 +599,46 @@ GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices) {
     return best;
 }
 
+int gemm_row_tile(int most_rows) { return most_rows <= 64 ? TILE_64x128 : TILE_128; }
+int gemm_tile_rows(int tile) { return kTileShape[tile].bm; }
+
+// K slices of a grouped launch.  With a weight matrix per group it is bound by their way from HBM, like a GEMM of few
+// rows, and by the last round: 9 groups x 32 column tiles on 512 workgroup slots leave 32 CUs with twice the work of
+// the others (346 rows, 14336 -> 4096: 259 us whole, 207 us in 7 slices + 10 us for their sum).  The smallest modelled time: a 64-row
+// workgroup takes 0.85 us a slab alone on its CU, 1.4 us when two share one (which is HBM's rate for 16 KB of weights
+// each), a 128-row one 0.75 us; the slices' way through memory as in gemm_plan.
+int gemm_grouped_splits(const GemmArgs &g, int max_splits, bool takes_slices) {
+    if (g.mode == GEMM_DUAL) return 1;
+    int n_tiles = 0, n_total = 0;
+    for (int s = 0; s < g.nseg; ++s) {
+        n_tiles += (g.n_seg[s] + kTileShape[g.tile].bn - 1) / kTileShape[g.tile].bn;
+        n_total += g.n_seg[s];
+    }
+    const int slabs = g.K / kKAlign, cap = 256 * kTileShape[g.tile].per_cu;
+    const float mb = (float)g.R * (float)n_total * 4e-6f;
+    int best = 1;
+    float best_us = -1.f;
+    for (int splits = 1; splits <= max_splits; ++splits) {
+        const int per = (slabs + splits - 1) / splits, wgs = g.n_row_tiles * n_tiles * splits;
+        if (splits > 1 && (per < 4 || (slabs + per - 1) / per != splits)) continue;
+        auto round = [&](int n) {
+            if (n == 0) return 0.f;
+            const float slab = g.tile == TILE_128 ? 0.75f : n <= 256 ? 0.85f : 1.4f;
+            return 2.f + (float)per * slab;
+        };
+        float us = (float)(wgs / cap) * round(cap) + round(wgs % cap);
+        if (splits > 1) us += mb * splits * (0.22f + 0.2f) + (takes_slices ? 0.f : 4.f + mb * 0.2f);
+        if (best_us < 0.f || us < best_us) { best_us = us; best = splits; }
+    }
+    return best;
+}
+
 hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st) {
     if (g.R <= 0) return hipSuccess;
     if (g.K % kKAlign) return hipErrorInvalidValue;
     if (g.splits < 1) g.splits = 1;
+    if (g.slice_rows < g.R) g.slice_rows = g.R;
+    if (g.row_tiles && g.tile != TILE_64x128 && g.tile != TILE_128) return hipErrorInvalidValue;
     if (g.tile == TILE_AUTO) g.tile = gemm_plan(g, 1, false).tile;
     if (is_register_staged(g.tile)) return launch_gemm_decode(g, st);
     g.K_ext = k_ext_of(g);

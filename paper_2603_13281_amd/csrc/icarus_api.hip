@@ -144,6 +144,8 @@ struct FullPlan {
     const int32_t *perm = nullptr;  // device [R]: grouped position -> row of the call
     const int32_t *inv = nullptr;   // device [R]: row of the call -> grouped position
     std::vector<int32_t> off;       // host [n_models + 2]: first grouped position of each group
+    const int32_t *row_tiles = nullptr;  // device [n_row_tiles][3]: row tiles of the groups (GemmArgs::row_tiles)
+    int n_row_tiles = 0, tile = 0;       // tile: kind of the grouped GEMMs
 };
 
 constexpr int kAttnTargetWgs = 1280;  // decode attention: sizing bound for pieces and partial results
@@ -172,7 +174,8 @@ WsLayout ws_layout(const icarus_ctx *ctx, size_t rows, size_t seqs, size_t max_c
     // of its rows' plan sequences (where a decode call keeps the regrouping of its rows)
     w.meta_ints = 4 * rows + 5 * std::max(rows, w.max_items) + (size_t)ctx->attn_wgs + 6 * std::max(rows, seqs) + 64 +
                   rows + seqs +  // + what a layer stack stages with the call: prompt tokens, last row of each sequence
-                  2 * rows;      // + the regrouping of rows for decoders with private weights
+                  2 * rows +     // + the regrouping of rows for decoders with private weights, and their row tiles
+                  3 * (rows / 64 + (size_t)c.n_models + 2);
     w.meta = take(w.meta_ints * 4);
     {
         size_t g = (size_t)c.n_q_heads / c.n_kv_heads;
@@ -801,7 +804,7 @@ icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const
 
 // ---- decode step with private decoder weights -----------------------------------------
 // The rows are regrouped (encoder rows, then the rows of model 0, 1, ...) for everything but attention, and every
-// projection runs once per group with that group's weights; q is written back in call order by the RoPE kernel
+// projection runs over row tiles that lie within a group, with that group's weights; q is written back in call order by the RoPE kernel
 // (row map), the attention output is regrouped by a gather, the result returned to call order by another.
 icarus_status run_layer_full(icarus_ctx *ctx, char *ws, const WsLayout &L, const RowMeta &rm, const HostPlan *hp, const FullPlan &fp,
                              int R, int slot_by_row, void *pool, const int32_t *bt, int max_blocks, const void *x_in, void *x_out,
@@ -815,58 +818,71 @@ icarus_status run_layer_full(icarus_ctx *ctx, char *ws, const WsLayout &L, const
              *z = (bf16_raw *)(ws + L.z), *h = (bf16_raw *)(ws + L.h);
     bf16_raw *xg = (bf16_raw *)(ws + L.xg), *ag = (bf16_raw *)(ws + L.ag), *yg = (bf16_raw *)(ws + L.yg);
     float *qkv = (float *)(ws + L.qkv);
-    auto Wg = [&](int p, int grp) {  // weight of projection p for group grp
-        if (grp == 0) return (const bf16_raw *)ctx->base.w[p];
-        return (const bf16_raw *)ctx->full.w[p] + (size_t)(grp - 1) * proj_out(c, p) * proj_in(c, p);
+    // One launch per projection over the row tiles of all groups, whichever weights they are multiplied with.  (A launch and
+    // a reduction per group -- 63 launches a step with 8 models, 15-30 us each for 33-117 MB of weights -- spent as long in
+    // their ends as in streaming: 64 sequences, 346 rows, QKV / O / gate+up / down 141 / 143 / 403 / 268 us,
+    // now 82 / 73 / 372 / 217 us.)
+    auto args = [&](int p, const void *X, int K, int N) {
+        GemmArgs g{};
+        g.X = (const bf16_raw *)X; g.ldx = K; g.R = R; g.K = K;
+        g.mode = GEMM_PLAIN; g.epi = EPI_F32; g.splits = 1; g.tile = fp.tile;
+        g.W[0] = (const bf16_raw *)ctx->base.w[p]; g.Wg[0] = (const bf16_raw *)ctx->full.w[p]; g.wg_stride = (size_t)N * K;
+        g.n_seg[0] = N; g.nseg = 1;
+        g.row_tiles = fp.row_tiles; g.n_row_tiles = fp.n_row_tiles;
+        return g;
     };
-    const int n_groups = c.n_models + 1;
+    auto most_splits = [&](int ldy) {
+        return (int)std::max<size_t>(1, std::min<size_t>(kGemmMaxSplits, L.gemm_part_bytes / ((size_t)R * ldy * 4)));
+    };
+    float *part = (float *)(ws + L.gemm_part);
     PHASE(ctx, st, ICARUS_PH_ELEMWISE, launch_gather_rows(x_in, fp.perm, xg, R, d * 2, st));
     PHASE(ctx, st, ICARUS_PH_NORM, launch_norm_shrink(dm, xg, ctx->base.norm_attn, xn, R, d, nullptr, nullptr, nullptr, nullptr, nullptr, 0, st));
-    for (int grp = 0; grp < n_groups; ++grp) {  // Q per group; K, V of the encoder rows
-        const int o0 = fp.off[grp], n = fp.off[grp + 1] - o0;
-        if (n <= 0) continue;
-        GemmArgs g{};
-        g.X = xn + (size_t)o0 * d; g.ldx = d; g.R = n; g.K = d;
-        g.mode = GEMM_PLAIN; g.epi = EPI_F32; g.splits = 1;
-        g.W[0] = Wg(ICARUS_PROJ_Q, grp); g.n_seg[0] = qd; g.nseg = 1;
-        if (grp == 0) { g.W[1] = Wg(ICARUS_PROJ_K, 0); g.n_seg[1] = kvd; g.W[2] = Wg(ICARUS_PROJ_V, 0); g.n_seg[2] = kvd; g.nseg = 3; }
-        g.Y = qkv + (size_t)o0 * ldq; g.ldy = ldq;
-        LORA_TRY(run_gemm(ctx, ws, L, ICARUS_PH_GEMM_QKV, g, st));
+    int qkv_splits = 1;
+    {   // Q of every group, then K and V of the encoder rows (the first ones), in the same number of slices
+        GemmArgs g = args(ICARUS_PROJ_Q, xn, d, qd);
+        qkv_splits = g.splits = gemm_grouped_splits(g, most_splits(ldq), true);
+        g.Y = qkv_splits > 1 ? part : qkv; g.ldy = ldq;
+        PHASE(ctx, st, ICARUS_PH_GEMM_QKV, launch_gemm_mfma(g, st));
+        GemmArgs k{};
+        k.X = xn; k.ldx = d; k.R = fp.off[1]; k.K = d; k.slice_rows = R;
+        k.mode = GEMM_PLAIN; k.epi = EPI_F32; k.splits = qkv_splits; k.tile = fp.tile;
+        k.W[0] = (const bf16_raw *)ctx->base.w[ICARUS_PROJ_K]; k.n_seg[0] = kvd;
+        k.W[1] = (const bf16_raw *)ctx->base.w[ICARUS_PROJ_V]; k.n_seg[1] = kvd; k.nseg = 2;
+        k.Y = (float *)g.Y + qd; k.ldy = ldq;
+        PHASE(ctx, st, ICARUS_PH_GEMM_QKV, launch_gemm_mfma(k, st));
+        PHASE(ctx, st, ICARUS_PH_ROPE_APPEND, launch_rope_append(dm, (const float *)g.Y, ldq, qkv_splits, (size_t)R * ldq, rm, bt, max_blocks, pool, q,
+                                                                 slot_out, slot_by_row, ctx->base.q_norm, ctx->base.k_norm, R, st, fp.perm));
     }
-    PHASE(ctx, st, ICARUS_PH_ROPE_APPEND, launch_rope_append(dm, qkv, ldq, 1, 0, rm, bt, max_blocks, pool, q, slot_out, slot_by_row,
-                                                             ctx->base.q_norm, ctx->base.k_norm, R, st, fp.perm));
     LORA_TRY(run_decode_attention(ctx, ws, L, rm, hp, q, pool, bt, max_blocks, attn, R, st));
     PHASE(ctx, st, ICARUS_PH_ELEMWISE, launch_gather_rows(attn, fp.perm, ag, R, qd * 2, st));
-    for (int grp = 0; grp < n_groups; ++grp) {  // O projection + residual
-        const int o0 = fp.off[grp], n = fp.off[grp + 1] - o0;
-        if (n <= 0) continue;
-        GemmArgs g{};
-        g.X = ag + (size_t)o0 * qd; g.ldx = qd; g.R = n; g.K = qd;
-        g.W[0] = Wg(ICARUS_PROJ_O, grp); g.n_seg[0] = d; g.nseg = 1;
-        g.mode = GEMM_PLAIN; g.epi = EPI_BF16_RESID; g.splits = 1;
-        g.Y = z + (size_t)o0 * d; g.ldy = d; g.resid = xg + (size_t)o0 * d; g.ldr = d;
-        LORA_TRY(run_gemm(ctx, ws, L, ICARUS_PH_GEMM_O, g, st));
+    {   // O projection + residual; slices, if there are any, are summed by the norm kernel
+        GemmArgs g = args(ICARUS_PROJ_O, ag, qd, d);
+        g.splits = gemm_grouped_splits(g, most_splits(d), true);
+        if (g.splits > 1) { g.Y = part; g.ldy = d; }
+        else { g.epi = EPI_BF16_RESID; g.Y = z; g.ldy = d; g.resid = xg; g.ldr = d; }
+        PHASE(ctx, st, ICARUS_PH_GEMM_O, launch_gemm_mfma(g, st));
+        if (g.splits > 1)
+            PHASE(ctx, st, ICARUS_PH_NORM, launch_sum_norm_shrink(dm, part, g.splits, (size_t)R * d, xg, z, ctx->base.norm_ffn, xn, R, d, nullptr,
+                                                                  nullptr, nullptr, nullptr, st));
+        else
+            PHASE(ctx, st, ICARUS_PH_NORM, launch_norm_shrink(dm, z, ctx->base.norm_ffn, xn, R, d, nullptr, nullptr, nullptr, nullptr, nullptr, 0, st));
     }
-    PHASE(ctx, st, ICARUS_PH_NORM, launch_norm_shrink(dm, z, ctx->base.norm_ffn, xn, R, d, nullptr, nullptr, nullptr, nullptr, nullptr, 0, st));
-    for (int grp = 0; grp < n_groups; ++grp) {  // gate, up, SwiGLU
-        const int o0 = fp.off[grp], n = fp.off[grp + 1] - o0;
-        if (n <= 0) continue;
-        GemmArgs g{};
-        g.X = xn + (size_t)o0 * d; g.ldx = d; g.R = n; g.K = d;
-        g.W[0] = Wg(ICARUS_PROJ_GATE, grp); g.W[1] = Wg(ICARUS_PROJ_UP, grp); g.n_seg[0] = F; g.nseg = 1;
-        g.mode = GEMM_DUAL; g.splits = 1;
-        g.Y = h + (size_t)o0 * F; g.ldy = F;
+    {   // gate, up, SwiGLU
+        GemmArgs g = args(ICARUS_PROJ_GATE, xn, d, F);
+        g.mode = GEMM_DUAL;
+        g.W[1] = (const bf16_raw *)ctx->base.w[ICARUS_PROJ_UP]; g.Wg[1] = (const bf16_raw *)ctx->full.w[ICARUS_PROJ_UP];
+        g.Y = h; g.ldy = F;
         PHASE(ctx, st, ICARUS_PH_GEMM_GATEUP, launch_gemm_mfma(g, st));
     }
-    for (int grp = 0; grp < n_groups; ++grp) {  // down projection + residual
-        const int o0 = fp.off[grp], n = fp.off[grp + 1] - o0;
-        if (n <= 0) continue;
-        GemmArgs g{};
-        g.X = h + (size_t)o0 * F; g.ldx = F; g.R = n; g.K = F;
-        g.W[0] = Wg(ICARUS_PROJ_DOWN, grp); g.n_seg[0] = d; g.nseg = 1;
-        g.mode = GEMM_PLAIN; g.epi = EPI_BF16_RESID; g.splits = 1;
-        g.Y = yg + (size_t)o0 * d; g.ldy = d; g.resid = z + (size_t)o0 * d; g.ldr = d;
-        LORA_TRY(run_gemm(ctx, ws, L, ICARUS_PH_GEMM_DOWN, g, st));
+    {   // down projection + residual
+        GemmArgs g = args(ICARUS_PROJ_DOWN, h, F, d);
+        g.splits = gemm_grouped_splits(g, most_splits(d), false);
+        g.ldy = d;
+        if (g.splits > 1) g.Y = part;
+        else { g.epi = EPI_BF16_RESID; g.Y = yg; g.resid = z; g.ldr = d; }
+        PHASE(ctx, st, ICARUS_PH_GEMM_DOWN, launch_gemm_mfma(g, st));
+        if (g.splits > 1)
+            PHASE(ctx, st, ICARUS_PH_GEMM_DOWN, launch_splitk_reduce(part, g.splits, R, d, EPI_BF16_RESID, yg, d, z, d, st));
     }
     PHASE(ctx, st, ICARUS_PH_ELEMWISE, launch_gather_rows(yg, fp.inv, x_out, R, d * 2, st));
     return ICARUS_OK;
@@ -1048,6 +1064,20 @@ icarus_status prepare_decode(icarus_ctx *ctx, const void *kv_pool, const int32_t
         pr->fp.perm = dmeta + used;
         pr->fp.inv = dmeta + used + R;
         used += (size_t)2 * R;
+        int most = 0;
+        for (int g = 0; g < n_groups; ++g) most = std::max(most, off[(size_t)g + 1] - off[g]);
+        pr->fp.tile = gemm_row_tile(most);
+        const int bm = gemm_tile_rows(pr->fp.tile);
+        int32_t *rt = m + used;
+        for (int g = 0; g < n_groups; ++g)
+            for (int r0 = off[g]; r0 < off[(size_t)g + 1]; r0 += bm) {
+                int32_t *e = rt + 3 * (size_t)pr->fp.n_row_tiles++;
+                e[0] = r0;
+                e[1] = std::min(r0 + bm, off[(size_t)g + 1]);
+                e[2] = g;
+            }
+        pr->fp.row_tiles = dmeta + used;
+        used += 3 * (size_t)pr->fp.n_row_tiles;
     }
     rc = stage_commit(ctx, slot, ws + L.meta, used * 4, st);
     if (rc) return rc;

@@ -112,10 +112,15 @@ struct GemmArgs {
     const bf16_raw *T; int ldt;                  // masked shrink result [R, ldt] or null
     const bf16_raw *B[2]; int r; int M_models;   // adapter B [M, n_seg[0], r] of segment 0 (DUAL: gate, up)
     int mode, epi;
-    void *Y; int ldy;                            // EPI_F32: float [splits][R][ldy]; else bf16 [R][ldy]
+    void *Y; int ldy;                            // EPI_F32: float [splits][slice_rows][ldy]; else bf16 [R][ldy]
+    int slice_rows;                              // R at least (0: R)
     const bf16_raw *resid; int ldr;              // EPI_BF16_RESID: added to the result
     int splits;                                  // split-K slices (EPI_F32 without adapters only)
     int tile;                                    // tile kind (TILE_AUTO: chosen by the launcher)
+    // Grouped launch (optional): row_tiles, device [n_row_tiles][3] = first row, end row, group of each row tile (gemm_tile_rows
+    // rows at most).  Group 0 multiplies W[0] (DUAL: W[0], W[1]), group j > 0 Wg[.] + (j - 1) * wg_stride elements.
+    const int32_t *row_tiles; int n_row_tiles;
+    const bf16_raw *Wg[2]; size_t wg_stride;
     // filled by the launcher
     int tiles_seg[3]; int m_tiles, n_tiles, K_ext, k_per_split;
     int panel_m, panel_n, panels_m, n_panels;       // tile order: panels of panel_m x panel_n tiles (n_panels per K slice)
@@ -143,6 +148,10 @@ hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st);
 // later kernel of the caller reads the slices as they are, no reduction is launched for them.
 struct GemmPlan { int tile, splits; };
 GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices);
+// Grouped launches: tile kind for groups of at most most_rows rows, its height, and the K slices to use.
+int gemm_row_tile(int most_rows);
+int gemm_tile_rows(int tile);
+int gemm_grouped_splits(const GemmArgs &g, int max_splits, bool takes_slices);
 // Tiles of gemm_decode.hip (TILE_REG_*): both operands loaded coalesced, parked in registers two slabs ahead and staged
 // through LDS by register stores; launch_gemm_mfma takes this path for them.
 bool gemm_decode_supported(const GemmArgs &g);

@@ -96,3 +96,33 @@ def test_private_weights_are_rejected_where_unsupported():
     with pytest.raises(binding.IcarusError) as e:
         layer.set_full_decoders(d)
     assert e.value.status_name == "INVALID_ARG"
+
+
+@pytest.mark.parametrize("S,n_active", [(1, 1), (3, 3), (66, 2), (130, 1)], ids=["two-groups", "all-models", "encoder-66", "encoder-130"])
+def test_grouped_projections_over_group_sizes(S, n_active):
+    # groups of one row, of a whole row tile and a bit (64 and 128 rows), models that no sequence runs; with few row tiles
+    # K is sliced, with many it is not; K = 2048 in the down projection
+    import oracle
+    from gpu_util import dev, host, make_layer, pool_to_device_layout
+    from helpers import assert_close, filled_batch
+    from paper_2603_13281_amd import synth
+    shape = synth.LLAMA_SMALL.replace(d_ffn=2048)
+    print("case: grouped projections, sequences", S, "active", n_active, flush=True)
+    base = synth.make_base(shape, seed=41, norm_ones=False)
+    full = synth.make_full_decoders(shape, base, seed=41)
+    rng = np.random.default_rng(41)
+    lens = [int(x) for x in rng.integers(0, 60, size=S)]
+    batch = synth.make_batch(shape, lens, [n_active] * S, seed=41)
+    orc = oracle.Oracle(_oracle_cfg(shape, batch.num_blocks), base, None, full=full)
+    layer = make_layer(shape, base, synth.make_lora(shape, seed=41), batch.num_blocks)
+    layer.set_full_decoders({p: dev(w, True) for p, w in full.items()})
+    pool = filled_batch(shape, batch, seed=41)
+    dpool = dev(pool_to_device_layout(pool), True)
+    x = synth.make_hidden(shape, batch.R, seed=41)
+    want, want_slots = orc.decode_step(pool, batch.block_tables, batch.ctx_lens, batch.row_seq, batch.row_model, x)
+    slots = torch.zeros(S, dtype=torch.int64, device="cuda")
+    got = layer.decode_step(dpool, torch.from_numpy(batch.block_tables).cuda(), batch.ctx_lens, batch.row_seq, batch.row_model,
+                            dev(x, True), slot_out=slots)
+    torch.cuda.synchronize()
+    assert np.array_equal(slots.cpu().numpy(), want_slots)
+    assert_close(host(got), want, 2e-2, "x_out")
