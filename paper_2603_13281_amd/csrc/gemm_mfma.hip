@@ -540,7 +540,8 @@ void gemm_set_panels(GemmArgs *g, int bm, int bn, int per_cu) {
             const float load = (float)fullest / (float)cap;  // a last round that is only partly filled is also a faster one
             const float rounds = fullest <= cap ? load : 0.5f * (load + (float)((fullest + cap - 1) / cap));
             const float bytes = (float)(pm * bm + pn * bn) / (float)((bm + bn) * pm * pn);  // of a tile on its own
-            const float score = rounds * (1.f + 0.5f * bytes);
+            float score = rounds * (1.f + 0.5f * bytes);
+            if (splits > 1 && pms * pns % 8) score *= 1.06f;  // else an XCD works on the same tiles in every slice
             if (!g->panel_m || score < best) {
                 best = score;
                 g->panel_m = pm; g->panel_n = pn; g->panels_m = pms; g->n_panels = pms * pns;
@@ -591,7 +592,7 @@ GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices) {
             float us = model_us(g, kind, splits);
             if (splits > 1) {
                 const float mb = (float)g.R * (float)n_total * 4e-6f;  // one slice
-                us += mb * splits * (0.11f + 0.2f) + (takes_slices ? 0.f : 4.f + mb * 0.2f);
+                us += mb * splits * 0.38f + (takes_slices ? 0.f : 4.f + mb * 0.2f);
             }
             if (best_us < 0.f || us < best_us) { best_us = us; best = {kind, splits}; }
         }
