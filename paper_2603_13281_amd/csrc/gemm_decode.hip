@@ -98,7 +98,7 @@ __global__ void __launch_bounds__(256) k_gemm_decode(GemmArgs g) {
     const int cl = lane & 31, half = lane >> 5;
     int tile_n, row_blk;
     int kz;
-    if (!tile_of_workgroup(g, blockIdx.x, &row_blk, &tile_n, &kz)) return;
+    if (!tile_of_workgroup(g, &row_blk, &tile_n, &kz)) return;
     const int row0 = row_blk * BM;
     const bool dual = g.mode == GEMM_DUAL;
 

@@ -106,7 +106,7 @@ __device__ __forceinline__ int swz(int row, int c) {
     return (line << 8) + ((p ^ (line & (CPR - 1))) << 4);
 }
 
-template <int BM, int BN, int BK, int NS, int WAVES_M, int WAVES_N>
+template <int BM, int BN, int BK, int NS, int WAVES_M, int WAVES_N, bool GROUPED>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) k_gemm_mfma(GemmArgs g) {
     constexpr int NW = WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // wave tile
@@ -128,7 +128,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) k_gemm_mfma(GemmArgs g
     // of each per tile.  Consecutive panels (on different XCDs at the same time) walk down the rows
     // first, sharing their weight columns in the memory-side cache, then the slices.
     int tile_m, tile_n, kz;
-    if (!tile_of_workgroup(g, blockIdx.x, &tile_m, &tile_n, &kz)) return;
+    if (!tile_of_workgroup(g, &tile_m, &tile_n, &kz)) return;
     const int k_begin = kz * g.k_per_split;
     const int k_end = min(g.K_ext, k_begin + g.k_per_split);
     const int nk = (k_end - k_begin + BK - 1) / BK;
@@ -139,7 +139,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) k_gemm_mfma(GemmArgs g
     // rows [row0, row_end) of this tile, and the weights they are multiplied with
     int row0 = tile_m * BM, row_end = g.R;
     const bf16_t *W0 = g.W[0], *W1 = g.W[1];
-    if (g.row_tiles) {
+    if constexpr (GROUPED) {
         row0 = g.row_tiles[3 * tile_m];
         row_end = g.row_tiles[3 * tile_m + 1];
         const int grp = g.row_tiles[3 * tile_m + 2];
@@ -447,9 +447,9 @@ __global__ void __launch_bounds__(256) k_bench_mfma(float *__restrict__ out, int
     out[(size_t)blockIdx.x * 256 + threadIdx.x] = s;
 }
 
-template <int BM, int BN, int BK, int NS, int WAVES_M, int WAVES_N>
+template <int BM, int BN, int BK, int NS, int WAVES_M, int WAVES_N, bool GROUPED = false>
 hipError_t launch_cfg(GemmArgs g, hipStream_t st) {
-    g.m_tiles = g.row_tiles ? g.n_row_tiles : (g.R + BM - 1) / BM;
+    g.m_tiles = GROUPED ? g.n_row_tiles : (g.R + BM - 1) / BM;
     g.n_tiles = 0;
     if (g.mode == GEMM_DUAL) {
         g.n_tiles = (g.n_seg[0] + BN / 2 - 1) / (BN / 2);
@@ -463,13 +463,13 @@ hipError_t launch_cfg(GemmArgs g, hipStream_t st) {
     gemm_set_panels(&g, BM, BN, (int)(((size_t)160 << 10) / shm));
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_gemm_mfma<BM, BN, BK, NS, WAVES_M, WAVES_N>,
+        hipError_t e = hipFuncSetAttribute((const void *)k_gemm_mfma<BM, BN, BK, NS, WAVES_M, WAVES_N, GROUPED>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     dim3 grid(gemm_grid(g));
-    hipLaunchKernelGGL((k_gemm_mfma<BM, BN, BK, NS, WAVES_M, WAVES_N>), grid, dim3(64 * WAVES_M * WAVES_N), shm, st, g);
+    hipLaunchKernelGGL((k_gemm_mfma<BM, BN, BK, NS, WAVES_M, WAVES_N, GROUPED>), grid, dim3(64 * WAVES_M * WAVES_N), shm, st, g);
     return hipGetLastError();
 }
 
@@ -548,6 +548,9 @@ void gemm_set_panels(GemmArgs *g, int bm, int bn, int per_cu) {
             }
         }
     }
+    g->inv_panels = gemm_inv(g->n_panels);
+    g->inv_panels_m = gemm_inv(g->panels_m);
+    g->inv_panel_m = gemm_inv(g->panel_m);
 }
 
 bool gemm_mfma_supported(const Dims &dm, int K) {
@@ -645,8 +648,8 @@ hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st) {
     g.K_ext = k_ext_of(g);
     g.k_per_split = ((g.K_ext + g.splits - 1) / g.splits + kKAlign - 1) / kKAlign * kKAlign;
     switch (g.tile) {
-    case TILE_64x128: return launch_cfg<64, 128, 64, 3, 2, 2>(g, st);
-    case TILE_128: return launch_cfg<128, 128, 64, 4, 2, 2>(g, st);
+    case TILE_64x128: return g.row_tiles ? launch_cfg<64, 128, 64, 3, 2, 2, true>(g, st) : launch_cfg<64, 128, 64, 3, 2, 2>(g, st);
+    case TILE_128: return g.row_tiles ? launch_cfg<128, 128, 64, 4, 2, 2, true>(g, st) : launch_cfg<128, 128, 64, 4, 2, 2>(g, st);
     case TILE_192x128: return launch_cfg<192, 128, 64, 3, 2, 2>(g, st);
     case TILE_256x256: return launch_cfg<256, 256, 64, 2, 2, 4>(g, st);
     default: return hipErrorInvalidValue;

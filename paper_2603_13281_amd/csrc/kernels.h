@@ -24,6 +24,8 @@ struct RowMeta {
     const int32_t *row_model;  // [R] -1 = logical encoder row, else adapter id
     const int32_t *row_pos;    // [R] position of the row's token
     const int32_t *row_kvlen;  // [R] cache positions the row attends to (0..kvlen-1)
+    const int32_t *rope_tiles = nullptr;  // prefill: the rows in tiles for launch_rope_append_tiles
+    int n_rope_tiles = 0;
 };
 
 // ---- generic vector kernels (any shape; fp32 accumulation) -------------------------------
@@ -49,6 +51,12 @@ hipError_t launch_silu_mul(const Dims &dm, const float *gate, const float *up, v
 hipError_t launch_rope_append(const Dims &dm, const float *qkv, int ldq, int splits, size_t slice, const RowMeta &rm,
                               const int32_t *bt, int max_blocks, void *pool, void *q_out, int64_t *slot_out, int slot_by_row,
                               const void *q_norm, const void *k_norm, int R, hipStream_t st, const int32_t *row_map = nullptr);
+// The same for encoder rows only, head_dim 128 and blocks of 16, by tiles of consecutive rows within one KV block: tiles (device)
+// = first row | rows << 16.  kv_only: q is neither read nor written.  slot_out is by row.
+bool rope_tiles_supported(const Dims &dm, int ldq, size_t slice);
+hipError_t launch_rope_append_tiles(const Dims &dm, const float *qkv, int ldq, int splits, size_t slice, const RowMeta &rm,
+                                    const int32_t *tiles, int n_tiles, bool kv_only, const int32_t *bt, int max_blocks, void *pool,
+                                    void *q_out, int64_t *slot_out, const void *q_norm, const void *k_norm, hipStream_t st);
 // out[row, h, :] = softmax(q[row,h,:] K^T / sqrt(D)) V over positions 0..row_kvlen[row]-1 of row_seq[row]
 hipError_t launch_attn_generic(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
                                const RowMeta &rm, void *out, int R, hipStream_t st);
@@ -124,23 +132,28 @@ struct GemmArgs {
     // filled by the launcher
     int tiles_seg[3]; int m_tiles, n_tiles, K_ext, k_per_split;
     int panel_m, panel_n, panels_m, n_panels;       // tile order: panels of panel_m x panel_n tiles (n_panels per K slice)
+    uint32_t inv_panels, inv_panels_m, inv_panel_m; // gemm_inv of n_panels, panels_m, panel_m
     int slabs_per_split;                            // decode kernel: 64-wide K slabs per split-K slice
 };
 bool gemm_mfma_supported(const Dims &dm, int K);
 // fills the tile order from m_tiles, n_tiles and splits, for bm x bn tiles and per_cu workgroups to a CU
 void gemm_set_panels(GemmArgs *g, int bm, int bn, int per_cu);
-// workgroups of the launch: whole panels for each of the 8 XCDs
-inline unsigned gemm_grid(const GemmArgs &g) {
-    return (unsigned)((g.n_panels * g.splits + 7) / 8 * 8 * (g.panel_m * g.panel_n));
+// grid of the launch: x = place in a panel * 8 + XCD, y = panels of an XCD in turn
+inline dim3 gemm_grid(const GemmArgs &g) {
+    return dim3((unsigned)(g.panel_m * g.panel_n * 8), (unsigned)((g.n_panels * g.splits + 7) / 8));
 }
-// tile and K slice of workgroup `id`; false: none
-__device__ __forceinline__ bool tile_of_workgroup(const GemmArgs &g, int id, int *tile_m, int *tile_n, int *kz) {
-    const int area = g.panel_m * g.panel_n, s = id >> 3;
-    const int p = (s / area) * 8 + (id & 7), within = s % area;
-    *kz = p / g.n_panels;
-    const int panel = p % g.n_panels;
-    *tile_m = (panel % g.panels_m) * g.panel_m + within % g.panel_m;
-    *tile_n = (panel / g.panels_m) * g.panel_n + within / g.panel_m;
+// x / n for x * n < 2^32, by the host's inv = ceil(2^32 / n) (0 for n = 1): a division would cost these short kernels
+// as much as a dozen loads
+inline uint32_t gemm_inv(int n) { return n > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint64_t)n - 1) / (uint64_t)n) : 0u; }
+__device__ __forceinline__ int gemm_div(int x, uint32_t inv) { return inv ? (int)__umulhi((uint32_t)x, inv) : x; }
+// tile and K slice of this workgroup; false: none
+__device__ __forceinline__ bool tile_of_workgroup(const GemmArgs &g, int *tile_m, int *tile_n, int *kz) {
+    const int within = blockIdx.x >> 3, p = blockIdx.y * 8 + (blockIdx.x & 7);
+    *kz = g.splits > 1 ? gemm_div(p, g.inv_panels) : (int)(p >= g.n_panels);
+    const int panel = p - *kz * g.n_panels;
+    const int pn = gemm_div(panel, g.inv_panels_m), wn = gemm_div(within, g.inv_panel_m);
+    *tile_m = (panel - pn * g.panels_m) * g.panel_m + within - wn * g.panel_m;
+    *tile_n = pn * g.panel_n + wn;
     return *kz < g.splits && *tile_m < g.m_tiles && *tile_n < g.n_tiles;
 }
 hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st);
