@@ -306,7 +306,6 @@ hipError_t launch_rope_append(const Dims &dm, const float *qkv, int ldq, int spl
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ attention (one block per row and query head)
 // four consecutive cache elements (aligned to four elements)
 template <typename KT> struct KVElem4;
 template <> struct KVElem4<float> {
@@ -321,6 +320,12 @@ template <> struct KVElem4<bf16_t> {
         f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
         f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
     }
+    static __device__ __forceinline__ void st(bf16_t *p, const float (&f)[4], float) {
+        uint2 v;
+        v.x = (uint32_t)f32_to_bf16(f[0]) | ((uint32_t)f32_to_bf16(f[1]) << 16);
+        v.y = (uint32_t)f32_to_bf16(f[2]) | ((uint32_t)f32_to_bf16(f[3]) << 16);
+        *(uint2 *)p = v;
+    }
 };
 template <> struct KVElem4<fp8_t> {
     static __device__ __forceinline__ void ld(const fp8_t *p, float scale, float (&f)[4]) {
@@ -328,8 +333,144 @@ template <> struct KVElem4<fp8_t> {
 #pragma unroll
         for (int e = 0; e < 4; ++e) f[e] = fp8_to_f32((v >> (8 * e)) & 0xffu) * scale;
     }
+    static __device__ __forceinline__ void st(fp8_t *p, const float (&f)[4], float scale) {
+        uint32_t v = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v |= f32_to_fp8(f[e] / scale) << (8 * e);
+        *(uint32_t *)p = v;
+    }
 };
 
+// ------------------------------------------------------------------ the same for prefill chunks
+// One workgroup per tile of up to 16 consecutive chunk rows that lie in one KV block (head_dim 128, blocks of 16, bf16
+// storage, encoder rows only), or, with few tiles, per tile and share of the heads.  Bound by memory: the row's fp32
+// projections in, q and the cache entries out.  A row at a time, each V value was a 2-byte store of its own, 32 bytes
+// from the next (the cache holds V transposed), and a rotated pair two more; here a thread rotates four pairs at a time,
+// and the tile's V goes through LDS into 16-byte pieces of the transposed plane.  16384 rows x 6144 columns: 169 us ->
+// 133 us, 4337 rows 50 -> 33 us, 512 rows x 10240 columns 26 -> 13 us.
+// tiles: device, first row | rows << 16.
+template <typename KT>
+__global__ void __launch_bounds__(256) k_rope_append_tile(const float *__restrict__ qkv, int ldq, int splits, size_t slice,
+                                                          const int32_t *__restrict__ tiles, const int32_t *__restrict__ row_seq,
+                                                          const int32_t *__restrict__ row_pos, const int32_t *__restrict__ bt,
+                                                          int max_blocks, KT *__restrict__ pool, bf16_t *__restrict__ q_out,
+                                                          int64_t *__restrict__ slot_out, const bf16_t *__restrict__ q_norm,
+                                                          const bf16_t *__restrict__ k_norm, int h_begin, int Hq, int Hkv,
+                                                          double log2_theta, float eps, int qk_norm, float k_scale, float v_scale) {
+    constexpr int D = 128, half = 64, Bk = 16;
+    __shared__ float cs_t[Bk][half], sn_t[Bk][half];
+    __shared__ __attribute__((aligned(16))) KT vt[D][Bk + 16 / sizeof(KT)];  // V of one head, transposed; rows 16 bytes apart from full banks
+    const int tile = tiles[blockIdx.x], row0 = tile & 0xffff, n = tile >> 16;
+    const int s = row_seq[row0], pos0 = row_pos[row0], off0 = pos0 % Bk;
+    const int blk = bt[(size_t)s * max_blocks + pos0 / Bk];
+    // heads h_begin .. Hq - 1 are q (none for a cache-only call), then Hkv k heads, then Hkv v heads; this workgroup's share
+    const int n_rot = Hq + Hkv, n_heads = n_rot + Hkv - h_begin;
+    const int h0 = h_begin + (int)((long long)n_heads * blockIdx.y / gridDim.y);
+    const int h1 = h_begin + (int)((long long)n_heads * (blockIdx.y + 1) / gridDim.y);
+    const int tid = threadIdx.x, t = tid >> 4, l = tid & 15;
+    if (h0 < n_rot)
+        for (int i = tid; i < n * half; i += 256) {
+            const double ang = (double)(pos0 + i / half) * exp2(-(2.0 * (double)(i % half) / (double)D) * log2_theta);
+            double sn_d, cs_d;
+            sincos(ang, &sn_d, &cs_d);
+            cs_t[i / half][i % half] = (float)cs_d;
+            sn_t[i / half][i % half] = (float)sn_d;
+        }
+    if (slot_out && blockIdx.y == 0 && tid < n) slot_out[row0 + tid] = (int64_t)blk * Bk + off0 + tid;
+    __syncthreads();
+    const bool live = t < n;  // 16 lanes per row; rows past the tile's last repeat it and store nothing
+    const float *src = qkv + (size_t)(row0 + min(t, n - 1)) * ldq;
+    auto load4 = [&](int col) {
+        float4 v = *(const float4 *)(src + col);
+        for (int z = 1; z < splits; ++z) {
+            const float4 a = *(const float4 *)(src + (size_t)z * slice + col);
+            v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
+        }
+        return v;
+    };
+    KT *const blk_k = pool + (size_t)blk * Hkv * 2 * Bk * D;
+    const int r1 = min(h1, n_rot);
+    float4 na = make_float4(0.f, 0.f, 0.f, 0.f), nb = na;  // one head ahead
+    if (h0 < r1) { na = load4(h0 * D + 4 * l); nb = load4(h0 * D + half + 4 * l); }
+    for (int h = h0; h < r1; ++h) {
+        const float4 va = na, vb = nb;
+        if (h + 1 < r1) { na = load4((h + 1) * D + 4 * l); nb = load4((h + 1) * D + half + 4 * l); }
+        float a[4] = {va.x, va.y, va.z, va.w}, b[4] = {vb.x, vb.y, vb.z, vb.w};
+        if (qk_norm) {
+            float ss = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ss += a[e] * a[e] + b[e] * b[e];
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+            const float inv = rsqrtf(ss / (float)D + eps);
+            const bf16_t *nw = h < Hq ? q_norm : k_norm;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                a[e] = a[e] * inv * bf16_to_f32(nw[4 * l + e]);
+                b[e] = b[e] * inv * bf16_to_f32(nw[half + 4 * l + e]);
+            }
+        }
+        if (!live) continue;
+        float ra[4], rb[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float cs = cs_t[t][4 * l + e], sn = sn_t[t][4 * l + e];
+            ra[e] = a[e] * cs - b[e] * sn;
+            rb[e] = b[e] * cs + a[e] * sn;
+        }
+        if (h < Hq) {
+            bf16_t *dst = q_out + ((size_t)(row0 + t) * Hq + h) * D + 4 * l;
+            KVElem4<bf16_t>::st(dst, ra, 1.f);
+            KVElem4<bf16_t>::st(dst + half, rb, 1.f);
+        } else {
+            KT *dst = blk_k + (size_t)(h - Hq) * 2 * Bk * D + (size_t)(off0 + t) * D + 4 * l;  // K plane [Bk][D]
+            KVElem4<KT>::st(dst, ra, k_scale);
+            KVElem4<KT>::st(dst + half, rb, k_scale);
+        }
+    }
+    constexpr int kPer = 16 / sizeof(KT);  // elements of a 16-byte piece: 8 or 16 tokens
+    for (int h = max(h0, n_rot); h < h1; ++h) {
+        const float4 va = load4(h * D + 4 * l), vb = load4(h * D + half + 4 * l);
+        __syncthreads();  // the previous head's pieces have been read
+        if (live) {
+            const float v[8] = {va.x, va.y, va.z, va.w, vb.x, vb.y, vb.z, vb.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) KVElem<KT>::st(&vt[(e >> 2) * half + 4 * l + (e & 3)][off0 + t], v[e], v_scale);
+        }
+        __syncthreads();
+        KT *dst = blk_k + ((size_t)(h - n_rot) * 2 + 1) * Bk * D;  // V plane [D][Bk]
+        for (int i = tid; i < D * Bk / kPer; i += 256) {
+            const int d = i / (Bk / kPer), o = i % (Bk / kPer) * kPer;
+            if (off0 <= o && off0 + n >= o + kPer) *(uint4 *)(dst + (size_t)d * Bk + o) = *(const uint4 *)&vt[d][o];
+            else  // a tile that fills its block in part: only the tokens it has
+                for (int e = max(off0, o); e < min(off0 + n, o + kPer); ++e) dst[(size_t)d * Bk + e] = vt[d][e];
+        }
+    }
+}
+
+bool rope_tiles_supported(const Dims &dm, int ldq, size_t slice) {
+    return dm.bf16 && dm.D == 128 && dm.Bk == 16 && ldq % 4 == 0 && slice % 4 == 0;
+}
+
+hipError_t launch_rope_append_tiles(const Dims &dm, const float *qkv, int ldq, int splits, size_t slice, const RowMeta &rm,
+                                    const int32_t *tiles, int n_tiles, bool kv_only, const int32_t *bt, int max_blocks, void *pool,
+                                    void *q_out, int64_t *slot_out, const void *q_norm, const void *k_norm, hipStream_t st) {
+    if (n_tiles <= 0) return hipSuccess;
+    if (!rope_tiles_supported(dm, ldq, slice)) return hipErrorInvalidValue;
+    const int h_begin = kv_only ? dm.Hq : 0, n_heads = dm.Hq - h_begin + 2 * dm.Hkv;
+    int parts = 1;  // few tiles: several workgroups per tile, each with four heads or more
+    while (parts < 16 && n_tiles * parts < 1536 && n_heads / (2 * parts) >= 4) parts *= 2;
+    auto launch = [&](auto kt) {
+        typedef decltype(kt) KT;
+        hipLaunchKernelGGL(k_rope_append_tile<KT>, dim3(n_tiles, parts), dim3(256), 0, st, qkv, ldq, splits, slice, tiles, rm.row_seq, rm.row_pos,
+                           bt, max_blocks, (KT *)pool, (bf16_t *)q_out, slot_out, (const bf16_t *)q_norm, (const bf16_t *)k_norm, h_begin,
+                           dm.Hq, dm.Hkv, log2(dm.theta), dm.eps, dm.qk_norm, dm.k_scale, dm.v_scale);
+        return hipGetLastError();
+    };
+    return dm.kv8 ? launch(fp8_t()) : launch(bf16_t());
+}
+
+// ------------------------------------------------------------------ attention (one block per row and query head)
 // Online softmax over chunks of 1024 cached positions.  Scores: a thread per position.  Output: thread (part, d) adds
 // every parts-th quad of positions to output element d; V^T rows hold a block's tokens side by side, so a quad is
 // one load, and 256 / D parts (D rounded up to a power of two) keep all threads on it.  Latency-bound at the sizes

@@ -171,7 +171,7 @@ WsLayout ws_layout(const icarus_ctx *ctx, size_t rows, size_t seqs, size_t max_c
     w.max_items = attn_max_items(ctx, seqs, max_ctx);
     // metadata: 4 row arrays and the attention plan (5 arrays per piece, the shares' first pieces, 6 arrays
     // per plan sequence); a prefill call has up to `rows` plan sequences, max_items pieces if any is cut, and an array
-    // of its rows' plan sequences (where a decode call keeps the regrouping of its rows)
+    // of its rows' plan sequences and one of row tiles, one per row at most (where a decode call keeps the regrouping of its rows)
     w.meta_ints = 4 * rows + 5 * std::max(rows, w.max_items) + (size_t)ctx->attn_wgs + 6 * std::max(rows, seqs) + 64 +
                   rows + seqs +  // + what a layer stack stages with the call: prompt tokens, last row of each sequence
                   2 * rows +     // + the regrouping of rows for decoders with private weights, and their row tiles
@@ -745,8 +745,14 @@ icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const
     }
     {   // split-K slices of the projection, if any were left, are summed by the RoPE kernel
         const float *src = qkv_splits ? (const float *)(ws + L.gemm_part) : qkv;
-        PHASE(ctx, st, ICARUS_PH_ROPE_APPEND, launch_rope_append(dm, src, ldq, std::max(1, qkv_splits), (size_t)R * ldq, rm, bt, max_blocks,
-                                                                 pool, q, slot_out, slot_by_row, ctx->base.q_norm, ctx->base.k_norm, R, st));
+        const size_t slice = (size_t)R * ldq;
+        if (rm.n_rope_tiles > 0 && rope_tiles_supported(dm, ldq, slice))
+            PHASE(ctx, st, ICARUS_PH_ROPE_APPEND,
+                  launch_rope_append_tiles(dm, src, ldq, std::max(1, qkv_splits), slice, rm, rm.rope_tiles, rm.n_rope_tiles, kv_only, bt, max_blocks,
+                                           pool, q, slot_out, ctx->base.q_norm, ctx->base.k_norm, st));
+        else
+            PHASE(ctx, st, ICARUS_PH_ROPE_APPEND, launch_rope_append(dm, src, ldq, std::max(1, qkv_splits), slice, rm, bt, max_blocks, pool, q,
+                                                                     slot_out, slot_by_row, ctx->base.q_norm, ctx->base.k_norm, R, st));
     }
     if (kv_only) return ICARUS_OK;
     bool merge_left = false;
@@ -1157,9 +1163,21 @@ icarus_status prepare_prefill(icarus_ctx *ctx, const void *kv_pool, const int32_
         pr->extra_dev = dmeta + used;
         used += n_extra;
     }
+    pr->rm = RowMeta{dmeta, dmeta + R, dmeta + 2 * R, dmeta + 3 * R};
+    if (rope_tiles_supported(ctx->dm, 4, 4)) {  // the chunk rows in tiles that lie within one KV block (at most one per row)
+        pr->rm.rope_tiles = dmeta + used;
+        int row = 0;
+        for (int s = 0; s < S; ++s)
+            for (int i = 0; i < chunk_lens[s];) {
+                const int n = std::min(chunk_lens[s] - i, c.block_size - (ctx_lens[s] + i) % c.block_size);
+                m[used++] = row | n << 16;
+                ++pr->rm.n_rope_tiles;
+                i += n;
+                row += n;
+            }
+    }
     rc = stage_commit(ctx, slot, ws + L.meta, used * 4, st);
     if (rc) return rc;
-    pr->rm = RowMeta{dmeta, dmeta + R, dmeta + 2 * R, dmeta + 3 * R};
     return ICARUS_OK;
 }
 

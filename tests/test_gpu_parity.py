@@ -11,7 +11,7 @@ import torch
 
 import oracle
 from paper_2603_13281_amd import synth
-from helpers import assert_cache_close, assert_close, fill_pool, filled_batch, mark_unwritten, oracle_config, read_pool
+from helpers import assert_cache_close, assert_close, assert_fp8_cache_close, fill_pool, filled_batch, mark_unwritten, oracle_config, read_pool
 from gpu_util import bf16_ulp, dev, fp8_pool_to_float, host, make_layer, pool_from_device_layout, pool_to_device_layout
 
 pytestmark = pytest.mark.gpu
@@ -483,3 +483,50 @@ def test_prefill_of_a_few_rows_on_vector_kernels(shape):
     torch.cuda.synchronize()
     assert_close(host(got), want, TOL[shape.bf16], "prefill x_out")
     assert np.array_equal(host(dpool).view(np.uint32), host(dpool2).view(np.uint32))
+
+
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
+@pytest.mark.parametrize("shape", [synth.LLAMA_SMALL, synth.QWEN_SMALL], ids=lambda s: s.name)
+def test_prefill_appends_by_block_tiles(shape, fp8):
+    # chunk rows appended in tiles that lie within one block: a single token anywhere in it, whole blocks, the end of one
+    # and the start of the next; every slot right, every other byte of the pool as it was, also in a cache-only call
+    _say("case: append tiles", shape.name, "fp8", fp8)
+    pre = [0, 1, 15, 16, 17, 31, 5, 64]
+    chunk = [1, 15, 17, 16, 33, 1, 40, 3]
+    ks, vs = 0.02, 0.013
+    base = synth.make_base(shape, seed=37, norm_ones=False)
+    batch = synth.make_batch(shape, pre, [0] * len(pre), seed=37, headroom=max(chunk))
+    kw = dict(kv_fp8=True, k_scale=ks, v_scale=vs) if fp8 else {}
+    layer = make_layer(shape, base, None, batch.num_blocks, **kw)
+    x = synth.make_hidden(shape, sum(chunk), seed=37, tag=5)
+    pool = filled_batch(shape, batch, seed=37)
+    cfg = oracle_config(shape, batch.num_blocks)
+    if fp8:
+        cfg = dataclasses.replace(cfg, **kw)
+        gen = torch.Generator(device="cuda:0")
+        gen.manual_seed(37)
+        dpool = torch.randint(0, 0x70, layer.cfg.pool_shape(), generator=gen, device="cuda:0", dtype=torch.uint8)
+        pool = pool_from_device_layout(fp8_pool_to_float(dpool, ks, vs), shape.block_size, shape.head_dim)
+    else:
+        dpool = dev(pool_to_device_layout(pool), True)
+    before, cache_only = dpool.clone(), dpool.clone()
+    orc = oracle.Oracle(cfg, base, None)
+    want_pool = pool.copy()
+    _, want_slots = orc.prefill(want_pool, batch.block_tables, pre, chunk, x)
+    bt = torch.from_numpy(batch.block_tables).cuda()
+    slots = torch.zeros(sum(chunk), dtype=torch.int64, device="cuda")
+    layer.prefill_kv(dpool, bt, pre, chunk, dev(x, True), slot_out=slots)
+    layer.prefill_kv(cache_only, bt, pre, chunk, dev(x, True), want_out=False)
+    torch.cuda.synchronize()
+    assert np.array_equal(slots.cpu().numpy(), want_slots)
+    assert torch.equal(dpool, cache_only)
+    if fp8:
+        got = pool_from_device_layout(fp8_pool_to_float(dpool, ks, vs), shape.block_size, shape.head_dim)
+        was = pool_from_device_layout(fp8_pool_to_float(before, ks, vs), shape.block_size, shape.head_dim)
+        for plane, scale in ((0, ks), (1, vs)):
+            assert_fp8_cache_close(got[:, plane], want_pool[:, plane], scale, True, "cache")
+    else:
+        got, was = (pool_from_device_layout(host(t), shape.block_size, shape.head_dim) for t in (dpool, before))
+        _cache_close(shape, got, want_pool, "cache")
+    changed = np.argwhere((got != was).any(axis=(1, 2, 4)))
+    assert sorted(int(b) * shape.block_size + int(o) for b, o in changed) == sorted(int(s) for s in want_slots)
