@@ -98,15 +98,17 @@ def test_private_weights_are_rejected_where_unsupported():
     assert e.value.status_name == "INVALID_ARG"
 
 
-@pytest.mark.parametrize("S,n_active", [(1, 1), (3, 3), (66, 2), (130, 1)], ids=["two-groups", "all-models", "encoder-66", "encoder-130"])
-def test_grouped_projections_over_group_sizes(S, n_active):
+@pytest.mark.parametrize("S,n_active,M,d_ffn", [(1, 1, 4, 2048), (3, 3, 4, 2048), (66, 2, 4, 2048), (130, 1, 4, 2048), (2, 8, 8, 6464)],
+                         ids=["two-groups", "all-models", "encoder-66", "encoder-130", "wide-gate-up"])
+def test_grouped_projections_over_group_sizes(S, n_active, M, d_ffn):
     # groups of one row, of a whole row tile and a bit (64 and 128 rows), models that no sequence runs; with few row tiles
-    # K is sliced, with many it is not; K = 2048 in the down projection
+    # K is sliced, with many it is not; K = 2048 in the down projection; more tiles than
+    # a round of workgroups, the last column tile ragged
     import oracle
     from gpu_util import dev, host, make_layer, pool_to_device_layout
     from helpers import assert_close, filled_batch
     from paper_2603_13281_amd import synth
-    shape = synth.LLAMA_SMALL.replace(d_ffn=2048)
+    shape = synth.LLAMA_SMALL.replace(d_ffn=d_ffn, n_models=M)
     print("case: grouped projections, sequences", S, "active", n_active, flush=True)
     base = synth.make_base(shape, seed=41, norm_ones=False)
     full = synth.make_full_decoders(shape, base, seed=41)

@@ -106,3 +106,30 @@ def test_stack_rejects_bad_arguments():
     with pytest.raises(binding.IcarusError) as e:       # two encoder rows in one sequence
         stack.decode(pools, dbt, [3], [0, 0], [-1, -1], torch.zeros(1, dtype=torch.int32, device="cuda:0"))
     assert e.value.status_name == "ROW_ORDER"
+
+
+def test_stack_with_a_wide_vocabulary():
+    """The LM head of a few rows against a vocabulary wide enough for its 64 x 256 tiles (448 of them), with a ragged
+    last one; prompt (2 logit rows) and one token step (5 rows)."""
+    from paper_2603_13281_amd import synth
+    print("case: wide vocabulary", flush=True)
+    shape = synth.LLAMA_SMALL.replace(d_model=256, d_ffn=512)
+    vocab, tol = 448 * 256 + 24, 2e-2
+    lens = np.array([20, 7], dtype=np.int32)
+    wts, orc, stack, pools = _build(shape, 1, vocab, 6, seed=13)
+    opools = orc.new_pools()
+    bt = np.arange(6, dtype=np.int32).reshape(2, 3)
+    dbt = torch.from_numpy(bt).to("cuda:0")
+    rng = np.random.default_rng(13)
+    tokens = rng.integers(0, vocab, size=int(lens.sum())).astype(np.int32)
+    zeros = np.zeros(2, dtype=np.int32)
+    nxt, lg = stack.prefill(pools, dbt, zeros, lens, tokens, want_logits=True)
+    want_lg, _ = orc.prefill(opools, bt, zeros, lens, tokens)
+    torch.cuda.synchronize()
+    _check_tokens(nxt.cpu().numpy(), lg.cpu().numpy().astype(np.float64), want_lg, tol, "wide vocabulary prefill")
+    row_seq, row_model = np.int32([0, 0, 0, 1, 1]), np.int32([-1, 0, 2, -1, 3])
+    cur = rng.integers(0, vocab, size=2).astype(np.int32)
+    got, lg = stack.decode(pools, dbt, lens, row_seq, row_model, torch.from_numpy(cur).to("cuda:0"), want_logits=True)
+    want_lg, _, _ = orc.decode(opools, bt, lens, row_seq, row_model, cur)
+    torch.cuda.synchronize()
+    _check_tokens(got.cpu().numpy(), lg.cpu().numpy().astype(np.float64), want_lg, tol, "wide vocabulary decode")
