@@ -477,7 +477,7 @@ hipError_t launch_cfg(GemmArgs g, hipStream_t st) {
 // a weight row twice, half each time, and stream at about 60 % of the rate).  The first four are k_gemm_mfma, the last
 // two k_gemm_decode.  first_us: what a workgroup takes apart from its slabs (start, first slab, epilogue); slab_us: a slab
 // with every CU busy, two workgroups to a CU in the second figure where two fit.  The figures are a fit to 5000 timings on
-// this GPU (65-4337 rows x the projections of a Llama-3-8B- and a Qwen3-32B-shaped layer x every tile x 1-12 slices; the
+// this GPU (80-4337 rows x the projections of a Llama-3-8B- and a Qwen3-32B-shaped layer x every tile x 1-12 slices; the
 // fit is 7-11 % off on average), see gemm_plan.
 struct TileShape { int bm, bn, per_cu; float first_us, slab_us, slab2_us; };
 constexpr TileShape kTileShape[TILE_KINDS] = {
@@ -572,31 +572,35 @@ bool few_rows_wide(const GemmArgs &g) {
 
 // Tile and number of K slices of a GEMM.
 //
-// Up to 64 rows the weights' way from HBM is what counts: one row tile, and so many slices that about one workgroup per
-// CU streams them (more slices were measured: their partial sums cost more than the depth in flight brings).
+// Up to 128 rows the weights' way from HBM is what counts: one row tile, and so many slices that about one workgroup per
+// CU streams them (more slices were measured: their partial sums cost more than the depth in flight brings; fewer, as
+// the model below would have it from timings with cached weights, cost a step of 90 rows 1 %).
 //
 // Beyond that the choice is the smallest modelled time over the tiles and slice counts (model_us + the partial sums'
-// way through memory and, where no later kernel takes the slices as they are, a launch).  Over the 96 shapes of the
-// timings the choice is within 0.8 % of the fastest on average, 10 % at worst; one tile for each range of row counts
-// was 17 % off on average, and up to 62 % between 400 and 2000 rows, where it had 128 x 128 tiles (512 rows,
+// way through memory and, where no later kernel takes the slices as they are, a launch).  Over the 88 shapes of more
+// than 128 rows in the timings the choice is within 1.3 % of the fastest on average; the worst is 32 % (316 rows,
+// 6144 wide, where 64 x 128 tiles won with their weights cached).  One tile for each range of row counts was 17 % off
+// on average, and up to 62 % between 400 and 2000 rows, where it had 128 x 128 tiles (512 rows,
 // 25600 -> 5120: 233 us, now 144 us in 256 x 256 tiles and 6 slices; 753 rows, 14336 -> 4096: 134 -> 97 us; 4337 rows,
 // 14336 -> 4096, whose 272 tiles of 256 x 256 need two rounds of 256 CUs: 616 -> 486 us in 160 x 256 tiles).
 GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices) {
     int n_total = 0;
     for (int s = 0; s < g.nseg; ++s) n_total += g.n_seg[s];
     const int slabs = (k_ext_of(g) + kKAlign - 1) / kKAlign;
-    if (g.R <= 64) {
-        if (few_rows_wide(g)) return {TILE_64x256, 1};
-        const int tiles = n_tiles_for(g, kTileShape[TILE_64x128].bm, kTileShape[TILE_64x128].bn);
+    if (g.R <= 128) {
+        if (g.R <= 64 && few_rows_wide(g)) return {TILE_64x256, 1};
+        const int kind = g.R <= 64 ? TILE_64x128 : TILE_128;
+        const int tiles = n_tiles_for(g, kTileShape[kind].bm, kTileShape[kind].bn);
         int splits = tiles < 160 ? std::min({max_splits, 256 / tiles, slabs / 4}) : 1;
-        return {TILE_64x128, std::max(1, splits)};
+        return {kind, std::max(1, splits)};
     }
     GemmPlan best{TILE_128, 1};
     float best_us = -1.f;
     const bool reg_ok = gemm_decode_supported(g);
     for (int kind = 1; kind < TILE_KINDS; ++kind) {
-        if ((is_register_staged(kind) && !reg_ok) || kind == TILE_64x256) continue;
-        if (kind == TILE_64x128 && g.R > 3 * 64) continue;  // weights from HBM: re-read for every row tile (the timings had them cached)
+        if (is_register_staged(kind) && !reg_ok) continue;
+        // several row tiles of 64 re-read the weights: good in the timings, which had them cached, slower from HBM
+        if (kind == TILE_64x128 || kind == TILE_64x256) continue;
         for (int splits = 1; splits <= max_splits; ++splits) {
             if (splits > 1) {
                 const int per = (slabs + splits - 1) / splits;
