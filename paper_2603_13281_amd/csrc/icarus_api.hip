@@ -746,7 +746,7 @@ icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const
     {   // split-K slices of the projection, if any were left, are summed by the RoPE kernel
         const float *src = qkv_splits ? (const float *)(ws + L.gemm_part) : qkv;
         const size_t slice = (size_t)R * ldq;
-        if (rm.n_rope_tiles > 0 && rope_tiles_supported(dm, ldq, slice))
+        if (rm.n_rope_tiles > 0 && rope_tiles_supported(dm, ldq, slice) && rope_tiles_pay(dm, R))
             PHASE(ctx, st, ICARUS_PH_ROPE_APPEND,
                   launch_rope_append_tiles(dm, src, ldq, std::max(1, qkv_splits), slice, rm, rm.rope_tiles, rm.n_rope_tiles, kv_only, bt, max_blocks,
                                            pool, q, slot_out, ctx->base.q_norm, ctx->base.k_norm, st));

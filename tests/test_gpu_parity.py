@@ -11,7 +11,7 @@ import torch
 
 import oracle
 from paper_2603_13281_amd import synth
-from helpers import assert_cache_close, assert_close, assert_fp8_cache_close, fill_pool, filled_batch, mark_unwritten, oracle_config, read_pool
+from helpers import assert_cache_close, assert_close, assert_fp8_cache_close, e4m3_spacing, fill_pool, filled_batch, mark_unwritten, oracle_config, read_pool
 from gpu_util import bf16_ulp, dev, fp8_pool_to_float, host, make_layer, pool_from_device_layout, pool_to_device_layout
 
 pytestmark = pytest.mark.gpu
@@ -485,14 +485,19 @@ def test_prefill_of_a_few_rows_on_vector_kernels(shape):
     assert np.array_equal(host(dpool).view(np.uint32), host(dpool2).view(np.uint32))
 
 
+@pytest.mark.parametrize("tiles", [False, True], ids=["rows", "tiles"])
 @pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
 @pytest.mark.parametrize("shape", [synth.LLAMA_SMALL, synth.QWEN_SMALL], ids=lambda s: s.name)
-def test_prefill_appends_by_block_tiles(shape, fp8):
-    # chunk rows appended in tiles that lie within one block: a single token anywhere in it, whole blocks, the end of one
-    # and the start of the next; every slot right, every other byte of the pool as it was, also in a cache-only call
-    _say("case: append tiles", shape.name, "fp8", fp8)
+def test_prefill_appends_by_block_tiles(shape, fp8, tiles):
+    # chunk rows appended one by one or, from 20480 (row, head) pairs on, in tiles that lie within one block: a single
+    # token anywhere in it, whole blocks, the end of one and the start of the next; every slot right, every other byte of
+    # the pool as it was, also in a cache-only call
+    _say("case: append tiles", shape.name, "fp8", fp8, "tiles", tiles)
     pre = [0, 1, 15, 16, 17, 31, 5, 64]
     chunk = [1, 15, 17, 16, 33, 1, 40, 3]
+    if tiles:
+        more = -(-20480 // (shape.n_q_heads + 2 * shape.n_kv_heads)) - sum(chunk)  # the least that takes the tiles
+        pre, chunk = pre + [3, 0, 30, 8], chunk + [more // 4] * 3 + [more - more // 4 * 3]
     ks, vs = 0.02, 0.013
     base = synth.make_base(shape, seed=37, norm_ones=False)
     batch = synth.make_batch(shape, pre, [0] * len(pre), seed=37, headroom=max(chunk))
@@ -523,8 +528,22 @@ def test_prefill_appends_by_block_tiles(shape, fp8):
     if fp8:
         got = pool_from_device_layout(fp8_pool_to_float(dpool, ks, vs), shape.block_size, shape.head_dim)
         was = pool_from_device_layout(fp8_pool_to_float(before, ks, vs), shape.block_size, shape.head_dim)
-        for plane, scale in ((0, ks), (1, vs)):
-            assert_fp8_cache_close(got[:, plane], want_pool[:, plane], scale, True, "cache")
+        if tiles:
+            # the same call into a bf16 cache rounds the same fp32 K and V: half a grid step here, 2^-8 of the value there
+            # (which the bf16 case compares with the oracle)
+            plain = make_layer(shape, base, None, batch.num_blocks)
+            bpool = dev(pool_to_device_layout(pool), True)
+            plain.prefill_kv(bpool, bt, pre, chunk, dev(x, True), want_out=False)
+            same = pool_from_device_layout(host(bpool), shape.block_size, shape.head_dim).astype(np.float64)
+            written = np.unique(want_slots)
+            at = lambda a, plane: a[written // shape.block_size, plane, :, written % shape.block_size].astype(np.float64)
+            for plane, scale in ((0, ks), (1, vs)):
+                g, b = at(got, plane), np.clip(at(same, plane), -448 * scale, 448 * scale)
+                step = e4m3_spacing(np.maximum(np.abs(g), np.abs(b)), scale)
+                assert (np.abs(g - b) <= 0.501 * step + 2.0 ** -8 * np.abs(b)).all(), "fp8 cache against the bf16 cache"
+        else:
+            for plane, scale in ((0, ks), (1, vs)):
+                assert_fp8_cache_close(got[:, plane], want_pool[:, plane], scale, True, "cache")
     else:
         got, was = (pool_from_device_layout(host(t), shape.block_size, shape.head_dim) for t in (dpool, before))
         _cache_close(shape, got, want_pool, "cache")
