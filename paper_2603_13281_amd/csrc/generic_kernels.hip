@@ -172,6 +172,14 @@ hipError_t launch_silu_mul(const Dims &dm, const float *gate, const float *up, v
 // next Hkv are v.  The row arrives as `splits` fp32 slices (split-K partials of the projection
 // GEMM, `slice` floats apart) that are summed here.  Angles are computed in double, once per
 // row: pos * theta^(-2i/D).
+
+// One rotated pair.  Which product is rounded before the sum is written out: a cache entry must not depend on which
+// of the two kernels below wrote it, and left to the compiler the two came out differently.
+__device__ __forceinline__ void rotate_pair(float a, float b, float cs, float sn, float *ra, float *rb) {
+    *ra = __builtin_fmaf(a, cs, -(b * sn));
+    *rb = __builtin_fmaf(a, sn, b * cs);
+}
+
 template <typename T, typename KT>
 __global__ void __launch_bounds__(256) k_rope_append(const float *__restrict__ qkv, int ldq, int splits, size_t slice,
                                                      const int32_t *__restrict__ row_seq,
@@ -258,7 +266,8 @@ __global__ void __launch_bounds__(256) k_rope_append(const float *__restrict__ q
             a = a * inv[h] * Elem<T>::ld(nw + i);
             b = b * inv[h] * Elem<T>::ld(nw + i + half);
         }
-        float ra = a * cs - b * sn, rb = b * cs + a * sn;
+        float ra, rb;
+        rotate_pair(a, b, cs, sn, &ra, &rb);
         if (h < Hq) {
             T *dst = q_out + ((size_t)row * Hq + h) * D;
             Elem<T>::st(dst + i, ra);
@@ -397,12 +406,14 @@ __global__ void __launch_bounds__(256) k_rope_append_tile(const float *__restric
         if (h + 1 < r1) { na = load4((h + 1) * D + 4 * l); nb = load4((h + 1) * D + half + 4 * l); }
         float a[4] = {va.x, va.y, va.z, va.w}, b[4] = {vb.x, vb.y, vb.z, vb.w};
         if (qk_norm) {
-            float ss = 0.f;
+            float p[4];  // pair 4 l + e; summed in the order of k_rope_append, which has a pair to a lane
 #pragma unroll
-            for (int e = 0; e < 4; ++e) ss += a[e] * a[e] + b[e] * b[e];
+            for (int e = 0; e < 4; ++e) {
+                p[e] = __builtin_fmaf(b[e], b[e], a[e] * a[e]);
 #pragma unroll
-            for (int o = 8; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-            const float inv = rsqrtf(ss / (float)D + eps);
+                for (int o = 8; o > 0; o >>= 1) p[e] += __shfl_xor(p[e], o, 64);
+            }
+            const float inv = rsqrtf(((p[0] + p[2]) + (p[1] + p[3])) / (float)D + eps);
             const bf16_t *nw = h < Hq ? q_norm : k_norm;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -414,9 +425,7 @@ __global__ void __launch_bounds__(256) k_rope_append_tile(const float *__restric
         float ra[4], rb[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float cs = cs_t[t][4 * l + e], sn = sn_t[t][4 * l + e];
-            ra[e] = a[e] * cs - b[e] * sn;
-            rb[e] = b[e] * cs + a[e] * sn;
+            rotate_pair(a[e], b[e], cs_t[t][4 * l + e], sn_t[t][4 * l + e], &ra[e], &rb[e]);
         }
         if (h < Hq) {
             bf16_t *dst = q_out + ((size_t)(row0 + t) * Hq + h) * D + 4 * l;

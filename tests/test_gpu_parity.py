@@ -485,6 +485,33 @@ def test_prefill_of_a_few_rows_on_vector_kernels(shape):
     assert np.array_equal(host(dpool).view(np.uint32), host(dpool2).view(np.uint32))
 
 
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
+@pytest.mark.parametrize("shape", [synth.LLAMA_SMALL, synth.QWEN_SMALL], ids=lambda s: s.name)
+def test_cache_entries_do_not_depend_on_the_append_path(shape, fp8):
+    # the same chunks in one call (appended by tiles) and in calls of too few rows for tiles leave the same bytes;
+    # K = 256 keeps the projections in one slice, so each row's products are summed in the same order in all calls
+    _say("case: append paths agree", shape.name, "fp8", fp8)
+    shape = shape.replace(d_model=256)
+    heads = shape.n_q_heads + 2 * shape.n_kv_heads
+    pre, chunk = [0, 3, 21], [-(-20480 // heads) - 250, 201, 60]
+    base = synth.make_base(shape, seed=43, norm_ones=False)
+    batch = synth.make_batch(shape, pre, [0] * len(pre), seed=43, headroom=max(chunk))
+    layer = make_layer(shape, base, None, batch.num_blocks, **(dict(kv_fp8=True, k_scale=0.02, v_scale=0.013) if fp8 else {}))
+    x = dev(synth.make_hidden(shape, sum(chunk), seed=43, tag=5), True)
+    pools = [torch.zeros(layer.cfg.pool_shape(), dtype=layer.cfg.pool_dtype, device="cuda:0") for _ in range(2)]
+    bt = torch.from_numpy(batch.block_tables).cuda()
+    whole = layer.prefill_kv(pools[0], bt, pre, chunk, x)
+    row = 0
+    for s, n in enumerate(chunk):
+        for t in range(0, n, 320):
+            m = min(320, n - t)
+            layer.prefill_kv(pools[1], bt[s:s + 1].clone(), [pre[s] + t], [m], x[row + t:row + t + m].clone())
+        row += n
+    torch.cuda.synchronize()
+    assert torch.isfinite(whole).all()
+    assert torch.equal(pools[0].view(torch.uint8), pools[1].view(torch.uint8))
+
+
 @pytest.mark.parametrize("tiles", [False, True], ids=["rows", "tiles"])
 @pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
 @pytest.mark.parametrize("shape", [synth.LLAMA_SMALL, synth.QWEN_SMALL], ids=lambda s: s.name)
