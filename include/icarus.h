@@ -230,6 +230,12 @@ icarus_status icarus_set_kernel_mode(icarus_ctx *ctx, int32_t mode);
  * which exercises the partial-result merge at sizes an oracle finishes in seconds.  Changes the workspace a call needs: query icarus_workspace_bytes afterwards. */
 icarus_status icarus_set_attn_piece_limit(icarus_ctx *ctx, int32_t tokens);
 
+/* For tests and measurements, host only: the order in which the workgroups of a GEMM take its row_tiles x col_tiles tiles of
+ * tile_rows x tile_cols in k_slices slices of K, per_cu workgroups to a CU.  order (host, [cap][4]): XCD, row tile, column
+ * tile, slice of each workgroup that has a tile, in launch order; *n: how many have one. */
+icarus_status icarus_gemm_tile_order(int32_t row_tiles, int32_t col_tiles, int32_t k_slices, int32_t tile_rows, int32_t tile_cols,
+                                     int32_t per_cu, int32_t *order /*host*/, int32_t cap, int32_t *n /*host*/);
+
 /* Per-phase kernel timing for measurements.  While enabled, every kernel launch of the entry
  * points above is bracketed by HIP events recorded on the caller's stream (this costs a few
  * microseconds per launch: leave it off when timing whole steps).  icarus_timing_read waits

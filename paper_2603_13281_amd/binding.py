@@ -29,7 +29,8 @@ EXPORTS = ("icarus_create", "icarus_destroy", "icarus_last_error", "icarus_works
            "icarus_stack_last_error", "icarus_stack_workspace_bytes", "icarus_stack_prefill", "icarus_stack_decode",
            "icarus_cache_create", "icarus_cache_destroy", "icarus_cache_last_error", "icarus_cache_acquire", "icarus_cache_extend",
            "icarus_cache_commit", "icarus_cache_release", "icarus_cache_get_stats", "icarus_set_full_decoders",
-           "icarus_validate_block_tables", "icarus_set_attn_piece_limit", "icarus_attn_shared_kv_static", "icarus_bench_read")
+           "icarus_validate_block_tables", "icarus_set_attn_piece_limit", "icarus_attn_shared_kv_static", "icarus_bench_read",
+           "icarus_gemm_tile_order")
 
 PHASES = ("norm", "lora", "gemm_qkv", "rope_append", "attn", "attn_merge", "gemm_o", "gemm_gateup", "gemm_down",
           "elementwise")
@@ -117,6 +118,8 @@ def _load():
     lib.icarus_bench_read.argtypes = [vp, sz, vp, vp]
     lib.icarus_bench_mfma.restype = C.c_int
     lib.icarus_bench_mfma.argtypes = [vp, C.c_int32, C.c_int32, vp]
+    lib.icarus_gemm_tile_order.restype = C.c_int
+    lib.icarus_gemm_tile_order.argtypes = [i32] * 6 + [vp, i32, vp]
     lib.icarus_stack_create.restype = C.c_int
     lib.icarus_stack_create.argtypes = [C.POINTER(_StackCfg), C.POINTER(vp)]
     lib.icarus_stack_destroy.restype = None
@@ -275,6 +278,16 @@ def bench_mfma(waves: int, iters: int, device="cuda:0") -> float:
         raise IcarusError(rc, "icarus_bench_mfma failed")
     torch.cuda.synchronize()
     return ev[0].elapsed_time(ev[1]) * 1e-3
+
+
+def gemm_tile_order(row_tiles: int, col_tiles: int, k_slices: int, tile_rows: int, tile_cols: int, per_cu: int = 1) -> np.ndarray:
+    """[workgroups, 4]: XCD, row tile, column tile and K slice of a GEMM's workgroups in launch order (host only)."""
+    cap = row_tiles * col_tiles * k_slices + 64
+    out, n = np.zeros((cap, 4), dtype=np.int32), C.c_int32()
+    rc = _lib.icarus_gemm_tile_order(row_tiles, col_tiles, k_slices, tile_rows, tile_cols, per_cu, out.ctypes.data, cap, C.byref(n))
+    if rc != 0:
+        raise IcarusError(rc, "icarus_gemm_tile_order failed")
+    return out[:min(cap, n.value)]
 
 
 class IcarusLayer:

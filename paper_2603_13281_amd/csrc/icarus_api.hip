@@ -1424,6 +1424,28 @@ icarus_status icarus_bench_mfma(float *out, int32_t waves, int32_t iters, void *
     return launch_bench_mfma(out, waves, iters, (hipStream_t)stream) == hipSuccess ? ICARUS_OK : ICARUS_ERR_HIP;
 }
 
+icarus_status icarus_gemm_tile_order(int32_t row_tiles, int32_t col_tiles, int32_t k_slices, int32_t tile_rows, int32_t tile_cols,
+                                     int32_t per_cu, int32_t *order, int32_t cap, int32_t *n) {
+    if (row_tiles <= 0 || col_tiles <= 0 || k_slices <= 0 || tile_rows <= 0 || tile_cols <= 0 || per_cu <= 0 || !order || !n)
+        return ICARUS_ERR_INVALID_ARG;
+    GemmArgs g{};
+    g.m_tiles = row_tiles; g.n_tiles = col_tiles; g.splits = k_slices;
+    gemm_set_panels(&g, tile_rows, tile_cols, per_cu);
+    const dim3 grid = gemm_grid(g);
+    *n = 0;
+    for (unsigned y = 0; y < grid.y; ++y)
+        for (unsigned x = 0; x < grid.x; ++x) {
+            int tm, tn, kz;
+            if (!tile_at(g, (int)x, (int)y, &tm, &tn, &kz)) continue;
+            if (*n < cap) {
+                int32_t *o = order + 4 * (size_t)*n;
+                o[0] = (int32_t)((y * grid.x + x) % 8); o[1] = tm; o[2] = tn; o[3] = kz;
+            }
+            ++*n;
+        }
+    return ICARUS_OK;
+}
+
 size_t icarus_workspace_bytes(const icarus_ctx *ctx, int32_t max_rows, int32_t max_seqs, int32_t max_ctx) {
     if (!ctx || max_rows < 0 || max_seqs < 0 || max_ctx < 0) return 0;
     return ws_layout(ctx, (size_t)std::max(1, max_rows), (size_t)std::max(1, max_seqs), (size_t)max_ctx).total;

@@ -146,18 +146,22 @@ inline dim3 gemm_grid(const GemmArgs &g) {
 // x / n for x * n < 2^32, by the host's inv = ceil(2^32 / n) (0 for n = 1): a division would cost these short kernels
 // as much as a dozen loads
 inline uint32_t gemm_inv(int n) { return n > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint64_t)n - 1) / (uint64_t)n) : 0u; }
-__device__ __forceinline__ int gemm_div(int x, uint32_t inv) { return inv ? (int)__umulhi((uint32_t)x, inv) : x; }
-// tile and K slice of this workgroup; false: none
-__device__ __forceinline__ bool tile_of_workgroup(const GemmArgs &g, int *tile_m, int *tile_n, int *kz) {
-    const int within = blockIdx.x >> 3, p = blockIdx.y * 8 + (blockIdx.x & 7);
+__host__ __device__ __forceinline__ int gemm_div(int x, uint32_t inv) { return inv ? (int)(((uint64_t)(uint32_t)x * inv) >> 32) : x; }
+// Tile and K slice of workgroup (bx, by); false: none.  Neighbouring columns of a panel go to one XCD.  Dealing the columns
+// of a single row tile over the XCDs instead depends on how the weight rows' strides fall: a step of 32 rows with an LM head
+// of 4096 -> 128256 425 -> 414 us, but with one of 4096 -> 65536 281 -> 322 us, and 9 rows of gate and up, 8192 -> 2 x 28672,
+// 177 -> 227 us.
+__host__ __device__ __forceinline__ bool tile_at(const GemmArgs &g, int bx, int by, int *tile_m, int *tile_n, int *kz) {
+    const int within = bx >> 3, p = by * 8 + (bx & 7);
     *kz = g.splits > 1 ? gemm_div(p, g.inv_panels) : (int)(p >= g.n_panels);
     const int panel = p - *kz * g.n_panels;
     const int pn = gemm_div(panel, g.inv_panels_m), wn = gemm_div(within, g.inv_panel_m);
     *tile_m = (panel - pn * g.panels_m) * g.panel_m + within - wn * g.panel_m;
-    // one row tile: nothing is shared inside a panel, and neighbouring columns on different XCDs stream better (an LM head's
-    // 501 tiles 222 us -> 206 us); with several the panel's columns stay together
-    *tile_n = g.m_tiles == 1 ? wn * g.n_panels + panel : pn * g.panel_n + wn;
+    *tile_n = pn * g.panel_n + wn;
     return *kz < g.splits && *tile_m < g.m_tiles && *tile_n < g.n_tiles;
+}
+__device__ __forceinline__ bool tile_of_workgroup(const GemmArgs &g, int *tile_m, int *tile_n, int *kz) {
+    return tile_at(g, blockIdx.x, blockIdx.y, tile_m, tile_n, kz);
 }
 hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st);
 // How a GEMM is run: tile kind and split-K slices, at most max_splits (1 where K cannot be split: DUAL).  takes_slices: a

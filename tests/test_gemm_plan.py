@@ -1,0 +1,28 @@
+"""How the GEMMs' tiles are laid over the chip, on the host."""
+import numpy as np
+import pytest
+
+from paper_2603_13281_amd import binding
+
+XCDS, CUS = 8, 256
+
+
+@pytest.mark.parametrize("tile", [(64, 128, 2), (128, 128, 1), (192, 128, 1), (256, 256, 1), (160, 256, 1)], ids=str)
+@pytest.mark.parametrize("rows,cols,slices", [(1, 1, 1), (1, 7, 12), (1, 33, 4), (1, 224, 1), (1, 448, 1), (1, 1002, 1), (1, 80, 3), (2, 20, 12),
+                                              (3, 448, 1), (9, 56, 2), (17, 112, 1), (64, 5, 3), (257, 31, 1)])
+def test_every_tile_of_every_slice_once(rows, cols, slices, tile):
+    order = binding.gemm_tile_order(rows, cols, slices, *tile)
+    assert len(order) == rows * cols * slices
+    assert len(np.unique(order[:, 1:], axis=0)) == len(order)
+    assert (order.min(axis=0) >= 0).all() and (order.max(axis=0) < [XCDS, rows, cols, slices]).all()
+
+
+@pytest.mark.parametrize("tile", [(64, 128, 2), (128, 128, 1), (160, 256, 1)], ids=str)
+@pytest.mark.parametrize("cols", [112, 128, 200, 224, 250, 448, 512, 1002])
+def test_one_row_tile_keeps_neighbouring_columns_on_an_xcd(cols, tile):
+    # dealt over the XCDs, a quarter of the time is lost where the columns' strides line up (K = 8192, and K = 4096 with 65536 outputs)
+    order = binding.gemm_tile_order(1, cols, 1, *tile)
+    xcd = np.empty(cols, dtype=np.int64)
+    xcd[order[:, 2]] = order[:, 0]
+    changes = int((np.diff(xcd) != 0).sum())
+    assert changes <= cols // 4, (changes, cols)
