@@ -236,6 +236,13 @@ icarus_status icarus_set_attn_piece_limit(icarus_ctx *ctx, int32_t tokens);
 icarus_status icarus_gemm_tile_order(int32_t row_tiles, int32_t col_tiles, int32_t k_slices, int32_t tile_rows, int32_t tile_cols,
                                      int32_t per_cu, int32_t *order /*host*/, int32_t cap, int32_t *n /*host*/);
 
+/* The same for the choice of a launch: a GEMM of `rows` rows over K = k against n_segs stacked weight matrices of n_seg[.] rows
+ * (host, at most 3; fused != 0: the gate/up pair of n_seg[0] rows each), adapter_cols = n_models * rank (a multiple of 8; 0: no
+ * adapters), at most max_slices slices of K, which a later kernel sums on the way if taken != 0.  choice (host): rows and weight
+ * rows of a tile, 1 if it is staged through registers, slices. */
+icarus_status icarus_gemm_choice(int32_t rows, int32_t k, const int32_t *n_seg /*host*/, int32_t n_segs, int32_t fused, int32_t adapter_cols,
+                                 int32_t max_slices, int32_t taken, int32_t *choice /*host [4]*/);
+
 /* Per-phase kernel timing for measurements.  While enabled, every kernel launch of the entry
  * points above is bracketed by HIP events recorded on the caller's stream (this costs a few
  * microseconds per launch: leave it off when timing whole steps).  icarus_timing_read waits

@@ -30,7 +30,7 @@ EXPORTS = ("icarus_create", "icarus_destroy", "icarus_last_error", "icarus_works
            "icarus_cache_create", "icarus_cache_destroy", "icarus_cache_last_error", "icarus_cache_acquire", "icarus_cache_extend",
            "icarus_cache_commit", "icarus_cache_release", "icarus_cache_get_stats", "icarus_set_full_decoders",
            "icarus_validate_block_tables", "icarus_set_attn_piece_limit", "icarus_attn_shared_kv_static", "icarus_bench_read",
-           "icarus_gemm_tile_order")
+           "icarus_gemm_tile_order", "icarus_gemm_choice")
 
 PHASES = ("norm", "lora", "gemm_qkv", "rope_append", "attn", "attn_merge", "gemm_o", "gemm_gateup", "gemm_down",
           "elementwise")
@@ -120,6 +120,8 @@ def _load():
     lib.icarus_bench_mfma.argtypes = [vp, C.c_int32, C.c_int32, vp]
     lib.icarus_gemm_tile_order.restype = C.c_int
     lib.icarus_gemm_tile_order.argtypes = [i32] * 6 + [vp, i32, vp]
+    lib.icarus_gemm_choice.restype = C.c_int
+    lib.icarus_gemm_choice.argtypes = [i32, i32, vp, i32, i32, i32, i32, i32, vp]
     lib.icarus_stack_create.restype = C.c_int
     lib.icarus_stack_create.argtypes = [C.POINTER(_StackCfg), C.POINTER(vp)]
     lib.icarus_stack_destroy.restype = None
@@ -288,6 +290,16 @@ def gemm_tile_order(row_tiles: int, col_tiles: int, k_slices: int, tile_rows: in
     if rc != 0:
         raise IcarusError(rc, "icarus_gemm_tile_order failed")
     return out[:min(cap, n.value)]
+
+
+def gemm_choice(rows: int, k: int, n, fused: bool = False, adapter_cols: int = 0, max_slices: int = 12, taken: bool = False):
+    """(tile rows, tile columns, staged through registers, K slices) of a GEMM's launch (host only); n: outputs per segment."""
+    seg = np.ascontiguousarray(np.atleast_1d(n), dtype=np.int32)
+    out = np.zeros(4, dtype=np.int32)
+    rc = _lib.icarus_gemm_choice(rows, k, seg.ctypes.data, len(seg), int(fused), adapter_cols, max_slices, int(taken), out.ctypes.data)
+    if rc != 0:
+        raise IcarusError(rc, "icarus_gemm_choice failed")
+    return int(out[0]), int(out[1]), bool(out[2]), int(out[3])
 
 
 class IcarusLayer:

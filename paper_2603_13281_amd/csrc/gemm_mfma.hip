@@ -483,7 +483,6 @@ struct TileShape { int bm, bn, per_cu; float first_us, slab_us, slab2_us; };
 constexpr TileShape kTileShape[TILE_KINDS] = {
     {0, 0, 0, 0.f, 0.f, 0.f},
     {64, 128, 2, 2.0f, 0.48f, 0.77f},
-    {64, 256, 1, 0.f, 0.f, 0.f},  // see few_rows_wide
     {128, 128, 1, 3.8f, 0.60f, 0.f},
     {192, 128, 1, 4.7f, 0.77f, 0.f},
     {256, 256, 1, 7.8f, 1.65f, 0.f},
@@ -561,18 +560,11 @@ bool gemm_mfma_supported(const Dims &dm, int K) {
     return dm.bf16 && K % kKAlign == 0 && r_ok && n_ok;
 }
 
-// Up to 64 rows: 64 x 256 tiles for an output as wide as an LM head's, else 64 x 128.  What a CU can take in counts in
-// 128-byte lines, activations included: 64 rows for every 256 weight rows instead of every 128 are a sixth of the lines
-// less (64 rows x 128256 outputs 224 -> 206 us).  Below 448 tiles (1.75 rounds of 256 CUs) the wider tile leaves CUs idle;
-// grouped launches, whose groups have few rows, were slower with it (gate and up of 9 groups 372 -> 394 us).
-bool few_rows_wide(const GemmArgs &g) {
-    if (g.mode == GEMM_DUAL || g.row_tiles) return false;
-    return n_tiles_for(g, kTileShape[TILE_64x256].bm, kTileShape[TILE_64x256].bn) >= 448;
-}
-
 // Tile and number of K slices of a GEMM.
 //
-// Up to 128 rows the weights' way from HBM is what counts: one row tile, and so many slices that about one workgroup per
+// Up to 128 rows the weights' way from HBM is what counts: one row tile, 128 wide (64 x 256 tiles for up to 64 rows of an LM
+// head: within 3 % either way at up to two rounds of CUs, 2-10 % slower where the last round is short -- 151936 and 202048 outputs --
+// and for K = 4096), and so many slices that about one workgroup per
 // CU streams them (more slices were measured: their partial sums cost more than the depth in flight brings; fewer, as
 // the model below would have it from timings with cached weights, cost a step of 90 rows 1 %).
 //
@@ -588,7 +580,6 @@ GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices) {
     for (int s = 0; s < g.nseg; ++s) n_total += g.n_seg[s];
     const int slabs = (k_ext_of(g) + kKAlign - 1) / kKAlign;
     if (g.R <= 128) {
-        if (g.R <= 64 && few_rows_wide(g)) return {TILE_64x256, 1};
         const int kind = g.R <= 64 ? TILE_64x128 : TILE_128;
         const int tiles = n_tiles_for(g, kTileShape[kind].bm, kTileShape[kind].bn);
         int splits = tiles < 160 ? std::min({max_splits, 256 / tiles, slabs / 4}) : 1;
@@ -600,7 +591,7 @@ GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices) {
     for (int kind = 1; kind < TILE_KINDS; ++kind) {
         if (is_register_staged(kind) && !reg_ok) continue;
         // several row tiles of 64 re-read the weights: good in the timings, which had them cached, slower from HBM
-        if (kind == TILE_64x128 || kind == TILE_64x256) continue;
+        if (kind == TILE_64x128) continue;
         for (int splits = 1; splits <= max_splits; ++splits) {
             if (splits > 1) {
                 const int per = (slabs + splits - 1) / splits;
@@ -620,6 +611,7 @@ GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices) {
 
 int gemm_row_tile(int most_rows) { return most_rows <= 64 ? TILE_64x128 : TILE_128; }
 int gemm_tile_rows(int tile) { return kTileShape[tile].bm; }
+int gemm_tile_cols(int tile) { return kTileShape[tile].bn; }
 
 // K slices of a grouped launch.  With a weight matrix per group it is bound by their way from HBM, like a GEMM of few
 // rows, and by the last round: 9 groups x 32 column tiles on 512 workgroup slots leave 32 CUs with twice the work of
@@ -664,7 +656,6 @@ hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st) {
     g.k_per_split = ((g.K_ext + g.splits - 1) / g.splits + kKAlign - 1) / kKAlign * kKAlign;
     switch (g.tile) {
     case TILE_64x128: return g.row_tiles ? launch_cfg<64, 128, 64, 3, 2, 2, true>(g, st) : launch_cfg<64, 128, 64, 3, 2, 2>(g, st);
-    case TILE_64x256: return launch_cfg<64, 256, 64, 3, 1, 4>(g, st);
     case TILE_128: return g.row_tiles ? launch_cfg<128, 128, 64, 4, 2, 2, true>(g, st) : launch_cfg<128, 128, 64, 4, 2, 2>(g, st);
     case TILE_192x128: return launch_cfg<192, 128, 64, 3, 2, 2>(g, st);
     case TILE_256x256: return launch_cfg<256, 256, 64, 2, 2, 4>(g, st);

@@ -1446,6 +1446,29 @@ icarus_status icarus_gemm_tile_order(int32_t row_tiles, int32_t col_tiles, int32
     return ICARUS_OK;
 }
 
+icarus_status icarus_gemm_choice(int32_t rows, int32_t k, const int32_t *n_seg, int32_t n_segs, int32_t fused, int32_t adapter_cols,
+                                 int32_t max_slices, int32_t taken, int32_t *choice) {
+    if (rows <= 0 || k <= 0 || k % 64 || !n_seg || n_segs < 1 || n_segs > 3 || (fused && n_segs != 1) || adapter_cols < 0 || adapter_cols % 8 ||
+        max_slices < 1 || !choice)
+        return ICARUS_ERR_INVALID_ARG;
+    static const bf16_raw some = 0;  // never read: only whether there are adapters counts
+    GemmArgs g{};
+    g.R = rows; g.K = g.ldx = k; g.nseg = n_segs;
+    for (int s = 0; s < n_segs; ++s) {
+        if (n_seg[s] <= 0) return ICARUS_ERR_INVALID_ARG;
+        g.n_seg[s] = n_seg[s];
+    }
+    g.mode = fused ? GEMM_DUAL : GEMM_PLAIN;
+    g.r = 8;
+    if (adapter_cols) { g.T = g.B[0] = g.B[1] = &some; g.M_models = adapter_cols / 8; g.ldt = fused ? 2 * adapter_cols : adapter_cols; }
+    const GemmPlan p = gemm_plan(g, fused ? 1 : max_slices, taken != 0);
+    choice[0] = gemm_tile_rows(p.tile);
+    choice[1] = gemm_tile_cols(p.tile);
+    choice[2] = p.tile == TILE_REG_192x256 || p.tile == TILE_REG_160x256;
+    choice[3] = p.splits;
+    return ICARUS_OK;
+}
+
 size_t icarus_workspace_bytes(const icarus_ctx *ctx, int32_t max_rows, int32_t max_seqs, int32_t max_ctx) {
     if (!ctx || max_rows < 0 || max_seqs < 0 || max_ctx < 0) return 0;
     return ws_layout(ctx, (size_t)std::max(1, max_rows), (size_t)std::max(1, max_seqs), (size_t)max_ctx).total;

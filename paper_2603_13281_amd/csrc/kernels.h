@@ -114,7 +114,7 @@ struct AttnPlan {
 // ICaRusLinear GEMM on matrix cores.  Y = X W^T (+ T Bcat^T), see gemm_mfma.hip.
 enum { GEMM_PLAIN = 0, GEMM_DUAL = 1 };          // DUAL: W[0] = gate, W[1] = up, Y = silu(gate) * up
 enum { EPI_F32 = 0, EPI_BF16_RESID = 1 };        // plain epilogues (DUAL always stores bf16)
-enum TileKind { TILE_AUTO = 0, TILE_64x128, TILE_64x256, TILE_128, TILE_192x128, TILE_256x256, TILE_REG_192x256, TILE_REG_160x256, TILE_KINDS };
+enum TileKind { TILE_AUTO = 0, TILE_64x128, TILE_128, TILE_192x128, TILE_256x256, TILE_REG_192x256, TILE_REG_160x256, TILE_KINDS };
 struct GemmArgs {
     const bf16_raw *X; int ldx; int R; int K;    // activations [R, K] (row stride ldx)
     const bf16_raw *W[3]; int n_seg[3]; int nseg; // weight segments stacked along N, each [n_seg, K]
@@ -171,6 +171,7 @@ GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices);
 // Grouped launches: tile kind for groups of at most most_rows rows, its height, and the K slices to use.
 int gemm_row_tile(int most_rows);
 int gemm_tile_rows(int tile);
+int gemm_tile_cols(int tile);
 int gemm_grouped_splits(const GemmArgs &g, int max_splits, bool takes_slices);
 // Tiles of gemm_decode.hip (TILE_REG_*): both operands loaded coalesced, parked in registers two slabs ahead and staged
 // through LDS by register stores; launch_gemm_mfma takes this path for them.

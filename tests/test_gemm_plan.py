@@ -26,3 +26,10 @@ def test_one_row_tile_keeps_neighbouring_columns_on_an_xcd(cols, tile):
     xcd[order[:, 2]] = order[:, 0]
     changes = int((np.diff(xcd) != 0).sum())
     assert changes <= cols // 4, (changes, cols)
+
+
+@pytest.mark.parametrize("vocab", [32000, 49152, 65536, 128256, 131072, 151936, 202048])
+@pytest.mark.parametrize("rows", [1, 8, 64])
+def test_lm_head_of_a_few_rows(rows, vocab):
+    # 64 x 256 tiles lost up to a tenth of the step where the last round of workgroups is short
+    assert binding.gemm_choice(rows, 4096, vocab, max_slices=1) == (64, 128, False, 1)

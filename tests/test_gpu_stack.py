@@ -109,7 +109,7 @@ def test_stack_rejects_bad_arguments():
 
 
 def test_stack_with_a_wide_vocabulary():
-    """The LM head of a few rows against a vocabulary wide enough for its 64 x 256 tiles (448 of them), with a ragged
+    """The LM head of a few rows against a vocabulary of more column tiles than a round of workgroups, with a ragged
     last one; prompt (2 logit rows) and one token step (5 rows)."""
     from paper_2603_13281_amd import synth
     print("case: wide vocabulary", flush=True)
