@@ -569,12 +569,17 @@ bool gemm_mfma_supported(const Dims &dm, int K) {
 // the model below would have it from timings with cached weights, cost a step of 90 rows 1 %).
 //
 // Beyond that the choice is the smallest modelled time over the tiles and slice counts (model_us + the partial sums'
-// way through memory and, where no later kernel takes the slices as they are, a launch).  Over the 88 shapes of more
-// than 128 rows in the timings the choice is within 1.3 % of the fastest on average; the worst is 32 % (316 rows,
-// 6144 wide, where 64 x 128 tiles won with their weights cached).  One tile for each range of row counts was 17 % off
-// on average, and up to 62 % between 400 and 2000 rows, where it had 128 x 128 tiles (512 rows,
-// 25600 -> 5120: 233 us, now 144 us in 256 x 256 tiles and 6 slices; 753 rows, 14336 -> 4096: 134 -> 97 us; 4337 rows,
-// 14336 -> 4096, whose 272 tiles of 256 x 256 need two rounds of 256 CUs: 616 -> 486 us in 160 x 256 tiles).
+// way through memory and, where no later kernel takes the slices as they are, a launch).  Near ties are decided by what
+// the model does not know -- how the strides of the slices fall on the HBM channels, what the row kernel after a sliced
+// projection pays -- so the plain choice has a start: up to 384 rows of a narrow output, 192-row tiles in as many slices as
+// the CUs hold at once, which the modelled time has to undercut by 4 %; with more rows no slices, by 3 %.
+// Measured inside a layer, weights from HBM, consumers of the slices included (5 widths of 2048-8192, 130-4337 rows, QKV, O,
+// gate/up, down: 1128 launches, every tile x 1-12 slices): within 0.8 % of the fastest on average, 18 % at worst (252 rows,
+// 5120 -> 10240).  Without the start for the plain choice 19 of them were 2-29 % slower than one tile for each range of
+// row counts (162 rows, 28672 -> 8192: 152 us in 192 x 256 tiles, 118 us in 192 x 128); with it 5, by 3 % at most.  The
+// fixed tiles in turn are 12 % from the fastest on average (512 rows, 25600 -> 5120: 233 us in 128 x 128 tiles, 144 us
+// in 256 x 256 and 6 slices; 4337 rows, 14336 -> 4096, whose 272 tiles of 256 x 256 need two rounds of 256 CUs: 616 us, in
+// 160 x 256 tiles 486 us).
 GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices) {
     int n_total = 0;
     for (int s = 0; s < g.nseg; ++s) n_total += g.n_seg[s];
@@ -585,24 +590,28 @@ GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices) {
         int splits = tiles < 160 ? std::min({max_splits, 256 / tiles, slabs / 4}) : 1;
         return {kind, std::max(1, splits)};
     }
+    auto modelled = [&](int kind, int splits) {
+        const float mb = (float)g.R * (float)n_total * 4e-6f;  // one slice
+        return model_us(g, kind, splits) + (splits > 1 ? mb * splits * 0.38f + (takes_slices ? 0.f : 4.f + mb * 0.2f) : 0.f);
+    };
+    const bool few = g.R <= 384;
     GemmPlan best{TILE_128, 1};
     float best_us = -1.f;
+    if (few && g.mode != GEMM_DUAL && n_tiles_for(g, 192, 256) < 160) {
+        const int tiles = n_tiles_for(g, 192, 128);
+        best = {TILE_192x128, tiles < 160 ? std::max(1, std::min({max_splits, 256 / tiles, slabs / 4})) : 1};
+        best_us = 0.96f * modelled(best.tile, best.splits);
+    }
     const bool reg_ok = gemm_decode_supported(g);
-    for (int kind = 1; kind < TILE_KINDS; ++kind) {
+    for (int kind = TILE_128; kind < TILE_KINDS; ++kind) {  // several row tiles of 64 would read the weights again
         if (is_register_staged(kind) && !reg_ok) continue;
-        // several row tiles of 64 re-read the weights: good in the timings, which had them cached, slower from HBM
-        if (kind == TILE_64x128) continue;
         for (int splits = 1; splits <= max_splits; ++splits) {
             if (splits > 1) {
                 const int per = (slabs + splits - 1) / splits;
                 if (per < 6) break;
                 if ((slabs + per - 1) / per != splits) continue;  // the last slice would be empty
             }
-            float us = model_us(g, kind, splits);
-            if (splits > 1) {
-                const float mb = (float)g.R * (float)n_total * 4e-6f;  // one slice
-                us += mb * splits * 0.38f + (takes_slices ? 0.f : 4.f + mb * 0.2f);
-            }
+            const float us = modelled(kind, splits) * (splits > 1 && !few ? 1.03f : 1.f);
             if (best_us < 0.f || us < best_us) { best_us = us; best = {kind, splits}; }
         }
     }
