@@ -43,6 +43,8 @@ CHOICES = [
     ((270, 8192, [8192], 128, 12, True), (192, 128, False, 2)),
     ((720, 8192, [5120], 256, 12, True), (128, 128, False, 1)),
     ((385, 8192, [8192], 0, 12, True), (128, 128, False, 1)),
+    ((10000, 4096, [4096], 0, 1, True), (256, 256, False, 1)),        # 349 us in 160 x 256, 327 us
+    ((8000, 8192, [5120], 0, 1, True), (256, 256, False, 1)),
 ]
 
 
