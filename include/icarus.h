@@ -243,6 +243,10 @@ icarus_status icarus_gemm_tile_order(int32_t row_tiles, int32_t col_tiles, int32
 icarus_status icarus_gemm_choice(int32_t rows, int32_t k, const int32_t *n_seg /*host*/, int32_t n_segs, int32_t fused, int32_t adapter_cols,
                                  int32_t max_slices, int32_t taken, int32_t *choice /*host [4]*/);
 
+/* The same for the grouped GEMMs of decoders with private weights: rows and weight rows of a tile (tile, host [2]) for groups of
+ * group_rows[.] rows (host, [n_groups]). */
+icarus_status icarus_gemm_group_tile(const int32_t *group_rows /*host*/, int32_t n_groups, int32_t *tile /*host [2]*/);
+
 /* Per-phase kernel timing for measurements.  While enabled, every kernel launch of the entry
  * points above is bracketed by HIP events recorded on the caller's stream (this costs a few
  * microseconds per launch: leave it off when timing whole steps).  icarus_timing_read waits

@@ -30,7 +30,7 @@ EXPORTS = ("icarus_create", "icarus_destroy", "icarus_last_error", "icarus_works
            "icarus_cache_create", "icarus_cache_destroy", "icarus_cache_last_error", "icarus_cache_acquire", "icarus_cache_extend",
            "icarus_cache_commit", "icarus_cache_release", "icarus_cache_get_stats", "icarus_set_full_decoders",
            "icarus_validate_block_tables", "icarus_set_attn_piece_limit", "icarus_attn_shared_kv_static", "icarus_bench_read",
-           "icarus_gemm_tile_order", "icarus_gemm_choice")
+           "icarus_gemm_tile_order", "icarus_gemm_choice", "icarus_gemm_group_tile")
 
 PHASES = ("norm", "lora", "gemm_qkv", "rope_append", "attn", "attn_merge", "gemm_o", "gemm_gateup", "gemm_down",
           "elementwise")
@@ -122,6 +122,8 @@ def _load():
     lib.icarus_gemm_tile_order.argtypes = [i32] * 6 + [vp, i32, vp]
     lib.icarus_gemm_choice.restype = C.c_int
     lib.icarus_gemm_choice.argtypes = [i32, i32, vp, i32, i32, i32, i32, i32, vp]
+    lib.icarus_gemm_group_tile.restype = C.c_int
+    lib.icarus_gemm_group_tile.argtypes = [vp, i32, vp]
     lib.icarus_stack_create.restype = C.c_int
     lib.icarus_stack_create.argtypes = [C.POINTER(_StackCfg), C.POINTER(vp)]
     lib.icarus_stack_destroy.restype = None
@@ -300,6 +302,16 @@ def gemm_choice(rows: int, k: int, n, fused: bool = False, adapter_cols: int = 0
     if rc != 0:
         raise IcarusError(rc, "icarus_gemm_choice failed")
     return int(out[0]), int(out[1]), bool(out[2]), int(out[3])
+
+
+def gemm_group_tile(group_rows):
+    """(rows, columns) of the tile the grouped GEMMs take for groups of these row counts (host only)."""
+    n = np.ascontiguousarray(group_rows, dtype=np.int32)
+    out = np.zeros(2, dtype=np.int32)
+    rc = _lib.icarus_gemm_group_tile(n.ctypes.data, len(n), out.ctypes.data)
+    if rc != 0:
+        raise IcarusError(rc, "icarus_gemm_group_tile failed")
+    return int(out[0]), int(out[1])
 
 
 class IcarusLayer:

@@ -476,18 +476,18 @@ hipError_t launch_cfg(GemmArgs g, hipStream_t st) {
 // Tile shapes: rows x weight rows of a workgroup, all with 64-wide K slabs (32-wide slabs ask for every 128-byte line of
 // a weight row twice, half each time, and stream at about 60 % of the rate).  The first four are k_gemm_mfma, the last
 // two k_gemm_decode.  first_us: what a workgroup takes apart from its slabs (start, first slab, epilogue); slab_us: a slab
-// with every CU busy, two workgroups to a CU in the second figure where two fit.  The figures are a fit to 5000 timings on
+// with every CU busy, for each of the per_cu workgroups that share one.  The figures are a fit to 5000 timings on
 // this GPU (80-4337 rows x the projections of a Llama-3-8B- and a Qwen3-32B-shaped layer x every tile x 1-12 slices; the
-// fit is 7-11 % off on average), see gemm_plan.
-struct TileShape { int bm, bn, per_cu; float first_us, slab_us, slab2_us; };
+// fit is 7-11 % off on average), see gemm_plan and gemm_row_tile.
+struct TileShape { int bm, bn, per_cu; float first_us, slab_us; };
 constexpr TileShape kTileShape[TILE_KINDS] = {
-    {0, 0, 0, 0.f, 0.f, 0.f},
-    {64, 128, 2, 2.0f, 0.48f, 0.77f},
-    {128, 128, 1, 3.8f, 0.60f, 0.f},
-    {192, 128, 1, 4.7f, 0.77f, 0.f},
-    {256, 256, 1, 7.8f, 1.65f, 0.f},
-    {192, 256, 1, 10.2f, 1.26f, 0.f},
-    {160, 256, 1, 9.3f, 1.13f, 0.f},
+    {0, 0, 0, 0.f, 0.f},
+    {64, 128, 2, 2.0f, 0.77f},
+    {128, 128, 1, 3.8f, 0.60f},
+    {192, 128, 1, 4.7f, 0.77f},
+    {256, 256, 1, 7.8f, 1.65f},
+    {192, 256, 1, 10.2f, 1.26f},
+    {160, 256, 1, 9.3f, 1.13f},
 };
 
 int n_tiles_for(const GemmArgs &g, int bm, int bn) {
@@ -504,17 +504,14 @@ int k_ext_of(const GemmArgs &g) {
     return g.K + ((g.T && g.B[0]) ? g.M_models * g.r : 0);
 }
 
-// Modelled time of a launch, in us: rounds of workgroups over the 256 CUs; a round that leaves CUs idle has faster slabs.
+// Modelled time of a launch, in us, for tiles with a CU of their own: rounds of workgroups over the 256 CUs; a round that
+// leaves CUs idle has faster slabs.
 float model_us(const GemmArgs &g, int kind, int splits) {
     const TileShape &t = kTileShape[kind];
     const int slabs = (k_ext_of(g) + kKAlign - 1) / kKAlign, per_slice = (slabs + splits - 1) / splits;
     const int64_t wgs = (int64_t)n_tiles_for(g, t.bm, t.bn) * splits;
-    auto round = [&](int64_t n) {
-        if (n == 0) return 0.f;
-        const float per = (float)n / 256.f;
-        return t.first_us + (float)per_slice * (per > 1.f ? t.slab2_us : t.slab_us) * (0.75f + 0.25f * std::min(1.f, per));
-    };
-    return (float)(wgs / (256 * t.per_cu)) * round(256 * t.per_cu) + round(wgs % (256 * t.per_cu));
+    auto round = [&](int64_t n) { return n ? t.first_us + (float)per_slice * t.slab_us * (0.75f + 0.25f * (float)n / 256.f) : 0.f; };
+    return (float)(wgs / 256) * round(256) + round(wgs % 256);
 }
 
 }  // namespace
@@ -622,23 +619,41 @@ GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices) {
     return best;
 }
 
-int gemm_row_tile(int most_rows) { return most_rows <= 64 ? TILE_64x128 : TILE_128; }
+// Tile of a grouped launch: the one whose row tiles together cost the fewest slabs.  off: first row of each group and the end
+// of the last.  Each row tile reads its group's weights once, so with a few rows per group the smallest tile that holds most
+// groups wins, with hundreds the large one.  Gate and up of 9 groups (4096 -> 2 x 14336), us in 64 x 128 / 128 x 128 / 192 x 128 /
+// 256 x 256 tiles: groups of 66 rows 474 / 404 / 449 / 488, one of 300 and eight of 38 rows 392 / 448 / 488 / 559, groups of
+// 130 rows 622 / 662 / 471 / 503, of 256 rows 855 / 710 / 863 / 531, of 1024 rows 3037 / 2604 / 2551 / 1785 (2014 in a launch
+// of 256 x 256 tiles per group).
+int gemm_row_tile(const int *off, int n_groups) {
+    int best = TILE_64x128;
+    float best_cost = -1.f;
+    for (int kind : {TILE_64x128, TILE_128, TILE_192x128, TILE_256x256}) {
+        const TileShape &t = kTileShape[kind];
+        int64_t tiles = 0;
+        for (int j = 0; j < n_groups; ++j) tiles += (off[j + 1] - off[j] + t.bm - 1) / t.bm;
+        const float cost = (float)tiles * t.slab_us / (float)(t.bn * t.per_cu);
+        if (best_cost < 0.f || cost < best_cost) { best_cost = cost; best = kind; }
+    }
+    return best;
+}
 int gemm_tile_rows(int tile) { return kTileShape[tile].bm; }
 int gemm_tile_cols(int tile) { return kTileShape[tile].bn; }
 
 // K slices of a grouped launch.  With a weight matrix per group it is bound by their way from HBM, like a GEMM of few
 // rows, and by the last round: 9 groups x 32 column tiles on 512 workgroup slots leave 32 CUs with twice the work of
-// the others (346 rows, 14336 -> 4096: 259 us whole, 207 us in 7 slices + 10 us for their sum).  The smallest modelled time: a 64-row
-// workgroup takes 0.85 us a slab alone on its CU, 1.4 us when two share one (which is HBM's rate for 16 KB of weights
-// each), a 128-row one 0.75 us; the slices' way through memory as in gemm_plan.
+// the others (346 rows, 14336 -> 4096: 259 us whole, 207 us in 7 slices + 10 us for their sum).  The smallest modelled time:
+// with weights from HBM a 64-row workgroup takes 0.85 us a slab alone on its CU, 1.4 us when two share one (which is HBM's
+// rate for 16 KB of weights each), the others a quarter more than slab_us; the slices' way through memory as in gemm_plan.
 int gemm_grouped_splits(const GemmArgs &g, int max_splits, bool takes_slices) {
     if (g.mode == GEMM_DUAL) return 1;
+    const TileShape &t = kTileShape[g.tile];
     int n_tiles = 0, n_total = 0;
     for (int s = 0; s < g.nseg; ++s) {
-        n_tiles += (g.n_seg[s] + kTileShape[g.tile].bn - 1) / kTileShape[g.tile].bn;
+        n_tiles += (g.n_seg[s] + t.bn - 1) / t.bn;
         n_total += g.n_seg[s];
     }
-    const int slabs = g.K / kKAlign, cap = 256 * kTileShape[g.tile].per_cu;
+    const int slabs = g.K / kKAlign, cap = 256 * t.per_cu;
     const float mb = (float)g.R * (float)n_total * 4e-6f;
     int best = 1;
     float best_us = -1.f;
@@ -647,8 +662,8 @@ int gemm_grouped_splits(const GemmArgs &g, int max_splits, bool takes_slices) {
         if (splits > 1 && (per < 4 || (slabs + per - 1) / per != splits)) continue;
         auto round = [&](int n) {
             if (n == 0) return 0.f;
-            const float slab = g.tile == TILE_128 ? 0.75f : n <= 256 ? 0.85f : 1.4f;
-            return 2.f + (float)per * slab;
+            const float slab = t.per_cu == 1 ? 1.25f * t.slab_us : n <= 256 ? 0.85f : 1.4f;
+            return t.first_us + (float)per * slab;
         };
         float us = (float)(wgs / cap) * round(cap) + round(wgs % cap);
         if (splits > 1) us += mb * splits * (0.22f + 0.2f) + (takes_slices ? 0.f : 4.f + mb * 0.2f);
@@ -662,7 +677,7 @@ hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st) {
     if (g.K % kKAlign) return hipErrorInvalidValue;
     if (g.splits < 1) g.splits = 1;
     if (g.slice_rows < g.R) g.slice_rows = g.R;
-    if (g.row_tiles && g.tile != TILE_64x128 && g.tile != TILE_128) return hipErrorInvalidValue;
+    if (g.row_tiles && (g.tile < TILE_64x128 || g.tile > TILE_256x256)) return hipErrorInvalidValue;
     if (g.tile == TILE_AUTO) g.tile = gemm_plan(g, 1, false).tile;
     if (is_register_staged(g.tile)) return launch_gemm_decode(g, st);
     g.K_ext = k_ext_of(g);
@@ -670,8 +685,8 @@ hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st) {
     switch (g.tile) {
     case TILE_64x128: return g.row_tiles ? launch_cfg<64, 128, 64, 3, 2, 2, true>(g, st) : launch_cfg<64, 128, 64, 3, 2, 2>(g, st);
     case TILE_128: return g.row_tiles ? launch_cfg<128, 128, 64, 4, 2, 2, true>(g, st) : launch_cfg<128, 128, 64, 4, 2, 2>(g, st);
-    case TILE_192x128: return launch_cfg<192, 128, 64, 3, 2, 2>(g, st);
-    case TILE_256x256: return launch_cfg<256, 256, 64, 2, 2, 4>(g, st);
+    case TILE_192x128: return g.row_tiles ? launch_cfg<192, 128, 64, 3, 2, 2, true>(g, st) : launch_cfg<192, 128, 64, 3, 2, 2>(g, st);
+    case TILE_256x256: return g.row_tiles ? launch_cfg<256, 256, 64, 2, 2, 4, true>(g, st) : launch_cfg<256, 256, 64, 2, 2, 4>(g, st);
     default: return hipErrorInvalidValue;
     }
 }

@@ -851,7 +851,8 @@ icarus_status run_layer_full(icarus_ctx *ctx, char *ws, const WsLayout &L, const
         PHASE(ctx, st, ICARUS_PH_GEMM_QKV, launch_gemm_mfma(g, st));
         GemmArgs k{};
         k.X = xn; k.ldx = d; k.R = fp.off[1]; k.K = d; k.slice_rows = R;
-        k.mode = GEMM_PLAIN; k.epi = EPI_F32; k.splits = qkv_splits; k.tile = fp.tile;
+        k.mode = GEMM_PLAIN; k.epi = EPI_F32; k.splits = qkv_splits;
+        k.tile = std::min<int>(fp.tile, TILE_128);  // few and narrow: larger tiles would leave most CUs idle
         k.W[0] = (const bf16_raw *)ctx->base.w[ICARUS_PROJ_K]; k.n_seg[0] = kvd;
         k.W[1] = (const bf16_raw *)ctx->base.w[ICARUS_PROJ_V]; k.n_seg[1] = kvd; k.nseg = 2;
         k.Y = (float *)g.Y + qd; k.ldy = ldq;
@@ -1070,9 +1071,7 @@ icarus_status prepare_decode(icarus_ctx *ctx, const void *kv_pool, const int32_t
         pr->fp.perm = dmeta + used;
         pr->fp.inv = dmeta + used + R;
         used += (size_t)2 * R;
-        int most = 0;
-        for (int g = 0; g < n_groups; ++g) most = std::max(most, off[(size_t)g + 1] - off[g]);
-        pr->fp.tile = gemm_row_tile(most);
+        pr->fp.tile = gemm_row_tile(off.data(), n_groups);
         const int bm = gemm_tile_rows(pr->fp.tile);
         int32_t *rt = m + used;
         for (int g = 0; g < n_groups; ++g)
@@ -1466,6 +1465,19 @@ icarus_status icarus_gemm_choice(int32_t rows, int32_t k, const int32_t *n_seg, 
     choice[1] = gemm_tile_cols(p.tile);
     choice[2] = p.tile == TILE_REG_192x256 || p.tile == TILE_REG_160x256;
     choice[3] = p.splits;
+    return ICARUS_OK;
+}
+
+icarus_status icarus_gemm_group_tile(const int32_t *group_rows, int32_t n_groups, int32_t *tile) {
+    if (!group_rows || n_groups <= 0 || !tile) return ICARUS_ERR_INVALID_ARG;
+    std::vector<int32_t> off((size_t)n_groups + 1, 0);
+    for (int j = 0; j < n_groups; ++j) {
+        if (group_rows[j] < 0 || group_rows[j] > 65535 - off[j]) return ICARUS_ERR_INVALID_ARG;
+        off[(size_t)j + 1] = off[j] + group_rows[j];
+    }
+    const int kind = gemm_row_tile(off.data(), n_groups);
+    tile[0] = gemm_tile_rows(kind);
+    tile[1] = gemm_tile_cols(kind);
     return ICARUS_OK;
 }
 

@@ -168,8 +168,8 @@ hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st);
 // later kernel of the caller reads the slices as they are, no reduction is launched for them.
 struct GemmPlan { int tile, splits; };
 GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices);
-// Grouped launches: tile kind for groups of at most most_rows rows, its height, and the K slices to use.
-int gemm_row_tile(int most_rows);
+// Grouped launches: tile kind for groups of rows [off[j], off[j + 1]), its height, and the K slices to use.
+int gemm_row_tile(const int *off, int n_groups);
 int gemm_tile_rows(int tile);
 int gemm_tile_cols(int tile);
 int gemm_grouped_splits(const GemmArgs &g, int max_splits, bool takes_slices);

@@ -54,6 +54,16 @@ def test_near_ties_keep_the_plain_launch(call, want):
     assert binding.gemm_choice(rows, k, n, False, cols, most, taken) == want
 
 
+@pytest.mark.parametrize("groups,want", [
+    ([1] * 9, (64, 128)), ([64] + [8] * 8, (64, 128)), ([64, 64, 0, 1], (64, 128)),
+    ([66] + [8] * 8, (64, 128)), ([300] + [38] * 8, (64, 128)),       # one group past the tile does not pad all the others
+    ([66] * 9, (128, 128)), ([100] * 9, (128, 128)), ([130] * 9, (192, 128)), ([300] + [150] * 8, (192, 128)),
+    ([200] * 9, (256, 256)), ([256] * 9, (256, 256)), ([1024] * 9, (256, 256)), ([0, 0], (64, 128)),
+], ids=str)
+def test_tile_of_grouped_projections(groups, want):
+    assert binding.gemm_group_tile(groups) == want
+
+
 def test_choices_are_launches_the_workspace_holds():
     # never more slices than asked for, none empty, K slices of four slabs or more
     rng = np.random.default_rng(5)

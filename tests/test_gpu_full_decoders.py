@@ -98,12 +98,14 @@ def test_private_weights_are_rejected_where_unsupported():
     assert e.value.status_name == "INVALID_ARG"
 
 
-@pytest.mark.parametrize("S,n_active,M,d_ffn", [(1, 1, 4, 2048), (3, 3, 4, 2048), (66, 2, 4, 2048), (130, 1, 4, 2048), (2, 8, 8, 6464)],
-                         ids=["two-groups", "all-models", "encoder-66", "encoder-130", "wide-gate-up"])
+@pytest.mark.parametrize("S,n_active,M,d_ffn", [(1, 1, 4, 2048), (3, 3, 4, 2048), (66, 2, 4, 2048), (130, 1, 4, 2048), (2, 8, 8, 6464),
+                                                (66, 4, 4, 2048), (130, 3, 4, 2048), (130, 4, 4, 2048), (193, 4, 4, 2048), (257, 4, 4, 1088)],
+                         ids=["two-groups", "all-models", "encoder-66", "encoder-130", "wide-gate-up", "66-each", "130-and-97", "130-each",
+                              "193-each", "257-each"])
 def test_grouped_projections_over_group_sizes(S, n_active, M, d_ffn):
-    # groups of one row, of a whole row tile and a bit (64 and 128 rows), models that no sequence runs; with few row tiles
-    # K is sliced, with many it is not; K = 2048 in the down projection; more tiles than
-    # a round of workgroups, the last column tile ragged
+    # groups of one row, of a whole row tile and a bit (64, 128, 192 and 256 rows, each with the tile that such groups take),
+    # models that no sequence runs; with few row tiles K is sliced, with many it is not; K = 2048 in the down projection; more
+    # tiles than a round of workgroups, the last column tile ragged
     import oracle
     from gpu_util import dev, host, make_layer, pool_to_device_layout
     from helpers import assert_close, filled_batch
