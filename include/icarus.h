@@ -247,6 +247,10 @@ icarus_status icarus_gemm_choice(int32_t rows, int32_t k, const int32_t *n_seg /
  * group_rows[.] rows (host, [n_groups]). */
 icarus_status icarus_gemm_group_tile(const int32_t *group_rows /*host*/, int32_t n_groups, int32_t *tile /*host [2]*/);
 
+/* The same for the cache append of a prefill call: 1 if `rows` chunk tokens that lie in `tiles` pieces of one KV block each go
+ * piece by piece, 0 if row by row. */
+int32_t icarus_append_in_tiles(const icarus_ctx *ctx, int32_t rows, int32_t tiles);
+
 /* Per-phase kernel timing for measurements.  While enabled, every kernel launch of the entry
  * points above is bracketed by HIP events recorded on the caller's stream (this costs a few
  * microseconds per launch: leave it off when timing whole steps).  icarus_timing_read waits

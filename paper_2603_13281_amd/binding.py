@@ -30,7 +30,7 @@ EXPORTS = ("icarus_create", "icarus_destroy", "icarus_last_error", "icarus_works
            "icarus_cache_create", "icarus_cache_destroy", "icarus_cache_last_error", "icarus_cache_acquire", "icarus_cache_extend",
            "icarus_cache_commit", "icarus_cache_release", "icarus_cache_get_stats", "icarus_set_full_decoders",
            "icarus_validate_block_tables", "icarus_set_attn_piece_limit", "icarus_attn_shared_kv_static", "icarus_bench_read",
-           "icarus_gemm_tile_order", "icarus_gemm_choice", "icarus_gemm_group_tile")
+           "icarus_gemm_tile_order", "icarus_gemm_choice", "icarus_gemm_group_tile", "icarus_append_in_tiles")
 
 PHASES = ("norm", "lora", "gemm_qkv", "rope_append", "attn", "attn_merge", "gemm_o", "gemm_gateup", "gemm_down",
           "elementwise")
@@ -124,6 +124,8 @@ def _load():
     lib.icarus_gemm_choice.argtypes = [i32, i32, vp, i32, i32, i32, i32, i32, vp]
     lib.icarus_gemm_group_tile.restype = C.c_int
     lib.icarus_gemm_group_tile.argtypes = [vp, i32, vp]
+    lib.icarus_append_in_tiles.restype = i32
+    lib.icarus_append_in_tiles.argtypes = [vp, i32, i32]
     lib.icarus_stack_create.restype = C.c_int
     lib.icarus_stack_create.argtypes = [C.POINTER(_StackCfg), C.POINTER(vp)]
     lib.icarus_stack_destroy.restype = None
@@ -398,6 +400,9 @@ class IcarusLayer:
 
     def workspace_bytes(self, max_rows: int, max_seqs: int, max_ctx: int) -> int:
         return int(_lib.icarus_workspace_bytes(self._h, max_rows, max_seqs, max_ctx))
+
+    def append_in_tiles(self, rows: int, tiles: int) -> bool:
+        return bool(_lib.icarus_append_in_tiles(self._h, rows, tiles))
 
     def set_attn_piece_limit(self, tokens: int):
         """Longest piece of the decode attention's plan, in tokens (0 = automatic); for tests and measurements."""

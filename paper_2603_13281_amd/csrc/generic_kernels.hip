@@ -463,9 +463,14 @@ bool rope_tiles_supported(const Dims &dm, int ldq, size_t slice) {
 
 // A tile's thread works through its slices, four heads and then V one after the other, 12-22 us however few tiles there
 // are; a row at a time, 24-200 rows fill the chip better.  Row kernel -> tiles, 48 heads (q, k and v): 24 rows 4.1 -> 22
-// us, 128 rows 7 -> 22, 256 rows 9.3 -> 12.5, 400 rows 11.5 -> 12.0, 512 rows 12.3 -> 10.4; 80 heads: 64 rows 8.3 -> 14.6,
-// 128 rows 14 -> 15.5, 256 rows 18.6 -> 11.7; FP8 cache: 256 rows of 48 heads 8.8 -> 13.5, 400 rows of 80 29.5 -> 14.8.
-bool rope_tiles_pay(const Dims &dm, int rows) { return (int64_t)rows * (dm.Hq + 2 * dm.Hkv) >= 20480; }
+// us, 128 rows 7 -> 22, 256 rows 9.3 -> 12.5, 400 rows 11.5 -> 12.0, 600 rows 16.3 -> 14.9; 80 heads: 64 rows 8.3 -> 14.6,
+// 128 rows 14 -> 15.5, 256 rows 18.6 -> 11.7; FP8 cache: 256 rows of 48 heads 8.8 -> 13.5, 512 rows 13.0 -> 14.1, 400 rows of
+// 80 29.5 -> 14.8.  And a tile takes as long for one row as for sixteen: short chunks go row by row.  48 heads: 1000 tiles of
+// one row 25.2 -> 41.0 us, of two 36.3 -> 42.6, of three 47.3 -> 45.3 (500: 28.6 -> 30.4), of four 60.4 -> 47.1; 80 heads: 50.5
+// -> 86.3, 77.8 -> 90.7, 113 -> 109, 158 -> 119.
+bool rope_tiles_pay(const Dims &dm, int rows, int n_tiles) {
+    return (int64_t)rows * (dm.Hq + 2 * dm.Hkv) >= 20480 && (int64_t)rows >= 4 * (int64_t)n_tiles;
+}
 
 hipError_t launch_rope_append_tiles(const Dims &dm, const float *qkv, int ldq, int splits, size_t slice, const RowMeta &rm,
                                     const int32_t *tiles, int n_tiles, bool kv_only, const int32_t *bt, int max_blocks, void *pool,

@@ -746,7 +746,7 @@ icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const
     {   // split-K slices of the projection, if any were left, are summed by the RoPE kernel
         const float *src = qkv_splits ? (const float *)(ws + L.gemm_part) : qkv;
         const size_t slice = (size_t)R * ldq;
-        if (rm.n_rope_tiles > 0 && rope_tiles_supported(dm, ldq, slice) && rope_tiles_pay(dm, R))
+        if (rm.n_rope_tiles > 0 && rope_tiles_supported(dm, ldq, slice) && rope_tiles_pay(dm, R, rm.n_rope_tiles))
             PHASE(ctx, st, ICARUS_PH_ROPE_APPEND,
                   launch_rope_append_tiles(dm, src, ldq, std::max(1, qkv_splits), slice, rm, rm.rope_tiles, rm.n_rope_tiles, kv_only, bt, max_blocks,
                                            pool, q, slot_out, ctx->base.q_norm, ctx->base.k_norm, st));
@@ -1479,6 +1479,10 @@ icarus_status icarus_gemm_group_tile(const int32_t *group_rows, int32_t n_groups
     tile[0] = gemm_tile_rows(kind);
     tile[1] = gemm_tile_cols(kind);
     return ICARUS_OK;
+}
+
+int32_t icarus_append_in_tiles(const icarus_ctx *ctx, int32_t rows, int32_t tiles) {
+    return ctx && rows > 0 && tiles > 0 && rope_tiles_supported(ctx->dm, 4, 4) && rope_tiles_pay(ctx->dm, rows, tiles);
 }
 
 size_t icarus_workspace_bytes(const icarus_ctx *ctx, int32_t max_rows, int32_t max_seqs, int32_t max_ctx) {

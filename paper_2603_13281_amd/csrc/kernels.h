@@ -54,7 +54,7 @@ hipError_t launch_rope_append(const Dims &dm, const float *qkv, int ldq, int spl
 // The same for encoder rows only, head_dim 128 and blocks of 16, by tiles of consecutive rows within one KV block: tiles (device)
 // = first row | rows << 16.  kv_only: q is neither read nor written.  slot_out is by row.
 bool rope_tiles_supported(const Dims &dm, int ldq, size_t slice);
-bool rope_tiles_pay(const Dims &dm, int rows);
+bool rope_tiles_pay(const Dims &dm, int rows, int n_tiles);
 hipError_t launch_rope_append_tiles(const Dims &dm, const float *qkv, int ldq, int splits, size_t slice, const RowMeta &rm,
                                     const int32_t *tiles, int n_tiles, bool kv_only, const int32_t *bt, int max_blocks, void *pool,
                                     void *q_out, int64_t *slot_out, const void *q_norm, const void *k_norm, hipStream_t st);
