@@ -923,7 +923,8 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
     const int item = blockIdx.x / Hkv, c = blockIdx.x % Hkv;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int s = pl.item_seq[item];
-    const int begin = pl.item_begin[item], n_tok = pl.item_len[item], left = pl.seq_kvlen[s] - begin;
+    const bool parts = pl.item_begin != nullptr;  // else every piece is a whole walk
+    const int begin = parts ? pl.item_begin[item] : 0, left = pl.seq_kvlen[s] - begin, n_tok = parts ? pl.item_len[item] : left;
     const int row0 = pl.seq_row0[s], T = pl.seq_rows[s];
     const int g = Hq / Hkv, G = T * g;
     const int m = lane & 15, q = lane >> 4;
@@ -970,7 +971,8 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
                 st.o[dt][qt][0] *= v_scale; st.o[dt][qt][1] *= v_scale; st.o[dt][qt][2] *= v_scale; st.o[dt][qt][3] *= v_scale;
             }
     }
-    finish<NT>(st, w * NT, NT, G, g, row0, c, Hq, Hkv, pl.item_direct[item], pl.item_part[item], pl.g_max, out, part_o, part_ml, lane);
+    finish<NT>(st, w * NT, NT, G, g, row0, c, Hq, Hkv, parts ? pl.item_direct[item] : 1, parts ? pl.item_part[item] : 0, pl.g_max, out, part_o,
+               part_ml, lane);
 }
 
 // Combine the partial results of sequences that were split into several pieces.  32 threads per (row, query head),

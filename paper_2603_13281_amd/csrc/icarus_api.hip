@@ -404,7 +404,10 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
         struct Cut { int32_t s, begin, len, n; };
         std::vector<Cut> cuts;
         const int round = attn_prefill_round(), max_piece = attn_prefill_max_ctx();
+        int cut_to = 0;  // what `cuts` holds
         auto cut = [&](int most) {
+            if (most == cut_to) return;
+            cut_to = most;
             cuts.clear();
             for (size_t i = 0; i < order.size();) {
                 const int bt_row = seq_bt ? seq_bt[order[i]] : order[i];
@@ -451,10 +454,9 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
             best_most = std::min(max_piece, std::max(round, ctx->attn_chunk_override / round * round));
         } else {
             cut(max_piece);
-            int64_t best = cost();
             // Enough pieces for several per CU need no cutting: the last ones end within a piece of each other.
             if (cuts.size() < (size_t)8 * cus) {
-                int64_t work = 0;
+                int64_t best = cost(), work = 0;
                 for (int s : order) work += kv_lens[s];
                 // one piece per CU, or up to five; lengths in between because a sequence's parts are of one length
                 for (int pct : {200, 150, 125, 105, 90, 78, 68, 60, 52, 45, 38, 32, 26, 20}) {
@@ -472,57 +474,66 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
             cut(max_piece);
             if (!fits()) return;
         }
+        // The arrays of parts are staged only if there are any: with them the copy of a call of hundreds of whole walks grows
+        // past 16 KB and starts the call later (300 chunks of one token, 11 -> 20 KB: 294 -> 315 us).
         const size_t n_items = cuts.size();
-        int32_t *item_seq = m + at, *item_begin = item_seq + n_items, *item_len = item_begin + n_items, *item_part = item_len + n_items,
-                *item_direct = item_part + n_items, *seq_kvlen = item_direct + n_items, *row0 = seq_kvlen + S, *rows = row0 + S,
-                *sbt = rows + S, *part0 = sbt + S, *nparts = part0 + S, *pseq = nparts + S;
-        int n_rows = 0;
+        bool any = false;
+        int max_len = 0, n_rows = 0;
+        for (const Cut &c : cuts) {
+            any = any || c.n > 1;
+            max_len = std::max(max_len, (int)c.len);
+        }
+        int32_t *item_seq = m + at, *seq_kvlen = item_seq + n_items, *row0 = seq_kvlen + S, *rows = row0 + S, *sbt = rows + S;
         for (int s = 0; s < S; ++s) {
             seq_kvlen[s] = kv_lens[s];
             row0[s] = seq_row0[s];
             rows[s] = seq_rows[s];
             sbt[s] = seq_bt ? seq_bt[s] : s;
-            part0[s] = 0;
-            nparts[s] = 0;
-            for (int t = 0; t < seq_rows[s]; ++t) pseq[seq_row0[s] + t] = s;
-            n_rows = std::max(n_rows, seq_row0[s] + seq_rows[s]);
         }
-        // partial results of a group are consecutive, in token order
-        for (const Cut &c : cuts) nparts[c.s] = c.n;
-        int slot = 0;
-        for (int s : order) {
-            part0[s] = slot;
-            if (nparts[s] > 1) slot += nparts[s];
-        }
-        std::vector<int32_t> used((size_t)S, 0);
-        int max_len = 0;
-        for (size_t i = 0; i < n_items; ++i) {
-            const Cut &c = cuts[i];
-            item_seq[i] = c.s;
-            item_begin[i] = c.begin;
-            item_len[i] = c.len;
-            item_direct[i] = c.n == 1;
-            item_part[i] = part0[c.s] + used[c.s]++;
-            max_len = std::max(max_len, (int)c.len);
-        }
+        for (size_t i = 0; i < n_items; ++i) item_seq[i] = cuts[i].s;
         pl->item_seq = d;
-        pl->item_begin = d + n_items;
-        pl->item_len = d + 2 * n_items;
-        pl->item_part = d + 3 * n_items;
-        pl->item_direct = d + 4 * n_items;
-        pl->seq_kvlen = d + 5 * n_items;
+        pl->seq_kvlen = d + n_items;
         pl->seq_row0 = pl->seq_kvlen + S;
         pl->seq_rows = pl->seq_row0 + S;
         pl->seq_bt = pl->seq_rows + S;
-        pl->seq_part0 = pl->seq_bt + S;
-        pl->seq_nparts = pl->seq_part0 + S;
-        pl->row_pseq = pl->seq_nparts + S;
+        hp->ints = n_items + 4 * (size_t)S;
+        if (any) {
+            int32_t *part0 = sbt + S, *nparts = part0 + S, *item_begin = nparts + S, *item_len = item_begin + n_items, *item_part = item_len + n_items,
+                    *item_direct = item_part + n_items, *pseq = item_direct + n_items;
+            for (int s = 0; s < S; ++s) {
+                part0[s] = nparts[s] = 0;
+                for (int t = 0; t < seq_rows[s]; ++t) pseq[seq_row0[s] + t] = s;
+                n_rows = std::max(n_rows, seq_row0[s] + seq_rows[s]);
+            }
+            // partial results of a group are consecutive, in token order
+            for (const Cut &c : cuts) nparts[c.s] = c.n;
+            int slot = 0;
+            for (int s : order) {
+                part0[s] = slot;
+                if (nparts[s] > 1) slot += nparts[s];
+            }
+            std::vector<int32_t> used((size_t)S, 0);
+            for (size_t i = 0; i < n_items; ++i) {
+                const Cut &c = cuts[i];
+                item_begin[i] = c.begin;
+                item_len[i] = c.len;
+                item_direct[i] = c.n == 1;
+                item_part[i] = part0[c.s] + used[c.s]++;
+            }
+            pl->seq_part0 = pl->seq_bt + S;
+            pl->seq_nparts = pl->seq_part0 + S;
+            pl->item_begin = pl->seq_nparts + S;
+            pl->item_len = pl->item_begin + n_items;
+            pl->item_part = pl->item_len + n_items;
+            pl->item_direct = pl->item_part + n_items;
+            pl->row_pseq = pl->item_direct + n_items;
+            hp->ints += 2 * (size_t)S + 4 * n_items + (size_t)n_rows;
+        }
         pl->n_items = (int)n_items;
         pl->chunk = max_len;
         pl->g_max = g_max;
         pl->causal = 1;
-        hp->has_split = slot > 0;
-        hp->ints = 5 * n_items + 6 * (size_t)S + (size_t)n_rows;
+        hp->has_split = any;
         hp->valid = true;
         return;
     }
@@ -746,7 +757,7 @@ icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const
     {   // split-K slices of the projection, if any were left, are summed by the RoPE kernel
         const float *src = qkv_splits ? (const float *)(ws + L.gemm_part) : qkv;
         const size_t slice = (size_t)R * ldq;
-        if (rm.n_rope_tiles > 0 && rope_tiles_supported(dm, ldq, slice) && rope_tiles_pay(dm, R, rm.n_rope_tiles))
+        if (rm.n_rope_tiles > 0 && rope_tiles_supported(dm, ldq, slice))
             PHASE(ctx, st, ICARUS_PH_ROPE_APPEND,
                   launch_rope_append_tiles(dm, src, ldq, std::max(1, qkv_splits), slice, rm, rm.rope_tiles, rm.n_rope_tiles, kv_only, bt, max_blocks,
                                            pool, q, slot_out, ctx->base.q_norm, ctx->base.k_norm, st));
@@ -1163,14 +1174,18 @@ icarus_status prepare_prefill(icarus_ctx *ctx, const void *kv_pool, const int32_
         used += n_extra;
     }
     pr->rm = RowMeta{dmeta, dmeta + R, dmeta + 2 * R, dmeta + 3 * R};
-    if (rope_tiles_supported(ctx->dm, 4, 4)) {  // the chunk rows in tiles that lie within one KV block (at most one per row)
+    // the chunk rows in tiles that lie within one KV block (at most one per row), if the append goes by tiles
+    int n_tiles = 0;
+    for (int s = 0; s < S; ++s)
+        if (chunk_lens[s] > 0) n_tiles += (ctx_lens[s] % c.block_size + chunk_lens[s] + c.block_size - 1) / c.block_size;
+    if (rope_tiles_supported(ctx->dm, 4, 4) && rope_tiles_pay(ctx->dm, R, n_tiles)) {
         pr->rm.rope_tiles = dmeta + used;
+        pr->rm.n_rope_tiles = n_tiles;
         int row = 0;
         for (int s = 0; s < S; ++s)
             for (int i = 0; i < chunk_lens[s];) {
                 const int n = std::min(chunk_lens[s] - i, c.block_size - (ctx_lens[s] + i) % c.block_size);
                 m[used++] = row | n << 16;
-                ++pr->rm.n_rope_tiles;
                 i += n;
                 row += n;
             }

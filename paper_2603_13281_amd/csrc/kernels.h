@@ -94,6 +94,7 @@ hipError_t launch_bench_mfma(float *out, int waves, int iters, hipStream_t st);
 // result per piece and kv-head.
 // Prefill (causal = 1): one workgroup per piece and kv-head; a piece is the whole walk of a token group, or a part of
 // it that leaves a partial result (launch_attn_merge combines them).  Inner boundaries on whole rounds of the walk.
+// Without any cut walk the arrays of parts are null: item_begin, _len, _part, _direct, seq_part0, _nparts, row_pseq.
 struct AttnPlan {
     const int32_t *item_seq;     // [n_items] plan sequence of the piece
     const int32_t *item_begin;   // [n_items] first token of the piece
