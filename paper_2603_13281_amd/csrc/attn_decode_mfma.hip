@@ -977,13 +977,14 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
 
 // Combine the partial results of sequences that were split into several pieces.  32 threads per (row, query head),
 // four output elements each; four pieces' loads in flight (a piece past the last repeats it with weight zero).
+// row_pseq: plan sequence of each of the R rows; null: a grid row per plan sequence, R rows of it at most.
 __global__ void __launch_bounds__(256) k_attn_merge(const float *__restrict__ part_o, const float *__restrict__ part_ml,
-                                                    AttnPlan pl, const int32_t *__restrict__ row_pseq /* row -> plan sequence */,
+                                                    AttnPlan pl, const int32_t *__restrict__ row_pseq,
                                                     bf16_t *__restrict__ out, int R, int Hq, int Hkv) {
     const int idx = blockIdx.x * 8 + (threadIdx.x >> 5), d = (threadIdx.x & 31) * 4;
-    if (idx >= R * Hq) return;
-    const int row = idx / Hq, h = idx % Hq;
-    const int s = row_pseq[row];
+    if (idx >= (row_pseq ? R : pl.seq_rows[blockIdx.y]) * Hq) return;
+    const int h = idx % Hq, row = idx / Hq + (row_pseq ? 0 : pl.seq_row0[blockIdx.y]);
+    const int s = row_pseq ? row_pseq[row] : blockIdx.y;
     const int g = Hq / Hkv, c = h / g;
     const int np = pl.seq_nparts[s];
     if (np <= 1) return;  // written directly by the attention kernel
@@ -1108,9 +1109,10 @@ hipError_t launch_attn_decode_mfma(const Dims &dm, const void *q, const void *po
 }
 
 hipError_t launch_attn_merge(const Dims &dm, const float *part_o, const float *part_ml, const AttnPlan &pl,
-                             const int32_t *row_pseq, void *out, int R, hipStream_t st) {
-    if (R <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_attn_merge, dim3((R * dm.Hq + 7) / 8), dim3(256), 0, st, part_o, part_ml, pl, row_pseq, (bf16_t *)out, R, dm.Hq, dm.Hkv);
+                             const int32_t *row_pseq, void *out, int R, int n_seq, hipStream_t st) {
+    if (R <= 0 || n_seq <= 0) return hipSuccess;
+    const dim3 grid((R * dm.Hq + 7) / 8, row_pseq ? 1 : n_seq);
+    hipLaunchKernelGGL(k_attn_merge, grid, dim3(256), 0, st, part_o, part_ml, pl, row_pseq, (bf16_t *)out, R, dm.Hq, dm.Hkv);
     return hipGetLastError();
 }
 

@@ -171,7 +171,7 @@ WsLayout ws_layout(const icarus_ctx *ctx, size_t rows, size_t seqs, size_t max_c
     w.max_items = attn_max_items(ctx, seqs, max_ctx);
     // metadata: 4 row arrays and the attention plan (5 arrays per piece, the shares' first pieces, 6 arrays
     // per plan sequence); a prefill call has up to `rows` plan sequences, max_items pieces if any is cut, and an array
-    // of its rows' plan sequences and one of row tiles, one per row at most (where a decode call keeps the regrouping of its rows)
+    // of row tiles, one per row at most (where a decode call keeps the regrouping of its rows)
     w.meta_ints = 4 * rows + 5 * std::max(rows, w.max_items) + (size_t)ctx->attn_wgs + 6 * std::max(rows, seqs) + 64 +
                   rows + seqs +  // + what a layer stack stages with the call: prompt tokens, last row of each sequence
                   2 * rows +     // + the regrouping of rows for decoders with private weights, and their row tiles
@@ -428,21 +428,25 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
         // Model of a launch, in tokens walked by one workgroup: the kernel gives a CU one workgroup, so attn_wgs / Hkv
         // pieces run at a time, each next one on the first CU that is free; a piece costs its tokens and
         // kPieceTokens on top (prologue, Q loads, output), and if any group is cut, the partial results cost a merge
-        // launch and their way through memory.
+        // launch and their way through memory.  With every CU at work a token takes up to a third longer, the more query
+        // tiles a group fills: *busy is what the CUs' mean load comes to then.
         const int cus = std::max(1, ctx->attn_wgs / Hkv);
-        auto cost = [&]() {
+        auto cost = [&](int64_t *busy) {
             constexpr int64_t kPieceTokens = 160, kMergeTokens = 160, kSlotTokens = 8;
-            std::vector<int64_t> busy((size_t)cus, 0);  // min-heap of finishing times
-            int64_t end = 0;
+            std::vector<int64_t> free_at((size_t)cus, 0);  // min-heap of finishing times
+            int64_t end = 0, sum = 0;
             size_t slots = 0;
             for (const Cut &c : cuts) {
-                std::pop_heap(busy.begin(), busy.end(), std::greater<int64_t>());
-                busy.back() += c.len + kPieceTokens;
-                end = std::max(end, busy.back());
-                std::push_heap(busy.begin(), busy.end(), std::greater<int64_t>());
+                std::pop_heap(free_at.begin(), free_at.end(), std::greater<int64_t>());
+                free_at.back() += c.len + kPieceTokens;
+                end = std::max(end, free_at.back());
+                std::push_heap(free_at.begin(), free_at.end(), std::greater<int64_t>());
+                sum += (c.len + kPieceTokens) * (100 + 35 * seq_rows[c.s] * g / attn_prefill_group_queries()) / 100;
                 slots += c.n > 1;
             }
-            return end + (slots ? kMergeTokens + kSlotTokens * (int64_t)slots : 0);
+            const int64_t merge = slots ? kMergeTokens + kSlotTokens * (int64_t)slots : 0;
+            *busy = sum / cus + merge;
+            return end + merge;
         };
         auto fits = [&]() {
             size_t slots = 0;
@@ -456,15 +460,19 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
             cut(max_piece);
             // Enough pieces for several per CU need no cutting: the last ones end within a piece of each other.
             if (cuts.size() < (size_t)8 * cus) {
-                int64_t best = cost(), work = 0;
+                int64_t busy = 0, whole = cost(&busy), best = fits() ? whole : INT64_MAX, work = 0;
+                if (best == whole) best = whole * 9 / 10;  // see below
                 for (int s : order) work += kv_lens[s];
                 // one piece per CU, or up to five; lengths in between because a sequence's parts are of one length
                 for (int pct : {200, 150, 125, 105, 90, 78, 68, 60, 52, 45, 38, 32, 26, 20}) {
                     const int most = (int)std::min<int64_t>(max_piece, std::max<int64_t>(2 * round, work * pct / (100 * (int64_t)cus)));
                     cut(most);
                     if (!fits()) continue;
-                    const int64_t c = cost();
-                    if (c < best) { best = c; best_most = most; }
+                    // A modelled gain of less than a tenth is none: 520 rows over 64-600 tokens, 32 heads on 8 kv-heads, were
+                    // 2 % of a small layer slower cut, two chunks of 300 rows over 500 tokens 3 %; 2000 rows over 64 tokens, which
+                    // keep every CU busy, 3 % for a modelled fifth.
+                    const int64_t c = cost(&busy);
+                    if (c < best && (best_most != max_piece || busy < best)) { best = c; best_most = most; }
                     if (most == 2 * round) break;
                 }
             }
@@ -478,7 +486,7 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
         // past 16 KB and starts the call later (300 chunks of one token, 11 -> 20 KB: 294 -> 315 us).
         const size_t n_items = cuts.size();
         bool any = false;
-        int max_len = 0, n_rows = 0;
+        int max_len = 0;
         for (const Cut &c : cuts) {
             any = any || c.n > 1;
             max_len = std::max(max_len, (int)c.len);
@@ -499,12 +507,8 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
         hp->ints = n_items + 4 * (size_t)S;
         if (any) {
             int32_t *part0 = sbt + S, *nparts = part0 + S, *item_begin = nparts + S, *item_len = item_begin + n_items, *item_part = item_len + n_items,
-                    *item_direct = item_part + n_items, *pseq = item_direct + n_items;
-            for (int s = 0; s < S; ++s) {
-                part0[s] = nparts[s] = 0;
-                for (int t = 0; t < seq_rows[s]; ++t) pseq[seq_row0[s] + t] = s;
-                n_rows = std::max(n_rows, seq_row0[s] + seq_rows[s]);
-            }
+                    *item_direct = item_part + n_items;
+            for (int s = 0; s < S; ++s) part0[s] = nparts[s] = 0;
             // partial results of a group are consecutive, in token order
             for (const Cut &c : cuts) nparts[c.s] = c.n;
             int slot = 0;
@@ -526,9 +530,9 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
             pl->item_len = pl->item_begin + n_items;
             pl->item_part = pl->item_len + n_items;
             pl->item_direct = pl->item_part + n_items;
-            pl->row_pseq = pl->item_direct + n_items;
-            hp->ints += 2 * (size_t)S + 4 * n_items + (size_t)n_rows;
+            hp->ints += 2 * (size_t)S + 4 * n_items;
         }
+        pl->n_seq = S;
         pl->n_items = (int)n_items;
         pl->chunk = max_len;
         pl->g_max = g_max;
@@ -656,7 +660,7 @@ icarus_status run_decode_attention(icarus_ctx *ctx, char *ws, const WsLayout &L,
     if (hp->pl.causal) {
         PHASE(ctx, st, ICARUS_PH_ATTN, launch_attn_prefill_mfma(ctx->dm, q, pool, bt, max_blocks, hp->pl, out, part_o, part_ml, st));
         if (hp->has_split)
-            PHASE(ctx, st, ICARUS_PH_ATTN_MERGE, launch_attn_merge(ctx->dm, part_o, part_ml, hp->pl, hp->pl.row_pseq, out, R, st));
+            PHASE(ctx, st, ICARUS_PH_ATTN_MERGE, launch_attn_merge(ctx->dm, part_o, part_ml, hp->pl, nullptr, out, hp->pl.g_max * ctx->dm.Hkv / ctx->dm.Hq, hp->pl.n_seq, st));
         return ICARUS_OK;
     }
     PHASE(ctx, st, ICARUS_PH_ATTN, launch_attn_decode_mfma(ctx->dm, q, pool, bt, max_blocks, hp->pl, out, part_o, part_ml, st));
@@ -664,7 +668,7 @@ icarus_status run_decode_attention(icarus_ctx *ctx, char *ws, const WsLayout &L,
         *merge_left = true;
         return ICARUS_OK;
     }
-    if (hp->has_split) PHASE(ctx, st, ICARUS_PH_ATTN_MERGE, launch_attn_merge(ctx->dm, part_o, part_ml, hp->pl, rm.row_seq, out, R, st));
+    if (hp->has_split) PHASE(ctx, st, ICARUS_PH_ATTN_MERGE, launch_attn_merge(ctx->dm, part_o, part_ml, hp->pl, rm.row_seq, out, R, R, st));
     return ICARUS_OK;
 }
 

@@ -94,7 +94,7 @@ hipError_t launch_bench_mfma(float *out, int waves, int iters, hipStream_t st);
 // result per piece and kv-head.
 // Prefill (causal = 1): one workgroup per piece and kv-head; a piece is the whole walk of a token group, or a part of
 // it that leaves a partial result (launch_attn_merge combines them).  Inner boundaries on whole rounds of the walk.
-// Without any cut walk the arrays of parts are null: item_begin, _len, _part, _direct, seq_part0, _nparts, row_pseq.
+// Without any cut walk the arrays of parts are null: item_begin, _len, _part, _direct, seq_part0, _nparts.
 struct AttnPlan {
     const int32_t *item_seq;     // [n_items] plan sequence of the piece
     const int32_t *item_begin;   // [n_items] first token of the piece
@@ -108,7 +108,7 @@ struct AttnPlan {
     const int32_t *seq_part0;    // [S] first partial slot
     const int32_t *seq_nparts;   // [S] number of pieces
     const int32_t *seq_bt;       // [S] row of the block table the sequence reads
-    const int32_t *row_pseq;     // [R] plan sequence of each row (prefill; at decode RowMeta::row_seq says it)
+    int n_seq;                         // S
     int n_items, n_wgs, chunk, g_max;  // n_wgs: shares; chunk: longest piece; g_max: largest stacked group (rows * Hq/Hkv)
     int causal;                  // 1: row t of a sequence attends to kv_len - (rows - 1 - t) tokens (prefill)
 };
@@ -216,8 +216,9 @@ hipError_t launch_attn_prefill_mfma(const Dims &dm, const void *q, const void *p
 // part_o: fp32 [slots, Hkv, g_max, D]; part_ml: fp32 [slots, Hkv, g_max, 2] (max in log2 units, sum)
 hipError_t launch_attn_decode_mfma(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
                                    const AttnPlan &pl, void *out, float *part_o, float *part_ml, hipStream_t st);
+// row_pseq: plan sequence of each of the R rows; or null: n_seq plan sequences of at most R rows
 hipError_t launch_attn_merge(const Dims &dm, const float *part_o, const float *part_ml, const AttnPlan &pl,
-                             const int32_t *row_pseq, void *out, int R, hipStream_t st);
+                             const int32_t *row_pseq, void *out, int R, int n_seq, hipStream_t st);
 
 // ---- layer stack helpers (index work) ----------------------------------------------------------
 // x[row, :] = embed[tok[idx ? idx[row] : row], :]   (rows of row_bytes bytes, a multiple of 16)
