@@ -570,7 +570,7 @@ bool gemm_mfma_supported(const Dims &dm, int K) {
 // the model does not know -- how the strides of the slices fall on the HBM channels, what the row kernel after a sliced
 // projection pays, what the register-staged tiles do to the clock -- so the plain choice has a start.  The modelled time has to
 // undercut by 4 %: up to 384 rows of a narrow output, 192-row tiles in as many slices as the CUs hold at once; from 1024
-// rows, 256 x 256 tiles that fill most of the CUs.  Between, slices have to earn 3 %.
+// rows, 256 x 256 tiles that fill most of the CUs.  In between, slices have to earn 3 %.
 // Measured inside a layer, weights from HBM, consumers of the slices included (5 widths of 2048-8192, 130-32768 rows, QKV, O,
 // gate/up, down: 1316 launches, every tile x 1-12 slices): within 0.7 % of the fastest on average, 18 % at worst (252 rows,
 // 5120 -> 10240).  Without the start for the plain choice 28 of them were 2-29 % slower than one tile for each range of
@@ -612,7 +612,7 @@ GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices) {
                 if (per < 6) break;
                 if ((slabs + per - 1) / per != splits) continue;  // the last slice would be empty
             }
-            const float us = modelled(kind, splits) * (splits > 1 && !few ? 1.03f : 1.f);
+            const float us = modelled(kind, splits) * (splits > 1 && !few && g.R < 1024 ? 1.03f : 1.f);
             if (best_us < 0.f || us < best_us) { best_us = us; best = {kind, splits}; }
         }
     }

@@ -45,6 +45,7 @@ CHOICES = [
     ((385, 8192, [8192], 0, 12, True), (128, 128, False, 1)),
     ((10000, 4096, [4096], 0, 1, True), (256, 256, False, 1)),        # 349 us in 160 x 256, 327 us
     ((8000, 8192, [5120], 0, 1, True), (256, 256, False, 1)),
+    ((4337, 14336, [4096], 0, 2, True), (192, 256, True, 2)),         # 457 us + 26 in the row kernel that sums them; 160 x 256 whole 502
 ]
 
 
