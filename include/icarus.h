@@ -251,6 +251,12 @@ icarus_status icarus_gemm_group_tile(const int32_t *group_rows /*host*/, int32_t
  * piece by piece, 0 if row by row. */
 int32_t icarus_append_in_tiles(const icarus_ctx *ctx, int32_t rows, int32_t tiles);
 
+/* For tests and measurements, host only: the pieces in which a prefill call walks its contexts on the matrix cores.  pieces (host,
+ * [cap][5]): first row and rows of the token group, first token and tokens of the piece, slot of its partial result (-1: whole
+ * walk); *n: how many there are, 0 if the call takes the vector kernel. */
+icarus_status icarus_prefill_plan(icarus_ctx *ctx, int32_t S, const int32_t *ctx_lens /*host*/, const int32_t *chunk_lens /*host*/,
+                                  int32_t *pieces /*host*/, int32_t cap, int32_t *n /*host*/);
+
 /* Per-phase kernel timing for measurements.  While enabled, every kernel launch of the entry
  * points above is bracketed by HIP events recorded on the caller's stream (this costs a few
  * microseconds per launch: leave it off when timing whole steps).  icarus_timing_read waits

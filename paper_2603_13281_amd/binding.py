@@ -30,7 +30,7 @@ EXPORTS = ("icarus_create", "icarus_destroy", "icarus_last_error", "icarus_works
            "icarus_cache_create", "icarus_cache_destroy", "icarus_cache_last_error", "icarus_cache_acquire", "icarus_cache_extend",
            "icarus_cache_commit", "icarus_cache_release", "icarus_cache_get_stats", "icarus_set_full_decoders",
            "icarus_validate_block_tables", "icarus_set_attn_piece_limit", "icarus_attn_shared_kv_static", "icarus_bench_read",
-           "icarus_gemm_tile_order", "icarus_gemm_choice", "icarus_gemm_group_tile", "icarus_append_in_tiles")
+           "icarus_gemm_tile_order", "icarus_gemm_choice", "icarus_gemm_group_tile", "icarus_append_in_tiles", "icarus_prefill_plan")
 
 PHASES = ("norm", "lora", "gemm_qkv", "rope_append", "attn", "attn_merge", "gemm_o", "gemm_gateup", "gemm_down",
           "elementwise")
@@ -126,6 +126,8 @@ def _load():
     lib.icarus_gemm_group_tile.argtypes = [vp, i32, vp]
     lib.icarus_append_in_tiles.restype = i32
     lib.icarus_append_in_tiles.argtypes = [vp, i32, i32]
+    lib.icarus_prefill_plan.restype = C.c_int
+    lib.icarus_prefill_plan.argtypes = [vp, i32, vp, vp, vp, i32, vp]
     lib.icarus_stack_create.restype = C.c_int
     lib.icarus_stack_create.argtypes = [C.POINTER(_StackCfg), C.POINTER(vp)]
     lib.icarus_stack_destroy.restype = None
@@ -400,6 +402,16 @@ class IcarusLayer:
 
     def workspace_bytes(self, max_rows: int, max_seqs: int, max_ctx: int) -> int:
         return int(_lib.icarus_workspace_bytes(self._h, max_rows, max_seqs, max_ctx))
+
+    def prefill_plan(self, ctx_lens, chunk_lens) -> np.ndarray:
+        """[pieces, 5]: first row, rows, first token, tokens, partial slot (-1: none) of each piece of the prefill attention."""
+        ctx, chunk = _host_i32(ctx_lens), _host_i32(chunk_lens)
+        out, n = np.zeros((0, 5), dtype=np.int32), C.c_int32()
+        for cap in (0, None):
+            if cap is None:
+                out = np.zeros((n.value, 5), dtype=np.int32)
+            self._check(_lib.icarus_prefill_plan(self._h, len(ctx), ctx.ctypes.data, chunk.ctypes.data, out.ctypes.data, len(out), C.byref(n)))
+        return out
 
     def append_in_tiles(self, rows: int, tiles: int) -> bool:
         return bool(_lib.icarus_append_in_tiles(self._h, rows, tiles))

@@ -161,6 +161,11 @@ size_t attn_max_items(const icarus_ctx *ctx, size_t seqs, size_t max_ctx) {
     return std::max<size_t>(4 * kAttnTargetWgs / ctx->cfg.n_kv_heads, (size_t)ctx->attn_wgs) + seqs * (2 + max_ctx / cap) + 1;
 }
 
+// Chunk tokens whose stacked query heads fill one workgroup of the prefill attention.
+size_t prefill_group_rows(const icarus_layer_config &c) {
+    return (size_t)std::max(1, attn_prefill_group_queries() / (c.n_q_heads / c.n_kv_heads));
+}
+
 WsLayout ws_layout(const icarus_ctx *ctx, size_t rows, size_t seqs, size_t max_ctx) {
     const icarus_layer_config &c = ctx->cfg;
     size_t es = c.dtype == ICARUS_BF16 ? 2 : 4;
@@ -168,7 +173,15 @@ WsLayout ws_layout(const icarus_ctx *ctx, size_t rows, size_t seqs, size_t max_c
     WsLayout w{};
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
-    w.max_items = attn_max_items(ctx, seqs, max_ctx);
+    const size_t decode_items = attn_max_items(ctx, seqs, max_ctx), g = (size_t)c.n_q_heads / c.n_kv_heads;
+    // A context longer than a prefill workgroup's block ids reach is walked in pieces whatever it costs: each of the call's
+    // token groups in as many as its longest context needs.  (With room for decode's pieces only, 4096 rows over 135000
+    // tokens, 8 query heads to a kv-head, fell to the vector kernel.)
+    const size_t walk = (size_t)attn_prefill_max_ctx();
+    size_t forced_items = 0;
+    if (max_ctx > walk && attn_prefill_mfma_supported(ctx->dm, 1))
+        forced_items = (rows / prefill_group_rows(c) + seqs) * ((max_ctx + walk - 1) / walk);
+    w.max_items = std::max(decode_items, forced_items);
     // metadata: 4 row arrays and the attention plan (5 arrays per piece, the shares' first pieces, 6 arrays
     // per plan sequence); a prefill call has up to `rows` plan sequences, max_items pieces if any is cut, and an array
     // of row tiles, one per row at most (where a decode call keeps the regrouping of its rows)
@@ -178,9 +191,8 @@ WsLayout ws_layout(const icarus_ctx *ctx, size_t rows, size_t seqs, size_t max_c
                   3 * (rows / 64 + (size_t)c.n_models + 2);
     w.meta = take(w.meta_ints * 4);
     {
-        size_t g = (size_t)c.n_q_heads / c.n_kv_heads;
         size_t g_bound = std::min<size_t>(kAttnGMax, rows * g);
-        w.max_partial = w.max_items * g_bound;
+        w.max_partial = std::max(decode_items * g_bound, forced_items * prefill_group_rows(c) * g);
         size_t pj = w.max_partial * c.n_kv_heads;
         w.part_o = take(pj * c.head_dim * 4);
         w.part_ml = take(pj * 2 * 4);
@@ -1127,6 +1139,25 @@ icarus_status check_prefill(icarus_ctx *ctx, int32_t max_blocks, int32_t S, cons
     return ICARUS_OK;
 }
 
+// The plan sequences of a prefill call: its chunks in groups of consecutive tokens.
+struct TokenGroups {
+    std::vector<int32_t> kv, row0, rows, bt;
+    TokenGroups(const icarus_layer_config &c, int S, const int32_t *ctx_lens, const int32_t *chunk_lens) {
+        const int tq = (int)prefill_group_rows(c);
+        int row = 0;
+        for (int s = 0; s < S; ++s) {
+            for (int t0 = 0; t0 < chunk_lens[s]; t0 += tq) {
+                const int n = std::min(tq, chunk_lens[s] - t0);
+                kv.push_back(ctx_lens[s] + t0 + n);
+                row0.push_back(row + t0);
+                rows.push_back(n);
+                bt.push_back(s);
+            }
+            row += chunk_lens[s];
+        }
+    }
+};
+
 icarus_status prepare_prefill(icarus_ctx *ctx, const void *kv_pool, const int32_t *block_tables, int32_t max_blocks, int32_t S,
                               const int32_t *ctx_lens, const int32_t *chunk_lens, int R, bool want_attention, void *workspace,
                               size_t workspace_bytes, hipStream_t st, const int32_t *extra, size_t n_extra, Prepared *pr) {
@@ -1155,20 +1186,8 @@ icarus_status prepare_prefill(icarus_ctx *ctx, const void *kv_pool, const int32_
     char *ws = (char *)workspace;
     const int32_t *dmeta = (const int32_t *)(ws + L.meta);
     if (want_attention) {
-        int g = c.n_q_heads / c.n_kv_heads, tq = std::max(1, attn_prefill_group_queries() / g);
-        std::vector<int32_t> vkv, vrow0, vrows, vbt;
-        int row = 0;
-        for (int s = 0; s < S; ++s) {
-            for (int t0 = 0; t0 < chunk_lens[s]; t0 += tq) {
-                int n = std::min(tq, chunk_lens[s] - t0);
-                vkv.push_back(ctx_lens[s] + t0 + n);
-                vrow0.push_back(row + t0);
-                vrows.push_back(n);
-                vbt.push_back(s);
-            }
-            row += chunk_lens[s];
-        }
-        build_attn_plan(ctx, m, (size_t)4 * R, dmeta, (int)vkv.size(), vkv.data(), vrow0.data(), vrows.data(), vbt.data(), true,
+        const TokenGroups tg(c, S, ctx_lens, chunk_lens);
+        build_attn_plan(ctx, m, (size_t)4 * R, dmeta, (int)tg.kv.size(), tg.kv.data(), tg.row0.data(), tg.rows.data(), tg.bt.data(), true,
                         L.max_items, L.max_partial, &pr->hp);
     }
     size_t used = (size_t)4 * R + pr->hp.ints;
@@ -1502,6 +1521,39 @@ icarus_status icarus_gemm_group_tile(const int32_t *group_rows, int32_t n_groups
 
 int32_t icarus_append_in_tiles(const icarus_ctx *ctx, int32_t rows, int32_t tiles) {
     return ctx && rows > 0 && tiles > 0 && rope_tiles_supported(ctx->dm, 4, 4) && rope_tiles_pay(ctx->dm, rows, tiles);
+}
+
+icarus_status icarus_prefill_plan(icarus_ctx *ctx, int32_t S, const int32_t *ctx_lens, const int32_t *chunk_lens, int32_t *pieces, int32_t cap,
+                                  int32_t *n) {
+    if (!ctx || !pieces || !n || cap < 0) return ICARUS_ERR_INVALID_ARG;
+    std::lock_guard<std::mutex> lk(ctx->mu);
+    int R = 0;
+    icarus_status rc = check_prefill(ctx, INT32_MAX, S, ctx_lens, chunk_lens, &R);
+    if (rc) return rc;
+    *n = 0;
+    if (R == 0) return ICARUS_OK;
+    int max_ctx = 0;
+    for (int s = 0; s < S; ++s) max_ctx = std::max(max_ctx, ctx_lens[s] + chunk_lens[s]);
+    const WsLayout L = ws_layout(ctx, (size_t)R, (size_t)S, (size_t)max_ctx);
+    std::vector<int32_t> m(L.meta_ints);
+    HostPlan hp;
+    const TokenGroups tg(ctx->cfg, S, ctx_lens, chunk_lens);
+    // device addresses as if the plan were staged at the start of m
+    build_attn_plan(ctx, m.data(), 0, m.data(), (int)tg.kv.size(), tg.kv.data(), tg.row0.data(), tg.rows.data(), tg.bt.data(), true, L.max_items,
+                    L.max_partial, &hp);
+    if (!hp.valid) return ICARUS_OK;
+    if (hp.ints > L.meta_ints) return fail(ctx, ICARUS_ERR_CAPACITY, "plan of %zu ints, room for %zu", hp.ints, L.meta_ints);
+    const AttnPlan &pl = hp.pl;
+    for (*n = 0; *n < pl.n_items; ++*n) {
+        if (*n >= cap) continue;
+        int32_t *o = pieces + 5 * (size_t)*n;
+        const int s = pl.item_seq[*n];
+        o[0] = pl.seq_row0[s]; o[1] = pl.seq_rows[s];
+        o[2] = pl.item_begin ? pl.item_begin[*n] : 0;
+        o[3] = pl.item_begin ? pl.item_len[*n] : pl.seq_kvlen[s];
+        o[4] = pl.item_begin && !pl.item_direct[*n] ? pl.item_part[*n] : -1;
+    }
+    return ICARUS_OK;
 }
 
 size_t icarus_workspace_bytes(const icarus_ctx *ctx, int32_t max_rows, int32_t max_seqs, int32_t max_ctx) {
