@@ -236,7 +236,23 @@ icarus_status icarus_set_attn_piece_limit(icarus_ctx *ctx, int32_t tokens);
 icarus_status icarus_gemm_tile_order(int32_t row_tiles, int32_t col_tiles, int32_t k_slices, int32_t tile_rows, int32_t tile_cols,
                                      int32_t per_cu, int32_t *order /*host*/, int32_t cap, int32_t *n /*host*/);
 
-/* The same for the choice of a launch: a GEMM of `rows` rows over K = k against n_segs stacked weight matrices of n_seg[.] rows
+/* For tests and measurements: one GEMM as the layers launch it, in a given tile and number of K slices (device arrays, bf16 unless
+ * noted, 16-byte aligned; a fixed choice of both runs whatever icarus_gemm_choice would say).
+ *   plain:  y = x [rows, k] . w^T + t . b^T over n_segs stacked weight matrices w[s] [n[s], k]; y float [rows, sum n], or with
+ *           resid [rows, n[0]] (one matrix) y = bf16(resid + .)
+ *   fused:  y = bf16(silu(gate) * up), w[0] and w[1] [n[0], k] the gate and up matrices
+ *   t:      [rows, models * rank] (fused: twice that, gate columns first) with b[0] (fused: and b[1]) [models, n[0], rank] for the
+ *           columns of w[0] (w[1]); null: no adapters
+ *   slices: of K (fused: 1); with more than one, partials (float [slices, rows, sum n]) holds them before they are summed. */
+typedef struct icarus_gemm_args {
+    const void *x, *w[3], *t, *b[2], *resid;
+    void *y, *partials;
+    int32_t rows, k, n[3], n_segs, fused, models, rank;
+    int32_t tile_rows, tile_cols, staged, slices; /* as icarus_gemm_choice names them */
+} icarus_gemm_args;
+icarus_status icarus_gemm(const icarus_gemm_args *args, void *stream);
+
+/* The choice of such a launch, host only: a GEMM of `rows` rows over K = k against n_segs stacked weight matrices of n_seg[.] rows
  * (host, at most 3; fused != 0: the gate/up pair of n_seg[0] rows each), adapter_cols = n_models * rank (a multiple of 8; 0: no
  * adapters), at most max_slices slices of K, which a later kernel sums on the way if taken != 0.  choice (host): rows and weight
  * rows of a tile, 1 if it is staged through registers, slices. */

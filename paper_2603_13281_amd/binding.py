@@ -30,7 +30,7 @@ EXPORTS = ("icarus_create", "icarus_destroy", "icarus_last_error", "icarus_works
            "icarus_cache_create", "icarus_cache_destroy", "icarus_cache_last_error", "icarus_cache_acquire", "icarus_cache_extend",
            "icarus_cache_commit", "icarus_cache_release", "icarus_cache_get_stats", "icarus_set_full_decoders",
            "icarus_validate_block_tables", "icarus_set_attn_piece_limit", "icarus_attn_shared_kv_static", "icarus_bench_read",
-           "icarus_gemm_tile_order", "icarus_gemm_choice", "icarus_gemm_group_tile", "icarus_append_in_tiles", "icarus_prefill_plan")
+           "icarus_gemm_tile_order", "icarus_gemm_choice", "icarus_gemm_group_tile", "icarus_append_in_tiles", "icarus_prefill_plan", "icarus_gemm")
 
 PHASES = ("norm", "lora", "gemm_qkv", "rope_append", "attn", "attn_merge", "gemm_o", "gemm_gateup", "gemm_down",
           "elementwise")
@@ -76,6 +76,13 @@ class _CacheCfg(C.Structure):
 class _CacheStats(C.Structure):
     _fields_ = [("lookups", C.c_int64), ("hit_tokens", C.c_int64), ("miss_tokens", C.c_int64), ("evictions", C.c_int64),
                 ("live", C.c_int32), ("cached", C.c_int32), ("free_blocks", C.c_int32), ("peak_live", C.c_int32)]
+
+
+class _Gemm(C.Structure):
+    _fields_ = [("x", C.c_void_p), ("w", C.c_void_p * 3), ("t", C.c_void_p), ("b", C.c_void_p * 2), ("resid", C.c_void_p),
+                ("y", C.c_void_p), ("partials", C.c_void_p), ("rows", C.c_int32), ("k", C.c_int32), ("n", C.c_int32 * 3),
+                ("n_segs", C.c_int32), ("fused", C.c_int32), ("models", C.c_int32), ("rank", C.c_int32),
+                ("tile_rows", C.c_int32), ("tile_cols", C.c_int32), ("staged", C.c_int32), ("slices", C.c_int32)]
 
 
 def _load():
@@ -128,6 +135,8 @@ def _load():
     lib.icarus_append_in_tiles.argtypes = [vp, i32, i32]
     lib.icarus_prefill_plan.restype = C.c_int
     lib.icarus_prefill_plan.argtypes = [vp, i32, vp, vp, vp, i32, vp]
+    lib.icarus_gemm.restype = C.c_int
+    lib.icarus_gemm.argtypes = [C.POINTER(_Gemm), vp]
     lib.icarus_stack_create.restype = C.c_int
     lib.icarus_stack_create.argtypes = [C.POINTER(_StackCfg), C.POINTER(vp)]
     lib.icarus_stack_destroy.restype = None
@@ -316,6 +325,39 @@ def gemm_group_tile(group_rows):
     if rc != 0:
         raise IcarusError(rc, "icarus_gemm_group_tile failed")
     return int(out[0]), int(out[1])
+
+
+def gemm(x, w, tile, slices: int = 1, fused: bool = False, t=None, b=None, resid=None) -> torch.Tensor:
+    """One GEMM in a given launch: x [rows, k], w a list of [n, k] (fused: gate, up), t [rows, models * rank (x 2 fused)], b a list of
+    [models, n, rank], resid [rows, n]; tile as gemm_choice returns it.  Float [rows, sum n], or bf16 with resid or fused."""
+    rows, k = x.shape
+    _want(x, "x", torch.bfloat16, (rows, k))
+    n = [int(v.shape[0]) for v in w]
+    for v in w:
+        _want(v, "w", torch.bfloat16, (v.shape[0], k), x.device)
+    a = _Gemm(rows=rows, k=k, n_segs=1 if fused else len(w), fused=int(fused), tile_rows=tile[0], tile_cols=tile[1], staged=int(tile[2]), slices=slices)
+    if len(w) > 3 or (fused and (len(w) != 2 or n[0] != n[1])):
+        raise ValueError("w: up to three matrices, or gate and up of one shape")
+    for i, v in enumerate(w):
+        a.w[i], a.n[i] = v.data_ptr(), n[i]
+    cols = n[0] if fused else sum(n)
+    if t is not None:
+        models, _, rank = b[0].shape
+        _want(t, "t", torch.bfloat16, (rows, models * rank * (2 if fused else 1)), x.device)
+        for i, v in enumerate(b):
+            _want(v, "b", torch.bfloat16, (models, n[0], rank), x.device)
+            a.b[i] = v.data_ptr()
+        a.t, a.models, a.rank = t.data_ptr(), models, rank
+    if resid is not None:
+        _want(resid, "resid", torch.bfloat16, (rows, cols), x.device)
+        a.resid = resid.data_ptr()
+    y = torch.empty(rows, cols, dtype=torch.bfloat16 if fused or resid is not None else torch.float32, device=x.device)
+    part = torch.empty(slices if slices > 1 else 0, rows, cols, dtype=torch.float32, device=x.device)
+    a.x, a.y, a.partials = x.data_ptr(), y.data_ptr(), part.data_ptr() if slices > 1 else None
+    rc = _lib.icarus_gemm(C.byref(a), C.c_void_p(torch.cuda.current_stream(x.device).cuda_stream))
+    if rc != 0:
+        raise IcarusError(rc, "icarus_gemm failed")
+    return y
 
 
 class IcarusLayer:

@@ -639,6 +639,7 @@ int gemm_row_tile(const int *off, int n_groups) {
 }
 int gemm_tile_rows(int tile) { return kTileShape[tile].bm; }
 int gemm_tile_cols(int tile) { return kTileShape[tile].bn; }
+bool gemm_tile_staged(int tile) { return is_register_staged(tile); }
 
 // K slices of a grouped launch.  With a weight matrix per group it is bound by their way from HBM, like a GEMM of few
 // rows, and by the last round: 9 groups x 32 column tiles on 512 workgroup slots leave 32 CUs with twice the work of

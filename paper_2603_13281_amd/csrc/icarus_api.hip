@@ -1483,6 +1483,44 @@ icarus_status icarus_gemm_tile_order(int32_t row_tiles, int32_t col_tiles, int32
     return ICARUS_OK;
 }
 
+icarus_status icarus_gemm(const icarus_gemm_args *a, void *stream) {
+    if (!a || a->rows <= 0 || a->rows > 65535 || a->k <= 0 || a->k % 64 || a->n_segs < 1 || a->n_segs > 3 || !a->x || !a->y) return ICARUS_ERR_INVALID_ARG;
+    if (a->fused ? a->n_segs != 1 || a->slices != 1 || a->resid : a->resid && a->n_segs != 1) return ICARUS_ERR_INVALID_ARG;
+    if (a->slices < 1 || a->slices > kGemmMaxSplits || (a->slices > 1 && !a->partials)) return ICARUS_ERR_INVALID_ARG;
+    if (a->t && (a->models < 1 || a->rank < 8 || (a->rank & (a->rank - 1)) || (!a->b[0] && !a->b[1]) || (a->b[1] && !a->fused)))
+        return ICARUS_ERR_INVALID_ARG;
+    for (const void *p : {a->x, a->w[0], a->w[1], a->w[2], a->t, a->b[0], a->b[1], a->resid, (const void *)a->y, (const void *)a->partials})
+        if (!aligned16(p)) return ICARUS_ERR_ALIGNMENT;
+    GemmArgs g{};
+    g.X = (const bf16_raw *)a->x; g.ldx = a->k; g.R = a->rows; g.K = a->k; g.nseg = a->n_segs;
+    int64_t n_total = 0;
+    for (int s = 0; s < (a->fused ? 2 : a->n_segs); ++s) {
+        if (!a->w[s] || a->n[a->fused ? 0 : s] <= 0 || a->n[a->fused ? 0 : s] % 8) return ICARUS_ERR_INVALID_ARG;
+        g.W[s] = (const bf16_raw *)a->w[s];
+        if (s >= a->n_segs) continue;
+        g.n_seg[s] = a->n[s];
+        n_total += a->n[s];
+    }
+    if (n_total > INT32_MAX) return ICARUS_ERR_INVALID_ARG;
+    if (a->t) {
+        g.T = (const bf16_raw *)a->t; g.r = a->rank; g.M_models = a->models; g.ldt = a->models * a->rank * (a->fused ? 2 : 1);
+        g.B[0] = (const bf16_raw *)a->b[0]; g.B[1] = (const bf16_raw *)a->b[1];
+    }
+    g.mode = a->fused ? GEMM_DUAL : GEMM_PLAIN;
+    g.epi = a->resid ? EPI_BF16_RESID : EPI_F32;
+    g.resid = (const bf16_raw *)a->resid; g.ldr = g.ldy = (int)n_total; g.Y = a->y; g.splits = 1;
+    for (int kind = TILE_AUTO + 1; kind < TILE_KINDS; ++kind)
+        if (gemm_tile_rows(kind) == a->tile_rows && gemm_tile_cols(kind) == a->tile_cols && gemm_tile_staged(kind) == (a->staged != 0)) g.tile = kind;
+    if (g.tile == TILE_AUTO || (a->staged && !gemm_decode_supported(g))) return ICARUS_ERR_UNSUPPORTED;
+    hipStream_t st = (hipStream_t)stream;
+    if (a->slices == 1) return launch_gemm_mfma(g, st) == hipSuccess ? ICARUS_OK : ICARUS_ERR_HIP;
+    GemmArgs p = g;
+    p.epi = EPI_F32; p.Y = a->partials; p.splits = a->slices;
+    if (launch_gemm_mfma(p, st) != hipSuccess) return ICARUS_ERR_HIP;
+    return launch_splitk_reduce((const float *)a->partials, a->slices, g.R, g.ldy, g.epi, g.Y, g.ldy, g.resid, g.ldr, st) == hipSuccess ? ICARUS_OK
+                                                                                                                                        : ICARUS_ERR_HIP;
+}
+
 icarus_status icarus_gemm_choice(int32_t rows, int32_t k, const int32_t *n_seg, int32_t n_segs, int32_t fused, int32_t adapter_cols,
                                  int32_t max_slices, int32_t taken, int32_t *choice) {
     if (rows <= 0 || k <= 0 || k % 64 || !n_seg || n_segs < 1 || n_segs > 3 || (fused && n_segs != 1) || adapter_cols < 0 || adapter_cols % 8 ||
@@ -1501,7 +1539,7 @@ icarus_status icarus_gemm_choice(int32_t rows, int32_t k, const int32_t *n_seg, 
     const GemmPlan p = gemm_plan(g, fused ? 1 : max_slices, taken != 0);
     choice[0] = gemm_tile_rows(p.tile);
     choice[1] = gemm_tile_cols(p.tile);
-    choice[2] = p.tile == TILE_REG_192x256 || p.tile == TILE_REG_160x256;
+    choice[2] = gemm_tile_staged(p.tile);
     choice[3] = p.splits;
     return ICARUS_OK;
 }

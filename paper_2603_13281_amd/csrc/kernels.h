@@ -173,6 +173,7 @@ GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices);
 int gemm_row_tile(const int *off, int n_groups);
 int gemm_tile_rows(int tile);
 int gemm_tile_cols(int tile);
+bool gemm_tile_staged(int tile);  // through registers (gemm_decode.hip)
 int gemm_grouped_splits(const GemmArgs &g, int max_splits, bool takes_slices);
 // Tiles of gemm_decode.hip (TILE_REG_*): both operands loaded coalesced, parked in registers two slabs ahead and staged
 // through LDS by register stores; launch_gemm_mfma takes this path for them.

@@ -65,6 +65,28 @@ def test_tile_of_grouped_projections(groups, want):
     assert binding.gemm_group_tile(groups) == want
 
 
+# what the layers of the benchmark shapes run: (rows, K, outputs, fused, most slices, taken) -> launch
+LAYERS = [
+    ((374, 4096, [4096, 1024, 1024], False, 12, True), (192, 128, False, 2)),
+    ((374, 4096, [14336], True, 1, False), (192, 256, True, 1)),
+    ((374, 14336, [4096], False, 12, False), (192, 128, False, 4)),
+    ((512, 25600, [5120], False, 12, False), (256, 256, False, 6)),
+    ((512, 5120, [25600], True, 1, False), (256, 256, False, 1)),
+    ((753, 14336, [4096], False, 12, False), (192, 256, True, 4)),
+    ((753, 4096, [14336], True, 1, False), (192, 256, True, 1)),
+    ((753, 5120, [8192, 1024, 1024], False, 8, True), (160, 256, True, 1)),
+    ((4337, 4096, [4096], False, 2, True), (160, 256, True, 1)),
+    ((4337, 14336, [4096], False, 2, False), (160, 256, True, 1)),
+    ((16384, 4096, [14336], True, 1, False), (256, 256, False, 1)),
+]
+
+
+@pytest.mark.parametrize("call,want", LAYERS, ids=[str(c[0][:3]) for c in LAYERS])
+def test_launches_of_the_benchmark_layers(call, want):
+    rows, k, n, fused, most, taken = call
+    assert binding.gemm_choice(rows, k, n, fused, 0, most, taken) == want
+
+
 def test_choices_are_launches_the_workspace_holds():
     # never more slices than asked for, none empty, K slices of four slabs or more
     rng = np.random.default_rng(5)

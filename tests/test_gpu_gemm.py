@@ -1,0 +1,101 @@
+"""The GEMM kernels in every tile and number of K slices that the launch choice can name, against float64 products of the same bf16
+inputs.  The choice itself is checked in test_gemm_plan.py; here a launch is asked for by name (icarus_gemm), so that a choice that
+only a 5120-wide layer makes is covered at sizes of a few hundred."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_13281_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+TILES = [(64, 128, False), (128, 128, False), (192, 128, False), (256, 256, False), (192, 256, True), (160, 256, True)]
+SLABS = {1: (4, 7, 40), 2: (12, 13), 3: (13, 36), 5: (24, 37), 12: (49, 96)}  # slices -> K / 64: even, odd, slices of unequal length and empty ones
+
+
+def _draw(shape, seed, std=1.0):
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(seed)
+    return (torch.randn(*shape, generator=gen, device="cuda:0") * std).to(torch.bfloat16)
+
+
+def _adapters(rows, n, models, rank, sides, seed):
+    """t with one model's columns per row (none for every fourth row, as the layers leave it) and B per side."""
+    t = _draw((rows, sides, models, rank), seed)
+    keep = torch.arange(rows, device="cuda:0") % (models + 1)
+    t *= (keep[:, None] == torch.arange(1, models + 1, device="cuda:0")[None]).to(t.dtype)[:, None, :, None]
+    return t.reshape(rows, -1).contiguous(), [_draw((models, n, rank), seed + 1 + s, 0.2) for s in range(sides)]
+
+
+def _product(x, w, t=None, b=None):
+    """float64 product and the sum of the absolute values of its terms."""
+    y, s = x.double() @ w.double().T, x.double().abs() @ w.double().abs().T
+    if t is not None:
+        cat = b.permute(1, 0, 2).reshape(b.shape[1], -1).double()
+        y, s = y + t.double() @ cat.T, s + t.double().abs() @ cat.abs().T
+    return y, s
+
+
+def _check(got, want, bound, what):
+    """bound: |error| of fp32 sums of these terms in any order (terms * 2^-23 * sum of their absolute values), plus the rounding of the store."""
+    assert torch.isfinite(got).all(), what
+    worst = ((got.double() - want).abs() / bound).max().item()
+    assert worst <= 1.0, (what, worst)
+
+
+@pytest.mark.parametrize("tile", TILES, ids=lambda t: f"{t[0]}x{t[1]}" + ("r" if t[2] else ""))
+@pytest.mark.parametrize("slices", list(SLABS))
+@pytest.mark.parametrize("models,rank", [(0, 0), (1, 8), (3, 16), (8, 32)], ids=["plain", "8", "48", "256"])
+def test_projection(tile, slices, models, rank):
+    # three stacked matrices with ragged last column tiles (q, k and v: adapters on the first only), and one with a residual;
+    # one row tile, one row more, and a row tile count that panels do not divide
+    bm, bn, _ = tile
+    for slabs in SLABS[slices]:
+        for rows in (1, bm + 1, 3 * bm - 5):
+            k, n = 64 * slabs, [bn + 8, 16, 2 * bn - 40]
+            x, w = _draw((rows, k), slabs), [_draw((m, k), 10 + i, 0.05) for i, m in enumerate(n)]
+            t, b = _adapters(rows, n[0], models, rank, 1, 20) if models else (None, None)
+            what = (tile, "slices", slices, "slabs", slabs, "rows", rows, "adapters", models * rank)
+            print("case:", *what, flush=True)
+            eps = (k + models * rank + 16) * 2.0 ** -23
+            parts = [_product(x, v, t if i == 0 else None, b[0] if t is not None else None) for i, v in enumerate(w)]
+            want, size = (torch.cat([p[j] for p in parts], 1) for j in (0, 1))
+            _check(binding.gemm(x, w, tile, slices, t=t, b=b), want, eps * size + 1e-30, what)
+            resid = _draw((rows, n[0]), 30)
+            want = parts[0][0] + resid.double()
+            _check(binding.gemm(x, w[:1], tile, slices, t=t, b=b, resid=resid), want,
+                   eps * (parts[0][1] + resid.double().abs()) + 2.0 ** -8 * want.abs() + 1e-30, what + ("residual",))
+
+
+@pytest.mark.parametrize("tile", TILES, ids=lambda t: f"{t[0]}x{t[1]}" + ("r" if t[2] else ""))
+@pytest.mark.parametrize("models,rank", [(0, 0), (1, 8), (3, 16), (8, 32)], ids=["plain", "8", "48", "256"])
+def test_gate_up(tile, models, rank):
+    # silu(gate) * up, adapters on both; |d silu| <= 1.1 |d gate|
+    bm, bn, _ = tile
+    for slabs in SLABS[1]:
+        for rows in (1, bm + 1, 3 * bm - 5):
+            for n in (bn // 2 + 8, 3 * bn // 2 - 24):
+                k = 64 * slabs
+                x, w = _draw((rows, k), slabs), [_draw((n, k), 10 + i, 0.05) for i in range(2)]
+                t, b = _adapters(rows, n, models, rank, 2, 20) if models else (None, None)
+                what = (tile, "fused", "slabs", slabs, "rows", rows, "n", n, "adapters", models * rank)
+                print("case:", *what, flush=True)
+                half = (lambda s: t[:, s * models * rank:(s + 1) * models * rank]) if models else (lambda s: None)
+                (g, gs), (u, us) = (_product(x, w[s], half(s), b[s] if models else None) for s in range(2))
+                silu = g * torch.sigmoid(g)
+                eps = (k + models * rank + 16) * 2.0 ** -23
+                bound = 1.1 * eps * gs * u.abs() + eps * us * silu.abs() + (2.0 ** -8 + (2 + g.abs()) * 2.0 ** -21) * (silu * u).abs() + 2.0 ** -100
+                _check(binding.gemm(x, w, tile, fused=True, t=t, b=b), silu * u, bound, what)
+
+
+def test_gemm_refuses_what_the_kernels_do_not_take():
+    x, w = _draw((4, 128), 1), _draw((16, 128), 2)
+    for kw in (dict(tile=(96, 128, False)), dict(tile=(256, 256, True)), dict(tile=TILES[0], slices=13), dict(tile=TILES[0], slices=0)):
+        with pytest.raises(binding.IcarusError):
+            binding.gemm(x, [w], **kw)
+    with pytest.raises(binding.IcarusError):
+        binding.gemm(_draw((4, 96), 1), [_draw((16, 96), 2)], TILES[0])      # K not a multiple of 64
+    with pytest.raises(binding.IcarusError):
+        binding.gemm(x, [_draw((12, 128), 2)], TILES[0])                      # outputs not a multiple of 8
+    with pytest.raises(binding.IcarusError):
+        binding.gemm(x, [w, w], TILES[0], slices=2, fused=True)
