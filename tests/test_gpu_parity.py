@@ -10,7 +10,7 @@ import pytest
 import torch
 
 import oracle
-from paper_2603_13281_amd import synth
+from paper_2603_13281_amd import binding, synth
 from helpers import assert_cache_close, assert_close, assert_fp8_cache_close, e4m3_spacing, fill_pool, filled_batch, mark_unwritten, oracle_config, read_pool
 from gpu_util import bf16_ulp, dev, fp8_pool_to_float, host, make_layer, pool_from_device_layout, pool_to_device_layout
 
@@ -391,9 +391,9 @@ def test_prefill_over_long_contexts(pre, chunk):
 @pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
 @pytest.mark.parametrize("limit", [0, 128, 384])
 def test_prefill_walks_cut_into_pieces(limit, fp8):
-    # the walks of a few token groups are cut into pieces (128-token rounds) and their partial results merged: last
-    # pieces of one token, of just under a round (joined to the one before) and of a whole round; a piece that some
-    # of a group's queries do not reach at all; whole and cut walks in one call; groups that fill one wave or all
+    # the walks of a few token groups are cut into pieces (128-token rounds) and their partial results merged: a part shorter
+    # than a round joins the piece before it, so last pieces have 128 to 255 tokens, and with at most 32 rows to a group every
+    # query reaches every piece; whole and cut walks in one call; groups that fill one wave or all
     _say("case: prefill pieces, limit", limit, "fp8", fp8)
     shape = synth.QWEN_SMALL                        # g = 8: 32 chunk tokens per group
     pre = [0, 127, 128, 255, 380, 1000, 2303, 5]
@@ -424,11 +424,73 @@ def test_prefill_walks_cut_into_pieces(limit, fp8):
     assert_close(host(got), want, 2e-2, "prefill x_out")
 
 
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
+def test_prefill_pieces_that_queries_do_not_reach(fp8):
+    # a query head per kv-head: groups of up to 256 rows, and a last piece of 128-255 tokens lies past what the first rows of
+    # the group attend to; they leave a maximum of -inf and a sum of 0 there, which the merge must weigh with zero
+    _say("case: unreached prefill pieces, fp8", fp8)
+    shape = synth.LLAMA_SMALL.replace(n_q_heads=4, n_kv_heads=4)
+    pre, chunk = [100, 0, 37, 260], [300, 513, 257, 256]
+    ks, vs = 0.02, 0.013
+    base = synth.make_base(shape, seed=47, norm_ones=False)
+    batch = synth.make_batch(shape, pre, [0] * len(pre), seed=47, headroom=max(chunk))
+    x = synth.make_hidden(shape, sum(chunk), seed=47, tag=5)
+    cfg = oracle_config(shape, batch.num_blocks)
+    kw = dict(kv_fp8=True, k_scale=ks, v_scale=vs) if fp8 else {}
+    layer = make_layer(shape, base, None, batch.num_blocks, **kw)
+    if fp8:
+        gen = torch.Generator(device="cuda:0")
+        gen.manual_seed(47)
+        dpool = torch.randint(0, 0x70, layer.cfg.pool_shape(), generator=gen, device="cuda:0", dtype=torch.uint8)
+        pool = pool_from_device_layout(fp8_pool_to_float(dpool, ks, vs), shape.block_size, shape.head_dim)
+        cfg = dataclasses.replace(cfg, **kw)
+    else:
+        pool = filled_batch(shape, batch, seed=47)
+        mark_unwritten(shape, batch, pool, np.nan)
+        dpool = dev(pool_to_device_layout(pool), True)
+    layer.set_attn_piece_limit(128)
+    pieces = layer.prefill_plan(pre, chunk)
+    first = {}                                      # tokens the first row of each group attends to
+    row = 0
+    for c, n in zip(pre, chunk):
+        first.update({row + t: c + t + 1 for t in range(0, n, 256)})
+        row += n
+    assert any(p[2] >= first[int(p[0])] for p in pieces), "no piece that a query does not reach"
+    want, _ = oracle.Oracle(cfg, base, None).prefill(pool, batch.block_tables, pre, chunk, x)
+    got = layer.prefill_kv(dpool, torch.from_numpy(batch.block_tables).cuda(), pre, chunk, dev(x, True))
+    torch.cuda.synchronize()
+    assert_close(host(got), want, 2e-2, "prefill x_out")
+
+
+def test_append_by_tiles_sums_the_slices_of_the_projection():
+    # the tiles add up the K slices that the QKV projection leaves; chunks that start inside a block
+    _say("case: append tiles over slices")
+    shape = synth.QWEN_SMALL.replace(d_model=3072, n_q_heads=48, n_kv_heads=8, d_ffn=512)
+    pre, chunk = [5, 30], [230, 100]
+    n = [shape.n_q_heads * 128, shape.n_kv_heads * 128, shape.n_kv_heads * 128]
+    assert binding.gemm_choice(sum(chunk), shape.d_model, n, max_slices=12, taken=True)[3] == 2
+    base = synth.make_base(shape, seed=53, norm_ones=False)
+    batch = synth.make_batch(shape, pre, [0, 0], seed=53, headroom=max(chunk))
+    layer = make_layer(shape, base, None, batch.num_blocks)
+    assert layer.append_in_tiles(sum(chunk), 24)
+    pool = filled_batch(shape, batch, seed=53)
+    x = synth.make_hidden(shape, sum(chunk), seed=53, tag=5)
+    dpool = dev(pool_to_device_layout(pool), True)
+    want, want_slots = oracle.Oracle(oracle_config(shape, batch.num_blocks), base, None).prefill(pool, batch.block_tables, pre, chunk, x)
+    slots = torch.zeros(sum(chunk), dtype=torch.int64, device="cuda")
+    got = layer.prefill_kv(dpool, torch.from_numpy(batch.block_tables).cuda(), pre, chunk, dev(x, True), slot_out=slots)
+    torch.cuda.synchronize()
+    assert np.array_equal(slots.cpu().numpy(), want_slots)
+    _cache_close(shape, pool_from_device_layout(host(dpool), shape.block_size, shape.head_dim), pool, "cache")
+    assert_close(host(got), want, 2e-2, "prefill x_out")
+
+
 @pytest.mark.parametrize("rows", [65, 129, 161, 250, 321, 449, 577, 770, 1100])
 @pytest.mark.parametrize("d_ffn", [4096, 8256])
 def test_prefill_row_counts_over_the_gemm_tiles(rows, d_ffn):
-    # every tile kind and slice count that the GEMM plan reaches at these widths, plain, with residual and gate/up: row
-    # counts one past a tile edge or well inside, a ragged last column tile (8256 outputs), panels that do not divide
+    # whole prefill layers at row counts one past a tile edge or well inside, a ragged last column tile (8256 outputs), panels
+    # that do not divide.  At 1024 columns nearly all projections run in 128 x 128 tiles, sliced and whole, gate/up also in the
+    # larger ones; every tile and slice count by itself is in test_gpu_gemm.py
     _say("case: prefill rows", rows, "d_ffn", d_ffn)
     shape = synth.LLAMA_SMALL.replace(d_model=1024, d_ffn=d_ffn)
     base = synth.make_base(shape, seed=23, norm_ones=False)
