@@ -145,18 +145,17 @@ __global__ void __launch_bounds__(256) k_gemm_decode(GemmArgs g) {
     const int ldsw = swz(lrow, c);  // chunk i lands 32 rows = 4096 bytes further
 
     // Chunk u of a slab: u < NA activation chunk u, else weight chunk u - NA.  Any slab index, branch-free: base
-    // range -> X / W at column sl * 64; past it -> T / Bcat; columns past T's last, whole slabs past the end, and
-    // weight rows without an adapter: finite activations against zero weights.
-    const bf16_t *x_past = t_cols ? g.T : g.X + (size_t)(base_slabs - 1) * kBK + 8 * c;
+    // range -> X / W at column sl * 64; past it -> T / Bcat; columns past T's last and whole slabs past the end: zeros on
+    // both sides (an infinite activation times a zero weight would be NaN); weight rows without an adapter: zeros.
     u32x4 xr[D][NA + NB];
     auto issue_chunk = [&](int sl, int u, u32x4 &dst) {
         const bool past = sl >= sl_end;  // the slab that rounds an odd count up; it may belong to the next K slice
         const bool xbase = sl < base_slabs, base = !past && xbase;
         const int t0 = (sl - base_slabs) * kBK + 8 * c;          // this thread's 8 columns of T
         if (u < NA) {
-            const int tcol = t_cols ? max(0, min(t0, t_cols - 8)) : 0;
-            const bf16_t *pa = pick(xbase, g.X + (size_t)sl * kBK, x_past);
-            dst = *(const u32x4 *)(pa + pick(xbase, offx[u], (t_cols ? offt[u] : offx[u] - 8 * c) + tcol));
+            const bool in_t = !past && !xbase && t0 < t_cols;
+            const bf16_t *pa = pick(base, g.X + (size_t)sl * kBK, pick(in_t, g.T, zero));
+            dst = *(const u32x4 *)(pa + pick(base, offx[u], pick(in_t, offt[u] + t0, 0)));
         } else {
             const int i = u - NA;
             const bool up = dual && (i % TN) >= TN / 2;

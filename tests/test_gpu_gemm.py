@@ -88,6 +88,30 @@ def test_gate_up(tile, models, rank):
                 _check(binding.gemm(x, w, tile, fused=True, t=t, b=b), silu * u, bound, what)
 
 
+@pytest.mark.parametrize("tile", TILES, ids=lambda t: f"{t[0]}x{t[1]}" + ("r" if t[2] else ""))
+@pytest.mark.parametrize("slabs,slices", [(7, 1), (8, 1), (13, 2), (37, 5)])
+@pytest.mark.parametrize("models", [0, 3])
+def test_infinite_activations_reach_only_their_products(tile, slabs, slices, models):
+    # a launch pads K (odd slab counts, slices, adapter columns up to a whole slab) with zeros on both sides: an infinity gives
+    # infinities of the weights' signs, no NaN, wherever in K it is
+    print("case: infinities", tile, slabs, slices, models, flush=True)
+    rows, n, k = slabs, tile[1] + 8, 64 * slabs
+    x, w = _draw((rows, k), 1), _draw((n, k), 2, 0.05)
+    w = torch.where(w == 0, torch.ones_like(w), w)
+    at = torch.arange(rows, device="cuda:0") * 64 + 9            # an infinity in every slab, one row each
+    x[torch.arange(rows, device="cuda:0"), at] = float("inf")
+    t, b = _adapters(rows, n, models, 16, 1, 20) if models else (None, None)
+    got = binding.gemm(x, [w], tile, slices, t=t, b=b)
+    want = torch.sign(w[:, at].T.float()) * float("inf")
+    assert torch.equal(got, want)
+    if models:                                                   # the last adapter column, next to the padding
+        x, t = _draw((rows, k), 1), t.clone()
+        t[0, -1] = float("inf")
+        b[0][-1, :, -1] = 1.0
+        got = binding.gemm(x, [w], tile, slices, t=t, b=b)
+        assert torch.isposinf(got[0]).all() and torch.isfinite(got[1:]).all()
+
+
 def test_gemm_refuses_what_the_kernels_do_not_take():
     x, w = _draw((4, 128), 1), _draw((16, 128), 2)
     for kw in (dict(tile=(96, 128, False)), dict(tile=(256, 256, True)), dict(tile=TILES[0], slices=13), dict(tile=TILES[0], slices=0)):
