@@ -569,13 +569,13 @@ bool gemm_mfma_supported(const Dims &dm, int K) {
 // way through memory and, where no later kernel takes the slices as they are, a launch).  Near ties are decided by what
 // the model does not know -- how the strides of the slices fall on the HBM channels, what the row kernel after a sliced
 // projection pays, what the register-staged tiles do to the clock -- so the plain choice has a start.  The modelled time has to
-// undercut by 4 %: up to 384 rows of a narrow output, 192-row tiles in as many slices as the CUs hold at once; from 1024
+// undercut by 3 %: up to 384 rows of a narrow output, 192-row tiles in as many slices as the CUs hold at once; from 1024
 // rows, 256 x 256 tiles that fill most of the CUs.  In between, slices have to earn 3 %.
 // Measured inside a layer, weights from HBM, consumers of the slices included (5 widths of 2048-8192, 130-32768 rows, QKV, O,
-// gate/up, down: 1316 launches, every tile x 1-12 slices): within 0.7 % of the fastest on average, 18 % at worst (252 rows,
+// gate/up, down: 1316 launches, every tile x 1-12 slices): within 0.6 % of the fastest on average, 18 % at worst (252 rows,
 // 5120 -> 10240).  Without the start for the plain choice 28 of them were 2-29 % slower than one tile for each range of
 // row counts (162 rows, 28672 -> 8192: 152 us in 192 x 256 tiles, 118 us in 192 x 128; 10000 rows, 4096 -> 4096: 349 us in
-// 160 x 256, 327 us in 256 x 256); with it 8, by 7 % at most.  The fixed tiles in turn are 10 % from the fastest on
+// 160 x 256, 327 us in 256 x 256); with it 9, by 7 % at most.  The fixed tiles in turn are 10 % from the fastest on
 // average (512 rows, 25600 -> 5120: 233 us in 128 x 128 tiles, 144 us in 256 x 256 and 6 slices; 4337 rows, 14336 -> 4096,
 // whose 272 tiles of 256 x 256 need two rounds of 256 CUs: 616 us, in 160 x 256 tiles 486 us).
 GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices) {
@@ -598,10 +598,10 @@ GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices) {
     if (few && g.mode != GEMM_DUAL && n_tiles_for(g, 192, 256) < 160) {
         const int tiles = n_tiles_for(g, 192, 128);
         best = {TILE_192x128, tiles < 160 ? std::max(1, std::min({max_splits, 256 / tiles, slabs / 4})) : 1};
-        best_us = 0.96f * modelled(best.tile, best.splits);
+        best_us = 0.97f * modelled(best.tile, best.splits);
     } else if (g.R >= 1024 && n_tiles_for(g, 256, 256) >= 192) {
         best = {TILE_256x256, 1};
-        best_us = 0.96f * modelled(best.tile, best.splits);
+        best_us = 0.97f * modelled(best.tile, best.splits);
     }
     const bool reg_ok = gemm_decode_supported(g);
     for (int kind = TILE_128; kind < TILE_KINDS; ++kind) {  // several row tiles of 64 would read the weights again

@@ -40,6 +40,7 @@ CHOICES = [
     ((162, 28672, [8192], 128, 12, False), (192, 128, False, 4)),     # modelled 1 % slower than 192 x 256 in 8 slices, measured 22 % faster
     ((189, 28672, [8192], 128, 12, False), (192, 128, False, 4)),
     ((374, 4096, [4096], 128, 12, True), (192, 128, False, 4)),
+    ((360, 25600, [5120], 256, 12, False), (192, 256, True, 6)),      # 112 us, 119 us in 192 x 128 and 3 slices: no near tie
     ((270, 8192, [8192], 128, 12, True), (192, 128, False, 2)),
     ((720, 8192, [5120], 256, 12, True), (128, 128, False, 1)),
     ((385, 8192, [8192], 0, 12, True), (128, 128, False, 1)),
