@@ -127,15 +127,15 @@ struct GemmArgs {
     const bf16_raw *resid; int ldr;              // EPI_BF16_RESID: added to the result
     int splits;                                  // split-K slices (EPI_F32 without adapters only)
     int tile;                                    // tile kind (TILE_AUTO: chosen by the launcher)
-    // Grouped launch (optional): row_tiles, device [n_row_tiles][3] = first row, end row, group of each row tile (gemm_tile_rows
-    // rows at most).  Group 0 multiplies W[0] (DUAL: W[0], W[1]), group j > 0 Wg[.] + (j - 1) * wg_stride elements.
-    const int32_t *row_tiles; int n_row_tiles;
-    const bf16_raw *Wg[2]; size_t wg_stride;
     // filled by the launcher
     int tiles_seg[3]; int m_tiles, n_tiles, K_ext, k_per_split;
     int panel_m, panel_n, panels_m, n_panels;       // tile order: panels of panel_m x panel_n tiles (n_panels per K slice)
     uint32_t inv_panels, inv_panels_m, inv_panel_m; // gemm_inv of n_panels, panels_m, panel_m
     int slabs_per_split;                            // decode kernel: 64-wide K slabs per split-K slice
+    // Grouped launch (optional): row_tiles, device [n_row_tiles][3] = first row, end row, group of each row tile (gemm_tile_rows
+    // rows at most).  Group 0 multiplies W[0] (DUAL: W[0], W[1]), group j > 0 Wg[.] + (j - 1) * wg_stride elements.
+    const int32_t *row_tiles; int n_row_tiles;
+    const bf16_raw *Wg[2]; size_t wg_stride;
 };
 bool gemm_mfma_supported(const Dims &dm, int K);
 // fills the tile order from m_tiles, n_tiles and splits, for bm x bn tiles and per_cu workgroups to a CU
@@ -145,21 +145,22 @@ inline dim3 gemm_grid(const GemmArgs &g) {
     return dim3((unsigned)(g.panel_m * g.panel_n * 8), (unsigned)((g.n_panels * g.splits + 7) / 8));
 }
 // x / n for x * n < 2^32, by the host's inv = ceil(2^32 / n) (0 for n = 1): a division would cost these short kernels
-// as much as a dozen loads
+// as much as a dozen loads.  Without a branch, so that the arguments of a whole tile_at are loaded at once: one after the
+// other behind branches they made the small decode launches 0.2 us longer (10.0 -> 10.3).
 inline uint32_t gemm_inv(int n) { return n > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint64_t)n - 1) / (uint64_t)n) : 0u; }
-__host__ __device__ __forceinline__ int gemm_div(int x, uint32_t inv) { return inv ? (int)(((uint64_t)(uint32_t)x * inv) >> 32) : x; }
+__host__ __device__ __forceinline__ int gemm_div(int x, uint32_t inv) { return (int)(((uint64_t)(uint32_t)x * inv) >> 32) + (x & -(int)(inv == 0)); }
 // Tile and K slice of workgroup (bx, by); false: none.  Neighbouring columns of a panel go to one XCD.  Dealing the columns
 // of a single row tile over the XCDs instead depends on how the weight rows' strides fall: a step of 32 rows with an LM head
 // of 4096 -> 128256 425 -> 414 us, but with one of 4096 -> 65536 281 -> 322 us, and 9 rows of gate and up, 8192 -> 2 x 28672,
 // 177 -> 227 us.
 __host__ __device__ __forceinline__ bool tile_at(const GemmArgs &g, int bx, int by, int *tile_m, int *tile_n, int *kz) {
     const int within = bx >> 3, p = by * 8 + (bx & 7);
-    *kz = g.splits > 1 ? gemm_div(p, g.inv_panels) : (int)(p >= g.n_panels);
+    *kz = gemm_div(p, g.inv_panels);
     const int panel = p - *kz * g.n_panels;
     const int pn = gemm_div(panel, g.inv_panels_m), wn = gemm_div(within, g.inv_panel_m);
     *tile_m = (panel - pn * g.panels_m) * g.panel_m + within - wn * g.panel_m;
     *tile_n = pn * g.panel_n + wn;
-    return *kz < g.splits && *tile_m < g.m_tiles && *tile_n < g.n_tiles;
+    return (*kz < g.splits) & (*tile_m < g.m_tiles) & (*tile_n < g.n_tiles);
 }
 __device__ __forceinline__ bool tile_of_workgroup(const GemmArgs &g, int *tile_m, int *tile_n, int *kz) {
     return tile_at(g, blockIdx.x, blockIdx.y, tile_m, tile_n, kz);
