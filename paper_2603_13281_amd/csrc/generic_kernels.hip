@@ -356,7 +356,7 @@ template <> struct KVElem4<fp8_t> {
 // projections in, q and the cache entries out.  A row at a time, each V value was a 2-byte store of its own, 32 bytes
 // from the next (the cache holds V transposed), and a rotated pair two more; here a thread rotates four pairs at a time,
 // and the tile's V goes through LDS into 16-byte pieces of the transposed plane.  16384 rows x 6144 columns: 169 us ->
-// 133 us, 4337 rows 50 -> 33 us, 512 rows x 10240 columns 26 -> 13 us.
+// 136 us, 4337 rows 50 -> 34 us, 512 rows x 10240 columns 26 -> 14 us.
 // tiles: device, first row | rows << 16.
 template <typename KT>
 __global__ void __launch_bounds__(256) k_rope_append_tile(const float *__restrict__ qkv, int ldq, int splits, size_t slice,
