@@ -255,7 +255,7 @@ icarus_status icarus_gemm(const icarus_gemm_args *args, void *stream);
 /* The choice of such a launch, host only: a GEMM of `rows` rows over K = k against n_segs stacked weight matrices of n_seg[.] rows
  * (host, at most 3; fused != 0: the gate/up pair of n_seg[0] rows each), adapter_cols = n_models * rank (a multiple of 8; 0: no
  * adapters), at most max_slices slices of K, which a later kernel sums on the way if taken != 0.  choice (host): rows and weight
- * rows of a tile, 1 if it is staged through registers, slices. */
+ * rows of a tile, a mark (1 for 192 and 160 rows by 256, else 0), slices. */
 icarus_status icarus_gemm_choice(int32_t rows, int32_t k, const int32_t *n_seg /*host*/, int32_t n_segs, int32_t fused, int32_t adapter_cols,
                                  int32_t max_slices, int32_t taken, int32_t *choice /*host [4]*/);
 

@@ -308,7 +308,7 @@ def gemm_tile_order(row_tiles: int, col_tiles: int, k_slices: int, tile_rows: in
 
 
 def gemm_choice(rows: int, k: int, n, fused: bool = False, adapter_cols: int = 0, max_slices: int = 12, taken: bool = False):
-    """(tile rows, tile columns, staged through registers, K slices) of a GEMM's launch (host only); n: outputs per segment."""
+    """(tile rows, tile columns, mark of 192 and 160 rows by 256, K slices) of a GEMM's launch (host only); n: outputs per segment."""
     seg = np.ascontiguousarray(np.atleast_1d(n), dtype=np.int32)
     out = np.zeros(4, dtype=np.int32)
     rc = _lib.icarus_gemm_choice(rows, k, seg.ctypes.data, len(seg), int(fused), adapter_cols, max_slices, int(taken), out.ctypes.data)

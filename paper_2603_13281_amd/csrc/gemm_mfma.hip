@@ -25,86 +25,13 @@
 #include <cstdio>
 #include <cstdlib>
 
-#include "device_util.h"
-#include "kernels.h"
+#include "gemm_tile.h"
 
 namespace icarus {
-
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 namespace {
 
 constexpr int kKAlign = 64;  // K of every GEMM is a multiple of this
-
-// Per-thread description of one 16-byte load of the weight (B) tile, fixed for the whole K loop.
-struct BRow {
-    const bf16_t *w;   // weight row + chunk offset: base-K loads are w + k
-    const bf16_t *b;   // adapter B of this output column: &B[0][n][0] + chunk offset inside a model
-    int kind;          // 0: no adapter columns; 1: adapter range [0, M*r); 2: range [M*r, 2*M*r) (up rows)
-};
-
-// LDS B-row b of weight tile tile_n -> weight row.  DUAL: a tile covers BN/2 output columns; inside
-// each wave column of WN LDS rows the first WN/2 are gate rows and the next WN/2 the up rows of the
-// same WN/2 output columns.
-// W0, W1: weights of segment 0 (DUAL: gate, up), which in a grouped launch are the row group's.
-template <int BN, int WN>
-__device__ __forceinline__ BRow b_row(const GemmArgs &g, const bf16_t *W0, const bf16_t *W1, int tile_n, int b) {
-    BRow o;
-    if (g.mode == GEMM_DUAL) {
-        int wn = b / WN, j = (b % WN) / (WN / 2), nn = b % (WN / 2);
-        int n = min(tile_n * (BN / 2) + wn * (WN / 2) + nn, g.n_seg[0] - 1);
-        o.w = (j ? W1 : W0) + (size_t)n * g.K;
-        const bf16_t *B = j ? g.B[1] : g.B[0];
-        o.kind = (g.T && B) ? 1 + j : 0;
-        o.b = o.kind ? B + (size_t)n * g.r : o.w;
-        return o;
-    }
-    // plain: up to three weight segments stacked along N; tiles never straddle segments
-    int t = tile_n;
-    const bf16_t *W = W0;
-    int n_seg = g.n_seg[0];
-    bool first = true;
-    if (g.nseg > 1 && t >= g.tiles_seg[0]) {
-        t -= g.tiles_seg[0]; W = g.W[1]; n_seg = g.n_seg[1]; first = false;
-        if (g.nseg > 2 && t >= g.tiles_seg[1]) { t -= g.tiles_seg[1]; W = g.W[2]; n_seg = g.n_seg[2]; }
-    }
-    int n = min(t * BN + b, n_seg - 1);
-    o.w = W + (size_t)n * g.K;
-    o.kind = (first && g.T && g.B[0]) ? 1 : 0;
-    o.b = o.kind ? g.B[0] + (size_t)n * g.r : o.w;
-    return o;
-}
-
-// 256 bytes of zeros: the source of LDS-direct loads that must read as zeros (adapter columns a
-// row does not have, padding past the last adapter column).
-__device__ uint4 g_zero_page[16];
-
-// 16-byte LDS-direct load: lane i of the wave copies 16 bytes from its own global address g to LDS
-// byte address lds_base + 16 i (lds_base wave-uniform).  The data bypasses the registers and the
-// load stays in flight, counted by vmcnt, until it has been written to LDS.  Written as inline
-// assembly so that the compiler does not tie later LDS reads to it with a full vmcnt(0) wait: the
-// pipeline below waits explicitly.  m0 carries the LDS base; nothing else in these kernels uses m0.
-__device__ __forceinline__ void dma16(const void *g, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(g) : "memory");
-}
-
-// s_waitcnt immediate (gfx9 encoding) for vmcnt <= N and lgkmcnt == 0: all LDS reads of the wave
-// have returned and at most N of its global loads are still in flight.
-constexpr int waitcnt_vm_lgkm0(int n) { return (n & 15) | (7 << 4) | (0 << 8) | ((n >> 4) << 14); }
-
-template <int N>
-__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(N)); }
-
-// Byte offset of 16-byte chunk c of tile row `row` inside an operand's LDS stage.  Rows are stored
-// densely (CPR chunks each); inside every 256-byte line (one pass over the 64 banks) the chunk
-// position is XOR-ed with the low bits of the line number, so that the 16-byte fragment reads of
-// 16 consecutive rows, which the LDS serves together, fall into 16 different bank groups.
-template <int CPR>
-__device__ __forceinline__ int swz(int row, int c) {
-    int q = row * CPR + c, line = q >> 4, p = q & 15;
-    return (line << 8) + ((p ^ (line & (CPR - 1))) << 4);
-}
 
 template <int BM, int BN, int BK, int NS, int WAVES_M, int WAVES_N, bool GROUPED>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) k_gemm_mfma(GemmArgs g) {
@@ -313,89 +240,9 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) k_gemm_mfma(GemmArgs g
         stage = next;
     }
 
-    // Epilogue.  Accumulator register r of MFMA tile (i, j) is row 8(r/4) + 4(lane/32) + r%4, column
-    // lane%32: a lane owns single columns, which would make 2-byte stores.  Each wave therefore turns
-    // 32 rows of its tile at a time through its own slice of the (now dead) ring, and reads them back
-    // row-major, 8 columns per lane, for 16- and 32-byte global accesses.
-    __syncthreads();  // every wave has left the K loop
-    constexpr bool kMayBeDual = TN % 2 == 0;
-    const bool dual = kMayBeDual && g.mode == GEMM_DUAL;
-    constexpr int kEs = WN + 8;  // scratch row stride in floats: rows 4 apart fall into different bank halves
-    static_assert(NW * 32 * kEs * 4 <= NS * kStage, "epilogue scratch must fit the ring");
-    float *scr = (float *)smem + w * 32 * kEs;
-    const int col_l = lane & 31, row_l = (lane >> 5) * 4;
-    int seg = 0, t = tile_n, col_base = 0;
-    if (!dual)
-        while (seg + 1 < g.nseg && t >= g.tiles_seg[seg]) { t -= g.tiles_seg[seg]; col_base += g.n_seg[seg]; ++seg; }
-    const int wcols = dual ? WN / 2 : WN;                                   // output columns of this wave
-    const int n_wave = dual ? tile_n * (BN / 2) + wn * (WN / 2) : t * BN + wn * WN;  // first of them, inside the segment
-    const int n_lim = g.n_seg[dual ? 0 : seg];
-    const int lpr = wcols / 8, rpp = 64 / lpr;                              // lanes per row, rows per pass
-    const int rr0 = lane / lpr, c8 = (lane % lpr) * 8;
-    // The residual rows of the next 32-row group are requested before this group is turned through
-    // LDS, so that their latency (HBM: another kernel wrote them) is not paid once per pass.
-    constexpr int kPasses = WN / 16;  // passes over a 32-row group when the wave's columns are all outputs
-    const bool with_resid = !dual && g.epi != EPI_F32;
-    uint4 rres[2][kPasses];
-    auto load_resid = [&](int i, uint4 (&dst)[kPasses]) {
-#pragma unroll
-        for (int p = 0; p < kPasses; ++p) {
-            const int row = row0 + wm * WM + i * 32 + rr0 + p * rpp, n_in = n_wave + c8;
-            dst[p] = (row < row_end && n_in < n_lim) ? *(const uint4 *)(g.resid + (size_t)row * g.ldr + col_base + n_in) : make_uint4(0u, 0u, 0u, 0u);
-        }
-    };
-    if (with_resid) load_resid(0, rres[0]);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        if (with_resid && i + 1 < TM) load_resid(i + 1, rres[(i + 1) & 1]);
-        if (dual) {
-            if constexpr (kMayBeDual) {
-#pragma unroll
-                for (int j = 0; j < TN / 2; ++j)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        float gt = acc[i][j][r], up = acc[i][j + TN / 2][r];
-                        scr[(8 * (r >> 2) + row_l + (r & 3)) * kEs + j * 32 + col_l] = gt * __builtin_amdgcn_rcpf(1.f + __expf(-gt)) * up;  // 1 ulp reciprocal: the result is rounded to bf16
-                    }
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) scr[(8 * (r >> 2) + row_l + (r & 3)) * kEs + j * 32 + col_l] = acc[i][j][r];
-        }
-#pragma unroll
-        for (int p = 0; p < kPasses; ++p) {
-            const int rr = rr0 + p * rpp;
-            if (rr >= 32) break;  // the fused gate/up tile has half the output columns: half the passes
-            const int row = row0 + wm * WM + i * 32 + rr, n_in = n_wave + c8;
-            if (row >= row_end || n_in >= n_lim) continue;  // output widths are multiples of 8
-            const float4 a = *(const float4 *)(scr + rr * kEs + c8), b = *(const float4 *)(scr + rr * kEs + c8 + 4);
-            float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-            const int n = col_base + n_in;
-            if (!dual && g.epi == EPI_F32) {
-                float *yp = (float *)g.Y + ((size_t)kz * g.slice_rows + row) * g.ldy + n;
-                *(float4 *)yp = a;
-                *(float4 *)(yp + 4) = b;
-                continue;
-            }
-            if (!dual) {  // EPI_BF16_RESID
-                const uint4 rv = rres[i & 1][p];
-                const uint32_t rw[4] = {rv.x, rv.y, rv.z, rv.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    v[2 * e] += __uint_as_float(rw[e] << 16);
-                    v[2 * e + 1] += __uint_as_float(rw[e] & 0xffff0000u);
-                }
-            }
-            uint4 o;
-            o.x = (uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16);
-            o.y = (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16);
-            o.z = (uint32_t)f32_to_bf16(v[4]) | ((uint32_t)f32_to_bf16(v[5]) << 16);
-            o.w = (uint32_t)f32_to_bf16(v[6]) | ((uint32_t)f32_to_bf16(v[7]) << 16);
-            *(uint4 *)((bf16_t *)g.Y + (size_t)row * g.ldy + n) = o;
-        }
-    }
+    __syncthreads();  // every wave has left the K loop: the ring is the epilogue's scratch
+    static_assert(NW * 32 * (WN + 8) * 4 <= NS * kStage, "epilogue scratch must fit the ring");
+    store_wave_tile<32, TM, TN, BN>(g, acc, (float *)smem + w * 32 * (WN + 8), tile_n, kz, row0 + wm * WM, row_end, wn);
 }
 
 // Second pass of a split-K GEMM: sum the fp32 partials P[z][row][n] and apply the epilogue.
@@ -474,8 +321,8 @@ hipError_t launch_cfg(GemmArgs g, hipStream_t st) {
 }
 
 // Tile shapes: rows x weight rows of a workgroup, all with 64-wide K slabs (32-wide slabs ask for every 128-byte line of
-// a weight row twice, half each time, and stream at about 60 % of the rate).  The first four are k_gemm_mfma, the last
-// two k_gemm_decode.  first_us: what a workgroup takes apart from its slabs (start, first slab, epilogue); slab_us: a slab
+// a weight row twice, half each time, and stream at about 60 % of the rate).  The first three are k_gemm_mfma, the
+// 256 wide ones k_gemm_quad.  first_us: what a workgroup takes apart from its slabs (start, first slab, epilogue); slab_us: a slab
 // with every CU busy, for each of the per_cu workgroups that share one.  The figures are a fit to 5000 timings on
 // this GPU (80-4337 rows x the projections of a Llama-3-8B- and a Qwen3-32B-shaped layer x every tile x 1-12 slices; the
 // fit is 7-11 % off on average), see gemm_plan and gemm_row_tile.
@@ -497,7 +344,7 @@ int n_tiles_for(const GemmArgs &g, int bm, int bn) {
     return m_tiles * n_tiles;
 }
 
-bool is_register_staged(int kind) { return kind >= TILE_REG_192x256; }
+bool is_quad(int kind) { return kind >= TILE_256x256; }
 
 int k_ext_of(const GemmArgs &g) {
     if (g.mode == GEMM_DUAL) return g.K + (g.T ? 2 * g.M_models * g.r : 0);
@@ -568,7 +415,7 @@ bool gemm_mfma_supported(const Dims &dm, int K) {
 // Beyond that the choice is the smallest modelled time over the tiles and slice counts (model_us + the partial sums'
 // way through memory and, where no later kernel takes the slices as they are, a launch).  Near ties are decided by what
 // the model does not know -- how the strides of the slices fall on the HBM channels, what the row kernel after a sliced
-// projection pays, what the register-staged tiles do to the clock -- so the plain choice has a start.  The modelled time has to
+// projection pays, what the wide tiles do to the clock -- so the plain choice has a start.  The modelled time has to
 // undercut by 3 %: up to 384 rows of a narrow output, 192-row tiles in as many slices as the CUs hold at once; from 1024
 // rows, 256 x 256 tiles that fill most of the CUs.  In between, slices have to earn 3 %.
 // Measured inside a layer, weights from HBM, consumers of the slices included (5 widths of 2048-8192, 130-32768 rows, QKV, O,
@@ -603,9 +450,7 @@ GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices) {
         best = {TILE_256x256, 1};
         best_us = 0.97f * modelled(best.tile, best.splits);
     }
-    const bool reg_ok = gemm_decode_supported(g);
     for (int kind = TILE_128; kind < TILE_KINDS; ++kind) {  // several row tiles of 64 would read the weights again
-        if (is_register_staged(kind) && !reg_ok) continue;
         for (int splits = 1; splits <= max_splits; ++splits) {
             if (splits > 1) {
                 const int per = (slabs + splits - 1) / splits;
@@ -639,7 +484,7 @@ int gemm_row_tile(const int *off, int n_groups) {
 }
 int gemm_tile_rows(int tile) { return kTileShape[tile].bm; }
 int gemm_tile_cols(int tile) { return kTileShape[tile].bn; }
-bool gemm_tile_staged(int tile) { return is_register_staged(tile); }
+bool gemm_tile_marked(int tile) { return tile >= TILE_192x256; }
 
 // K slices of a grouped launch.  With a weight matrix per group it is bound by their way from HBM, like a GEMM of few
 // rows, and by the last round: 9 groups x 32 column tiles on 512 workgroup slots leave 32 CUs with twice the work of
@@ -680,14 +525,17 @@ hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st) {
     if (g.slice_rows < g.R) g.slice_rows = g.R;
     if (g.row_tiles && (g.tile < TILE_64x128 || g.tile > TILE_256x256)) return hipErrorInvalidValue;
     if (g.tile == TILE_AUTO) g.tile = gemm_plan(g, 1, false).tile;
-    if (is_register_staged(g.tile)) return launch_gemm_decode(g, st);
+    if (is_quad(g.tile) && std::max(g.K, g.ldx) > kQuadMaxK) {
+        if (g.row_tiles) return hipErrorInvalidValue;
+        g.tile = TILE_128;
+    }
     g.K_ext = k_ext_of(g);
     g.k_per_split = ((g.K_ext + g.splits - 1) / g.splits + kKAlign - 1) / kKAlign * kKAlign;
+    if (is_quad(g.tile)) return launch_gemm_quad(g, st);
     switch (g.tile) {
     case TILE_64x128: return g.row_tiles ? launch_cfg<64, 128, 64, 3, 2, 2, true>(g, st) : launch_cfg<64, 128, 64, 3, 2, 2>(g, st);
     case TILE_128: return g.row_tiles ? launch_cfg<128, 128, 64, 4, 2, 2, true>(g, st) : launch_cfg<128, 128, 64, 4, 2, 2>(g, st);
     case TILE_192x128: return g.row_tiles ? launch_cfg<192, 128, 64, 3, 2, 2, true>(g, st) : launch_cfg<192, 128, 64, 3, 2, 2>(g, st);
-    case TILE_256x256: return g.row_tiles ? launch_cfg<256, 256, 64, 2, 2, 4, true>(g, st) : launch_cfg<256, 256, 64, 2, 2, 4>(g, st);
     default: return hipErrorInvalidValue;
     }
 }

@@ -1099,6 +1099,7 @@ icarus_status prepare_decode(icarus_ctx *ctx, const void *kv_pool, const int32_t
         pr->fp.inv = dmeta + used + R;
         used += (size_t)2 * R;
         pr->fp.tile = gemm_row_tile(off.data(), n_groups);
+        if (std::max({ctx->cfg.d_model, ctx->cfg.n_q_heads * ctx->cfg.head_dim, ctx->cfg.d_ffn}) > kQuadMaxK) pr->fp.tile = std::min<int>(pr->fp.tile, TILE_192x128);
         const int bm = gemm_tile_rows(pr->fp.tile);
         int32_t *rt = m + used;
         for (int g = 0; g < n_groups; ++g)
@@ -1510,8 +1511,8 @@ icarus_status icarus_gemm(const icarus_gemm_args *a, void *stream) {
     g.epi = a->resid ? EPI_BF16_RESID : EPI_F32;
     g.resid = (const bf16_raw *)a->resid; g.ldr = g.ldy = (int)n_total; g.Y = a->y; g.splits = 1;
     for (int kind = TILE_AUTO + 1; kind < TILE_KINDS; ++kind)
-        if (gemm_tile_rows(kind) == a->tile_rows && gemm_tile_cols(kind) == a->tile_cols && gemm_tile_staged(kind) == (a->staged != 0)) g.tile = kind;
-    if (g.tile == TILE_AUTO || (a->staged && !gemm_decode_supported(g))) return ICARUS_ERR_UNSUPPORTED;
+        if (gemm_tile_rows(kind) == a->tile_rows && gemm_tile_cols(kind) == a->tile_cols && gemm_tile_marked(kind) == (a->staged != 0)) g.tile = kind;
+    if (g.tile == TILE_AUTO) return ICARUS_ERR_UNSUPPORTED;
     hipStream_t st = (hipStream_t)stream;
     if (a->slices == 1) return launch_gemm_mfma(g, st) == hipSuccess ? ICARUS_OK : ICARUS_ERR_HIP;
     GemmArgs p = g;
@@ -1539,7 +1540,7 @@ icarus_status icarus_gemm_choice(int32_t rows, int32_t k, const int32_t *n_seg, 
     const GemmPlan p = gemm_plan(g, fused ? 1 : max_slices, taken != 0);
     choice[0] = gemm_tile_rows(p.tile);
     choice[1] = gemm_tile_cols(p.tile);
-    choice[2] = gemm_tile_staged(p.tile);
+    choice[2] = gemm_tile_marked(p.tile);
     choice[3] = p.splits;
     return ICARUS_OK;
 }

@@ -115,7 +115,7 @@ struct AttnPlan {
 // ICaRusLinear GEMM on matrix cores.  Y = X W^T (+ T Bcat^T), see gemm_mfma.hip.
 enum { GEMM_PLAIN = 0, GEMM_DUAL = 1 };          // DUAL: W[0] = gate, W[1] = up, Y = silu(gate) * up
 enum { EPI_F32 = 0, EPI_BF16_RESID = 1 };        // plain epilogues (DUAL always stores bf16)
-enum TileKind { TILE_AUTO = 0, TILE_64x128, TILE_128, TILE_192x128, TILE_256x256, TILE_REG_192x256, TILE_REG_160x256, TILE_KINDS };
+enum TileKind { TILE_AUTO = 0, TILE_64x128, TILE_128, TILE_192x128, TILE_256x256, TILE_192x256, TILE_160x256, TILE_KINDS };
 struct GemmArgs {
     const bf16_raw *X; int ldx; int R; int K;    // activations [R, K] (row stride ldx)
     const bf16_raw *W[3]; int n_seg[3]; int nseg; // weight segments stacked along N, each [n_seg, K]
@@ -131,7 +131,6 @@ struct GemmArgs {
     int tiles_seg[3]; int m_tiles, n_tiles, K_ext, k_per_split;
     int panel_m, panel_n, panels_m, n_panels;       // tile order: panels of panel_m x panel_n tiles (n_panels per K slice)
     uint32_t inv_panels, inv_panels_m, inv_panel_m; // gemm_inv of n_panels, panels_m, panel_m
-    int slabs_per_split;                            // decode kernel: 64-wide K slabs per split-K slice
     // Grouped launch (optional): row_tiles, device [n_row_tiles][3] = first row, end row, group of each row tile (gemm_tile_rows
     // rows at most).  Group 0 multiplies W[0] (DUAL: W[0], W[1]), group j > 0 Wg[.] + (j - 1) * wg_stride elements.
     const int32_t *row_tiles; int n_row_tiles;
@@ -174,12 +173,11 @@ GemmPlan gemm_plan(const GemmArgs &g, int max_splits, bool takes_slices);
 int gemm_row_tile(const int *off, int n_groups);
 int gemm_tile_rows(int tile);
 int gemm_tile_cols(int tile);
-bool gemm_tile_staged(int tile);  // through registers (gemm_decode.hip)
 int gemm_grouped_splits(const GemmArgs &g, int max_splits, bool takes_slices);
-// Tiles of gemm_decode.hip (TILE_REG_*): both operands loaded coalesced, parked in registers two slabs ahead and staged
-// through LDS by register stores; launch_gemm_mfma takes this path for them.
-bool gemm_decode_supported(const GemmArgs &g);
-hipError_t launch_gemm_decode(GemmArgs g, hipStream_t st);
+bool gemm_tile_marked(int tile);  // the mark of 192 and 160 rows by 256 in icarus_gemm_choice and icarus_gemm
+// Tiles of gemm_quad.hip (256, 192 or 160 rows by 256); launch_gemm_mfma takes this path for them.  g.K_ext and g.k_per_split are set.
+constexpr int kQuadMaxK = 1 << 23;  // a row's offset within its tile is kept in 32 bits of bytes
+hipError_t launch_gemm_quad(const GemmArgs &g, hipStream_t st);
 // Sum split-K partials P[splits][R][N] (fp32) and apply the epilogue `epi` into Y.
 hipError_t launch_splitk_reduce(const float *P, int splits, int R, int N, int epi, void *Y, int ldy, const void *resid,
                                 int ldr, hipStream_t st);
