@@ -713,215 +713,267 @@ __global__ void __launch_bounds__(256) k_attn_decode(const bf16_t *__restrict__ 
   }
 }
 
-// compute_group for a group that sits in LDS as fragments (src[i * 64]: K fragments i = 0..7, then
-// V^T fragments) with the wave's Q fragments in registers (qr[qt][ks]).  A wave issues in order and a
-// fragment read takes a few hundred cycles to come back, so the reads are batched ahead of the MFMAs
-// that need them instead of sitting between them: the eight K fragments at the top, the eight V^T
-// fragments as soon as the S^T MFMAs are issued (into the registers the K fragments leave), so that
-// they travel while the softmax arithmetic runs and the P V MFMAs follow each other without a wait.
-template <int NT, bool tail>
-__device__ __forceinline__ void compute_group_lds(State<NT> &st, const bf16x8 *__restrict__ src, const bf16x8 (&qr)[NT][kKS],
-                                                  int left, const int (&stag)[NT], float scale_log2, int lane) {
-    const int q = lane >> 4;
-    const int tbase = 16 * (q >> 1) + 8 * (q & 1);
-    float sv[NT][8];
-    __builtin_amdgcn_s_setprio(1);  // matrix-core sections run at raised priority, see prefill_walk
-    {
-        f32x4 s0[NT], s1[NT];
+constexpr int kPrefillWaves = 4, kPrefillNT = 4;  // 4 waves x 4 tiles x 16 = 256 stacked queries per workgroup
+constexpr int kRoundGroups = 4;                   // 32-token groups of a round of the prefill walk
+
+template <int V> struct Int { static constexpr int value = V; };
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
+}
+
+// The walk of one prefill wave over a piece, its four query tiles as two pairs.
+//
+// q comes multiplied by the softmax scale and log2 e (launch_rope_append), so a score is an exponent of 2 as it leaves the
+// matrix cores, and the accumulators of a group's scores start from minus the softmax reference instead of from zero: the
+// exponent needs no arithmetic.  The reference is lazy (see compute_group): it moves only when a score exceeds it by more than
+// kSlack; the scores are then formed again from zero (relative to a reference far from them they would have lost bits).
+//
+// A wave is alone on its SIMD and issues in order, so it has to put its own vector instructions beneath its own MFMAs: an
+// MFMA takes the pipe 16 cycles and the issue slot 4.  Group g is four steps of 16 MFMAs, each with independent work of
+// the other pair between them, in the order they are written here (a scheduling barrier behind every MFMA):
+//     1  S^T of pair 0                  exponentials of pair 1 of group g - 1
+//     2  P V of pair 1 of group g - 1   V^T fragments of g into the registers this leaves; the check of pair 0's scores; one
+//                                       quarter of a group of the next round is published and requested for the round after it
+//     3  S^T of pair 1                  exponentials of pair 0
+//     4  P V of pair 0                  the check of pair 1's scores; then K fragments of g + 1
+// Eight waves of two tiles, the phases of a wave one after the other, hid little of each other (matrix pipe busy 47 % of the
+// cycles) and read each fragment from LDS for two tiles instead of four: 32 chunks of 512 rows over 8192 tokens 2.38 ms, now
+// 1.91 ms = 1.19 PFLOP/s (busy 56-58 % at 1.97 GHz).  How many vector instructions stand beside an MFMA is what it hangs on:
+// measured in a loop, one is free (8.8 ns), a second costs 1.3-1.7 ns, a second exponential 4 ns, and a two-way dot product 6.5 ns
+// each (it shares the pipe), hence one exponential behind each MFMA of steps 1 and 3 and the denominators on the matrix cores.
+//
+// The ring has two stages of one round (four groups) each; the four waves bring a quarter of each group (K rows or V^T rows),
+// through registers, requested a whole round before it is published, and read every group as MFMA fragments in lane
+// order.  A stage is published while the other one is read, and its last reads precede the one barrier of a round, which
+// sits before the first reads of the next round.  Past the end of the piece the loads repeat its last block.
+// ring: [2][4][16][64] x 16 B.
+struct PrefillWalk {
+    State<kPrefillNT> &st;
+    bf16x8 (&qr)[kPrefillNT][kKS];
+    const int (&stag)[kPrefillNT];
+    const int lane;
+    f32x4 neg[kPrefillNT];    // minus the reference (State::m) in all four elements; 0 while there is none
+    int limit[2];             // per pair: bits of the largest relative score that leaves the reference alone; INT_MIN: a query has none
+    f32x4 sc[kPrefillNT][2];  // scores of the two 16-token halves of a group
+    bf16x8 pb[kPrefillNT];    // probabilities
+    f32x4 den[kPrefillNT];    // denominators, four times the same sum
+    bf16x8 ones;
+    bf16x8 kf[2 * kKS], vf[kDT];
+    int top;                  // of a check: the largest bits so far
+
+    __device__ __forceinline__ PrefillWalk(State<kPrefillNT> &s, bf16x8 (&q)[kPrefillNT][kKS], const int (&g)[kPrefillNT], int l)
+        : st(s), qr(q), stag(g), lane(l) {
 #pragma unroll
-        for (int qt = 0; qt < NT; ++qt) { s0[qt] = f32x4{0.f, 0.f, 0.f, 0.f}; s1[qt] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-        bf16x8 kf[2 * kKS];
-#pragma unroll
-        for (int i = 0; i < 2 * kKS; ++i) kf[i] = src[i * 64];
-        __builtin_amdgcn_sched_barrier(0);  // all reads first
-#pragma unroll
-        for (int ks = 0; ks < kKS; ++ks) {
-#pragma unroll
-            for (int qt = 0; qt < NT; ++qt) {
-                s0[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks], qr[qt][ks], s0[qt], 0, 0, 0);
-                s1[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kKS + ks], qr[qt][ks], s1[qt], 0, 0, 0);
-            }
+        for (int t = 0; t < kPrefillNT; ++t) {
+            neg[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            sc[t][0] = sc[t][1] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};  // a pair 1 of no group: probabilities of zero
+            den[t] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
-        for (int qt = 0; qt < NT; ++qt)
+        for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.f;
+        limit[0] = limit[1] = INT32_MIN;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {  // raw scores, see compute_group
-                sv[qt][i] = s0[qt][i];
-                sv[qt][4 + i] = s1[qt][i];
-            }
+        for (int dt = 0; dt < kDT; ++dt) vf[dt] = zero8();
     }
-    __builtin_amdgcn_s_setprio(0);
-    bf16x8 vf[kDT];
+    // MFMA m of 16 of the scores of pair P, relative to the reference.  In assembly: the compiler gives every MFMA of a kernel
+    // that may use the accumulation registers its result in them, and the scores would be copied out for the arithmetic.  What
+    // reads a result is at least four MFMAs (64 cycles) behind it.
+    template <int P>
+    __device__ __forceinline__ void score(int m) {
+        const int ks = m >> 2, t = 2 * P + ((m >> 1) & 1), hf = m & 1;
+        if (ks == 0) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" : "=&v"(sc[t][hf]) : "v"(kf[4 * hf]), "a"(qr[t][0]), "v"(neg[t]));
+        else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(sc[t][hf]) : "v"(kf[4 * hf + ks]), "a"(qr[t][ks]));
+    }
+    // MFMA m of 16 of P V of pair P
+    template <int P>
+    __device__ __forceinline__ void pv(int m) {
+        const int dt = m >> 1, t = 2 * P + (m & 1);
+        st.o[dt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], pb[t], st.o[dt][t], 0, 0, 0);
+    }
+    // the denominators of pair P: one more row of V, of ones (32 additions per group would cost the wave more than four MFMAs)
+    template <int P>
+    __device__ __forceinline__ void sum(int t) {
+        den[2 * P + t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[2 * P + t], den[2 * P + t], 0, 0, 0);
+    }
+    // exponential i of the 16 of pair P, beside the rounding of those before it (i = 16: the last two)
+    template <int P>
+    __device__ __forceinline__ void exp_one(int i) {
+        auto at = [&](int n) -> float { return sc[2 * P + (n >> 3)][(n >> 2) & 1][n & 3]; };
+        if (i < 16) sc[2 * P + (i >> 3)][(i >> 2) & 1][i & 3] = __builtin_amdgcn_exp2f(at(i));
+        if (i == 0) return;
+        const int t = 2 * P + ((i - 1) >> 3), e = (i - 1) & 7;
+        if (!(e & 1)) return;
+        uint32_t two = pack_bf16(at(i - 2), at(i - 1));
+        asm volatile("" : "+v"(two));  // here, not all of them ahead of the next step's MFMAs
+        u32x4 w = __builtin_bit_cast(u32x4, pb[t]);
+        w[e >> 1] = two;
+        pb[t] = __builtin_bit_cast(bf16x8, w);
+    }
+    // part i of 8 of pair P's check: as integers positive floats keep their order, and negative ones are below every limit
+    template <int P>
+    __device__ __forceinline__ void check_part(int i) {
+        const int t = 2 * P + (i >> 2), e = (i & 3) * 2;
+        const int a = __float_as_int(sc[t][e >> 2][e & 3]), b = __float_as_int(sc[t][e >> 2][(e & 3) + 1]);
+        top = i ? max(max(top, a), b) : max(a, b);
+    }
+    // The scores of pair P anew, relative to a reference that is moved up to their maximum.
+    // masked: `left` tokens of the sequence remain from this group's first on for its last row
+    template <int P, bool masked>
+    __device__ __forceinline__ void rescore(int left) {
+        const int q = lane >> 4, tbase = 16 * (q >> 1) + 8 * (q & 1);
 #pragma unroll
-    for (int dt = 0; dt < kDT; ++dt) vf[dt] = src[(2 * kKS + dt) * 64];
-    __builtin_amdgcn_sched_barrier(0);  // the reads stay ahead of the arithmetic
-    bf16x8 pb[NT];
-#pragma unroll
-    for (int qt = 0; qt < NT; ++qt) {
-        if (tail) {
-            const int lim = left - stag[qt];
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (tbase + e >= lim) sv[qt][e] = -INFINITY;
+        for (int m = 0; m < 16; ++m) {
+            const int ks = m >> 2, t = 2 * P + ((m >> 1) & 1), hf = m & 1;
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            sc[t][hf] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[4 * hf + ks], qr[t][ks], ks ? sc[t][hf] : zero, 0, 0, 0);
         }
-        float mx = sv[qt][0];
+        limit[P] = __float_as_int(kSlack);
 #pragma unroll
-        for (int e = 1; e < 8; ++e) mx = fmaxf(mx, sv[qt][e]);
-        mx *= scale_log2;
-        if (__any(mx > st.m[qt] + kSlack)) {  // see compute_group: lazy softmax reference
+        for (int t = 2 * P; t < 2 * P + 2; ++t) {
+            if (masked) {
+                const int lim = left - stag[t];
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (tbase + e >= lim) sc[t][e >> 2][e & 3] = -INFINITY;
+            }
+            float mx = sc[t][0][0];
+#pragma unroll
+            for (int e = 1; e < 8; ++e) mx = fmaxf(mx, sc[t][e >> 2][e & 3]);
             mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-            const float m_old = st.m[qt];
-            const float m_new = fmaxf(m_old, mx);
-            st.m[qt] = m_new;
-            float alpha = (tail && m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(m_old - m_new);
-            st.l[qt] *= alpha;
+            const float m_old = st.m[t], m_new = fmaxf(m_old, mx);
+            const bool none = m_new == -INFINITY;  // the query has had no valid token yet: nothing to rescale
+            const float alpha = none ? 1.f : __builtin_amdgcn_exp2f(m_old - m_new), ng = none ? 0.f : -m_new;
+            if (none) limit[P] = INT32_MIN;
+            st.m[t] = m_new;
+            den[t] *= alpha;
+            ICARUS_IN_ACC(den[t]);
 #pragma unroll
             for (int dt = 0; dt < kDT; ++dt) {
-                st.o[dt][qt][0] *= alpha; st.o[dt][qt][1] *= alpha; st.o[dt][qt][2] *= alpha; st.o[dt][qt][3] *= alpha;
+                st.o[dt][t][0] *= alpha; st.o[dt][t][1] *= alpha; st.o[dt][t][2] *= alpha; st.o[dt][t][3] *= alpha;
+                ICARUS_IN_ACC(st.o[dt][t]);
             }
-        }
-        const float m_ref = st.m[qt];
-        float rs = 0.f;
+            neg[t] = f32x4{ng, ng, ng, ng};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[qt][e], scale_log2, -m_ref));
-            if (tail && m_ref == -INFINITY) p = 0.f;
-            rs += p;
-            pb[qt][e] = (__bf16)p;
+            for (int e = 0; e < 8; ++e) sc[t][e >> 2][e & 3] += ng;
         }
-        st.l[qt] += rs;
     }
-    __builtin_amdgcn_s_setprio(1);
+    // One group that every query attends to.  src: its fragments; next: those of the group after it, in the next round (LAST: read
+    // after before_next()) or in this one.  between: runs beside steps 2 and 4, part i of 8.
+    template <bool LAST, typename Between, typename BeforeNext>
+    __device__ __forceinline__ void group(const bf16x8 *__restrict__ src, const bf16x8 *__restrict__ next, Between between, BeforeNext before_next) {
 #pragma unroll
-    for (int dt = 0; dt < kDT; ++dt) {
-        if (tail) {  // stale cache bytes past the end may hold anything: zero those V columns
+        for (int t = 0; t < kPrefillNT; ++t) {
+#pragma unroll
+            for (int dt = 0; dt < kDT; ++dt) ICARUS_IN_ACC(st.o[dt][t]);
+#pragma unroll
+            for (int ks = 0; ks < kKS; ++ks) ICARUS_IN_ACC(qr[t][ks]);
+            ICARUS_IN_ACC(den[t]);
+            asm volatile("" : "+v"(sc[t][0]), "+v"(sc[t][1]), "+v"(neg[t]));
+        }
+#pragma unroll
+        for (int m = 0; m < 16; ++m) {
+            score<0>(m);
+            exp_one<1>(m);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        exp_one<1>(16);
+#pragma unroll
+        for (int m = 0; m < 16; ++m) {
+            pv<1>(m);
+            if (m & 1) vf[m >> 1] = src[(2 * kKS + (m >> 1)) * 64];
+            if (m >= 4 && m < 12) check_part<0>(m - 4);
+            if (m & 2) between(2 * (m >> 3) + (m >> 2) % 2, m & 1);
+            if (m >= 14) sum<1>(m - 14);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (__builtin_expect(__any(top > limit[0]), 0)) rescore<0, false>(0);
+#pragma unroll
+        for (int m = 0; m < 16; ++m) {
+            score<1>(m);
+            exp_one<0>(m);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        exp_one<0>(16);
+        auto read_next = [&](int i) { kf[k_order(i)] = next[k_order(i) * 64]; };
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            pv<0>(m);
+            if (m >= 4) { check_part<1>(2 * (m - 4)); check_part<1>(2 * (m - 4) + 1); }
+            if (!LAST) read_next(m);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (__builtin_expect(__any(top > limit[1]), 0)) {
+            if (!LAST) {
+                int at = 0;
+                asm volatile("" : "+v"(at));
+                read_k(src + at);
+            }
+            rescore<1, false>(0);
+            if (!LAST) read_k(next);
+        }
+        if (LAST) before_next();
+#pragma unroll
+        for (int m = 8; m < 16; ++m) {
+            pv<0>(m);
+            if (LAST) read_next(m - 8);
+            between(4 + (m - 8) / 2, m & 1);
+            if (m >= 14) sum<0>(m - 14);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __device__ __forceinline__ void read_k(const bf16x8 *__restrict__ src) {
+#pragma unroll
+        for (int i = 0; i < 2 * kKS; ++i) kf[k_order(i)] = src[k_order(i) * 64];
+    }
+    // K fragment i in the order in which step 1 needs them
+    static constexpr int k_order(int i) { return i & 1 ? kKS + (i >> 1) : i >> 1; }
+    template <int P>
+    __device__ __forceinline__ void finish_pair() {
+#pragma unroll
+        for (int i = 0; i <= 16; ++i) exp_one<P>(i);
+#pragma unroll
+        for (int m = 0; m < 16; ++m) pv<P>(m);
+        sum<P>(0);
+        sum<P>(1);
+    }
+    // One of the last groups, with masks (no pair 1 is pending).
+    __device__ __forceinline__ void masked_group(const bf16x8 *__restrict__ src, int left) {
+        const int q = lane >> 4, tbase = 16 * (q >> 1) + 8 * (q & 1);
+        read_k(src);
+#pragma unroll
+        for (int dt = 0; dt < kDT; ++dt) {
+            vf[dt] = src[(2 * kKS + dt) * 64];
+            // stale cache bytes past the end may hold anything: zero those V columns
 #pragma unroll
             for (int e = 0; e < 8; ++e)
                 if (tbase + e >= left) vf[dt][e] = (__bf16)0.f;
         }
-#pragma unroll
-        for (int qt = 0; qt < NT; ++qt) st.o[dt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], pb[qt], st.o[dt][qt], 0, 0, 0);
+        rescore<0, true>(left);
+        finish_pair<0>();
+        rescore<1, true>(left);
+        finish_pair<1>();
     }
-    __builtin_amdgcn_s_setprio(0);
-}
-
-// Half of a group's loads: part 0 = the 8 K fragments, part 1 = the 8 V^T fragments, in the order
-// they take in a KVFrag (k[t][ks] as 4t + ks, then v[dt]).
-__device__ __forceinline__ void load_half(bf16x8 (&h)[8], int part, const bf16_t *__restrict__ pool, int blk0, int blk1, int c,
-                                          int Hkv, int lane) {
-    const int m = lane & 15, q = lane >> 4;
-    const size_t head_stride = (size_t)2 * kBk * kD;
-    if (part == 0) {
-        const bf16_t *kb = pool + ((size_t)((m >> 3) ? blk1 : blk0) * Hkv + c) * head_stride;
-        const int tok0 = 8 * ((m >> 2) & 1) + (m & 3);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int ks = 0; ks < kKS; ++ks) h[t * kKS + ks] = *(const bf16x8 *)(kb + (size_t)(tok0 + 4 * t) * kD + 32 * ks + 8 * q);
-    } else {
-        const bf16_t *vb = pool + ((size_t)((q >> 1) ? blk1 : blk0) * Hkv + c) * head_stride + (size_t)kBk * kD;
-#pragma unroll
-        for (int dt = 0; dt < kDT; ++dt) h[dt] = *(const bf16x8 *)(vb + (size_t)(16 * dt + m) * kBk + 8 * (q & 1));
-    }
-}
-static_assert(2 * kKS == 8 && kDT == 8, "a half group is 8 fragments");
-
-// The same half group from an FP8 cache: raw codes, r[i] = the 8 codes that become fragment i
-// (K: i = 4 t + k-step, in the k-step order of KVRaw8; V^T: i = d tile).
-__device__ __forceinline__ void load_half8(uint2 (&r)[8], int part, const uint8_t *__restrict__ pool, int blk0, int blk1, int c,
-                                           int Hkv, int lane) {
-    const int m = lane & 15, q = lane >> 4;
-    const size_t head_stride = (size_t)2 * kBk * kD;
-    if (part == 0) {
-        const uint8_t *kb = pool + ((size_t)((m >> 3) ? blk1 : blk0) * Hkv + c) * head_stride;
-        const int tok0 = 8 * ((m >> 2) & 1) + (m & 3);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int sl = 0; sl < 2; ++sl) {
-                const uint4 v = *(const uint4 *)(kb + (size_t)(tok0 + 4 * t) * kD + 64 * sl + 16 * q);
-                r[4 * t + 2 * sl] = uint2{v.x, v.y};
-                r[4 * t + 2 * sl + 1] = uint2{v.z, v.w};
-            }
-    } else {
-        const uint8_t *vb = pool + ((size_t)((q >> 1) ? blk1 : blk0) * Hkv + c) * head_stride + (size_t)kBk * kD;
-#pragma unroll
-        for (int dt = 0; dt < kDT; ++dt) r[dt] = *(const uint2 *)(vb + (size_t)(16 * dt + m) * kBk + 8 * (q & 1));
-    }
-}
-
-// Prefill walk: the eight waves hold different query tiles and every wave needs every group, so a
-// group is loaded once -- in round r wave w loads half (w & 1: K or V^T) of group 4r + w/2 into
-// registers, one round ahead -- published to an LDS ring as MFMA fragments in lane order, and read
-// from there by all eight.  The ring has two stages of one round each: a wave publishes round r into
-// stage r % 2, whose last readers (round r - 2) all passed the barrier of round r - 1, so one barrier
-// per round is enough and the waves may drift up to a round apart (the matrix-core work of one then
-// overlaps the softmax arithmetic of the other on the same SIMD).  ring: [2][4][16][64] x 16 B.
-template <int NT, bool KV8 = false>
-__device__ __forceinline__ void prefill_walk(State<NT> &st, const void *__restrict__ pool_v, const int *__restrict__ blds,
-                                             int n_blk, int n_tok, int left, int n_clean, const int (&stag)[NT], bool busy, int w, int c,
-                                             int Hkv, bf16x8 *__restrict__ ring, const bf16x8 (&qr)[NT][kKS], float scale_log2,
-                                             int lane) {
-    // left: tokens of the sequence from this piece's first on (n_tok or more); busy: this wave holds queries
-    const int n_grp = (n_tok + kGrp - 1) / kGrp;  // groups, the masked ones included
-    const int n_round = (n_grp + 3) / 4;          // the same for every wave
-    const int part = w & 1, gl = w >> 1;
-    auto blk_of = [&](int grp, int which) {
-        return __builtin_amdgcn_readfirstlane(blds[min(grp * 2 + which, n_blk - 1)]);
-    };
-    bf16x8 h[8];
-    uint2 h8[8];
-    auto load = [&](int grp) {
-        if constexpr (KV8) load_half8(h8, part, (const uint8_t *)pool_v, blk_of(grp, 0), blk_of(grp, 1), c, Hkv, lane);
-        else load_half(h, part, (const bf16_t *)pool_v, blk_of(grp, 0), blk_of(grp, 1), c, Hkv, lane);
-    };
-    if (gl < n_grp) load(gl);
-#pragma nounroll
-    for (int r = 0; r < n_round; ++r) {
-        bf16x8 *stage = ring + (size_t)(r & 1) * 4 * 16 * 64;
-        const int mine = 4 * r + gl;
-        if (mine < n_grp) {
-            bf16x8 *dst = stage + ((size_t)gl * 16 + part * 8) * 64 + lane;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                if constexpr (KV8) dst[i * 64] = cvt8(h8[i].x, h8[i].y);  // codes are exact in bf16
-                else dst[i * 64] = h[i];
-            }
-        }
-        if (mine + 4 < n_grp) load(mine + 4);
-        __syncthreads();
-        if (!busy) continue;  // a wave of a partly filled group only helps to load
-        // the round's unmasked groups, then its masked ones: two loops of one code path each (with both paths
-        // in one loop body the accumulators are copied between the registers the two paths leave them in)
-        const int n_here = min(4, n_grp - 4 * r), n_plain = max(0, min(n_here, n_clean - 4 * r));
-#pragma nounroll
-        for (int gi = 0; gi < n_plain; ++gi)
-            compute_group_lds<NT, false>(st, stage + (size_t)gi * 16 * 64 + lane, qr, kGrp, stag, scale_log2, lane);
-#pragma nounroll
-        for (int gi = n_plain; gi < n_here; ++gi)
-            compute_group_lds<NT, true>(st, stage + (size_t)gi * 16 * 64 + lane, qr, left - (4 * r + gi) * kGrp, stag, scale_log2, lane);
-    }
-}
-
-constexpr int kPrefillWaves = 8, kPrefillNT = 2;  // 8 waves x 2 tiles x 16 = 256 stacked queries per workgroup
+};
 
 // Causal attention of a prefill chunk.  A workgroup owns one kv-head of one group of T consecutive
 // chunk tokens (T * g <= 256 stacked queries; token t attends to kv_len - (T-1-t) positions) and
 // walks the sequence's cache, or one piece of it, once for all of them; wave w holds query tiles
-// [w NT, (w+1) NT).  Bound by MFMA and softmax issue, so what counts is that every CU has a walk: with
+// [4 w, 4 w + 4).  Bound by the matrix cores, so what counts is that every CU has a walk: with
 // whole walks only, 14 groups x 8 kv-heads of a round of agent turns (60-400 rows over 600-8192 cached
 // tokens each) took 240 us on 112 CUs, cut into pieces 109 us + 12.5 us for
 // the merge; 512 rows over 32000 tokens (16 groups) 990 us -> 574 + 12.5 us.
-template <int NT, bool KV8 = false>
-__global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_t *__restrict__ qg, const void *__restrict__ pool,
+template <bool KV8>
+__global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_t *__restrict__ qg, const void *__restrict__ pool_v,
                                                                      const int32_t *__restrict__ bt, int max_blocks, AttnPlan pl,
                                                                      bf16_t *__restrict__ out, float *__restrict__ part_o,
-                                                                     float *__restrict__ part_ml, int Hq, int Hkv, float scale_log2,
-                                                                     float v_scale) {
+                                                                     float *__restrict__ part_ml, int Hq, int Hkv, float v_scale) {
+    constexpr int NT = kPrefillNT;
     extern __shared__ float lds[];
     const int item = blockIdx.x / Hkv, c = blockIdx.x % Hkv;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int s = pl.item_seq[item];
     const bool parts = pl.item_begin != nullptr;  // else every piece is a whole walk
     const int begin = parts ? pl.item_begin[item] : 0, left = pl.seq_kvlen[s] - begin, n_tok = parts ? pl.item_len[item] : left;
@@ -931,45 +983,147 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
     const int32_t *btr = bt + (size_t)pl.seq_bt[s] * max_blocks + begin / kBk;
     // LDS: [KV ring, two stages of 64 KB] [block ids]; the wave's Q fragments (B operands) stay in registers
     bf16x8 *ring = (bf16x8 *)lds;
+    const uint32_t ring0 = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)lds;
+    int *blds = (int *)(ring + 2 * kRoundGroups * 16 * 64);
+    const int n_blk = (n_tok + kBk - 1) / kBk;
+    for (int i = threadIdx.x; i < n_blk; i += 64 * kPrefillWaves) blds[i] = btr[i];
     bf16x8 qr[NT][kKS];
+    State<NT> st;
+    int stag[NT];
 #pragma unroll
     for (int qt = 0; qt < NT; ++qt) {
-        int j = 16 * (w * NT + qt) + m;
+        const int j = 16 * (w * NT + qt) + m;
         const bf16_t *qp = qg + ((size_t)(row0 + j / g) * Hq + c * g + j % g) * kD;
 #pragma unroll
         for (int ks = 0; ks < kKS; ++ks) {  // FP8 cache: the k-step order of KVRaw8
             const int d0 = KV8 ? 64 * (ks >> 1) + 16 * q + 8 * (ks & 1) : 32 * ks + 8 * q;
             qr[qt][ks] = j < G ? *(const bf16x8 *)(qp + d0) : zero8();
         }
+        st.m[qt] = -INFINITY;
+        st.l[qt] = 0.f;
+#pragma unroll
+        for (int dt = 0; dt < kDT; ++dt) st.o[dt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        stag[qt] = T - 1 - min(j / g, T - 1);
     }
-    int *blds = (int *)(ring + 2 * 4 * 16 * 64);
-    const int n_blk = (n_tok + kBk - 1) / kBk;
-    for (int i = threadIdx.x; i < n_blk; i += 64 * kPrefillWaves) blds[i] = btr[i];
     // every load so far has landed: the walk's waits then count its own prefetch loads only (left to its own
     // bookkeeping the compiler waits for the Q fragments inside the loop, and with them for the prefetch)
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
     __syncthreads();
 
-    State<NT> st;
-    int stag[NT];
+    // This wave's quarter of every group: w = 0, 1 the K rows of tile w, w = 2, 3 the V^T rows of four d tiles; four fragments.
+    const bool kside = w < 2;
+    const int sel = kside ? m >> 3 : q >> 1;  // which of the group's two blocks this lane reads
+    const int at = kside ? (8 * ((m >> 2) & 1) + (m & 3) + 4 * w) * kD + (KV8 ? 16 : 8) * q : kBk * kD + (64 * (w - 2) + m) * kBk + 8 * (q & 1);
+    constexpr size_t head_stride = (size_t)2 * kBk * kD;
+    auto id_of = [&](int grp) { return blds[min(2 * grp + sel, n_blk - 1)]; };
+    // The bf16 cache's fragments go straight to LDS: those of round r + 1 are requested in the first two groups of round r.
+    // FP8 codes pass through registers, requested a round earlier, and are published as bf16 (the codes are exact in it).
+    uint4 codes[kRoundGroups][2];  // of four fragments
+    int ids[kRoundGroups];
+    auto request = [&](auto GI, int i, int stage) {  // part i of 4
+        constexpr int gi = decltype(GI)::value;
+        const size_t off = ((size_t)ids[gi] * Hkv + c) * head_stride + at;
+        if constexpr (KV8) {
+            if (i) return;
+            const uint8_t *p = (const uint8_t *)pool_v + off;
+            if (kside) {
+                codes[gi][0] = *(const uint4 *)p;
+                codes[gi][1] = *(const uint4 *)(p + 64);
+            } else {
+#pragma unroll
+                for (int f = 0; f < 2; ++f) {
+                    const uint2 a = *(const uint2 *)(p + (2 * f) * 16 * kBk), b = *(const uint2 *)(p + (2 * f + 1) * 16 * kBk);
+                    codes[gi][f] = uint4{a.x, a.y, b.x, b.y};
+                }
+            }
+        } else {
+            dma16((const bf16_t *)pool_v + off + i * (kside ? 32 : 16 * kBk),
+                  ring0 + (uint32_t)((stage * kRoundGroups + gi) * 16 + 4 * w + i) * 1024);
+        }
+    };
+    auto publish = [&](auto GI, int i, int stage) {
+        constexpr int gi = decltype(GI)::value;
+        const uint4 v = codes[gi][i >> 1];
+        ring[((size_t)(stage * kRoundGroups + gi) * 16 + 4 * w + i) * 64 + lane] = i & 1 ? cvt8(v.z, v.w) : cvt8(v.x, v.y);
+    };
+    constexpr Int<0> I0; constexpr Int<1> I1; constexpr Int<2> I2; constexpr Int<3> I3;
+    auto each = [&](auto &&f) { f(I0); f(I1); f(I2); f(I3); };
+    auto read_ids = [&](int r) {
+#pragma unroll
+        for (int gi = 0; gi < kRoundGroups; ++gi) ids[gi] = id_of(kRoundGroups * r + gi);
+    };
+    auto meet = [&] {  // what this wave brought has landed in LDS, and so has what the others brought
+        if constexpr (!KV8) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+        __syncthreads();
+    };
+
+    const int n_grp = (n_tok + kGrp - 1) / kGrp;                          // groups, the masked ones included
+    const int n_round = (n_grp + kRoundGroups - 1) / kRoundGroups;        // the same for every wave
+    const int n_clean = min(n_grp, max(0, left - (T - 1)) / kGrp);         // groups valid for every query (further ones may be in later pieces)
+    const bool busy = 16 * w * NT < G;                                    // a wave without queries only helps to load
+    PrefillWalk walk(st, qr, stag, lane);
+    read_ids(0);
+    each([&](auto GI) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) request(GI, i, 0);
+    });
+    read_ids(1);
+    if constexpr (KV8) {
+        each([&](auto GI) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) publish(GI, i, 0);
+            request(GI, 0, 0);
+        });
+        read_ids(2);
+    }
+    meet();
+    if (busy && n_clean > 0) walk.read_k(ring + lane);
+#pragma nounroll
+    for (int r = 0; r < n_round; ++r) {
+        const int here = r & 1;
+        const bf16x8 *stage = ring + (size_t)here * kRoundGroups * 16 * 64 + lane;
+        const bf16x8 *other = ring + (size_t)(here ^ 1) * kRoundGroups * 16 * 64 + lane;
+        const int n_here = min(kRoundGroups, n_grp - kRoundGroups * r), n_plain = busy ? max(0, min(n_here, n_clean - kRoundGroups * r)) : 0;
+        bool met = false;  // the barrier of this round is behind us
+        each([&](auto GI) {
+            constexpr int gi = decltype(GI)::value;
+            auto between = [&](int i, int sub) {  // parts 0-3 beside step 2, 4-7 beside step 4
+                if (sub) return;
+                if constexpr (KV8) {
+                    if (i < 4) publish(GI, i, here ^ 1);
+                    else if (i == 4) request(GI, 0, 0);
+                    else if (i == 7) ids[gi] = id_of(kRoundGroups * (r + 3) + gi);
+                } else if constexpr (gi < 2) {
+                    if (i < 4) request(Int<2 * gi>(), i, here ^ 1);
+                    else request(Int<2 * gi + 1>(), i - 4, here ^ 1);
+                } else if (gi == 2 && i == 3) {
+                    read_ids(r + 2);
+                }
+            };
+            if (gi < n_plain) {
+                walk.template group<gi + 1 == kRoundGroups>(stage + gi * 16 * 64, gi + 1 < kRoundGroups ? stage + (gi + 1) * 16 * 64 : other, between, meet);
+                if (gi + 1 == kRoundGroups) met = true;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) between(i, 0);
+            }
+        });
+        if (busy) {
+            if (n_plain > 0 && kRoundGroups * r + n_plain == n_clean) walk.finish_pair<1>();  // no group follows that would
+#pragma nounroll
+            for (int gi = n_plain; gi < n_here; ++gi) walk.masked_group(stage + gi * 16 * 64, left - (kRoundGroups * r + gi) * kGrp);
+        }
+        if (!met) meet();
+    }
 #pragma unroll
     for (int qt = 0; qt < NT; ++qt) {
-        st.m[qt] = -INFINITY;
-        st.l[qt] = 0.f;
-#pragma unroll
-        for (int dt = 0; dt < kDT; ++dt) st.o[dt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        stag[qt] = T - 1 - min((16 * (w * NT + qt) + m) / g, T - 1);
-    }
-    const int n_clean = max(0, left - (T - 1)) / kGrp;  // groups valid for every query (further ones may be in later pieces)
-    const bool busy = __builtin_amdgcn_readfirstlane(16 * w * NT) < G;
-    prefill_walk<NT, KV8>(st, pool, blds, n_blk, n_tok, left, n_clean, stag, busy, w, c, Hkv, ring, qr, scale_log2, lane);
-    if constexpr (KV8) {
-#pragma unroll
-        for (int qt = 0; qt < NT; ++qt)
+        st.l[qt] = 0.25f * walk.den[qt][0];  // each of the four lanes that share a query has the whole sum
+        if constexpr (KV8) {
 #pragma unroll
             for (int dt = 0; dt < kDT; ++dt) {
                 st.o[dt][qt][0] *= v_scale; st.o[dt][qt][1] *= v_scale; st.o[dt][qt][2] *= v_scale; st.o[dt][qt][3] *= v_scale;
             }
+        }
     }
     finish<NT>(st, w * NT, NT, G, g, row0, c, Hq, Hkv, parts ? pl.item_direct[item] : 1, parts ? pl.item_part[item] : 0, pl.g_max, out, part_o,
                part_ml, lane);
@@ -1052,7 +1206,8 @@ bool attn_decode_mfma_supported(const Dims &dm, int g_max) {
 constexpr size_t kPrefillRing = (size_t)2 * 4 * 16 * 64 * 16, kLdsBytes = (size_t)160 << 10;
 constexpr int kPrefillMaxCtx = (int)((kLdsBytes - kPrefillRing) / 4) * kBk;
 int attn_prefill_max_ctx() { return kPrefillMaxCtx; }
-int attn_prefill_round() { return 4 * kGrp; }
+int attn_prefill_round() { return kRoundGroups * kGrp; }
+float attn_prefill_q_scale(const Dims &dm) { return kLog2e / sqrtf((float)dm.D) * (dm.kv8 ? dm.k_scale : 1.f); }
 
 int attn_prefill_group_queries() { return kPrefillWaves * kPrefillNT * 16; }  // stacked queries one prefill workgroup holds
 
@@ -1064,8 +1219,6 @@ hipError_t launch_attn_prefill_mfma(const Dims &dm, const void *q, const void *p
                                     const AttnPlan &pl, void *out, float *part_o, float *part_ml, hipStream_t st) {
     if (pl.n_items <= 0) return hipSuccess;
     if (!pl.causal || pl.chunk > kPrefillMaxCtx) return hipErrorInvalidValue;
-    constexpr int NT = kPrefillNT;
-    float scale_log2 = kLog2e / sqrtf((float)dm.D) * (dm.kv8 ? dm.k_scale : 1.f);
     const size_t shm = kPrefillRing + (size_t)((pl.chunk + kBk - 1) / kBk) * 4;  // two ring stages + the block ids
     auto launch = [&](auto kernel, bool &attr_set) -> hipError_t {
         if (!attr_set) {
@@ -1074,11 +1227,11 @@ hipError_t launch_attn_prefill_mfma(const Dims &dm, const void *q, const void *p
             attr_set = true;
         }
         hipLaunchKernelGGL(kernel, dim3(pl.n_items * dm.Hkv), dim3(64 * kPrefillWaves), shm, st, (const bf16_t *)q, pool, bt, max_blocks, pl,
-                           (bf16_t *)out, part_o, part_ml, dm.Hq, dm.Hkv, scale_log2, dm.kv8 ? dm.v_scale : 1.f);
+                           (bf16_t *)out, part_o, part_ml, dm.Hq, dm.Hkv, dm.kv8 ? dm.v_scale : 1.f);
         return hipGetLastError();
     };
     static bool set_bf16 = false, set_fp8 = false;
-    return dm.kv8 ? launch(k_attn_prefill<NT, true>, set_fp8) : launch(k_attn_prefill<NT, false>, set_bf16);
+    return dm.kv8 ? launch(k_attn_prefill<true>, set_fp8) : launch(k_attn_prefill<false>, set_bf16);
 }
 
 hipError_t launch_attn_decode_mfma(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
