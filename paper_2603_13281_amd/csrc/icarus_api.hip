@@ -749,10 +749,10 @@ icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const
     if (in_splits > 0) {
         PHASE(ctx, st, ICARUS_PH_NORM, launch_sum_norm_shrink(dm, (const float *)(ws + L.gemm_part), in_splits, (size_t)R * d, z,
                                                               const_cast<void *>(x_in), ctx->base.norm_attn, xn, R, d,
-                                                              lq ? Aw(ICARUS_PROJ_Q) : nullptr, nullptr, rm.row_model, T, st));
+                                                              lq ? Aw(ICARUS_PROJ_Q) : nullptr, nullptr, rm, T, st));
     } else {
         PHASE(ctx, st, ICARUS_PH_NORM, launch_norm_shrink(dm, x_in, ctx->base.norm_attn, xn, R, d, lq ? Aw(ICARUS_PROJ_Q) : nullptr,
-                                                          nullptr, rm.row_model, T, nullptr, 0, st));
+                                                          nullptr, rm, T, nullptr, 0, st));
     }
     int qkv_splits = 0, o_splits = 0;
     {   // Q (ICaRusLinear) and the encoder's K, V in one GEMM over [W_q; W_k; W_v]
@@ -793,9 +793,9 @@ icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const
         if (merge_left)
             PHASE(ctx, st, ICARUS_PH_ATTN_MERGE,
                   launch_merge_shrink(dm, (const float *)(ws + L.part_o), (const float *)(ws + L.part_ml), hp->pl, rm.row_seq, attn, R,
-                                      l_o ? Aw(ICARUS_PROJ_O) : nullptr, rm.row_model, T, st));
+                                      l_o ? Aw(ICARUS_PROJ_O) : nullptr, rm, T, st));
         else if (l_o)
-            PHASE(ctx, st, ICARUS_PH_LORA, launch_row_shrink(dm, attn, qd, R, qd, Aw(ICARUS_PROJ_O), rm.row_model, T, st));
+            PHASE(ctx, st, ICARUS_PH_LORA, launch_row_shrink(dm, attn, qd, R, qd, Aw(ICARUS_PROJ_O), rm, T, st));
         if (l_o) { g.T = T; g.ldt = mr; g.B[0] = Bw(ICARUS_PROJ_O); }
         g.Y = z; g.ldy = d; g.resid = (const bf16_raw *)x_in; g.ldr = d;
         LORA_TRY(run_gemm(ctx, ws, L, ICARUS_PH_GEMM_O, g, st, &o_splits));
@@ -807,10 +807,10 @@ icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const
     if (o_splits)
         PHASE(ctx, st, ICARUS_PH_NORM, launch_sum_norm_shrink(dm, (const float *)(ws + L.gemm_part), o_splits, (size_t)R * d, x_in, z,
                                                               ctx->base.norm_ffn, xn, R, d, lg ? Aw(ICARUS_PROJ_GATE) : nullptr,
-                                                              lg ? Aw(ICARUS_PROJ_UP) : nullptr, rm.row_model, T, st));
+                                                              lg ? Aw(ICARUS_PROJ_UP) : nullptr, rm, T, st));
     else
         PHASE(ctx, st, ICARUS_PH_NORM, launch_norm_shrink(dm, z, ctx->base.norm_ffn, xn, R, d, lg ? Aw(ICARUS_PROJ_GATE) : nullptr,
-                                                          lg ? Aw(ICARUS_PROJ_UP) : nullptr, rm.row_model, T, nullptr, 0, st));
+                                                          lg ? Aw(ICARUS_PROJ_UP) : nullptr, rm, T, nullptr, 0, st));
     {   // gate and up (ICaRusLinear x 2) with the SwiGLU product in the epilogue
         GemmArgs g{};
         g.X = xn; g.ldx = d; g.R = R; g.K = d;
@@ -826,7 +826,7 @@ icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const
         g.W[0] = W(ICARUS_PROJ_DOWN); g.n_seg[0] = d; g.nseg = 1;
         g.mode = GEMM_PLAIN; g.epi = EPI_BF16_RESID; g.splits = 1; g.r = c.lora_rank; g.M_models = c.n_models;
         if (lo(ICARUS_PROJ_DOWN)) {
-            PHASE(ctx, st, ICARUS_PH_LORA, launch_row_shrink(dm, h, F, R, F, Aw(ICARUS_PROJ_DOWN), rm.row_model, T, st));
+            PHASE(ctx, st, ICARUS_PH_LORA, launch_row_shrink(dm, h, F, R, F, Aw(ICARUS_PROJ_DOWN), rm, T, st));
             g.T = T; g.ldt = mr; g.B[0] = Bw(ICARUS_PROJ_DOWN);
         }
         g.Y = x_out; g.ldy = d; g.resid = z; g.ldr = d;
@@ -869,7 +869,7 @@ icarus_status run_layer_full(icarus_ctx *ctx, char *ws, const WsLayout &L, const
     };
     float *part = (float *)(ws + L.gemm_part);
     PHASE(ctx, st, ICARUS_PH_ELEMWISE, launch_gather_rows(x_in, fp.perm, xg, R, d * 2, st));
-    PHASE(ctx, st, ICARUS_PH_NORM, launch_norm_shrink(dm, xg, ctx->base.norm_attn, xn, R, d, nullptr, nullptr, nullptr, nullptr, nullptr, 0, st));
+    PHASE(ctx, st, ICARUS_PH_NORM, launch_norm_shrink(dm, xg, ctx->base.norm_attn, xn, R, d, nullptr, nullptr, rm, nullptr, nullptr, 0, st));
     int qkv_splits = 1;
     {   // Q of every group, then K and V of the encoder rows (the first ones), in the same number of slices
         GemmArgs g = args(ICARUS_PROJ_Q, xn, d, qd);
@@ -897,9 +897,9 @@ icarus_status run_layer_full(icarus_ctx *ctx, char *ws, const WsLayout &L, const
         PHASE(ctx, st, ICARUS_PH_GEMM_O, launch_gemm_mfma(g, st));
         if (g.splits > 1)
             PHASE(ctx, st, ICARUS_PH_NORM, launch_sum_norm_shrink(dm, part, g.splits, (size_t)R * d, xg, z, ctx->base.norm_ffn, xn, R, d, nullptr,
-                                                                  nullptr, nullptr, nullptr, st));
+                                                                  nullptr, rm, nullptr, st));
         else
-            PHASE(ctx, st, ICARUS_PH_NORM, launch_norm_shrink(dm, z, ctx->base.norm_ffn, xn, R, d, nullptr, nullptr, nullptr, nullptr, nullptr, 0, st));
+            PHASE(ctx, st, ICARUS_PH_NORM, launch_norm_shrink(dm, z, ctx->base.norm_ffn, xn, R, d, nullptr, nullptr, rm, nullptr, nullptr, 0, st));
     }
     {   // gate, up, SwiGLU
         GemmArgs g = args(ICARUS_PROJ_GATE, xn, d, F);
@@ -1112,9 +1112,14 @@ icarus_status prepare_decode(icarus_ctx *ctx, const void *kv_pool, const int32_t
         pr->fp.row_tiles = dmeta + used;
         used += 3 * (size_t)pr->fp.n_row_tiles;
     }
+    pr->rm = RowMeta{dmeta, dmeta + R, dmeta + 2 * R, dmeta + 3 * R};
+    if (!ctx->full_set && ctx->cfg.n_models > 0 && layer_mfma_supported(ctx)) {  // at most R + 16 entries, where the regrouping would be
+        pr->rm.n_order = row_order(row_model, R, m + used);
+        if (pr->rm.n_order) pr->rm.order = dmeta + used;
+        used += (size_t)pr->rm.n_order;
+    }
     rc = stage_commit(ctx, slot, ws + L.meta, used * 4, st);
     if (rc) return rc;
-    pr->rm = RowMeta{dmeta, dmeta + R, dmeta + 2 * R, dmeta + 3 * R};
     return ICARUS_OK;
 }
 
@@ -1293,9 +1298,9 @@ icarus_status run_stack(icarus_stack *st, char *ws, const StackLayout &SL, const
     if (layer_mfma_supported(c0) && gemm_mfma_supported(dm, dm.d)) {
         if (pending > 0)  // the last layer left its output in pieces (only when head_takes_slices)
             STACK_TRY(launch_sum_norm_shrink(dm, (const float *)(ws + pr.L.gemm_part), pending, (size_t)R * dm.d, ws + pr.L.z, xa, st->final_norm,
-                                             xn, n_head, dm.d, nullptr, nullptr, nullptr, nullptr, s));
+                                             xn, n_head, dm.d, nullptr, nullptr, pr.rm, nullptr, s));
         else
-            STACK_TRY(launch_norm_shrink(dm, xh, st->final_norm, xn, n_head, dm.d, nullptr, nullptr, nullptr, nullptr, nullptr, 0, s));
+            STACK_TRY(launch_norm_shrink(dm, xh, st->final_norm, xn, n_head, dm.d, nullptr, nullptr, pr.rm, nullptr, nullptr, 0, s));
         GemmArgs g{};
         g.X = (const bf16_raw *)xn; g.ldx = dm.d; g.R = n_head; g.K = dm.d;
         g.W[0] = (const bf16_raw *)st->lm_head; g.n_seg[0] = st->vocab; g.nseg = 1;

@@ -25,6 +25,8 @@ struct RowMeta {
     const int32_t *row_pos;    // [R] position of the row's token
     const int32_t *row_kvlen;  // [R] cache positions the row attends to (0..kvlen-1)
     float q_scale = 1.f;       // q is multiplied by this before it is rounded and stored (attn_prefill_q_scale)
+    const int32_t *order = nullptr;  // decode with adapters: rows for the workgroups of the row kernels, see row_order
+    int n_order = 0;
     const int32_t *rope_tiles = nullptr;  // prefill: the rows in tiles for launch_rope_append_tiles
     int n_rope_tiles = 0;
 };
@@ -186,24 +188,27 @@ hipError_t launch_splitk_reduce(const float *P, int splits, int R, int N, int ep
 // as extra K columns: T[row, t*M*r + j*r + i] = lora_scale * (A_t[j] x_row)_i for j = row_model[row], zero
 // in every other column (encoder rows: all zero).  A: [M][r][K].
 bool row_shrink_supported(int r, int targets);
+// Order of the rows over the workgroups of the kernels below: entry = row | (model + 1) << 16, -1: none; at most R + 16 entries,
+// a multiple of 8.  Returns how many; 0: few rows, in the order they have.
+int row_order(const int32_t *row_model, int R, int32_t *order);
 // y = rmsnorm(x) * wn for R rows of K, and (A0 != null) the shrink of y for one or two targets that
 // share y; also sets zero[0..n_zero) = 0.
 hipError_t launch_norm_shrink(const Dims &dm, const void *x, const void *wn, void *y, int R, int K, const void *A0, const void *A1,
-                              const int32_t *row_model, void *T, int *zero, int n_zero, hipStream_t st);
+                              const RowMeta &rm, void *T, int *zero, int n_zero, hipStream_t st);
 // the same on rows that are still in pieces: xsum = resid + sum of `splits` fp32 slices [R, K] (`slice` floats
 // apart, the split-K partials of the projection before the norm) is formed, rounded, stored, and normalised
 hipError_t launch_sum_norm_shrink(const Dims &dm, const float *part, int splits, size_t slice, const void *resid, void *xsum,
-                                  const void *wn, void *y, int R, int K, const void *A0, const void *A1, const int32_t *row_model,
+                                  const void *wn, void *y, int R, int K, const void *A0, const void *A1, const RowMeta &rm,
                                   void *T, hipStream_t st);
 // the shrink alone, of x [R, K] (row stride ldx)
-hipError_t launch_row_shrink(const Dims &dm, const void *x, int ldx, int R, int K, const void *A0, const int32_t *row_model, void *T,
+hipError_t launch_row_shrink(const Dims &dm, const void *x, int ldx, int R, int K, const void *A0, const RowMeta &rm, void *T,
                              hipStream_t st);
 
 bool attn_decode_mfma_supported(const Dims &dm, int g_max);
 // Merge of the attention partials of cut sequences (as launch_attn_merge) and, with A0, the shrink of the O projection
 // on the merged rows, in one kernel: attn [R][Hq*D] is completed in place, T as for launch_row_shrink.
 hipError_t launch_merge_shrink(const Dims &dm, const float *part_o, const float *part_ml, const struct AttnPlan &pl,
-                               const int32_t *row_pseq, void *attn, int R, const void *A0, const int32_t *row_model, void *T,
+                               const int32_t *row_pseq, void *attn, int R, const void *A0, const RowMeta &rm, void *T,
                                hipStream_t st);
 // Causal attention of prefill chunks: each plan sequence is a group of consecutive chunk tokens with at
 // most attn_prefill_group_queries() stacked queries (tokens x Hq/Hkv).  Whole walks write `out`, pieces of cut ones

@@ -11,13 +11,18 @@
 #include "kernels.h"
 
 #include <algorithm>
+#include <vector>
 
 namespace icarus {
 
 namespace {
 
 constexpr int kRowThreads = 512;  // threads per row: 8 waves share the K range of one row
-constexpr int kRowMaxWorkgroups = 512;  // a row's accumulators are split over more workgroups while the launch stays below this
+// A row's accumulators are split over more workgroups while the launch stays below this.  Where every part forms the row for itself
+// (norm, sums, merge) two rows per CU are the limit; the shrink alone only reads it.  Workgroups <= 512 -> 1024, us: 14336 columns, rank
+// 16: 316 rows 16.1 -> 12.8, 360 rows 18.7 -> 16.4; 25600 columns, rank 32, 144 rows 24.7 -> 19.4; with norm or sums 316 rows 10.6 -> 12.7,
+// 14.7 -> 19.0, merge 12.1 -> 14.1.
+constexpr int kRowMaxWorkgroups = 512, kRowMaxWorkgroupsPlain = 1024;
 
 __device__ __forceinline__ void unpack8(uint4 v, float (&f)[8]) {
     f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
@@ -78,7 +83,7 @@ struct RowArgs {
     bf16_t *x; int ldx; int K;                       // the rows [R][ldx], K used columns
     const bf16_t *wn; float eps; bf16_t *y;          // NORM: y = rmsnorm(x) * wn, [R][K]
     const bf16_t *A0, *A1; int r, M;                 // adapter A of the one or two targets reading this input, [M][r][K]
-    const int32_t *row_model; float scale; bf16_t *T; int ldt;  // T [R][ldt], ldt = targets * M * r
+    const int32_t *row_model, *order; float scale; bf16_t *T; int ldt;  // order: row and model of a workgroup (row_order) or null; T [R][ldt], ldt = targets * M * r
     int *zero; int n_zero;                           // small per-call counters cleared by row 0
     const float *psum; int splits; size_t slice; const bf16_t *resid;  // SRC_SLICES
     const float *part_o, *part_ml;                   // SRC_ATTN: partials [(piece, kv-head, query)][D] and [..][2]
@@ -95,7 +100,7 @@ constexpr int kHeadChunks = 16;  // 16-byte chunks per attention head (head_dim 
 // the compiler then knows how many younger loads are in flight when it waits for a group and leaves them in
 // flight; with a load under a run-time condition it waits for everything, the group requested ahead included).
 template <int SRC, bool NORM, int NACC, bool SHRINK>
-__device__ __forceinline__ void row_body(const RowArgs &a, int j, float *__restrict__ red,
+__device__ __forceinline__ void row_body(const RowArgs &a, int row, int j, float *__restrict__ red,
                                          float (*__restrict__ part)[NACC > 0 ? NACC : 1], float *__restrict__ res) {
     constexpr int NA = NACC > 0 ? NACC : 1;
     constexpr int GRP = (NA == 16 || NA == 32) ? 4 : (NA >= 8 ? 8 : NA);  // adapter rows per group of loads (two groups in flight)
@@ -104,7 +109,7 @@ __device__ __forceinline__ void row_body(const RowArgs &a, int j, float *__restr
     constexpr bool FIRST_PASS = NORM || SRC != SRC_PLAIN;
     constexpr bool WIDE = NA >= 32;
     constexpr bool shrink = SHRINK;
-    const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     // blockIdx.y: which NACC of the row's targets * r accumulators this workgroup computes.  Every part forms the
     // row with the same arithmetic in the same order and stores it (the same bytes from every part: a thread
     // reads back chunks it stored itself, never another workgroup's).
@@ -319,26 +324,34 @@ __device__ __forceinline__ void row_body(const RowArgs &a, int j, float *__restr
     }
 }
 
-template <int SRC, bool NORM, int NACC>
+// ORDERED: a workgroup's row comes from `order` (an instantiation of its own: a branch on the pointer cost the others 0.4-0.9 us)
+template <int SRC, bool NORM, int NACC, bool ORDERED>
 __global__ void __launch_bounds__(kRowThreads, NACC == 64 ? 2 : 4) k_row(RowArgs a) {  // four waves per SIMD = two rows per CU, where the registers allow
     constexpr int NA = NACC > 0 ? NACC : 1;
     __shared__ float red[16];
     __shared__ float part[kRowThreads / 64][NA];
     __shared__ float res[NA];
-    const int j = NACC > 0 ? a.row_model[blockIdx.x] : -1;  // uniform over the workgroup
-    if (NACC > 0 && j >= 0) row_body<SRC, NORM, NACC, true>(a, j, red, part, res);
-    else row_body<SRC, NORM, NACC, false>(a, j, red, part, res);
+    const int e = ORDERED ? a.order[blockIdx.x] : 0;
+    if (ORDERED && e < 0) return;
+    const int row = ORDERED ? e & 0xffff : (int)blockIdx.x;
+    const int j = ORDERED ? (e >> 16) - 1 : NACC > 0 ? a.row_model[blockIdx.x] : -1;  // uniform over the workgroup
+    if (NACC > 0 && j >= 0) row_body<SRC, NORM, NACC, true>(a, row, j, red, part, res);
+    else row_body<SRC, NORM, NACC, false>(a, row, j, red, part, res);
 }
 
 // nacc: the row's accumulators (targets * r).  With few rows they are split over several workgroups per row
 // (each computes 8 or more of them against its share of the adapter rows and forms the row for itself), so
 // that a handful of rows still spreads over the chip and a thread's chain of dependent load groups gets shorter.
 template <int SRC, bool NORM>
-hipError_t launch_row(int nacc, int R, hipStream_t st, const RowArgs &a) {
+hipError_t launch_row(int nacc, int R, const RowMeta &rm, hipStream_t st, const RowArgs &a) {
+    const bool ordered = nacc > 0 && rm.order;
     int parts = 1;
-    while (nacc / (2 * parts) >= 8 && R * 2 * parts <= kRowMaxWorkgroups) parts *= 2;
+    const int most = SRC == SRC_PLAIN && !NORM ? kRowMaxWorkgroupsPlain : kRowMaxWorkgroups;
+    while (nacc / (2 * parts) >= 8 && R * 2 * parts <= most) parts *= 2;
     nacc /= parts;
-#define ICARUS_ROW(N) hipLaunchKernelGGL((k_row<SRC, NORM, N>), dim3(R, parts), dim3(kRowThreads), 0, st, a)
+#define ICARUS_ROW(N)                                                                                                          \
+    if (ordered) hipLaunchKernelGGL((k_row<SRC, NORM, N, (N > 0)>), dim3(rm.n_order, parts), dim3(kRowThreads), 0, st, a);      \
+    else hipLaunchKernelGGL((k_row<SRC, NORM, N, false>), dim3(R, parts), dim3(kRowThreads), 0, st, a)
     switch (nacc) {
     case 0: ICARUS_ROW(0); break;
     case 8: ICARUS_ROW(8); break;
@@ -351,15 +364,44 @@ hipError_t launch_row(int nacc, int R, hipStream_t st, const RowArgs &a) {
     return hipGetLastError();
 }
 
-RowArgs shrink_args(const Dims &dm, const void *A0, const void *A1, const int32_t *row_model, void *T) {
+RowArgs shrink_args(const Dims &dm, const void *A0, const void *A1, const RowMeta &rm, void *T) {
     RowArgs a{};
     int targets = A0 ? (A1 ? 2 : 1) : 0;
-    a.A0 = (const bf16_t *)A0; a.A1 = (const bf16_t *)A1; a.r = dm.r; a.M = dm.M; a.row_model = row_model;
+    a.A0 = (const bf16_t *)A0; a.A1 = (const bf16_t *)A1; a.r = dm.r; a.M = dm.M; a.row_model = rm.row_model; a.order = rm.order;
     a.scale = dm.lora_scale; a.T = (bf16_t *)T; a.ldt = targets * dm.M * dm.r;
     return a;
 }
 
 }  // namespace
+
+// The workgroups of a launch go to the 8 XCDs in turn.  The rows that have an adapter are dealt to them in runs of the same
+// model, so that an XCD's L2 holds the adapters of one or two models instead of all of them (A of one projection is 0.1-0.5 MB a
+// model at rank 16, 1.6 MB for 25600 columns at rank 32, beside an L2 of 4 MB), and evenly, so that no CU has two of them while
+// another has none; rows without one, which cost less, follow.  316 rows of 8 models, 4096 and 14336 columns: 12.7 -> 10.6 us
+// (norm and Q), 13.9 -> 12.1 (merge and O), 18.0 -> 14.7 (sums, norm, gate and up), 18.0 -> 16.1 (down); 144 rows, 25600 columns 28.6 -> 24.7.
+// A row's own loads then wait for its entry: 64 rows 7.5 -> 7.7, 9.7 -> 10.1 us, hence from 97 rows on.
+constexpr int kRowOrderMin = 97;
+int row_order(const int32_t *row_model, int R, int32_t *order) {
+    if (R < kRowOrderMin) return 0;
+    std::vector<int32_t> rows[2];  // with an adapter, by model; without
+    for (int r = 0; r < R; ++r) rows[row_model[r] < 0].push_back(r);
+    std::stable_sort(rows[0].begin(), rows[0].end(), [&](int32_t a, int32_t b) { return row_model[a] < row_model[b]; });
+    int longest = 0;
+    for (int x = 0; x < 8; ++x) {
+        int n = 0;
+        for (int k = 0; k < 2; ++k) longest = std::max(longest, n += (int)((x + 1) * rows[k].size() / 8 - x * rows[k].size() / 8));
+    }
+    for (int x = 0; x < 8; ++x) {
+        int n = 0;
+        for (int k = 0; k < 2; ++k)
+            for (size_t i = x * rows[k].size() / 8; i < (x + 1) * rows[k].size() / 8; ++i) {
+                const int r = rows[k][i];
+                order[8 * n++ + x] = r | (row_model[r] + 1) << 16;
+            }
+        for (; n < longest; ++n) order[8 * n + x] = -1;
+    }
+    return 8 * longest;
+}
 
 bool row_shrink_supported(int r, int targets) {
     int n = r * targets;
@@ -367,41 +409,41 @@ bool row_shrink_supported(int r, int targets) {
 }
 
 hipError_t launch_norm_shrink(const Dims &dm, const void *x, const void *wn, void *y, int R, int K, const void *A0, const void *A1,
-                              const int32_t *row_model, void *T, int *zero, int n_zero, hipStream_t st) {
+                              const RowMeta &rm, void *T, int *zero, int n_zero, hipStream_t st) {
     if (R <= 0) return hipSuccess;
-    RowArgs a = shrink_args(dm, A0, A1, row_model, T);
+    RowArgs a = shrink_args(dm, A0, A1, rm, T);
     a.x = (bf16_t *)x; a.ldx = K; a.K = K; a.wn = (const bf16_t *)wn; a.eps = dm.eps; a.y = (bf16_t *)y;
     a.zero = zero; a.n_zero = n_zero;
-    return launch_row<SRC_PLAIN, true>(a.ldt / std::max(1, dm.M), R, st, a);
+    return launch_row<SRC_PLAIN, true>(a.ldt / std::max(1, dm.M), R, rm, st, a);
 }
 
 hipError_t launch_sum_norm_shrink(const Dims &dm, const float *part, int splits, size_t slice, const void *resid, void *xsum,
-                                  const void *wn, void *y, int R, int K, const void *A0, const void *A1, const int32_t *row_model,
+                                  const void *wn, void *y, int R, int K, const void *A0, const void *A1, const RowMeta &rm,
                                   void *T, hipStream_t st) {
     if (R <= 0) return hipSuccess;
-    RowArgs a = shrink_args(dm, A0, A1, row_model, T);
+    RowArgs a = shrink_args(dm, A0, A1, rm, T);
     a.x = (bf16_t *)xsum; a.ldx = K; a.K = K; a.wn = (const bf16_t *)wn; a.eps = dm.eps; a.y = (bf16_t *)y;
     a.psum = part; a.splits = splits; a.slice = slice; a.resid = (const bf16_t *)resid;
-    return launch_row<SRC_SLICES, true>(a.ldt / std::max(1, dm.M), R, st, a);
+    return launch_row<SRC_SLICES, true>(a.ldt / std::max(1, dm.M), R, rm, st, a);
 }
 
-hipError_t launch_row_shrink(const Dims &dm, const void *x, int ldx, int R, int K, const void *A0, const int32_t *row_model, void *T,
+hipError_t launch_row_shrink(const Dims &dm, const void *x, int ldx, int R, int K, const void *A0, const RowMeta &rm, void *T,
                              hipStream_t st) {
     if (R <= 0) return hipSuccess;
-    RowArgs a = shrink_args(dm, A0, nullptr, row_model, T);
+    RowArgs a = shrink_args(dm, A0, nullptr, rm, T);
     a.x = (bf16_t *)x; a.ldx = ldx; a.K = K;
-    return launch_row<SRC_PLAIN, false>(dm.r, R, st, a);
+    return launch_row<SRC_PLAIN, false>(dm.r, R, rm, st, a);
 }
 
 hipError_t launch_merge_shrink(const Dims &dm, const float *part_o, const float *part_ml, const AttnPlan &pl, const int32_t *row_pseq,
-                               void *attn, int R, const void *A0, const int32_t *row_model, void *T, hipStream_t st) {
+                               void *attn, int R, const void *A0, const RowMeta &rm, void *T, hipStream_t st) {
     if (R <= 0) return hipSuccess;
     if (dm.D != kHeadChunks * 8) return hipErrorInvalidValue;
-    RowArgs a = shrink_args(dm, A0, nullptr, row_model, T);
+    RowArgs a = shrink_args(dm, A0, nullptr, rm, T);
     a.x = (bf16_t *)attn; a.ldx = dm.Hq * dm.D; a.K = dm.Hq * dm.D;
     a.part_o = part_o; a.part_ml = part_ml; a.row_pseq = row_pseq; a.seq_nparts = pl.seq_nparts; a.seq_part0 = pl.seq_part0;
     a.seq_row0 = pl.seq_row0; a.Hq = dm.Hq; a.Hkv = dm.Hkv; a.g_max = pl.g_max;
-    return launch_row<SRC_ATTN, false>(A0 ? dm.r : 0, R, st, a);
+    return launch_row<SRC_ATTN, false>(A0 ? dm.r : 0, R, rm, st, a);
 }
 
 }  // namespace icarus
