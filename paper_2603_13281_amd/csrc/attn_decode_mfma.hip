@@ -550,8 +550,8 @@ __device__ __forceinline__ void finish(State<NT> &st, int qt0, int n, int G, int
 #pragma unroll
             for (int dt = 0; dt < kDT; ++dt) {
                 uint2 pk;
-                pk.x = (uint32_t)f32_to_bf16(st.o[dt][qt][0] * inv) | ((uint32_t)f32_to_bf16(st.o[dt][qt][1] * inv) << 16);
-                pk.y = (uint32_t)f32_to_bf16(st.o[dt][qt][2] * inv) | ((uint32_t)f32_to_bf16(st.o[dt][qt][3] * inv) << 16);
+                pk.x = pack_bf16(st.o[dt][qt][0] * inv, st.o[dt][qt][1] * inv);
+                pk.y = pack_bf16(st.o[dt][qt][2] * inv, st.o[dt][qt][3] * inv);
                 *(uint2 *)(op + 16 * dt + 4 * q) = pk;
             }
         } else {
@@ -718,10 +718,6 @@ constexpr int kRoundGroups = 4;                   // 32-token groups of a round 
 
 template <int V> struct Int { static constexpr int value = V; };
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
-}
 
 // The walk of one prefill wave over a piece, its four query tiles as two pairs.
 //
@@ -1171,8 +1167,8 @@ __global__ void __launch_bounds__(256) k_attn_merge(const float *__restrict__ pa
         }
     }
     uint2 pk;
-    pk.x = (uint32_t)f32_to_bf16(num[0] / den) | ((uint32_t)f32_to_bf16(num[1] / den) << 16);
-    pk.y = (uint32_t)f32_to_bf16(num[2] / den) | ((uint32_t)f32_to_bf16(num[3] / den) << 16);
+    pk.x = pack_bf16(num[0] / den, num[1] / den);
+    pk.y = pack_bf16(num[2] / den, num[3] / den);
     *(uint2 *)(out + ((size_t)row * Hq + h) * kD + d) = pk;
 }
 

@@ -261,10 +261,9 @@ __global__ void __launch_bounds__(256) k_splitk_reduce(const float *__restrict__
     } else {
         const bf16_t *rp = resid + (size_t)row * ldr + n;
         bf16_t *yp = (bf16_t *)Y + (size_t)row * ldy + n;
-        yp[0] = f32_to_bf16(v.x + bf16_to_f32(rp[0]));
-        yp[1] = f32_to_bf16(v.y + bf16_to_f32(rp[1]));
-        yp[2] = f32_to_bf16(v.z + bf16_to_f32(rp[2]));
-        yp[3] = f32_to_bf16(v.w + bf16_to_f32(rp[3]));
+        const uint2 r = *(const uint2 *)rp;  // rows and columns in fours: 8-byte aligned
+        *(uint2 *)yp = make_uint2(pack_bf16(v.x + __uint_as_float(r.x << 16), v.y + __uint_as_float(r.x & 0xffff0000u)),
+                                  pack_bf16(v.z + __uint_as_float(r.y << 16), v.w + __uint_as_float(r.y & 0xffff0000u)));
     }
 }
 

@@ -331,8 +331,8 @@ template <> struct KVElem4<bf16_t> {
     }
     static __device__ __forceinline__ void st(bf16_t *p, const float (&f)[4], float) {
         uint2 v;
-        v.x = (uint32_t)f32_to_bf16(f[0]) | ((uint32_t)f32_to_bf16(f[1]) << 16);
-        v.y = (uint32_t)f32_to_bf16(f[2]) | ((uint32_t)f32_to_bf16(f[3]) << 16);
+        v.x = pack_bf16(f[0], f[1]);
+        v.y = pack_bf16(f[2], f[3]);
         *(uint2 *)p = v;
     }
 };

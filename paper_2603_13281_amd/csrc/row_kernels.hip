@@ -31,10 +31,6 @@ __device__ __forceinline__ void unpack8(uint4 v, float (&f)[8]) {
     f[6] = __uint_as_float(v.w << 16); f[7] = __uint_as_float(v.w & 0xffff0000u);
 }
 
-__device__ __forceinline__ uint32_t pack2(float a, float b) {
-    return (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16);
-}
-
 // Rows with 32 or more accumulators (the gate and up adapters share their input) spend their time in arithmetic: 16
 // vector instructions per 8 products, and 6 exchanges per accumulator to sum it over the wave.  They take the two-way
 // bf16 dot product (fp32 sums; x and A as stored) and sum all accumulators together: 316 rows, 2 x 16 accumulators,
@@ -226,7 +222,7 @@ __device__ __forceinline__ void row_body(const RowArgs &a, int row, int j, float
             }
             if (formed) {
                 uint4 o;
-                o.x = pack2(f[0], f[1]); o.y = pack2(f[2], f[3]); o.z = pack2(f[4], f[5]); o.w = pack2(f[6], f[7]);
+                o.x = pack_bf16(f[0], f[1]); o.y = pack_bf16(f[2], f[3]); o.z = pack_bf16(f[4], f[5]); o.w = pack_bf16(f[6], f[7]);
                 *(uint4 *)(xr + c * 8) = o;
                 unpack8(o, f);
             } else {
@@ -272,14 +268,14 @@ __device__ __forceinline__ void row_body(const RowArgs &a, int row, int j, float
                         float wf[8];
                         unpack8(wb[b], wf);
                         uint4 o;
-                        o.x = pack2(f[0] * inv * wf[0], f[1] * inv * wf[1]);
-                        o.y = pack2(f[2] * inv * wf[2], f[3] * inv * wf[3]);
-                        o.z = pack2(f[4] * inv * wf[4], f[5] * inv * wf[5]);
-                        o.w = pack2(f[6] * inv * wf[6], f[7] * inv * wf[7]);
+                        o.x = pack_bf16(f[0] * inv * wf[0], f[1] * inv * wf[1]);
+                        o.y = pack_bf16(f[2] * inv * wf[2], f[3] * inv * wf[3]);
+                        o.z = pack_bf16(f[4] * inv * wf[4], f[5] * inv * wf[5]);
+                        o.w = pack_bf16(f[6] * inv * wf[6], f[7] * inv * wf[7]);
                         *(uint4 *)(a.y + (size_t)row * K + c * 8) = o;
                         unpack8(o, f);  // the shrink sees the row as stored
                     }
-                    if (WIDE) xv = make_uint4(pack2(f[0], f[1]), pack2(f[2], f[3]), pack2(f[4], f[5]), pack2(f[6], f[7]));
+                    if (WIDE) xv = make_uint4(pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]), pack_bf16(f[4], f[5]), pack_bf16(f[6], f[7]));
                 }
                 if (shrink && WIDE) {
 #pragma unroll
