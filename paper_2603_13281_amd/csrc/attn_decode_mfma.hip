@@ -764,12 +764,17 @@ struct PrefillWalk {
 #pragma unroll
         for (int t = 0; t < kPrefillNT; ++t) {
             neg[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-            sc[t][0] = sc[t][1] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};  // a pair 1 of no group: probabilities of zero
             den[t] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.f;
         limit[0] = limit[1] = INT32_MIN;
+        none_pending();
+    }
+    // a pair 1 of no group: probabilities of zero
+    __device__ __forceinline__ void none_pending() {
+#pragma unroll
+        for (int t = 2; t < kPrefillNT; ++t) sc[t][0] = sc[t][1] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
         for (int dt = 0; dt < kDT; ++dt) vf[dt] = zero8();
     }
@@ -815,25 +820,18 @@ struct PrefillWalk {
         top = i ? max(max(top, a), b) : max(a, b);
     }
     // The scores of pair P anew, relative to a reference that is moved up to their maximum.
-    // masked: `left` tokens of the sequence remain from this group's first on for its last row
     template <int P, bool masked>
     __device__ __forceinline__ void rescore(int left) {
-        const int q = lane >> 4, tbase = 16 * (q >> 1) + 8 * (q & 1);
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
             const int ks = m >> 2, t = 2 * P + ((m >> 1) & 1), hf = m & 1;
             const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
             sc[t][hf] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[4 * hf + ks], qr[t][ks], ks ? sc[t][hf] : zero, 0, 0, 0);
         }
+        if (masked) mask<P>(left);
         limit[P] = __float_as_int(kSlack);
 #pragma unroll
         for (int t = 2 * P; t < 2 * P + 2; ++t) {
-            if (masked) {
-                const int lim = left - stag[t];
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (tbase + e >= lim) sc[t][e >> 2][e & 3] = -INFINITY;
-            }
             float mx = sc[t][0][0];
 #pragma unroll
             for (int e = 1; e < 8; ++e) mx = fmaxf(mx, sc[t][e >> 2][e & 3]);
@@ -844,22 +842,35 @@ struct PrefillWalk {
             const float alpha = none ? 1.f : __builtin_amdgcn_exp2f(m_old - m_new), ng = none ? 0.f : -m_new;
             if (none) limit[P] = INT32_MIN;
             st.m[t] = m_new;
-            den[t] *= alpha;
-            ICARUS_IN_ACC(den[t]);
+            if (__any(m_old > -INFINITY)) {  // else nothing has been summed
+                den[t] *= alpha;
+                ICARUS_IN_ACC(den[t]);
 #pragma unroll
-            for (int dt = 0; dt < kDT; ++dt) {
-                st.o[dt][t][0] *= alpha; st.o[dt][t][1] *= alpha; st.o[dt][t][2] *= alpha; st.o[dt][t][3] *= alpha;
-                ICARUS_IN_ACC(st.o[dt][t]);
+                for (int dt = 0; dt < kDT; ++dt) {
+                    st.o[dt][t][0] *= alpha; st.o[dt][t][1] *= alpha; st.o[dt][t][2] *= alpha; st.o[dt][t][3] *= alpha;
+                    ICARUS_IN_ACC(st.o[dt][t]);
+                }
             }
             neg[t] = f32x4{ng, ng, ng, ng};
 #pragma unroll
             for (int e = 0; e < 8; ++e) sc[t][e >> 2][e & 3] += ng;
         }
     }
-    // One group that every query attends to.  src: its fragments; next: those of the group after it, in the next round (LAST: read
-    // after before_next()) or in this one.  between: runs beside steps 2 and 4, part i of 8.
-    template <bool LAST, typename Between, typename BeforeNext>
-    __device__ __forceinline__ void group(const bf16x8 *__restrict__ src, const bf16x8 *__restrict__ next, Between between, BeforeNext before_next) {
+    // scores of the tokens that a query does not attend to
+    template <int P>
+    __device__ __forceinline__ void mask(int left) {
+        const int q = lane >> 4, tbase = 16 * (q >> 1) + 8 * (q & 1);
+#pragma unroll
+        for (int t = 2 * P; t < 2 * P + 2; ++t)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (tbase + e >= left - stag[t]) sc[t][e >> 2][e & 3] = -INFINITY;
+    }
+    // One group.  src: its fragments; next: those of the group after it, in the next round (LAST: read after before_next()) or
+    // in this one.  between: runs beside steps 2 and 4, part i of 8.  MASKED: one of the last groups, `left` tokens of the sequence
+    // remain from its first on for its last row; else every query attends to all of it.
+    template <bool LAST, bool MASKED, typename Between, typename BeforeNext>
+    __device__ __forceinline__ void group(const bf16x8 *__restrict__ src, const bf16x8 *__restrict__ next, int left, Between between, BeforeNext before_next) {
 #pragma unroll
         for (int t = 0; t < kPrefillNT; ++t) {
 #pragma unroll
@@ -880,12 +891,21 @@ struct PrefillWalk {
         for (int m = 0; m < 16; ++m) {
             pv<1>(m);
             if (m & 1) vf[m >> 1] = src[(2 * kKS + (m >> 1)) * 64];
+            if (MASKED && m == 4) mask<0>(left);
             if (m >= 4 && m < 12) check_part<0>(m - 4);
             if (m & 2) between(2 * (m >> 3) + (m >> 2) % 2, m & 1);
             if (m >= 14) sum<1>(m - 14);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (__builtin_expect(__any(top > limit[0]), 0)) rescore<0, false>(0);
+        if (__builtin_expect(__any(top > limit[0]), 0)) rescore<0, MASKED>(left);
+        if (MASKED && left < kGrp) {  // stale cache bytes past the end may hold anything: zero those V columns
+            const int q = lane >> 4, tbase = 16 * (q >> 1) + 8 * (q & 1);
+#pragma unroll
+            for (int dt = 0; dt < kDT; ++dt)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (tbase + e >= left) vf[dt][e] = (__bf16)0.f;
+        }
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
             score<1>(m);
@@ -897,6 +917,7 @@ struct PrefillWalk {
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
             pv<0>(m);
+            if (MASKED && m == 4) mask<1>(left);
             if (m >= 4) { check_part<1>(2 * (m - 4)); check_part<1>(2 * (m - 4) + 1); }
             if (!LAST) read_next(m);
             __builtin_amdgcn_sched_barrier(0);
@@ -907,7 +928,7 @@ struct PrefillWalk {
                 asm volatile("" : "+v"(at));
                 read_k(src + at);
             }
-            rescore<1, false>(0);
+            rescore<1, MASKED>(left);
             if (!LAST) read_k(next);
         }
         if (LAST) before_next();
@@ -934,23 +955,6 @@ struct PrefillWalk {
         for (int m = 0; m < 16; ++m) pv<P>(m);
         sum<P>(0);
         sum<P>(1);
-    }
-    // One of the last groups, with masks (no pair 1 is pending).
-    __device__ __forceinline__ void masked_group(const bf16x8 *__restrict__ src, int left) {
-        const int q = lane >> 4, tbase = 16 * (q >> 1) + 8 * (q & 1);
-        read_k(src);
-#pragma unroll
-        for (int dt = 0; dt < kDT; ++dt) {
-            vf[dt] = src[(2 * kKS + dt) * 64];
-            // stale cache bytes past the end may hold anything: zero those V columns
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (tbase + e >= left) vf[dt][e] = (__bf16)0.f;
-        }
-        rescore<0, true>(left);
-        finish_pair<0>();
-        rescore<1, true>(left);
-        finish_pair<1>();
     }
 };
 
@@ -1060,6 +1064,7 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
     PrefillWalk walk(st, qr, stag, lane);
     read_ids(0);
     each([&](auto GI) {
+        if (!KV8 && GI.value >= n_grp) return;
 #pragma unroll
         for (int i = 0; i < 4; ++i) request(GI, i, 0);
     });
@@ -1097,17 +1102,28 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
                 }
             };
             if (gi < n_plain) {
-                walk.template group<gi + 1 == kRoundGroups>(stage + gi * 16 * 64, gi + 1 < kRoundGroups ? stage + (gi + 1) * 16 * 64 : other, between, meet);
+                walk.template group<gi + 1 == kRoundGroups, false>(stage + gi * 16 * 64, gi + 1 < kRoundGroups ? stage + (gi + 1) * 16 * 64 : other, 0,
+                                                                   between, meet);
                 if (gi + 1 == kRoundGroups) met = true;
             } else {
+                if (KV8 || r + 1 < n_round) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) between(i, 0);
+                    for (int i = 0; i < 8; ++i) between(i, 0);
+                }
             }
         });
         if (busy) {
-            if (n_plain > 0 && kRoundGroups * r + n_plain == n_clean) walk.finish_pair<1>();  // no group follows that would
+            if (n_plain > 0 && kRoundGroups * r + n_plain == n_clean) walk.finish_pair<1>();  // no group of this loop follows that would
+            if (n_plain < n_here) {  // the masked groups, which bring nothing
+                walk.read_k(stage + n_plain * 16 * 64);
+                walk.none_pending();
 #pragma nounroll
-            for (int gi = n_plain; gi < n_here; ++gi) walk.masked_group(stage + gi * 16 * 64, left - (kRoundGroups * r + gi) * kGrp);
+                for (int gi = n_plain; gi < n_here; ++gi)
+                    walk.group<false, true>(stage + gi * 16 * 64, stage + min(gi + 1, kRoundGroups - 1) * 16 * 64, left - (kRoundGroups * r + gi) * kGrp,
+                                            [](int, int) {}, [] {});
+                walk.finish_pair<1>();
+                walk.none_pending();
+            }
         }
         if (!met) meet();
     }
