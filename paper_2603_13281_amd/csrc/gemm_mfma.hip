@@ -320,11 +320,13 @@ hipError_t launch_cfg(GemmArgs g, hipStream_t st) {
 }
 
 // Tile shapes: rows x weight rows of a workgroup, all with 64-wide K slabs (32-wide slabs ask for every 128-byte line of
-// a weight row twice, half each time, and stream at about 60 % of the rate).  The first three are k_gemm_mfma, the
-// 256 wide ones k_gemm_quad.  first_us: what a workgroup takes apart from its slabs (start, first slab, epilogue); slab_us: a slab
+// a weight row twice, half each time, and stream at about 60 % of the rate).  The first two are k_gemm_mfma, the
+// others k_gemm_quad (192 x 128: gemm_quad.hip may take lower tiles).  first_us: what a workgroup takes apart from its slabs (start, first slab, epilogue); slab_us: a slab
 // with every CU busy, for each of the per_cu workgroups that share one.  The figures are a fit to 5000 timings on
 // this GPU (80-4337 rows x the projections of a Llama-3-8B- and a Qwen3-32B-shaped layer x every tile x 1-12 slices; the
-// fit is 7-11 % off on average), see gemm_plan and gemm_row_tile.
+// fit is 7-11 % off on average), see gemm_plan and gemm_row_tile.  They are of a kernel before k_gemm_quad, which is 5-16 % faster
+// in every one of its tiles: what they are for, the order of the choices, holds (144, 316, 512 and 753 rows of the four
+// projections, every tile and slice count timed anew: the choice is the fastest of these tiles or within 5 %).
 struct TileShape { int bm, bn, per_cu; float first_us, slab_us; };
 constexpr TileShape kTileShape[TILE_KINDS] = {
     {0, 0, 0, 0.f, 0.f},
@@ -343,7 +345,7 @@ int n_tiles_for(const GemmArgs &g, int bm, int bn) {
     return m_tiles * n_tiles;
 }
 
-bool is_quad(int kind) { return kind >= TILE_256x256; }
+bool is_quad(int kind) { return kind >= TILE_192x128; }
 
 int k_ext_of(const GemmArgs &g) {
     if (g.mode == GEMM_DUAL) return g.K + (g.T ? 2 * g.M_models * g.r : 0);
@@ -534,7 +536,6 @@ hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st) {
     switch (g.tile) {
     case TILE_64x128: return g.row_tiles ? launch_cfg<64, 128, 64, 3, 2, 2, true>(g, st) : launch_cfg<64, 128, 64, 3, 2, 2>(g, st);
     case TILE_128: return g.row_tiles ? launch_cfg<128, 128, 64, 4, 2, 2, true>(g, st) : launch_cfg<128, 128, 64, 4, 2, 2>(g, st);
-    case TILE_192x128: return g.row_tiles ? launch_cfg<192, 128, 64, 3, 2, 2, true>(g, st) : launch_cfg<192, 128, 64, 3, 2, 2>(g, st);
     default: return hipErrorInvalidValue;
     }
 }

@@ -1,7 +1,8 @@
-// ICaRusLinear (see gemm_mfma.hip) in wide tiles: 256 weight rows x 256, 192 or 160 stacked rows, for the projections of a
-// prefill chunk and the wide ones of a decode batch.
+// ICaRusLinear (see gemm_mfma.hip) for more than 128 rows: tiles of 256 weight rows x 256, 192 or 160 stacked rows, for the
+// projections of a prefill chunk and the wide ones of a decode batch, and of 128 x 192, 160 or 128 for the narrow ones.
 //
-// Bound: the matrix cores, and the power they draw.  Eight waves sit 2 x 4 over the tile; a wave owns (BM / 2) x 64 outputs in
+// Bound: the matrix cores, and the power they draw.  Eight waves sit 2 x 4 over a wide tile, four 2 x 2 over a narrow one, which
+// leaves room for a second workgroup on its CU; a wave owns (BM / 2) x 64 outputs in
 // 16x16x32 bf16 MFMAs.  K advances 64 columns (whole 128-byte lines of every row) at a time through two LDS stages filled by
 // LDS-direct loads.  What a slab's loads get is time: with the fragments read K step by K step, as in gemm_mfma.hip, every
 // part of a stage is in use until the last step, and a load has three quarters of a slab to arrive; measured at 16384 x 28672 x
@@ -22,7 +23,8 @@
 // left: the clock settles at 1.83 GHz with the pipe busy 81 % of the cycles, against 1.65 GHz and 73 % in 32x32x16.
 // Measured (us, the kernel this one replaced / this one): 16384 rows, gate and up of 4096 -> 2 x 14336 in 256 x 256 tiles
 // 2987 / 2557 (1.50 PFLOP/s), 14336 -> 4096 1500 / 1275; 4337 rows, 14336 -> 4096 in 160 x 256 484 / 397; 753 rows, gate and
-// up in 192 x 256 175 / 149; 316 rows in 160 x 256 84 / 75.  Not kept: four waves of 128 x 128 (a third fewer LDS reads, one wave
+// up in 192 x 256 175 / 149; 316 rows in 160 x 256 84 / 75.  Narrow tiles: 753 rows, 14336 -> 4096 in 2 slices 102 / 96; 316 rows,
+// 14336 -> 4096 in 4 slices 58.7 / 53.5; 144 rows, 8192 -> 5120 in 6 slices 34.4 / 32.2.  Not kept: four waves of 128 x 128 (a third fewer LDS reads, one wave
 // a SIMD; 0-4 % slower), three stages of 160-row tiles (0-7 % slower), raised priority around the MFMAs (1 % slower).
 //
 // MFMA 16x16x32 bf16 operand layout (lane l): A[row l%16][k 8(l/16)..+7], B[k 8(l/16)..+7][col l%16],
@@ -43,16 +45,16 @@ __device__ __forceinline__ void dma16_at(const void *base, uint32_t off, uint32_
 template <int V> struct Int { static constexpr int value = V; };
 
 // MT0, MT1: 16-row tiles of a wave in the two halves of its rows
-template <int MT0, int MT1>
+template <int MT0, int MT1, int WAVES_N>
 struct QuadShape {
-    static constexpr int BM = 32 * (MT0 + MT1), BN = 256, BK = 64;
+    static constexpr int BM = 32 * (MT0 + MT1), BN = 64 * WAVES_N, BK = 64;
     static constexpr int kXStage = BM * BK * 2, kWStage = BN * BK * 2, kLds = 2 * (kXStage + kWStage);  // LDS: two stages of X, two of W
 };
 
-template <int MT0, int MT1, bool GROUPED>
-__global__ void __launch_bounds__(512) k_gemm_quad(GemmArgs g) {
-    using Shape = QuadShape<MT0, MT1>;
-    constexpr int WAVES_N = 4, NW = 8, BM = Shape::BM, BN = Shape::BN, BK = Shape::BK;
+template <int MT0, int MT1, int WAVES_N, bool GROUPED>
+__global__ void __launch_bounds__(128 * WAVES_N, WAVES_N == 4 ? 1 : 2) k_gemm_quad(GemmArgs g) {
+    using Shape = QuadShape<MT0, MT1, WAVES_N>;
+    constexpr int NW = 2 * WAVES_N, BM = Shape::BM, BN = Shape::BN, BK = Shape::BK;
     constexpr int WM = BM / 2, WN = 64, NT = 2, KS = BK / 32;
     constexpr int kRow = BK * 2;                          // bytes of a tile row in LDS
     constexpr int kXStage = Shape::kXStage, kWStage = Shape::kWStage, kBOff = 2 * kXStage;
@@ -273,9 +275,9 @@ __global__ void __launch_bounds__(512) k_gemm_quad(GemmArgs g) {
     store_wave_tile<16, MT0 + MT1, 2 * NT, BN>(g, acc, (float *)smem + w * 32 * (WN + 8), tile_n, kz, row0 + wm * WM, row_end, wn);
 }
 
-template <int MT0, int MT1, bool GROUPED>
+template <int MT0, int MT1, int WAVES_N, bool GROUPED>
 hipError_t launch_quad(GemmArgs g, hipStream_t st) {
-    using Shape = QuadShape<MT0, MT1>;
+    using Shape = QuadShape<MT0, MT1, WAVES_N>;
     constexpr int BM = Shape::BM, BN = Shape::BN;
     g.m_tiles = GROUPED ? g.n_row_tiles : (g.R + BM - 1) / BM;
     g.n_tiles = 0;
@@ -287,24 +289,32 @@ hipError_t launch_quad(GemmArgs g, hipStream_t st) {
             g.n_tiles += g.tiles_seg[s];
         }
     }
-    gemm_set_panels(&g, BM, BN, 1);
+    gemm_set_panels(&g, BM, BN, WAVES_N == 4 ? 1 : 2);
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_gemm_quad<MT0, MT1, GROUPED>, hipFuncAttributeMaxDynamicSharedMemorySize, Shape::kLds);
+        hipError_t e = hipFuncSetAttribute((const void *)k_gemm_quad<MT0, MT1, WAVES_N, GROUPED>, hipFuncAttributeMaxDynamicSharedMemorySize, Shape::kLds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     dim3 grid(gemm_grid(g));
-    hipLaunchKernelGGL((k_gemm_quad<MT0, MT1, GROUPED>), grid, dim3(512), Shape::kLds, st, g);
+    hipLaunchKernelGGL((k_gemm_quad<MT0, MT1, WAVES_N, GROUPED>), grid, dim3(128 * WAVES_N), Shape::kLds, st, g);
     return hipGetLastError();
 }
 
 }  // namespace
 hipError_t launch_gemm_quad(const GemmArgs &g, hipStream_t st) {
     switch (g.tile) {
-    case TILE_256x256: return g.row_tiles ? launch_quad<4, 4, true>(g, st) : launch_quad<4, 4, false>(g, st);
-    case TILE_192x256: return launch_quad<3, 3, false>(g, st);
-    case TILE_160x256: return launch_quad<3, 2, false>(g, st);
+    case TILE_192x128: {
+        if (g.row_tiles) return launch_quad<3, 3, 2, true>(g, st);
+        // As many lower tiles, if they hold the rows: no MFMAs for padding (316 rows in tiles of 192 / 160: 14336 -> 4096 in 4
+        // slices 54.4 / 53.5 us, 4096 -> 4096 28.5 / 26.7; 144 rows, 8192 -> 5120 in 6 slices 34.4 / 32.2)
+        const int tiles = (g.R + 191) / 192;
+        if (g.R <= 128 * tiles) return launch_quad<2, 2, 2, false>(g, st);
+        return g.R <= 160 * tiles ? launch_quad<3, 2, 2, false>(g, st) : launch_quad<3, 3, 2, false>(g, st);
+    }
+    case TILE_256x256: return g.row_tiles ? launch_quad<4, 4, 4, true>(g, st) : launch_quad<4, 4, 4, false>(g, st);
+    case TILE_192x256: return launch_quad<3, 3, 4, false>(g, st);
+    case TILE_160x256: return launch_quad<3, 2, 4, false>(g, st);
     default: return hipErrorInvalidValue;
     }
 }

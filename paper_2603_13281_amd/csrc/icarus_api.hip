@@ -1099,7 +1099,7 @@ icarus_status prepare_decode(icarus_ctx *ctx, const void *kv_pool, const int32_t
         pr->fp.inv = dmeta + used + R;
         used += (size_t)2 * R;
         pr->fp.tile = gemm_row_tile(off.data(), n_groups);
-        if (std::max({ctx->cfg.d_model, ctx->cfg.n_q_heads * ctx->cfg.head_dim, ctx->cfg.d_ffn}) > kQuadMaxK) pr->fp.tile = std::min<int>(pr->fp.tile, TILE_192x128);
+        if (std::max({ctx->cfg.d_model, ctx->cfg.n_q_heads * ctx->cfg.head_dim, ctx->cfg.d_ffn}) > kQuadMaxK) pr->fp.tile = std::min<int>(pr->fp.tile, TILE_128);
         const int bm = gemm_tile_rows(pr->fp.tile);
         int32_t *rt = m + used;
         for (int g = 0; g < n_groups; ++g)

@@ -112,6 +112,22 @@ def test_infinite_activations_reach_only_their_products(tile, slabs, slices, mod
         assert torch.isposinf(got[0]).all() and torch.isfinite(got[1:]).all()
 
 
+@pytest.mark.parametrize("rows", [128, 129, 160, 161, 192, 193, 256, 257, 320, 321, 384, 480, 481])
+def test_lower_tiles_where_as_many_hold_the_rows(rows):
+    # a launch in 192 x 128 tiles is one of 128 or 160 rows each, if it needs no more of them
+    print("case: 192 x 128", rows, flush=True)
+    k, n, models, rank = 64 * 9, 136, 3, 16
+    x, w = _draw((rows, k), 1), [_draw((n, k), 10 + i, 0.05) for i in range(2)]
+    t, b = _adapters(rows, n, models, rank, 1, 20)
+    eps = (k + models * rank + 16) * 2.0 ** -23
+    want, size = _product(x, w[0], t, b[0])
+    _check(binding.gemm(x, w[:1], (192, 128, False), 2, t=t, b=b), want, eps * size + 1e-30, rows)
+    (g, gs), (u, us) = (_product(x, v) for v in w)
+    silu = g * torch.sigmoid(g)
+    bound = 1.1 * eps * gs * u.abs() + eps * us * silu.abs() + (2.0 ** -8 + (2 + g.abs()) * 2.0 ** -21) * (silu * u).abs() + 2.0 ** -100
+    _check(binding.gemm(x, w, (192, 128, False), fused=True), silu * u, bound, (rows, "fused"))
+
+
 def test_gemm_refuses_what_the_kernels_do_not_take():
     x, w = _draw((4, 128), 1), _draw((16, 128), 2)
     for kw in (dict(tile=(96, 128, False)), dict(tile=(256, 256, True)), dict(tile=TILES[0], slices=13), dict(tile=TILES[0], slices=0)):
