@@ -5,6 +5,7 @@
 #include "kernels.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace icarus {
 
@@ -494,107 +495,138 @@ hipError_t launch_rope_append_tiles(const Dims &dm, const float *qkv, int ldq, i
 }
 
 // ------------------------------------------------------------------ attention (one block per row and query head)
-// Online softmax over chunks of 1024 cached positions.  Scores: a thread per position.  Output: thread (part, d) adds
-// every parts-th quad of positions to output element d; V^T rows hold a block's tokens side by side, so a quad is
-// one load, and 256 / D parts (D rounded up to a power of two) keep all threads on it.  Latency-bound at the sizes
-// this kernel is for: with one element and one position at a time, 128 positions x 64 dims took 20.5 us, now 8.6 us.
-// quads: D and Bk are multiples of 4 (else one element, one position at a time).
-template <typename T, typename KT>
-__global__ void __launch_bounds__(256) k_attn_generic(const T *__restrict__ q, const KT *__restrict__ pool,
-                                                      const int32_t *__restrict__ bt, int max_blocks,
-                                                      const int32_t *__restrict__ row_seq, const int32_t *__restrict__ row_kvlen,
-                                                      T *__restrict__ out, int Hq, int Hkv, int D, int Bk, float scale,
-                                                      float k_scale, float v_scale, int parts, int quads) {
-    __shared__ float sc[1024];
-    __shared__ int sblk[1024];
-    __shared__ float sum[256];
+// Online softmax over chunks of 1024 cached positions.  Scores: LPT threads per position, each every LPT-th quad of its
+// elements.  Output: thread (part, d) adds every parts-th quad of positions to output element d; V^T rows hold a block's
+// tokens side by side, so a quad is one load, and four neighbouring threads take the quads of a row of sixteen tokens.
+// Latency-bound at the sizes this kernel is for, and next by the lines that its loads touch: with a thread per position and
+// a part per wave every load touched a line per lane.  Rows x 4 heads x 64 in float32, us, that with 256 threads a workgroup /
+// this: 3 rows over 128 tokens 7.5 / 6.5, 12 rows over 1000 30.0 / 13.7, 96 rows over 1000 55.0 / 34.1, 768 rows 381 / 190.
+// quads: D and Bk are multiples of 4 (else one element, one position at a time; LPT is 1).
+template <typename T, typename KT, int NT, int LPT>
+__global__ void __launch_bounds__(NT) k_attn_generic(const T *__restrict__ q, const KT *__restrict__ pool,
+                                                     const int32_t *__restrict__ bt, int max_blocks,
+                                                     const int32_t *__restrict__ row_seq, const int32_t *__restrict__ row_kvlen,
+                                                     T *__restrict__ out, int Hq, int Hkv, int D, int Bk, float scale,
+                                                     float k_scale, float v_scale, int parts, int quads) {
+    __shared__ __attribute__((aligned(16))) float sc[1024];
+    __shared__ size_t soff[1024];  // where a position's V elements are, within its head
+    __shared__ float sum[NT];
     __shared__ float red[16];
-    extern __shared__ float qs[];  // [D]
+    extern __shared__ __attribute__((aligned(16))) float qs[];  // [D]
     int row = blockIdx.y, h = blockIdx.x;
     int c = h / (Hq / Hkv);
     int s = row_seq[row], n = row_kvlen[row];
     const int32_t *btr = bt + (size_t)s * max_blocks;
-    for (int i = threadIdx.x; i < D; i += 256) qs[i] = Elem<T>::ld(q + ((size_t)row * Hq + h) * D + i);
+    for (int i = threadIdx.x; i < D; i += NT) qs[i] = Elem<T>::ld(q + ((size_t)row * Hq + h) * D + i);
     __syncthreads();
-    const int width = 256 / parts, part = threadIdx.x / width, d = threadIdx.x % width;
+    const int width = NT / parts, pl = parts >= 4 ? 4 : 1;  // parts, and so width, are powers of two
+    const int part = threadIdx.x % pl + pl * (threadIdx.x / (pl * width)), d = threadIdx.x / pl % width;
+    const int sub = threadIdx.x % LPT;
     size_t head_stride = (size_t)2 * Bk * D, blk_stride = (size_t)Hkv * head_stride;
     const KT *head = pool + (size_t)c * head_stride;
     float m = -INFINITY, l = 0.f, acc = 0.f;
     for (int c0 = 0; c0 < n; c0 += 1024) {
         int cnt = min(1024, n - c0);
         float lmax = -INFINITY;
-        for (int t = threadIdx.x; t < cnt; t += 256) {
+        for (int t = threadIdx.x / LPT; t < cnt; t += NT / LPT) {
             int tok = c0 + t;
-            const int blk = btr[tok / Bk];
-            sblk[t] = blk;
-            const KT *kr = head + (size_t)blk * blk_stride + (size_t)(tok % Bk) * D;
+            const int in_blk = tok % Bk;
+            const size_t off = (size_t)btr[tok / Bk] * blk_stride;
+            const KT *kr = head + off + (size_t)in_blk * D;
             float dot = 0.f;
-            if (quads) {
-                for (int i = 0; i < D; i += 4) {
+            if (LPT > 1 || quads) {
+#pragma unroll 8
+                for (int i = 4 * sub; i < D; i += 4 * LPT) {
                     float kv[4];
                     KVElem4<KT>::ld(kr + i, k_scale, kv);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) dot += qs[i + e] * kv[e];
+                    const float4 qv = *(const float4 *)(qs + i);
+                    dot += qv.x * kv[0];
+                    dot += qv.y * kv[1];
+                    dot += qv.z * kv[2];
+                    dot += qv.w * kv[3];
                 }
             } else {
                 for (int i = 0; i < D; ++i) dot += qs[i] * KVElem<KT>::ld(kr + i, k_scale);
             }
+#pragma unroll
+            for (int o = 1; o < LPT; o *= 2) dot += __shfl_xor(dot, o, 64);  // the threads of a position go round together
             dot *= scale;
-            sc[t] = dot;
+            if (sub == 0) {
+                sc[t] = dot;
+                soff[t] = off + in_blk;
+            }
             lmax = fmaxf(lmax, dot);
         }
-        float cmax = block_max(lmax, red);
+        float cmax = block_max(lmax, red);  // barriers inside also publish sc[] and soff[]
         float m_new = fmaxf(m, cmax);
         float lsum = 0.f;
-        for (int t = threadIdx.x; t < cnt; t += 256) {
+        for (int t = threadIdx.x; t < cnt; t += NT) {
             float p = __expf(sc[t] - m_new);
             sc[t] = p;
             lsum += p;
         }
-        float csum = block_sum(lsum, red);  // barriers inside also publish sc[] and sblk[]
+        float csum = block_sum(lsum, red);  // likewise the probabilities
         float alpha = (m == -INFINITY) ? 0.f : __expf(m - m_new);
         l = l * alpha + csum;
         if (d < D) {
             float a = acc * alpha;
             const KT *vd = head + (size_t)Bk * D + (size_t)d * Bk;
             if (quads) {
-#pragma unroll 4
+#pragma unroll 8
                 for (int t = 4 * part; t + 3 < cnt; t += 4 * parts) {
                     float v[4];
-                    KVElem4<KT>::ld(vd + (size_t)sblk[t] * blk_stride + (c0 + t) % Bk, v_scale, v);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) a += sc[t + e] * v[e];
+                    KVElem4<KT>::ld(vd + soff[t], v_scale, v);
+                    const float4 p = *(const float4 *)(sc + t);
+                    a += p.x * v[0];
+                    a += p.y * v[1];
+                    a += p.z * v[2];
+                    a += p.w * v[3];
                 }
                 if (part == 0)  // the last, partial quad: what lies past the context may be anything
-                    for (int t = cnt & ~3; t < cnt; ++t) a += sc[t] * KVElem<KT>::ld(vd + (size_t)sblk[t] * blk_stride + (c0 + t) % Bk, v_scale);
+                    for (int t = cnt & ~3; t < cnt; ++t) a += sc[t] * KVElem<KT>::ld(vd + soff[t], v_scale);
             } else {
-                for (int t = part; t < cnt; t += parts) a += sc[t] * KVElem<KT>::ld(vd + (size_t)sblk[t] * blk_stride + (c0 + t) % Bk, v_scale);
+                for (int t = part; t < cnt; t += parts) a += sc[t] * KVElem<KT>::ld(vd + soff[t], v_scale);
             }
             acc = a;
         }
         m = m_new;
         __syncthreads();
     }
-    sum[threadIdx.x] = acc;
+    sum[part * width + d] = acc;
     __syncthreads();
     if (threadIdx.x < D) {
+        acc = sum[threadIdx.x];
         for (int p = 1; p < parts; ++p) acc += sum[p * width + threadIdx.x];
         Elem<T>::st(out + ((size_t)row * Hq + h) * D + threadIdx.x, l > 0.f ? acc / l : 0.f);
     }
 }
 
+// Workgroups up to which each gets a CU, and so 1024 threads.  Rows x 4 heads x 64 in float32, us with 256 / 1024 threads:
+// 48 workgroups over 1000 tokens 22.6 / 13.7, 192 over 128 tokens 6.8 / 6.7 and over 1000 28.8 / 17.6; 384 9.0 / 13.3 and
+// 34.1 / 33.3, 768 11.1 / 20.4 and 47.6 / 54.1.
+constexpr int kGenericWide = 256;
+
 hipError_t launch_attn_generic(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
                                const RowMeta &rm, void *out, int R, hipStream_t st) {
     if (R <= 0) return hipSuccess;
     float scale = 1.0f / sqrtf((float)dm.D);
-    int parts = 1;
-    while (256 / (2 * parts) >= dm.D) parts *= 2;
     const int quads = dm.D % 4 == 0 && dm.Bk % 4 == 0;
     dim3 grid(dm.Hq, R);
-    DISPATCH_TK(dm.bf16, dm.kv8, hipLaunchKernelGGL((k_attn_generic<T, KT>), grid, dim3(256), sizeof(float) * dm.D, st, (const T *)q,
-                                                    (const KT *)pool, bt, max_blocks, rm.row_seq, rm.row_kvlen, (T *)out, dm.Hq, dm.Hkv,
-                                                    dm.D, dm.Bk, scale, dm.k_scale, dm.v_scale, parts, quads));
-    return hipGetLastError();
+    auto launch = [&](auto nt, auto lpt) {
+        constexpr int NT = decltype(nt)::value, LPT = decltype(lpt)::value;
+        int parts = 1;
+        while (parts < 32 && NT / (2 * parts) >= dm.D) parts *= 2;
+        DISPATCH_TK(dm.bf16, dm.kv8, hipLaunchKernelGGL((k_attn_generic<T, KT, NT, LPT>), grid, dim3(NT), sizeof(float) * dm.D, st, (const T *)q,
+                                                        (const KT *)pool, bt, max_blocks, rm.row_seq, rm.row_kvlen, (T *)out, dm.Hq, dm.Hkv,
+                                                        dm.D, dm.Bk, scale, dm.k_scale, dm.v_scale, parts, quads));
+        return hipGetLastError();
+    };
+    constexpr std::integral_constant<int, 1> one;
+    constexpr std::integral_constant<int, 4> four;
+    if (!quads) return launch(std::integral_constant<int, 256>(), one);
+    const bool wide = (int64_t)dm.Hq * R <= kGenericWide;
+    if (wide) return launch(std::integral_constant<int, 1024>(), four);
+    return launch(std::integral_constant<int, 256>(), four);
 }
 
 }  // namespace icarus
