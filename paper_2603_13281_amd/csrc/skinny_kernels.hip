@@ -5,8 +5,11 @@
 // sixteen at a time between two barriers (32-94 us a projection, 340 us a step of 3 rows).  Here a wave owns a few
 // output columns and all rows: its 64 lanes split K in 16-byte pieces, so a column of 1024 bytes is one load per lane,
 // and the sums meet in registers.  The adapter delta, the residual and the SwiGLU product are added where the sum
-// is, and one launch serves the projections that read the same rows: 9 launches for that step instead of 18, 4-5 us
-// each, which is what a dependent launch takes here (49 us a step).
+// is, and one launch serves the projections that read the same rows: 9 launches for that step instead of 18.  A projection
+// is a chain of loads and exchanges: the row's model is asked for first, then the pieces of weights and rows, then, while
+// those come, the adapter's columns and the residual; the sums of all columns and rows go through the lanes together
+// (wave_sums).  Loads behind one another and a sum at a time took 5.4 us for 3 rows, 256 -> 768, and 9.5 for 12 rows, this 4.0
+// and 5.8.
 #include "device_util.h"
 #include "kernels.h"
 
@@ -20,15 +23,13 @@ namespace {
 template <typename T> struct Vec16;
 template <> struct Vec16<float> {
     static constexpr int N = 4;
-    static __device__ __forceinline__ void ld(const float *p, float (&f)[4]) {
-        const float4 v = *(const float4 *)p;
-        f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
-    }
+    typedef float4 Raw;
+    static __device__ __forceinline__ void un(const float4 &v, float (&f)[4]) { f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w; }
 };
 template <> struct Vec16<bf16_t> {
     static constexpr int N = 8;
-    static __device__ __forceinline__ void ld(const bf16_t *p, float (&f)[8]) {
-        const uint4 v = *(const uint4 *)p;
+    typedef uint4 Raw;
+    static __device__ __forceinline__ void un(const uint4 &v, float (&f)[8]) {
         f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
         f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
         f[4] = __uint_as_float(v.z << 16); f[5] = __uint_as_float(v.z & 0xffff0000u);
@@ -38,8 +39,29 @@ template <> struct Vec16<bf16_t> {
 // one element at a time: rows that are not whole 16-byte pieces
 template <typename T> struct Vec1 {
     static constexpr int N = 1;
-    static __device__ __forceinline__ void ld(const T *p, float (&f)[1]) { f[0] = Elem<T>::ld(p); }
+    typedef T Raw;
+    static __device__ __forceinline__ void un(const T &v, float (&f)[1]) { f[0] = Elem<T>::ld(&v); }
 };
+template <typename V, typename T> __device__ __forceinline__ typename V::Raw ld_raw(const T *p) { return *(const typename V::Raw *)p; }
+template <typename V, typename T> __device__ __forceinline__ void ld_vec(const T *p, float (&f)[V::N]) { V::un(ld_raw<V>(p), f); }
+
+// Sums over the wave's lanes of NV values each (a power of two up to 64): lane l gets that of value l / (64 / NV).  A lane hands
+// half of what it has to its partner and goes on with the other half, NV - 1 + log2(64 / NV) exchanges instead of 6 NV.
+template <int NV, int N = NV / 2, int O = 32>
+__device__ __forceinline__ float wave_sums(float (&v)[NV]) {
+    if constexpr (O > 0) {
+        const bool upper = threadIdx.x & O;
+        if constexpr (N > 0) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const float keep = upper ? v[i + N] : v[i], give = upper ? v[i] : v[i + N];
+                v[i] = keep + __shfl_xor(give, O, 64);
+            }
+        } else v[0] += __shfl_xor(v[0], O, 64);
+        return wave_sums<NV, N / 2, O / 2>(v);
+    }
+    return v[0];
+}
 
 // One workgroup per row: y = rmsnorm(x) * wn (NORM), and for a decoder row t[target][row][0..r) = scale * A[model] y (or
 // x) for up to two targets; a wave takes every fourth of the targets * r outputs.
@@ -54,7 +76,7 @@ __global__ void __launch_bounds__(256) k_row_generic(const T *__restrict__ x, in
         float ss = 0.f;
         for (int k = threadIdx.x * V::N; k < K; k += 256 * V::N) {
             float f[V::N];
-            V::ld(xr + k, f);
+            ld_vec<V>(xr + k, f);
 #pragma unroll
             for (int e = 0; e < V::N; ++e) ss += f[e] * f[e];
         }
@@ -73,8 +95,8 @@ __global__ void __launch_bounds__(256) k_row_generic(const T *__restrict__ x, in
         float acc = 0.f;
         for (int k = lane * V::N; k < K; k += 64 * V::N) {
             float f[V::N], g[V::N];
-            V::ld(xr + k, f);
-            V::ld(a + k, g);
+            ld_vec<V>(xr + k, f);
+            ld_vec<V>(a + k, g);
 #pragma unroll
             for (int e = 0; e < V::N; ++e) acc += f[e] * g[e];
         }
@@ -112,40 +134,25 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(SkinnyArgs a) {
             wrow[c] = (const T *)a.W[s] + (size_t)(n - (s ? a.n_end[s - 1] : 0)) * a.K;
         }
     }
-    float acc[kCols][RM];
-#pragma unroll
-    for (int c = 0; c < kCols; ++c)
-#pragma unroll
-        for (int m = 0; m < RM; ++m) acc[c][m] = 0.f;
+    // sum (column c, row m) ends in lanes (c * RM + m) * kShare and the kShare - 1 after it
+    constexpr int kShare = 64 / (kCols * RM);
+    const int c = lane / kShare / RM, row = lane / kShare % RM, n = n0 + c;
+    const bool mine = c < NO && row < a.R && n < N, first = mine && lane % kShare == 0;
+    const int j = mine && a.t && n < a.n_end[0] ? a.row_model[row] : -1;
     const T *X = (const T *)a.X;
-    for (int k = lane * V::N; k < a.K; k += 64 * V::N) {
-        float wv[kCols][V::N];
+    int k = lane * V::N;
+    typename V::Raw wv[kCols], xv[RM];
+    auto load = [&] {
 #pragma unroll
-        for (int c = 0; c < kCols; ++c) V::ld(wrow[c] + k, wv[c]);
+        for (int i = 0; i < kCols; ++i) wv[i] = ld_raw<V>(wrow[i] + k);
 #pragma unroll
-        for (int m = 0; m < RM; ++m) {
-            float xv[V::N];
-            V::ld(X + (size_t)min(m, a.R - 1) * a.ldx + k, xv);
-#pragma unroll
-            for (int c = 0; c < kCols; ++c)
-#pragma unroll
-                for (int e = 0; e < V::N; ++e) acc[c][m] += wv[c][e] * xv[e];
-        }
-    }
-    // lane c * RM + m keeps sum (column c, row m)
-    float mine = 0.f, up = 0.f;
-#pragma unroll
-    for (int c = 0; c < kCols; ++c)
-#pragma unroll
-        for (int m = 0; m < RM; ++m) {
-            const float s = wave_sum(acc[c][m]);
-            if (c < NO) { if (lane == c * RM + m) mine = s; }
-            else if (lane == (c - NO) * RM + m) up = s;
-        }
-    const int c = lane / RM, row = lane % RM, n = n0 + c;
-    if (c >= NO || row >= a.R || n >= N) return;
-    const int j = a.t ? a.row_model[row] : -1;
-    if (j >= 0 && n < a.n_end[0]) {
+        for (int m = 0; m < RM; ++m) xv[m] = ld_raw<V>(X + (size_t)min(m, a.R - 1) * a.ldx + k);
+    };
+    if (k < a.K) load();
+    // what is added to the sum is fetched beneath the first pieces
+    float res = 0.f, delta[2] = {0.f, 0.f};
+    if (MODE == SKINNY_RESID && first) res = Elem<T>::ld((const T *)a.resid + (size_t)row * a.ldy + n);
+    if (j >= 0) {
 #pragma unroll
         for (int d = 0; d < (dual ? 2 : 1); ++d) {
             const T *b = (const T *)a.B[d];
@@ -153,13 +160,37 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(SkinnyArgs a) {
             b += ((size_t)j * a.n_end[0] + n) * a.r;
             const float *tr = a.t + ((size_t)d * a.R + row) * a.r;
             float v = 0.f;
+#pragma unroll 8
             for (int i = 0; i < a.r; ++i) v += Elem<T>::ld(b + i) * tr[i];
-            (d ? up : mine) += v;
+            delta[d] = v;
         }
     }
-    if (MODE == SKINNY_F32) ((float *)a.Y)[(size_t)row * a.ldy + n] = mine;
-    else if (MODE == SKINNY_RESID) Elem<T>::st((T *)a.Y + (size_t)row * a.ldy + n, Elem<T>::ld((const T *)a.resid + (size_t)row * a.ldy + n) + mine);
-    else Elem<T>::st((T *)a.Y + (size_t)row * a.ldy + n, mine / (1.f + __expf(-mine)) * up);
+    float acc[kCols * RM];
+#pragma unroll
+    for (int i = 0; i < kCols * RM; ++i) acc[i] = 0.f;
+    while (k < a.K) {
+#pragma unroll
+        for (int m = 0; m < RM; ++m) {
+            float xf[V::N];
+            V::un(xv[m], xf);
+#pragma unroll
+            for (int i = 0; i < kCols; ++i) {
+                float wf[V::N];
+                V::un(wv[i], wf);
+#pragma unroll
+                for (int e = 0; e < V::N; ++e) acc[i * RM + m] += wf[e] * xf[e];
+            }
+        }
+        k += 64 * V::N;
+        if (k < a.K) load();
+    }
+    float sum = wave_sums(acc), up = 0.f;
+    if (dual) up = __shfl_xor(sum, 32, 64) + delta[1];  // the upper half of the lanes holds the up projection
+    sum += delta[0];
+    if (!first) return;
+    if (MODE == SKINNY_F32) ((float *)a.Y)[(size_t)row * a.ldy + n] = sum;
+    else if (MODE == SKINNY_RESID) Elem<T>::st((T *)a.Y + (size_t)row * a.ldy + n, res + sum);
+    else Elem<T>::st((T *)a.Y + (size_t)row * a.ldy + n, sum / (1.f + __expf(-sum)) * up);
 }
 
 template <typename F>
