@@ -20,7 +20,8 @@
  *    (hipHostMalloc) the first time its turn comes or when a call needs a
  *    larger one, and a call that finds its buffer still in use by the call
  *    made 16 calls earlier blocks the HOST until that call's metadata copy has
- *    run (back-pressure: at most 16 calls of one context are in flight).
+ *    run (back-pressure: at most 16 such calls of one context are in flight).
+ *    Metadata of up to 960 ints goes on as kernel arguments: nothing to wait for.
  *    icarus_attn_shared_kv_static uses neither the ring nor a workspace.
  *  - "host" / "device" after a pointer says where the memory lives.
  *  - Small integer metadata (lengths, row lists) is passed as HOST arrays so it
