@@ -740,10 +740,9 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 // measured in a loop, one is free (8.8 ns), a second costs 1.3-1.7 ns, a second exponential 4 ns, and a two-way dot product 6.5 ns
 // each (it shares the pipe), hence one exponential behind each MFMA of steps 1 and 3 and the denominators on the matrix cores.
 //
-// The ring has two stages of one round (four groups) each; the four waves bring a quarter of each group (K rows or V^T rows),
-// through registers, requested a whole round before it is published, and read every group as MFMA fragments in lane
-// order.  A stage is published while the other one is read, and its last reads precede the one barrier of a round, which
-// sits before the first reads of the next round.  Past the end of the piece the loads repeat its last block.
+// The ring has two stages of one round (four groups) each; the four waves bring a quarter of each group (K rows or V^T rows)
+// by LDS-direct loads, and read every group as MFMA fragments in lane order.  A stage is filled while the other one is read,
+// and its last reads precede the one barrier of a round, which sits before the first reads of the next round.  Past the end of the piece the loads repeat its last block.
 // ring: [2][4][16][64] x 16 B.
 struct PrefillWalk {
     State<kPrefillNT> &st;
@@ -965,11 +964,10 @@ struct PrefillWalk {
 // whole walks only, 14 groups x 8 kv-heads of a round of agent turns (60-400 rows over 600-8192 cached
 // tokens each) took 240 us on 112 CUs, cut into pieces 109 us + 12.5 us for
 // the merge; 512 rows over 32000 tokens (16 groups) 990 us -> 574 + 12.5 us.
-template <bool KV8>
-__global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_t *__restrict__ qg, const void *__restrict__ pool_v,
+__global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_t *__restrict__ qg, const bf16_t *__restrict__ pool,
                                                                      const int32_t *__restrict__ bt, int max_blocks, AttnPlan pl,
                                                                      bf16_t *__restrict__ out, float *__restrict__ part_o,
-                                                                     float *__restrict__ part_ml, int Hq, int Hkv, float v_scale) {
+                                                                     float *__restrict__ part_ml, int Hq, int Hkv) {
     constexpr int NT = kPrefillNT;
     extern __shared__ float lds[];
     const int item = blockIdx.x / Hkv, c = blockIdx.x % Hkv;
@@ -995,10 +993,7 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
         const int j = 16 * (w * NT + qt) + m;
         const bf16_t *qp = qg + ((size_t)(row0 + j / g) * Hq + c * g + j % g) * kD;
 #pragma unroll
-        for (int ks = 0; ks < kKS; ++ks) {  // FP8 cache: the k-step order of KVRaw8
-            const int d0 = KV8 ? 64 * (ks >> 1) + 16 * q + 8 * (ks & 1) : 32 * ks + 8 * q;
-            qr[qt][ks] = j < G ? *(const bf16x8 *)(qp + d0) : zero8();
-        }
+        for (int ks = 0; ks < kKS; ++ks) qr[qt][ks] = j < G ? *(const bf16x8 *)(qp + 32 * ks + 8 * q) : zero8();
         st.m[qt] = -INFINITY;
         st.l[qt] = 0.f;
 #pragma unroll
@@ -1013,38 +1008,15 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
     // This wave's quarter of every group: w = 0, 1 the K rows of tile w, w = 2, 3 the V^T rows of four d tiles; four fragments.
     const bool kside = w < 2;
     const int sel = kside ? m >> 3 : q >> 1;  // which of the group's two blocks this lane reads
-    const int at = kside ? (8 * ((m >> 2) & 1) + (m & 3) + 4 * w) * kD + (KV8 ? 16 : 8) * q : kBk * kD + (64 * (w - 2) + m) * kBk + 8 * (q & 1);
+    const int at = kside ? (8 * ((m >> 2) & 1) + (m & 3) + 4 * w) * kD + 8 * q : kBk * kD + (64 * (w - 2) + m) * kBk + 8 * (q & 1);
     constexpr size_t head_stride = (size_t)2 * kBk * kD;
     auto id_of = [&](int grp) { return blds[min(2 * grp + sel, n_blk - 1)]; };
-    // The bf16 cache's fragments go straight to LDS: those of round r + 1 are requested in the first two groups of round r.
-    // FP8 codes pass through registers, requested a round earlier, and are published as bf16 (the codes are exact in it).
-    uint4 codes[kRoundGroups][2];  // of four fragments
+    // The fragments go straight to LDS: those of round r + 1 are requested in the first two groups of round r.
     int ids[kRoundGroups];
     auto request = [&](auto GI, int i, int stage) {  // part i of 4
         constexpr int gi = decltype(GI)::value;
-        const size_t off = ((size_t)ids[gi] * Hkv + c) * head_stride + at;
-        if constexpr (KV8) {
-            if (i) return;
-            const uint8_t *p = (const uint8_t *)pool_v + off;
-            if (kside) {
-                codes[gi][0] = *(const uint4 *)p;
-                codes[gi][1] = *(const uint4 *)(p + 64);
-            } else {
-#pragma unroll
-                for (int f = 0; f < 2; ++f) {
-                    const uint2 a = *(const uint2 *)(p + (2 * f) * 16 * kBk), b = *(const uint2 *)(p + (2 * f + 1) * 16 * kBk);
-                    codes[gi][f] = uint4{a.x, a.y, b.x, b.y};
-                }
-            }
-        } else {
-            dma16((const bf16_t *)pool_v + off + i * (kside ? 32 : 16 * kBk),
-                  ring0 + (uint32_t)((stage * kRoundGroups + gi) * 16 + 4 * w + i) * 1024);
-        }
-    };
-    auto publish = [&](auto GI, int i, int stage) {
-        constexpr int gi = decltype(GI)::value;
-        const uint4 v = codes[gi][i >> 1];
-        ring[((size_t)(stage * kRoundGroups + gi) * 16 + 4 * w + i) * 64 + lane] = i & 1 ? cvt8(v.z, v.w) : cvt8(v.x, v.y);
+        dma16(pool + ((size_t)ids[gi] * Hkv + c) * head_stride + at + i * (kside ? 32 : 16 * kBk),
+              ring0 + (uint32_t)((stage * kRoundGroups + gi) * 16 + 4 * w + i) * 1024);
     };
     constexpr Int<0> I0; constexpr Int<1> I1; constexpr Int<2> I2; constexpr Int<3> I3;
     auto each = [&](auto &&f) { f(I0); f(I1); f(I2); f(I3); };
@@ -1053,7 +1025,7 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
         for (int gi = 0; gi < kRoundGroups; ++gi) ids[gi] = id_of(kRoundGroups * r + gi);
     };
     auto meet = [&] {  // what this wave brought has landed in LDS, and so has what the others brought
-        if constexpr (!KV8) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
         __syncthreads();
     };
 
@@ -1064,19 +1036,11 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
     PrefillWalk walk(st, qr, stag, lane);
     read_ids(0);
     each([&](auto GI) {
-        if (!KV8 && GI.value >= n_grp) return;
+        if (GI.value >= n_grp) return;
 #pragma unroll
         for (int i = 0; i < 4; ++i) request(GI, i, 0);
     });
     read_ids(1);
-    if constexpr (KV8) {
-        each([&](auto GI) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) publish(GI, i, 0);
-            request(GI, 0, 0);
-        });
-        read_ids(2);
-    }
     meet();
     if (busy && n_clean > 0) walk.read_k(ring + lane);
 #pragma nounroll
@@ -1090,11 +1054,7 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
             constexpr int gi = decltype(GI)::value;
             auto between = [&](int i, int sub) {  // parts 0-3 beside step 2, 4-7 beside step 4
                 if (sub) return;
-                if constexpr (KV8) {
-                    if (i < 4) publish(GI, i, here ^ 1);
-                    else if (i == 4) request(GI, 0, 0);
-                    else if (i == 7) ids[gi] = id_of(kRoundGroups * (r + 3) + gi);
-                } else if constexpr (gi < 2) {
+                if constexpr (gi < 2) {
                     if (i < 4) request(Int<2 * gi>(), i, here ^ 1);
                     else request(Int<2 * gi + 1>(), i - 4, here ^ 1);
                 } else if (gi == 2 && i == 3) {
@@ -1106,7 +1066,7 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
                                                                    between, meet);
                 if (gi + 1 == kRoundGroups) met = true;
             } else {
-                if (KV8 || r + 1 < n_round) {
+                if (r + 1 < n_round) {
 #pragma unroll
                     for (int i = 0; i < 8; ++i) between(i, 0);
                 }
@@ -1130,12 +1090,265 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
 #pragma unroll
     for (int qt = 0; qt < NT; ++qt) {
         st.l[qt] = 0.25f * walk.den[qt][0];  // each of the four lanes that share a query has the whole sum
-        if constexpr (KV8) {
+    }
+    finish<NT>(st, w * NT, NT, G, g, row0, c, Hq, Hkv, parts ? pl.item_direct[item] : 1, parts ? pl.item_part[item] : 0, pl.g_max, out, part_o,
+               part_ml, lane);
+}
+
+// The same attention in eight waves of two query tiles, one phase after the other, two waves a SIMD: the kernel for the
+// FP8 cache, whose codes pass through registers that k_attn_prefill does not have (32000 tokens, 512 rows 281 us, there 293; 8 chunks
+// of 64 rows over 500 tokens 31 / 42), and for pieces of up to kShortPiece tokens, where a wave's first and last groups, which
+// nothing hides, are most of the walk (bf16 here / there: 51 rows alone 11.2 / 13.7, pieces of 364 tokens 33.2 / 34.5, of 516
+// tokens 36.0 / 35.2, whole walks of 2256 tokens 186 / 161).
+constexpr int kShortWaves = 8, kShortNT = 2, kShortPiece = 512;
+static_assert(kShortWaves * kShortNT == kPrefillWaves * kPrefillNT, "the plan's groups fit both");
+
+// compute_group for a group that sits in LDS as fragments (src[i * 64]: K fragments i = 0..7, then
+// V^T fragments) with the wave's Q fragments in registers (qr[qt][ks]).  A wave issues in order and a
+// fragment read takes a few hundred cycles to come back, so the reads are batched ahead of the MFMAs
+// that need them instead of sitting between them: the eight K fragments at the top, the eight V^T
+// fragments as soon as the S^T MFMAs are issued (into the registers the K fragments leave), so that
+// they travel while the softmax arithmetic runs and the P V MFMAs follow each other without a wait.
+template <int NT, bool tail>
+__device__ __forceinline__ void compute_group_lds(State<NT> &st, const bf16x8 *__restrict__ src, const bf16x8 (&qr)[NT][kKS],
+                                                  int left, const int (&stag)[NT], int lane) {
+    const int q = lane >> 4;
+    const int tbase = 16 * (q >> 1) + 8 * (q & 1);
+    float sv[NT][8];
+    __builtin_amdgcn_s_setprio(1);  // matrix-core sections run at raised priority, see prefill_walk_short
+    {
+        f32x4 s0[NT], s1[NT];
+#pragma unroll
+        for (int qt = 0; qt < NT; ++qt) { s0[qt] = f32x4{0.f, 0.f, 0.f, 0.f}; s1[qt] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+        bf16x8 kf[2 * kKS];
+#pragma unroll
+        for (int i = 0; i < 2 * kKS; ++i) kf[i] = src[i * 64];
+        __builtin_amdgcn_sched_barrier(0);  // all reads first
+#pragma unroll
+        for (int ks = 0; ks < kKS; ++ks) {
+#pragma unroll
+            for (int qt = 0; qt < NT; ++qt) {
+                s0[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks], qr[qt][ks], s0[qt], 0, 0, 0);
+                s1[qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kKS + ks], qr[qt][ks], s1[qt], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int qt = 0; qt < NT; ++qt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {  // raw scores, see compute_group
+                sv[qt][i] = s0[qt][i];
+                sv[qt][4 + i] = s1[qt][i];
+            }
+    }
+    __builtin_amdgcn_s_setprio(0);
+    bf16x8 vf[kDT];
+#pragma unroll
+    for (int dt = 0; dt < kDT; ++dt) vf[dt] = src[(2 * kKS + dt) * 64];
+    __builtin_amdgcn_sched_barrier(0);  // the reads stay ahead of the arithmetic
+    bf16x8 pb[NT];
+#pragma unroll
+    for (int qt = 0; qt < NT; ++qt) {
+        if (tail) {
+            const int lim = left - stag[qt];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (tbase + e >= lim) sv[qt][e] = -INFINITY;
+        }
+        float mx = sv[qt][0];
+#pragma unroll
+        for (int e = 1; e < 8; ++e) mx = fmaxf(mx, sv[qt][e]);
+        if (__any(mx > st.m[qt] + kSlack)) {  // see compute_group: lazy softmax reference
+            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            const float m_old = st.m[qt];
+            const float m_new = fmaxf(m_old, mx);
+            st.m[qt] = m_new;
+            float alpha = (tail && m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(m_old - m_new);
+            st.l[qt] *= alpha;
+#pragma unroll
+            for (int dt = 0; dt < kDT; ++dt) {
+                st.o[dt][qt][0] *= alpha; st.o[dt][qt][1] *= alpha; st.o[dt][qt][2] *= alpha; st.o[dt][qt][3] *= alpha;
+            }
+        }
+        const float m_ref = st.m[qt];
+        float rs = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float p = __builtin_amdgcn_exp2f(sv[qt][e] - m_ref);
+            if (tail && m_ref == -INFINITY) p = 0.f;
+            rs += p;
+            pb[qt][e] = (__bf16)p;
+        }
+        st.l[qt] += rs;
+    }
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int dt = 0; dt < kDT; ++dt) {
+        if (tail) {  // stale cache bytes past the end may hold anything: zero those V columns
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (tbase + e >= left) vf[dt][e] = (__bf16)0.f;
+        }
+#pragma unroll
+        for (int qt = 0; qt < NT; ++qt) st.o[dt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], pb[qt], st.o[dt][qt], 0, 0, 0);
+    }
+    __builtin_amdgcn_s_setprio(0);
+}
+
+// Half of a group's loads: part 0 = the 8 K fragments, part 1 = the 8 V^T fragments, in the order
+// they take in a KVFrag (k[t][ks] as 4t + ks, then v[dt]).
+__device__ __forceinline__ void load_half(bf16x8 (&h)[8], int part, const bf16_t *__restrict__ pool, int blk0, int blk1, int c,
+                                          int Hkv, int lane) {
+    const int m = lane & 15, q = lane >> 4;
+    const size_t head_stride = (size_t)2 * kBk * kD;
+    if (part == 0) {
+        const bf16_t *kb = pool + ((size_t)((m >> 3) ? blk1 : blk0) * Hkv + c) * head_stride;
+        const int tok0 = 8 * ((m >> 2) & 1) + (m & 3);
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int ks = 0; ks < kKS; ++ks) h[t * kKS + ks] = *(const bf16x8 *)(kb + (size_t)(tok0 + 4 * t) * kD + 32 * ks + 8 * q);
+    } else {
+        const bf16_t *vb = pool + ((size_t)((q >> 1) ? blk1 : blk0) * Hkv + c) * head_stride + (size_t)kBk * kD;
+#pragma unroll
+        for (int dt = 0; dt < kDT; ++dt) h[dt] = *(const bf16x8 *)(vb + (size_t)(16 * dt + m) * kBk + 8 * (q & 1));
+    }
+}
+static_assert(2 * kKS == 8 && kDT == 8, "a half group is 8 fragments");
+
+// The same half group from an FP8 cache: raw codes, r[i] = the 8 codes that become fragment i
+// (K: i = 4 t + k-step, in the k-step order of KVRaw8; V^T: i = d tile).
+__device__ __forceinline__ void load_half8(uint2 (&r)[8], int part, const uint8_t *__restrict__ pool, int blk0, int blk1, int c,
+                                           int Hkv, int lane) {
+    const int m = lane & 15, q = lane >> 4;
+    const size_t head_stride = (size_t)2 * kBk * kD;
+    if (part == 0) {
+        const uint8_t *kb = pool + ((size_t)((m >> 3) ? blk1 : blk0) * Hkv + c) * head_stride;
+        const int tok0 = 8 * ((m >> 2) & 1) + (m & 3);
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int sl = 0; sl < 2; ++sl) {
+                const uint4 v = *(const uint4 *)(kb + (size_t)(tok0 + 4 * t) * kD + 64 * sl + 16 * q);
+                r[4 * t + 2 * sl] = uint2{v.x, v.y};
+                r[4 * t + 2 * sl + 1] = uint2{v.z, v.w};
+            }
+    } else {
+        const uint8_t *vb = pool + ((size_t)((q >> 1) ? blk1 : blk0) * Hkv + c) * head_stride + (size_t)kBk * kD;
+#pragma unroll
+        for (int dt = 0; dt < kDT; ++dt) r[dt] = *(const uint2 *)(vb + (size_t)(16 * dt + m) * kBk + 8 * (q & 1));
+    }
+}
+
+// Short prefill walk: the eight waves hold different query tiles and every wave needs every group, so a
+// group is loaded once -- in round r wave w loads half (w & 1: K or V^T) of group 4r + w/2 into
+// registers, one round ahead -- published to an LDS ring as MFMA fragments in lane order, and read
+// from there by all eight.  The ring has two stages of one round each: a wave publishes round r into
+// stage r % 2, whose last readers (round r - 2) all passed the barrier of round r - 1, so one barrier
+// per round is enough and the waves may drift up to a round apart (the matrix-core work of one then
+// overlaps the softmax arithmetic of the other on the same SIMD).  ring: [2][4][16][64] x 16 B.
+template <int NT, bool KV8>
+__device__ __forceinline__ void prefill_walk_short(State<NT> &st, const void *__restrict__ pool_v, const int *__restrict__ blds,
+                                             int n_blk, int n_tok, int left, int n_clean, const int (&stag)[NT], bool busy, int w, int c,
+                                             int Hkv, bf16x8 *__restrict__ ring, const bf16x8 (&qr)[NT][kKS], int lane) {
+    // left: tokens of the sequence from this piece's first on (n_tok or more); busy: this wave holds queries
+    const int n_grp = (n_tok + kGrp - 1) / kGrp;  // groups, the masked ones included
+    const int n_round = (n_grp + 3) / 4;          // the same for every wave
+    const int part = w & 1, gl = w >> 1;
+    auto blk_of = [&](int grp, int which) {
+        return __builtin_amdgcn_readfirstlane(blds[min(grp * 2 + which, n_blk - 1)]);
+    };
+    bf16x8 h[8];
+    uint2 h8[8];
+    auto load = [&](int grp) {
+        if constexpr (KV8) load_half8(h8, part, (const uint8_t *)pool_v, blk_of(grp, 0), blk_of(grp, 1), c, Hkv, lane);
+        else load_half(h, part, (const bf16_t *)pool_v, blk_of(grp, 0), blk_of(grp, 1), c, Hkv, lane);
+    };
+    if (gl < n_grp) load(gl);
+#pragma nounroll
+    for (int r = 0; r < n_round; ++r) {
+        bf16x8 *stage = ring + (size_t)(r & 1) * 4 * 16 * 64;
+        const int mine = 4 * r + gl;
+        if (mine < n_grp) {
+            bf16x8 *dst = stage + ((size_t)gl * 16 + part * 8) * 64 + lane;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if constexpr (KV8) dst[i * 64] = cvt8(h8[i].x, h8[i].y);  // codes are exact in bf16
+                else dst[i * 64] = h[i];
+            }
+        }
+        if (mine + 4 < n_grp) load(mine + 4);
+        __syncthreads();
+        if (!busy) continue;  // a wave of a partly filled group only helps to load
+        // the round's unmasked groups, then its masked ones: two loops of one code path each (with both paths
+        // in one loop body the accumulators are copied between the registers the two paths leave them in)
+        const int n_here = min(4, n_grp - 4 * r), n_plain = max(0, min(n_here, n_clean - 4 * r));
+#pragma nounroll
+        for (int gi = 0; gi < n_plain; ++gi)
+            compute_group_lds<NT, false>(st, stage + (size_t)gi * 16 * 64 + lane, qr, kGrp, stag, lane);
+#pragma nounroll
+        for (int gi = n_plain; gi < n_here; ++gi)
+            compute_group_lds<NT, true>(st, stage + (size_t)gi * 16 * 64 + lane, qr, left - (4 * r + gi) * kGrp, stag, lane);
+    }
+}
+
+template <bool KV8>
+__global__ void __launch_bounds__(64 * kShortWaves) k_attn_prefill_short(const bf16_t *__restrict__ qg, const void *__restrict__ pool,
+                                                                     const int32_t *__restrict__ bt, int max_blocks, AttnPlan pl,
+                                                                     bf16_t *__restrict__ out, float *__restrict__ part_o,
+                                                                     float *__restrict__ part_ml, int Hq, int Hkv, float v_scale) {
+    constexpr int NT = kShortNT;
+    extern __shared__ float lds[];
+    const int item = blockIdx.x / Hkv, c = blockIdx.x % Hkv;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int s = pl.item_seq[item];
+    const bool parts = pl.item_begin != nullptr;  // else every piece is a whole walk
+    const int begin = parts ? pl.item_begin[item] : 0, left = pl.seq_kvlen[s] - begin, n_tok = parts ? pl.item_len[item] : left;
+    const int row0 = pl.seq_row0[s], T = pl.seq_rows[s];
+    const int g = Hq / Hkv, G = T * g;
+    const int m = lane & 15, q = lane >> 4;
+    const int32_t *btr = bt + (size_t)pl.seq_bt[s] * max_blocks + begin / kBk;
+    // LDS: [KV ring, two stages of 64 KB] [block ids]; the wave's Q fragments (B operands) stay in registers
+    bf16x8 *ring = (bf16x8 *)lds;
+    bf16x8 qr[NT][kKS];
+#pragma unroll
+    for (int qt = 0; qt < NT; ++qt) {
+        int j = 16 * (w * NT + qt) + m;
+        const bf16_t *qp = qg + ((size_t)(row0 + j / g) * Hq + c * g + j % g) * kD;
+#pragma unroll
+        for (int ks = 0; ks < kKS; ++ks) {  // FP8 cache: the k-step order of KVRaw8
+            const int d0 = KV8 ? 64 * (ks >> 1) + 16 * q + 8 * (ks & 1) : 32 * ks + 8 * q;
+            qr[qt][ks] = j < G ? *(const bf16x8 *)(qp + d0) : zero8();
+        }
+    }
+    int *blds = (int *)(ring + 2 * 4 * 16 * 64);
+    const int n_blk = (n_tok + kBk - 1) / kBk;
+    for (int i = threadIdx.x; i < n_blk; i += 64 * kShortWaves) blds[i] = btr[i];
+    // every load so far has landed: the walk's waits then count its own prefetch loads only (left to its own
+    // bookkeeping the compiler waits for the Q fragments inside the loop, and with them for the prefetch)
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    __syncthreads();
+
+    State<NT> st;
+    int stag[NT];
+#pragma unroll
+    for (int qt = 0; qt < NT; ++qt) {
+        st.m[qt] = -INFINITY;
+        st.l[qt] = 0.f;
+#pragma unroll
+        for (int dt = 0; dt < kDT; ++dt) st.o[dt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        stag[qt] = T - 1 - min((16 * (w * NT + qt) + m) / g, T - 1);
+    }
+    const int n_clean = max(0, left - (T - 1)) / kGrp;  // groups valid for every query (further ones may be in later pieces)
+    const bool busy = __builtin_amdgcn_readfirstlane(16 * w * NT) < G;
+    prefill_walk_short<NT, KV8>(st, pool, blds, n_blk, n_tok, left, n_clean, stag, busy, w, c, Hkv, ring, qr, lane);
+    if constexpr (KV8) {
+#pragma unroll
+        for (int qt = 0; qt < NT; ++qt)
 #pragma unroll
             for (int dt = 0; dt < kDT; ++dt) {
                 st.o[dt][qt][0] *= v_scale; st.o[dt][qt][1] *= v_scale; st.o[dt][qt][2] *= v_scale; st.o[dt][qt][3] *= v_scale;
             }
-        }
     }
     finish<NT>(st, w * NT, NT, G, g, row0, c, Hq, Hkv, parts ? pl.item_direct[item] : 1, parts ? pl.item_part[item] : 0, pl.g_max, out, part_o,
                part_ml, lane);
@@ -1232,18 +1445,30 @@ hipError_t launch_attn_prefill_mfma(const Dims &dm, const void *q, const void *p
     if (pl.n_items <= 0) return hipSuccess;
     if (!pl.causal || pl.chunk > kPrefillMaxCtx) return hipErrorInvalidValue;
     const size_t shm = kPrefillRing + (size_t)((pl.chunk + kBk - 1) / kBk) * 4;  // two ring stages + the block ids
-    auto launch = [&](auto kernel, bool &attr_set) -> hipError_t {
-        if (!attr_set) {
-            hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
-            if (e != hipSuccess) return e;
-            attr_set = true;
-        }
-        hipLaunchKernelGGL(kernel, dim3(pl.n_items * dm.Hkv), dim3(64 * kPrefillWaves), shm, st, (const bf16_t *)q, pool, bt, max_blocks, pl,
-                           (bf16_t *)out, part_o, part_ml, dm.Hq, dm.Hkv, dm.kv8 ? dm.v_scale : 1.f);
+    const dim3 grid(pl.n_items * dm.Hkv);
+    auto allow_lds = [](auto kernel, bool &set) {
+        if (set) return hipSuccess;
+        const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+        set = e == hipSuccess;
+        return e;
+    };
+    if (!dm.kv8 && pl.chunk > kShortPiece) {
+        static bool set = false;
+        const hipError_t e = allow_lds(k_attn_prefill, set);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_attn_prefill, grid, dim3(64 * kPrefillWaves), shm, st, (const bf16_t *)q, (const bf16_t *)pool, bt, max_blocks, pl,
+                           (bf16_t *)out, part_o, part_ml, dm.Hq, dm.Hkv);
+        return hipGetLastError();
+    }
+    auto launch = [&](auto kernel, bool &set) {
+        const hipError_t e = allow_lds(kernel, set);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * kShortWaves), shm, st, (const bf16_t *)q, pool, bt, max_blocks, pl, (bf16_t *)out, part_o,
+                           part_ml, dm.Hq, dm.Hkv, dm.kv8 ? dm.v_scale : 1.f);
         return hipGetLastError();
     };
     static bool set_bf16 = false, set_fp8 = false;
-    return dm.kv8 ? launch(k_attn_prefill<true>, set_fp8) : launch(k_attn_prefill<false>, set_bf16);
+    return dm.kv8 ? launch(k_attn_prefill_short<true>, set_fp8) : launch(k_attn_prefill_short<false>, set_bf16);
 }
 
 hipError_t launch_attn_decode_mfma(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,

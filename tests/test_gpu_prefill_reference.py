@@ -39,7 +39,7 @@ def _pool(shape, batch, kind, reach):
 @pytest.mark.parametrize("shape", [synth.LLAMA_SMALL, synth.QWEN_SMALL], ids=lambda s: s.name)
 @pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
 @pytest.mark.parametrize("kind", ["slope", "step"])
-@pytest.mark.parametrize("limit", [0, 128])
+@pytest.mark.parametrize("limit", [0, 128, 1024])  # 1024: whole walks, of more than 512 tokens: the kernel for long pieces
 def test_scores_far_from_the_reference(shape, fp8, kind, limit):
     print("case: far scores", shape.name, "fp8", fp8, kind, "pieces", limit, flush=True)
     base = synth.make_base(shape, seed=3, norm_ones=False)
