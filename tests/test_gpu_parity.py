@@ -129,9 +129,8 @@ def test_decode_row_counts_of_every_gemm_tile(rows):
 
 @pytest.mark.parametrize("rows,d_ffn", [(330, 10304), (150, 20608), (131, 20608), (160, 20608), (161, 20608)])
 def test_decode_wide_ffn_takes_the_wide_projection_gemm(rows, d_ffn):
-    # A fused gate/up projection wide enough for 160 tiles of 192 x 256 goes to the register-staged GEMM kernel
-    # (two row tiles of 192 at 330 rows; at most 160 rows: the 160 x 256 tile with three slabs of loads in flight,
-    # partly filled at 131 and 150 rows, full at 160; 161 rows: one 192-row tile again; the last column tile is
+    # A fused gate/up projection wide enough for 160 tiles of 192 x 256 goes to the 256 wide tiles
+    # (two row tiles of 192 at 330 rows; at most 160 rows: the 160 x 256 tile, partly filled at 131 and 150 rows, full at 160; 161 rows: one 192-row tile again; the last column tile is
     # ragged: d_ffn is not a multiple of 128).  Element by element against the oracle; the down projection then
     # contracts over the same odd width.
     _say("case: wide ffn", rows, "rows, d_ffn", d_ffn)
