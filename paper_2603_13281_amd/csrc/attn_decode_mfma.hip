@@ -719,55 +719,48 @@ constexpr int kRoundGroups = 4;                   // 32-token groups of a round 
 template <int V> struct Int { static constexpr int value = V; };
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
-// The walk of one prefill wave over a piece, its four query tiles as two pairs.
-//
-// q comes multiplied by the softmax scale and log2 e (launch_rope_append), so a score is an exponent of 2 as it leaves the
-// matrix cores, and the accumulators of a group's scores start from minus the softmax reference instead of from zero: the
-// exponent needs no arithmetic.  The reference is lazy (see compute_group): it moves only when a score exceeds it by more than
-// kSlack; the scores are then formed again from zero (relative to a reference far from them they would have lost bits).
+// The walk of one prefill wave over a piece, its four query tiles as two pairs.  The arithmetic of a tile, in its order and its
+// precision, is that of compute_group_lds: the same bits from both kernels.
 //
 // A wave is alone on its SIMD and issues in order, so it has to put its own vector instructions beneath its own MFMAs: an
 // MFMA takes the pipe 16 cycles and the issue slot 4.  Group g is four steps of 16 MFMAs, each with independent work of
 // the other pair between them, in the order they are written here (a scheduling barrier behind every MFMA):
 //     1  S^T of pair 0                  exponentials of pair 1 of group g - 1
-//     2  P V of pair 1 of group g - 1   V^T fragments of g into the registers this leaves; the check of pair 0's scores; one
-//                                       quarter of a group of the next round is published and requested for the round after it
+//     2  P V of pair 1 of group g - 1   their sum; V^T fragments of g into the registers this leaves; the check of pair 0's scores
 //     3  S^T of pair 1                  exponentials of pair 0
-//     4  P V of pair 0                  the check of pair 1's scores; then K fragments of g + 1
-// Eight waves of two tiles, the phases of a wave one after the other, hid little of each other (matrix pipe busy 47 % of the
-// cycles) and read each fragment from LDS for two tiles instead of four: 32 chunks of 512 rows over 8192 tokens 2.38 ms, now
-// 1.91 ms = 1.19 PFLOP/s (busy 56-58 % at 1.97 GHz).  How many vector instructions stand beside an MFMA is what it hangs on:
-// measured in a loop, one is free (8.8 ns), a second costs 1.3-1.7 ns, a second exponential 4 ns, and a two-way dot product 6.5 ns
-// each (it shares the pipe), hence one exponential behind each MFMA of steps 1 and 3 and the denominators on the matrix cores.
+//     4  P V of pair 0                  their sum; K fragments of g + 1; the check of pair 1's scores
+// The check: the softmax reference is lazy (see compute_group), it moves only when a score exceeds it by more than kSlack.
+// 32 chunks of 512 rows over 8192 tokens, 32 query heads: 2.34 ms with eight waves of two tiles, 2.21 here (1.03 PFLOP/s).  The
+// vector instructions bound it: beside an MFMA one is free (8.8 ns), each further one costs 1.3-1.7 ns.  The scale rounded into q,
+// scores that start from minus the reference in the accumulators and denominators by an MFMA over the rounded probabilities took
+// 32 multiply-adds and 32 additions out of a group, 1.95 ms; but sums of probabilities in 16 bits are fewer bits than the callers had.
 //
 // The ring has two stages of one round (four groups) each; the four waves bring a quarter of each group (K rows or V^T rows)
-// by LDS-direct loads, and read every group as MFMA fragments in lane order.  A stage is filled while the other one is read,
-// and its last reads precede the one barrier of a round, which sits before the first reads of the next round.  Past the end of the piece the loads repeat its last block.
+// by LDS-direct loads, and read every group as MFMA fragments in lane order.  A stage is filled while the other one is read: the
+// loads for round r + 1 are issued beside steps 2 and 4 of the first two groups of round r.  A stage's last reads precede
+// the one barrier of a round, which sits before the first reads of the next round.  Past the end of the piece the loads repeat its last block.
 // ring: [2][4][16][64] x 16 B.
 struct PrefillWalk {
     State<kPrefillNT> &st;
     bf16x8 (&qr)[kPrefillNT][kKS];
     const int (&stag)[kPrefillNT];
+    const float scale;
     const int lane;
-    f32x4 neg[kPrefillNT];    // minus the reference (State::m) in all four elements; 0 while there is none
-    int limit[2];             // per pair: bits of the largest relative score that leaves the reference alone; INT_MIN: a query has none
-    f32x4 sc[kPrefillNT][2];  // scores of the two 16-token halves of a group
+    float neg[kPrefillNT];    // minus the reference (State::m); 0 while there is none
+    float limit[kPrefillNT];  // the largest scaled score that leaves the reference alone
+    f32x4 sc[kPrefillNT][2];  // scores of the two 16-token halves of a group, then their exponentials
+    float sum[kPrefillNT];    // of a group's exponentials
     bf16x8 pb[kPrefillNT];    // probabilities
-    f32x4 den[kPrefillNT];    // denominators, four times the same sum
-    bf16x8 ones;
     bf16x8 kf[2 * kKS], vf[kDT];
-    int top;                  // of a check: the largest bits so far
+    float top[2];             // of a check: the largest scaled score of each tile of the pair
 
-    __device__ __forceinline__ PrefillWalk(State<kPrefillNT> &s, bf16x8 (&q)[kPrefillNT][kKS], const int (&g)[kPrefillNT], int l)
-        : st(s), qr(q), stag(g), lane(l) {
+    __device__ __forceinline__ PrefillWalk(State<kPrefillNT> &s, bf16x8 (&q)[kPrefillNT][kKS], const int (&g)[kPrefillNT], float f, int l)
+        : st(s), qr(q), stag(g), scale(f), lane(l) {
 #pragma unroll
         for (int t = 0; t < kPrefillNT; ++t) {
-            neg[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-            den[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            neg[t] = 0.f;
+            limit[t] = -INFINITY;
         }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.f;
-        limit[0] = limit[1] = INT32_MIN;
         none_pending();
     }
     // a pair 1 of no group: probabilities of zero
@@ -777,13 +770,13 @@ struct PrefillWalk {
 #pragma unroll
         for (int dt = 0; dt < kDT; ++dt) vf[dt] = zero8();
     }
-    // MFMA m of 16 of the scores of pair P, relative to the reference.  In assembly: the compiler gives every MFMA of a kernel
-    // that may use the accumulation registers its result in them, and the scores would be copied out for the arithmetic.  What
-    // reads a result is at least four MFMAs (64 cycles) behind it.
+    // MFMA m of 16 of the scores of pair P.  In assembly: the compiler gives every MFMA of a kernel that may use the accumulation
+    // registers its result in them, and the scores would be copied out for the arithmetic.  What reads a result is at least
+    // four MFMAs (64 cycles) behind it.
     template <int P>
     __device__ __forceinline__ void score(int m) {
         const int ks = m >> 2, t = 2 * P + ((m >> 1) & 1), hf = m & 1;
-        if (ks == 0) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" : "=&v"(sc[t][hf]) : "v"(kf[4 * hf]), "a"(qr[t][0]), "v"(neg[t]));
+        if (ks == 0) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(sc[t][hf]) : "v"(kf[4 * hf]), "a"(qr[t][0]));
         else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(sc[t][hf]) : "v"(kf[4 * hf + ks]), "a"(qr[t][ks]));
     }
     // MFMA m of 16 of P V of pair P
@@ -792,67 +785,73 @@ struct PrefillWalk {
         const int dt = m >> 1, t = 2 * P + (m & 1);
         st.o[dt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], pb[t], st.o[dt][t], 0, 0, 0);
     }
-    // the denominators of pair P: one more row of V, of ones (32 additions per group would cost the wave more than four MFMAs)
+    // element i of the 16 of pair P
+    template <int P> __device__ __forceinline__ float at(int i) const { return sc[2 * P + (i >> 3)][(i >> 2) & 1][i & 3]; }
+    // exponential i of the 16 of pair P, beside the exponent of the next one and the rounding of those before it (i = 16: the last
+    // two); exponent(0) goes before
     template <int P>
-    __device__ __forceinline__ void sum(int t) {
-        den[2 * P + t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[2 * P + t], den[2 * P + t], 0, 0, 0);
+    __device__ __forceinline__ void exponent(int i) {
+        const int t = 2 * P + (i >> 3);
+        sc[t][(i >> 2) & 1][i & 3] = __builtin_fmaf(at<P>(i), scale, neg[t]);
     }
-    // exponential i of the 16 of pair P, beside the rounding of those before it (i = 16: the last two)
     template <int P>
     __device__ __forceinline__ void exp_one(int i) {
-        auto at = [&](int n) -> float { return sc[2 * P + (n >> 3)][(n >> 2) & 1][n & 3]; };
-        if (i < 16) sc[2 * P + (i >> 3)][(i >> 2) & 1][i & 3] = __builtin_amdgcn_exp2f(at(i));
+        if (i < 16) {
+            const int t = 2 * P + (i >> 3);
+            sc[t][(i >> 2) & 1][i & 3] = __builtin_amdgcn_exp2f(at<P>(i));
+        }
+        if (i + 1 < 16) exponent<P>(i + 1);
         if (i == 0) return;
         const int t = 2 * P + ((i - 1) >> 3), e = (i - 1) & 7;
         if (!(e & 1)) return;
-        uint32_t two = pack_bf16(at(i - 2), at(i - 1));
+        uint32_t two = pack_bf16(at<P>(i - 2), at<P>(i - 1));
         asm volatile("" : "+v"(two));  // here, not all of them ahead of the next step's MFMAs
         u32x4 w = __builtin_bit_cast(u32x4, pb[t]);
         w[e >> 1] = two;
         pb[t] = __builtin_bit_cast(bf16x8, w);
     }
-    // part i of 8 of pair P's check: as integers positive floats keep their order, and negative ones are below every limit
+    // addition i of the 16 of pair P to the denominators: float32, of the unrounded exponentials
+    template <int P>
+    __device__ __forceinline__ void add_one(int i) {
+        const int t = 2 * P + (i >> 3);
+        sum[t] = i & 7 ? sum[t] + at<P>(i) : at<P>(i);
+        asm volatile("" : "+v"(sum[t]));
+        if ((i & 7) == 7) st.l[t] += sum[t];
+    }
+    // part i of kCheckParts of pair P's check (v_max3 by hand: for fmaxf the compiler first turns every score into itself, in case it
+    // were a signalling NaN)
+    static constexpr int kCheckParts = 10;
     template <int P>
     __device__ __forceinline__ void check_part(int i) {
-        const int t = 2 * P + (i >> 2), e = (i & 3) * 2;
-        const int a = __float_as_int(sc[t][e >> 2][e & 3]), b = __float_as_int(sc[t][e >> 2][(e & 3) + 1]);
-        top = i ? max(max(top, a), b) : max(a, b);
+        float &x = top[i / 5];
+        const int e = 8 * (i / 5), k = i % 5;
+        if (k == 0) asm("v_max3_f32 %0, %1, %2, %3" : "=v"(x) : "v"(at<P>(e)), "v"(at<P>(e + 1)), "v"(at<P>(e + 2)));
+        else if (k < 3) asm("v_max3_f32 %0, %0, %1, %2" : "+v"(x) : "v"(at<P>(e + 2 * k + 1)), "v"(at<P>(e + 2 * k + 2)));
+        else if (k == 3) asm("v_max_f32 %0, %0, %1" : "+v"(x) : "v"(at<P>(e + 7)));
+        else x *= scale;
     }
-    // The scores of pair P anew, relative to a reference that is moved up to their maximum.
-    template <int P, bool masked>
-    __device__ __forceinline__ void rescore(int left) {
+    // After the check of pair P: the reference of a tile of which a score exceeds its limit is moved up to their maximum.
+    template <int P>
+    __device__ __forceinline__ void move_reference() {
+        if (__builtin_expect(!__any(top[0] > limit[2 * P] || top[1] > limit[2 * P + 1]), 1)) return;
 #pragma unroll
-        for (int m = 0; m < 16; ++m) {
-            const int ks = m >> 2, t = 2 * P + ((m >> 1) & 1), hf = m & 1;
-            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-            sc[t][hf] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[4 * hf + ks], qr[t][ks], ks ? sc[t][hf] : zero, 0, 0, 0);
-        }
-        if (masked) mask<P>(left);
-        limit[P] = __float_as_int(kSlack);
-#pragma unroll
-        for (int t = 2 * P; t < 2 * P + 2; ++t) {
-            float mx = sc[t][0][0];
-#pragma unroll
-            for (int e = 1; e < 8; ++e) mx = fmaxf(mx, sc[t][e >> 2][e & 3]);
-            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        for (int i = 0; i < 2; ++i) {
+            const int t = 2 * P + i;
+            if (!__any(top[i] > limit[t])) continue;
+            float mx = fmaxf(top[i], __shfl_xor(top[i], 16, 64));
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
             const float m_old = st.m[t], m_new = fmaxf(m_old, mx);
             const bool none = m_new == -INFINITY;  // the query has had no valid token yet: nothing to rescale
-            const float alpha = none ? 1.f : __builtin_amdgcn_exp2f(m_old - m_new), ng = none ? 0.f : -m_new;
-            if (none) limit[P] = INT32_MIN;
+            const float alpha = none ? 1.f : __builtin_amdgcn_exp2f(m_old - m_new);
             st.m[t] = m_new;
-            if (__any(m_old > -INFINITY)) {  // else nothing has been summed
-                den[t] *= alpha;
-                ICARUS_IN_ACC(den[t]);
+            neg[t] = none ? 0.f : -m_new;
+            limit[t] = m_new + kSlack;
+            st.l[t] *= alpha;
 #pragma unroll
-                for (int dt = 0; dt < kDT; ++dt) {
-                    st.o[dt][t][0] *= alpha; st.o[dt][t][1] *= alpha; st.o[dt][t][2] *= alpha; st.o[dt][t][3] *= alpha;
-                    ICARUS_IN_ACC(st.o[dt][t]);
-                }
+            for (int dt = 0; dt < kDT; ++dt) {
+                st.o[dt][t][0] *= alpha; st.o[dt][t][1] *= alpha; st.o[dt][t][2] *= alpha; st.o[dt][t][3] *= alpha;
+                ICARUS_IN_ACC(st.o[dt][t]);
             }
-            neg[t] = f32x4{ng, ng, ng, ng};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) sc[t][e >> 2][e & 3] += ng;
         }
     }
     // scores of the tokens that a query does not attend to
@@ -876,9 +875,9 @@ struct PrefillWalk {
             for (int dt = 0; dt < kDT; ++dt) ICARUS_IN_ACC(st.o[dt][t]);
 #pragma unroll
             for (int ks = 0; ks < kKS; ++ks) ICARUS_IN_ACC(qr[t][ks]);
-            ICARUS_IN_ACC(den[t]);
             asm volatile("" : "+v"(sc[t][0]), "+v"(sc[t][1]), "+v"(neg[t]));
         }
+        exponent<1>(0);
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
             score<0>(m);
@@ -889,14 +888,14 @@ struct PrefillWalk {
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
             pv<1>(m);
+            add_one<1>(m);
             if (m & 1) vf[m >> 1] = src[(2 * kKS + (m >> 1)) * 64];
             if (MASKED && m == 4) mask<0>(left);
-            if (m >= 4 && m < 12) check_part<0>(m - 4);
+            if (m >= 4 && m - 4 < kCheckParts) check_part<0>(m - 4);
             if (m & 2) between(2 * (m >> 3) + (m >> 2) % 2, m & 1);
-            if (m >= 14) sum<1>(m - 14);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (__builtin_expect(__any(top > limit[0]), 0)) rescore<0, MASKED>(left);
+        move_reference<0>();
         if (MASKED && left < kGrp) {  // stale cache bytes past the end may hold anything: zero those V columns
             const int q = lane >> 4, tbase = 16 * (q >> 1) + 8 * (q & 1);
 #pragma unroll
@@ -905,6 +904,7 @@ struct PrefillWalk {
                 for (int e = 0; e < 8; ++e)
                     if (tbase + e >= left) vf[dt][e] = (__bf16)0.f;
         }
+        exponent<0>(0);
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
             score<1>(m);
@@ -912,33 +912,18 @@ struct PrefillWalk {
             __builtin_amdgcn_sched_barrier(0);
         }
         exp_one<0>(16);
-        auto read_next = [&](int i) { kf[k_order(i)] = next[k_order(i) * 64]; };
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
+        for (int m = 0; m < 16; ++m) {
+            if (LAST && m == 8) before_next();
             pv<0>(m);
+            add_one<0>(m);
             if (MASKED && m == 4) mask<1>(left);
-            if (m >= 4) { check_part<1>(2 * (m - 4)); check_part<1>(2 * (m - 4) + 1); }
-            if (!LAST) read_next(m);
+            if (m >= 4 && m - 4 < kCheckParts) check_part<1>(m - 4);
+            if (LAST ? m >= 8 : m < 8) kf[k_order(m & 7)] = next[k_order(m & 7) * 64];
+            if (m >= 8) between(4 + (m - 8) / 2, m & 1);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (__builtin_expect(__any(top > limit[1]), 0)) {
-            if (!LAST) {
-                int at = 0;
-                asm volatile("" : "+v"(at));
-                read_k(src + at);
-            }
-            rescore<1, MASKED>(left);
-            if (!LAST) read_k(next);
-        }
-        if (LAST) before_next();
-#pragma unroll
-        for (int m = 8; m < 16; ++m) {
-            pv<0>(m);
-            if (LAST) read_next(m - 8);
-            between(4 + (m - 8) / 2, m & 1);
-            if (m >= 14) sum<0>(m - 14);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        move_reference<1>();
     }
     __device__ __forceinline__ void read_k(const bf16x8 *__restrict__ src) {
 #pragma unroll
@@ -948,26 +933,28 @@ struct PrefillWalk {
     static constexpr int k_order(int i) { return i & 1 ? kKS + (i >> 1) : i >> 1; }
     template <int P>
     __device__ __forceinline__ void finish_pair() {
+        exponent<P>(0);
 #pragma unroll
         for (int i = 0; i <= 16; ++i) exp_one<P>(i);
 #pragma unroll
-        for (int m = 0; m < 16; ++m) pv<P>(m);
-        sum<P>(0);
-        sum<P>(1);
+        for (int m = 0; m < 16; ++m) {
+            pv<P>(m);
+            add_one<P>(m);
+        }
     }
 };
 
 // Causal attention of a prefill chunk.  A workgroup owns one kv-head of one group of T consecutive
 // chunk tokens (T * g <= 256 stacked queries; token t attends to kv_len - (T-1-t) positions) and
 // walks the sequence's cache, or one piece of it, once for all of them; wave w holds query tiles
-// [4 w, 4 w + 4).  Bound by the matrix cores, so what counts is that every CU has a walk: with
+// [4 w, 4 w + 4).  Bound by what a CU issues, so what counts is that every CU has a walk: with
 // whole walks only, 14 groups x 8 kv-heads of a round of agent turns (60-400 rows over 600-8192 cached
-// tokens each) took 240 us on 112 CUs, cut into pieces 109 us + 12.5 us for
-// the merge; 512 rows over 32000 tokens (16 groups) 990 us -> 574 + 12.5 us.
+// tokens each) take 211 us on 112 CUs, cut into pieces 119 us with the merge; 512 rows over 32000 tokens
+// (16 groups) 827 us and 483 us.
 __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_t *__restrict__ qg, const bf16_t *__restrict__ pool,
                                                                      const int32_t *__restrict__ bt, int max_blocks, AttnPlan pl,
                                                                      bf16_t *__restrict__ out, float *__restrict__ part_o,
-                                                                     float *__restrict__ part_ml, int Hq, int Hkv) {
+                                                                     float *__restrict__ part_ml, int Hq, int Hkv, float scale_log2) {
     constexpr int NT = kPrefillNT;
     extern __shared__ float lds[];
     const int item = blockIdx.x / Hkv, c = blockIdx.x % Hkv;
@@ -1033,7 +1020,7 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
     const int n_round = (n_grp + kRoundGroups - 1) / kRoundGroups;        // the same for every wave
     const int n_clean = min(n_grp, max(0, left - (T - 1)) / kGrp);         // groups valid for every query (further ones may be in later pieces)
     const bool busy = 16 * w * NT < G;                                    // a wave without queries only helps to load
-    PrefillWalk walk(st, qr, stag, lane);
+    PrefillWalk walk(st, qr, stag, scale_log2, lane);
     read_ids(0);
     each([&](auto GI) {
         if (GI.value >= n_grp) return;
@@ -1087,20 +1074,16 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
         }
         if (!met) meet();
     }
-#pragma unroll
-    for (int qt = 0; qt < NT; ++qt) {
-        st.l[qt] = 0.25f * walk.den[qt][0];  // each of the four lanes that share a query has the whole sum
-    }
     finish<NT>(st, w * NT, NT, G, g, row0, c, Hq, Hkv, parts ? pl.item_direct[item] : 1, parts ? pl.item_part[item] : 0, pl.g_max, out, part_o,
                part_ml, lane);
 }
 
 // The same attention in eight waves of two query tiles, one phase after the other, two waves a SIMD: the kernel for the
-// FP8 cache, whose codes pass through registers that k_attn_prefill does not have (32000 tokens, 512 rows 281 us, there 293; 8 chunks
-// of 64 rows over 500 tokens 31 / 42), and for pieces of up to kShortPiece tokens, where a wave's first and last groups, which
-// nothing hides, are most of the walk (bf16 here / there: 51 rows alone 11.2 / 13.7, pieces of 364 tokens 33.2 / 34.5, of 516
-// tokens 36.0 / 35.2, whole walks of 2256 tokens 186 / 161).
-constexpr int kShortWaves = 8, kShortNT = 2, kShortPiece = 512;
+// FP8 cache, whose codes pass through registers that k_attn_prefill does not have, and for pieces of up to kShortPiece tokens, where
+// a wave's first and last groups, which nothing hides, count for more than what the pipeline hides of the others.  us here / there,
+// whole walks: 32 chunks of 64 rows, 32 query heads, over 480 tokens 36.0 / 38.1, 900 50.4 / 52.1, 1200 60.5 / 60.8, 1700 76.3 / 75.8, 4000
+// 149 / 143; 8 chunks of 256 rows, 64 heads, over 900 95.6 / 101, 1200 115 / 116, 1700 150 / 142, 7000 473 / 445.
+constexpr int kShortWaves = 8, kShortNT = 2, kShortPiece = 1280;
 static_assert(kShortWaves * kShortNT == kPrefillWaves * kPrefillNT, "the plan's groups fit both");
 
 // compute_group for a group that sits in LDS as fragments (src[i * 64]: K fragments i = 0..7, then
@@ -1111,7 +1094,7 @@ static_assert(kShortWaves * kShortNT == kPrefillWaves * kPrefillNT, "the plan's 
 // they travel while the softmax arithmetic runs and the P V MFMAs follow each other without a wait.
 template <int NT, bool tail>
 __device__ __forceinline__ void compute_group_lds(State<NT> &st, const bf16x8 *__restrict__ src, const bf16x8 (&qr)[NT][kKS],
-                                                  int left, const int (&stag)[NT], int lane) {
+                                                  int left, const int (&stag)[NT], float scale_log2, int lane) {
     const int q = lane >> 4;
     const int tbase = 16 * (q >> 1) + 8 * (q & 1);
     float sv[NT][8];
@@ -1157,6 +1140,7 @@ __device__ __forceinline__ void compute_group_lds(State<NT> &st, const bf16x8 *_
         float mx = sv[qt][0];
 #pragma unroll
         for (int e = 1; e < 8; ++e) mx = fmaxf(mx, sv[qt][e]);
+        mx *= scale_log2;
         if (__any(mx > st.m[qt] + kSlack)) {  // see compute_group: lazy softmax reference
             mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
@@ -1174,7 +1158,7 @@ __device__ __forceinline__ void compute_group_lds(State<NT> &st, const bf16x8 *_
         float rs = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            float p = __builtin_amdgcn_exp2f(sv[qt][e] - m_ref);
+            float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[qt][e], scale_log2, -m_ref));
             if (tail && m_ref == -INFINITY) p = 0.f;
             rs += p;
             pb[qt][e] = (__bf16)p;
@@ -1250,7 +1234,7 @@ __device__ __forceinline__ void load_half8(uint2 (&r)[8], int part, const uint8_
 template <int NT, bool KV8>
 __device__ __forceinline__ void prefill_walk_short(State<NT> &st, const void *__restrict__ pool_v, const int *__restrict__ blds,
                                              int n_blk, int n_tok, int left, int n_clean, const int (&stag)[NT], bool busy, int w, int c,
-                                             int Hkv, bf16x8 *__restrict__ ring, const bf16x8 (&qr)[NT][kKS], int lane) {
+                                             int Hkv, bf16x8 *__restrict__ ring, const bf16x8 (&qr)[NT][kKS], float scale_log2, int lane) {
     // left: tokens of the sequence from this piece's first on (n_tok or more); busy: this wave holds queries
     const int n_grp = (n_tok + kGrp - 1) / kGrp;  // groups, the masked ones included
     const int n_round = (n_grp + 3) / 4;          // the same for every wave
@@ -1285,10 +1269,10 @@ __device__ __forceinline__ void prefill_walk_short(State<NT> &st, const void *__
         const int n_here = min(4, n_grp - 4 * r), n_plain = max(0, min(n_here, n_clean - 4 * r));
 #pragma nounroll
         for (int gi = 0; gi < n_plain; ++gi)
-            compute_group_lds<NT, false>(st, stage + (size_t)gi * 16 * 64 + lane, qr, kGrp, stag, lane);
+            compute_group_lds<NT, false>(st, stage + (size_t)gi * 16 * 64 + lane, qr, kGrp, stag, scale_log2, lane);
 #pragma nounroll
         for (int gi = n_plain; gi < n_here; ++gi)
-            compute_group_lds<NT, true>(st, stage + (size_t)gi * 16 * 64 + lane, qr, left - (4 * r + gi) * kGrp, stag, lane);
+            compute_group_lds<NT, true>(st, stage + (size_t)gi * 16 * 64 + lane, qr, left - (4 * r + gi) * kGrp, stag, scale_log2, lane);
     }
 }
 
@@ -1296,7 +1280,7 @@ template <bool KV8>
 __global__ void __launch_bounds__(64 * kShortWaves) k_attn_prefill_short(const bf16_t *__restrict__ qg, const void *__restrict__ pool,
                                                                      const int32_t *__restrict__ bt, int max_blocks, AttnPlan pl,
                                                                      bf16_t *__restrict__ out, float *__restrict__ part_o,
-                                                                     float *__restrict__ part_ml, int Hq, int Hkv, float v_scale) {
+                                                                     float *__restrict__ part_ml, int Hq, int Hkv, float scale_log2, float v_scale) {
     constexpr int NT = kShortNT;
     extern __shared__ float lds[];
     const int item = blockIdx.x / Hkv, c = blockIdx.x % Hkv;
@@ -1341,7 +1325,7 @@ __global__ void __launch_bounds__(64 * kShortWaves) k_attn_prefill_short(const b
     }
     const int n_clean = max(0, left - (T - 1)) / kGrp;  // groups valid for every query (further ones may be in later pieces)
     const bool busy = __builtin_amdgcn_readfirstlane(16 * w * NT) < G;
-    prefill_walk_short<NT, KV8>(st, pool, blds, n_blk, n_tok, left, n_clean, stag, busy, w, c, Hkv, ring, qr, lane);
+    prefill_walk_short<NT, KV8>(st, pool, blds, n_blk, n_tok, left, n_clean, stag, busy, w, c, Hkv, ring, qr, scale_log2, lane);
     if constexpr (KV8) {
 #pragma unroll
         for (int qt = 0; qt < NT; ++qt)
@@ -1432,7 +1416,6 @@ constexpr size_t kPrefillRing = (size_t)2 * 4 * 16 * 64 * 16, kLdsBytes = (size_
 constexpr int kPrefillMaxCtx = (int)((kLdsBytes - kPrefillRing) / 4) * kBk;
 int attn_prefill_max_ctx() { return kPrefillMaxCtx; }
 int attn_prefill_round() { return kRoundGroups * kGrp; }
-float attn_prefill_q_scale(const Dims &dm) { return kLog2e / sqrtf((float)dm.D) * (dm.kv8 ? dm.k_scale : 1.f); }
 
 int attn_prefill_group_queries() { return kPrefillWaves * kPrefillNT * 16; }  // stacked queries one prefill workgroup holds
 
@@ -1446,6 +1429,7 @@ hipError_t launch_attn_prefill_mfma(const Dims &dm, const void *q, const void *p
     if (!pl.causal || pl.chunk > kPrefillMaxCtx) return hipErrorInvalidValue;
     const size_t shm = kPrefillRing + (size_t)((pl.chunk + kBk - 1) / kBk) * 4;  // two ring stages + the block ids
     const dim3 grid(pl.n_items * dm.Hkv);
+    const float scale_log2 = kLog2e / sqrtf((float)dm.D) * (dm.kv8 ? dm.k_scale : 1.f);
     auto allow_lds = [](auto kernel, bool &set) {
         if (set) return hipSuccess;
         const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
@@ -1457,14 +1441,14 @@ hipError_t launch_attn_prefill_mfma(const Dims &dm, const void *q, const void *p
         const hipError_t e = allow_lds(k_attn_prefill, set);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_attn_prefill, grid, dim3(64 * kPrefillWaves), shm, st, (const bf16_t *)q, (const bf16_t *)pool, bt, max_blocks, pl,
-                           (bf16_t *)out, part_o, part_ml, dm.Hq, dm.Hkv);
+                           (bf16_t *)out, part_o, part_ml, dm.Hq, dm.Hkv, scale_log2);
         return hipGetLastError();
     }
     auto launch = [&](auto kernel, bool &set) {
         const hipError_t e = allow_lds(kernel, set);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kernel, grid, dim3(64 * kShortWaves), shm, st, (const bf16_t *)q, pool, bt, max_blocks, pl, (bf16_t *)out, part_o,
-                           part_ml, dm.Hq, dm.Hkv, dm.kv8 ? dm.v_scale : 1.f);
+                           part_ml, dm.Hq, dm.Hkv, scale_log2, dm.kv8 ? dm.v_scale : 1.f);
         return hipGetLastError();
     };
     static bool set_bf16 = false, set_fp8 = false;

@@ -189,7 +189,7 @@ __global__ void __launch_bounds__(256) k_rope_append(const float *__restrict__ q
                                                      T *__restrict__ q_out, int64_t *__restrict__ slot_out, int slot_by_row,
                                                      const T *__restrict__ q_norm, const T *__restrict__ k_norm,
                                                      int Hq, int Hkv, int D, int Bk, double log2_theta, float eps, int qk_norm,
-                                                     float k_scale, float v_scale, float q_scale, const int32_t *__restrict__ row_map) {
+                                                     float k_scale, float v_scale, const int32_t *__restrict__ row_map) {
     extern __shared__ float sm[];  // the row [n_heads * D] | cos, sin [D/2 each] | inv_rms per head [Hq + Hkv]
     // row_map (optional): the projections were computed on a permutation of the call's rows; input row i is the
     // call's row row_map[i], whose metadata it takes and at whose place q is written
@@ -271,8 +271,8 @@ __global__ void __launch_bounds__(256) k_rope_append(const float *__restrict__ q
         rotate_pair(a, b, cs, sn, &ra, &rb);
         if (h < Hq) {
             T *dst = q_out + ((size_t)row * Hq + h) * D;
-            Elem<T>::st(dst + i, ra * q_scale);
-            Elem<T>::st(dst + i + half, rb * q_scale);
+            Elem<T>::st(dst + i, ra);
+            Elem<T>::st(dst + i + half, rb);
         } else {
             KT *dst = kdst + ((size_t)(h - Hq) * 2 + 0) * Bk * D + (size_t)off * D;  // K plane [Bk][D]
             KVElem<KT>::st(dst + i, ra, k_scale);
@@ -311,7 +311,7 @@ hipError_t launch_rope_append(const Dims &dm, const float *qkv, int ldq, int spl
         }
         hipLaunchKernelGGL((k_rope_append<T, KT>), dim3(R, parts), dim3(256), shm, st, qkv, ldq, splits, slice, rm.row_seq, rm.row_model,
                            rm.row_pos, bt, max_blocks, (KT *)pool, (T *)q_out, slot_out, slot_by_row, (const T *)q_norm,
-                           (const T *)k_norm, dm.Hq, dm.Hkv, dm.D, dm.Bk, l2t, dm.eps, dm.qk_norm, dm.k_scale, dm.v_scale, rm.q_scale, row_map);
+                           (const T *)k_norm, dm.Hq, dm.Hkv, dm.D, dm.Bk, l2t, dm.eps, dm.qk_norm, dm.k_scale, dm.v_scale, row_map);
     });
     return hipGetLastError();
 }
@@ -366,8 +366,7 @@ __global__ void __launch_bounds__(256) k_rope_append_tile(const float *__restric
                                                           int max_blocks, KT *__restrict__ pool, bf16_t *__restrict__ q_out,
                                                           int64_t *__restrict__ slot_out, const bf16_t *__restrict__ q_norm,
                                                           const bf16_t *__restrict__ k_norm, int h_begin, int Hq, int Hkv,
-                                                          double log2_theta, float eps, int qk_norm, float k_scale, float v_scale,
-                                                          float q_scale) {
+                                                          double log2_theta, float eps, int qk_norm, float k_scale, float v_scale) {
     constexpr int D = 128, half = 64, Bk = 16;
     __shared__ float cs_t[Bk][half], sn_t[Bk][half];
     __shared__ __attribute__((aligned(16))) KT vt[D][Bk + 16 / sizeof(KT)];  // V of one head, transposed; rows 16 bytes apart from full banks
@@ -431,8 +430,6 @@ __global__ void __launch_bounds__(256) k_rope_append_tile(const float *__restric
         }
         if (h < Hq) {
             bf16_t *dst = q_out + ((size_t)(row0 + t) * Hq + h) * D + 4 * l;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { ra[e] *= q_scale; rb[e] *= q_scale; }
             KVElem4<bf16_t>::st(dst, ra, 1.f);
             KVElem4<bf16_t>::st(dst + half, rb, 1.f);
         } else {
@@ -488,7 +485,7 @@ hipError_t launch_rope_append_tiles(const Dims &dm, const float *qkv, int ldq, i
         typedef decltype(kt) KT;
         hipLaunchKernelGGL(k_rope_append_tile<KT>, dim3(n_tiles, parts), dim3(256), 0, st, qkv, ldq, splits, slice, tiles, rm.row_seq, rm.row_pos,
                            bt, max_blocks, (KT *)pool, (bf16_t *)q_out, slot_out, (const bf16_t *)q_norm, (const bf16_t *)k_norm, h_begin,
-                           dm.Hq, dm.Hkv, log2(dm.theta), dm.eps, dm.qk_norm, dm.k_scale, dm.v_scale, rm.q_scale);
+                           dm.Hq, dm.Hkv, log2(dm.theta), dm.eps, dm.qk_norm, dm.k_scale, dm.v_scale);
         return hipGetLastError();
     };
     return dm.kv8 ? launch(fp8_t()) : launch(bf16_t());

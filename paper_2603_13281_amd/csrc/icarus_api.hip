@@ -1208,7 +1208,6 @@ icarus_status prepare_prefill(icarus_ctx *ctx, const void *kv_pool, const int32_
         used += n_extra;
     }
     pr->rm = RowMeta{dmeta, dmeta + R, dmeta + 2 * R, dmeta + 3 * R};
-    if (pr->hp.valid) pr->rm.q_scale = attn_prefill_q_scale(ctx->dm);  // the vector kernel scales by itself
     // the chunk rows in tiles that lie within one KV block (at most one per row), if the append goes by tiles
     int n_tiles = 0;
     for (int s = 0; s < S; ++s)

@@ -24,7 +24,6 @@ struct RowMeta {
     const int32_t *row_model;  // [R] -1 = logical encoder row, else adapter id
     const int32_t *row_pos;    // [R] position of the row's token
     const int32_t *row_kvlen;  // [R] cache positions the row attends to (0..kvlen-1)
-    float q_scale = 1.f;       // q is multiplied by this before it is rounded and stored (attn_prefill_q_scale)
     const int32_t *order = nullptr;  // decode with adapters: rows for the workgroups of the row kernels, see row_order
     int n_order = 0;
     const int32_t *rope_tiles = nullptr;  // prefill: the rows in tiles for launch_rope_append_tiles
@@ -216,8 +215,6 @@ hipError_t launch_merge_shrink(const Dims &dm, const float *part_o, const float 
 int attn_prefill_group_queries();
 int attn_prefill_max_ctx();  // longest piece, in tokens
 int attn_prefill_round();    // tokens of a round of the walk: pieces are cut between rounds
-// q of the prefill attention comes multiplied by this: the softmax scale, log2 e and the K scale of an FP8 cache.
-float attn_prefill_q_scale(const Dims &dm);
 bool attn_prefill_mfma_supported(const Dims &dm, int g_max);
 hipError_t launch_attn_prefill_mfma(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
                                     const AttnPlan &pl, void *out, float *part_o, float *part_ml, hipStream_t st);
