@@ -237,6 +237,10 @@ icarus_status icarus_set_attn_piece_limit(icarus_ctx *ctx, int32_t tokens);
 icarus_status icarus_gemm_tile_order(int32_t row_tiles, int32_t col_tiles, int32_t k_slices, int32_t tile_rows, int32_t tile_cols,
                                      int32_t per_cu, int32_t *order /*host*/, int32_t cap, int32_t *n /*host*/);
 
+/* The order in which a decode call's row kernels take its rows, host only: order (host, room for n_rows + 16) gets n (host) entries
+ * row | (model + 1) << 16, or -1 for a workgroup without one, entry i for XCD i % 8; n = 0: the rows as they come. */
+icarus_status icarus_row_order(const int32_t *row_model /*host*/, int32_t n_rows, int32_t *order /*host*/, int32_t *n /*host*/);
+
 /* For tests and measurements: one GEMM as the layers launch it, in a given tile and number of K slices (device arrays, bf16 unless
  * noted, 16-byte aligned; a fixed choice of both runs whatever icarus_gemm_choice would say).
  *   plain:  y = x [rows, k] . w^T + t . b^T over n_segs stacked weight matrices w[s] [n[s], k]; y float [rows, sum n], or with

@@ -30,7 +30,7 @@ EXPORTS = ("icarus_create", "icarus_destroy", "icarus_last_error", "icarus_works
            "icarus_cache_create", "icarus_cache_destroy", "icarus_cache_last_error", "icarus_cache_acquire", "icarus_cache_extend",
            "icarus_cache_commit", "icarus_cache_release", "icarus_cache_get_stats", "icarus_set_full_decoders",
            "icarus_validate_block_tables", "icarus_set_attn_piece_limit", "icarus_attn_shared_kv_static", "icarus_bench_read",
-           "icarus_gemm_tile_order", "icarus_gemm_choice", "icarus_gemm_group_tile", "icarus_append_in_tiles", "icarus_prefill_plan", "icarus_gemm")
+           "icarus_gemm_tile_order", "icarus_gemm_choice", "icarus_gemm_group_tile", "icarus_append_in_tiles", "icarus_prefill_plan", "icarus_row_order", "icarus_gemm")
 
 PHASES = ("norm", "lora", "gemm_qkv", "rope_append", "attn", "attn_merge", "gemm_o", "gemm_gateup", "gemm_down",
           "elementwise")
@@ -125,6 +125,8 @@ def _load():
     lib.icarus_bench_read.argtypes = [vp, sz, vp, vp]
     lib.icarus_bench_mfma.restype = C.c_int
     lib.icarus_bench_mfma.argtypes = [vp, C.c_int32, C.c_int32, vp]
+    lib.icarus_row_order.restype = C.c_int
+    lib.icarus_row_order.argtypes = [vp, i32, vp, vp]
     lib.icarus_gemm_tile_order.restype = C.c_int
     lib.icarus_gemm_tile_order.argtypes = [i32] * 6 + [vp, i32, vp]
     lib.icarus_gemm_choice.restype = C.c_int
@@ -305,6 +307,16 @@ def gemm_tile_order(row_tiles: int, col_tiles: int, k_slices: int, tile_rows: in
     if rc != 0:
         raise IcarusError(rc, "icarus_gemm_tile_order failed")
     return out[:min(cap, n.value)]
+
+
+def row_order(row_model) -> np.ndarray:
+    """Entries row | (model + 1) << 16 (-1: none) in which a decode call's row kernels take its rows; empty: as they come (host only)."""
+    model = np.ascontiguousarray(row_model, dtype=np.int32)
+    out, n = np.zeros(len(model) + 16, dtype=np.int32), C.c_int32()
+    rc = _lib.icarus_row_order(model.ctypes.data, len(model), out.ctypes.data, C.byref(n))
+    if rc != 0:
+        raise IcarusError(rc, "icarus_row_order failed")
+    return out[:n.value]
 
 
 def gemm_choice(rows: int, k: int, n, fused: bool = False, adapter_cols: int = 0, max_slices: int = 12, taken: bool = False):

@@ -1494,6 +1494,12 @@ icarus_status icarus_gemm_tile_order(int32_t row_tiles, int32_t col_tiles, int32
     return ICARUS_OK;
 }
 
+icarus_status icarus_row_order(const int32_t *row_model, int32_t n_rows, int32_t *order, int32_t *n) {
+    if (!row_model || n_rows <= 0 || n_rows > 65535 || !order || !n) return ICARUS_ERR_INVALID_ARG;
+    *n = row_order(row_model, n_rows, order);
+    return ICARUS_OK;
+}
+
 icarus_status icarus_gemm(const icarus_gemm_args *a, void *stream) {
     if (!a || a->rows <= 0 || a->rows > 65535 || a->k <= 0 || a->k % 64 || a->n_segs < 1 || a->n_segs > 3 || !a->x || !a->y) return ICARUS_ERR_INVALID_ARG;
     if (a->fused ? a->n_segs != 1 || a->slices != 1 || a->resid : a->resid && a->n_segs != 1) return ICARUS_ERR_INVALID_ARG;

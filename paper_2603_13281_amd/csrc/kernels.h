@@ -188,7 +188,7 @@ hipError_t launch_splitk_reduce(const float *P, int splits, int R, int N, int ep
 // in every other column (encoder rows: all zero).  A: [M][r][K].
 bool row_shrink_supported(int r, int targets);
 // Order of the rows over the workgroups of the kernels below: entry = row | (model + 1) << 16, -1: none; at most R + 16 entries,
-// a multiple of 8.  Returns how many; 0: few rows, in the order they have.
+// a multiple of 8.  Returns how many; 0: few rows, or a model that an entry does not hold: the rows in the order they have.
 int row_order(const int32_t *row_model, int R, int32_t *order);
 // y = rmsnorm(x) * wn for R rows of K, and (A0 != null) the shrink of y for one or two targets that
 // share y; also sets zero[0..n_zero) = 0.

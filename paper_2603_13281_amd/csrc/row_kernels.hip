@@ -377,8 +377,9 @@ RowArgs shrink_args(const Dims &dm, const void *A0, const void *A1, const RowMet
 // (norm and Q), 13.9 -> 12.1 (merge and O), 18.0 -> 14.7 (sums, norm, gate and up), 18.0 -> 16.1 (down); 144 rows, 25600 columns 28.6 -> 24.7.
 // A row's own loads then wait for its entry: 64 rows 7.5 -> 7.7, 9.7 -> 10.1 us, hence from 97 rows on.
 constexpr int kRowOrderMin = 97;
+constexpr int kRowOrderMaxModel = 0x7ffe;  // an entry has 15 bits for model + 1
 int row_order(const int32_t *row_model, int R, int32_t *order) {
-    if (R < kRowOrderMin) return 0;
+    if (R < kRowOrderMin || *std::max_element(row_model, row_model + R) > kRowOrderMaxModel) return 0;
     std::vector<int32_t> rows[2];  // with an adapter, by model; without
     for (int r = 0; r < R; ++r) rows[row_model[r] < 0].push_back(r);
     std::stable_sort(rows[0].begin(), rows[0].end(), [&](int32_t a, int32_t b) { return row_model[a] < row_model[b]; });
