@@ -321,7 +321,7 @@ hipError_t launch_cfg(GemmArgs g, hipStream_t st) {
 
 // Tile shapes: rows x weight rows of a workgroup, all with 64-wide K slabs (32-wide slabs ask for every 128-byte line of
 // a weight row twice, half each time, and stream at about 60 % of the rate).  The first two are k_gemm_mfma, the
-// others k_gemm_quad (192 x 128: gemm_quad.hip may take lower tiles).  first_us: what a workgroup takes apart from its slabs (start, first slab, epilogue); slab_us: a slab
+// others k_gemm_quad (192 x 128: gemm_quad.hip may take lower tiles, and see launch_gemm_mfma).  first_us: what a workgroup takes apart from its slabs (start, first slab, epilogue); slab_us: a slab
 // with every CU busy, for each of the per_cu workgroups that share one.  The figures are a fit to 5000 timings on
 // this GPU (80-4337 rows x the projections of a Llama-3-8B- and a Qwen3-32B-shaped layer x every tile x 1-12 slices; the
 // fit is 7-11 % off on average), see gemm_plan and gemm_row_tile.  They are of a kernel before k_gemm_quad, which is 5-16 % faster
@@ -532,6 +532,15 @@ hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st) {
     }
     g.K_ext = k_ext_of(g);
     g.k_per_split = ((g.K_ext + g.splits - 1) / g.splits + kKAlign - 1) / kKAlign * kKAlign;
+    // Tiles of 192 rows by 128 that are needed in full (gemm_quad.hip has lower ones), with adapters: the slabs of adapter columns are
+    // code that a workgroup of k_gemm_quad runs once, fetched as it goes (a form with fewer instructions per load but more of them in
+    // all took 1.3 us longer still); four such slabs cost 1.3-2 us more there than in this kernel's loop, which only a long K earns back.  us with 8
+    // adapters of rank 32, this kernel / that: 171-189 rows, 5120 -> 10240 in 3 slices 38.3 / 40.9, 8192 -> 5120 in 6 32.1 / 34.6; 324-378
+    // rows, 8192 -> 5120 in 3 44.0 / 46.6; 370 rows, 20480 -> 5120 in 3 93.3 / 93.8; 171-189 rows, 25600 -> 5120 in 6 83.7 / 81.5.  Rank 16:
+    // 180 rows, 4096 -> 6144 in 5 30.4 / 25.7; 370 rows, 4096 -> 4096 in 4 35.0 / 29.9.
+    const int cols = g.K_ext - g.K;
+    if (g.tile == TILE_192x128 && !g.row_tiles && g.mode == GEMM_PLAIN && g.R > 160 * ((g.R + 191) / 192) && cols >= 256 && g.K <= 64 * cols)
+        return launch_cfg<192, 128, 64, 3, 2, 2>(g, st);
     if (is_quad(g.tile)) return launch_gemm_quad(g, st);
     switch (g.tile) {
     case TILE_64x128: return g.row_tiles ? launch_cfg<64, 128, 64, 3, 2, 2, true>(g, st) : launch_cfg<64, 128, 64, 3, 2, 2>(g, st);

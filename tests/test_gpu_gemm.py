@@ -128,6 +128,20 @@ def test_lower_tiles_where_as_many_hold_the_rows(rows):
     _check(binding.gemm(x, w, (192, 128, False), fused=True), silu * u, bound, (rows, "fused"))
 
 
+@pytest.mark.parametrize("rows", [160, 161, 192, 193, 320, 321, 384, 480, 481])
+@pytest.mark.parametrize("k", [64 * 9, 64 * 257])
+def test_full_192_row_tiles_with_many_adapter_columns(rows, k):
+    # 8 adapters of rank 32: up to K = 16384 k_gemm_mfma takes the tiles that are needed in full, k_gemm_quad the lower ones and longer K
+    print("case: 192 x 128, 256 adapter columns", rows, k, flush=True)
+    n, models, rank = [136, 24], 8, 32
+    x, w = _draw((rows, k), 1), [_draw((m, k), 10 + i, 0.05) for i, m in enumerate(n)]
+    t, b = _adapters(rows, n[0], models, rank, 1, 20)
+    eps = (k + models * rank + 16) * 2.0 ** -23
+    (q, qs), (v, vs) = _product(x, w[0], t, b[0]), _product(x, w[1])
+    for slices in (1, 3):
+        _check(binding.gemm(x, w, (192, 128, False), slices, t=t, b=b), torch.cat([q, v], 1), eps * torch.cat([qs, vs], 1) + 1e-30, (rows, k, slices))
+
+
 def test_gemm_refuses_what_the_kernels_do_not_take():
     x, w = _draw((4, 128), 1), _draw((16, 128), 2)
     for kw in (dict(tile=(96, 128, False)), dict(tile=(256, 256, True)), dict(tile=TILES[0], slices=13), dict(tile=TILES[0], slices=0)):
