@@ -494,17 +494,22 @@ hipError_t launch_rope_append_tiles(const Dims &dm, const float *qkv, int ldq, i
 // ------------------------------------------------------------------ attention (one block per row and query head)
 // Online softmax over chunks of 1024 cached positions.  Scores: LPT threads per position, each every LPT-th quad of its
 // elements.  Output: thread (part, d) adds every parts-th quad of positions to output element d; V^T rows hold a block's
-// tokens side by side, so a quad is one load, and four neighbouring threads take the quads of a row of sixteen tokens.
+// tokens side by side, so a quad is one load, and neighbouring threads take the quads of a block's row (pl of them, up to four).
 // Latency-bound at the sizes this kernel is for, and next by the lines that its loads touch: with a thread per position and
-// a part per wave every load touched a line per lane.  Rows x 4 heads x 64 in float32, us, that with 256 threads a workgroup /
-// this: 3 rows over 128 tokens 7.5 / 6.5, 12 rows over 1000 30.0 / 13.7, 96 rows over 1000 55.0 / 34.1, 768 rows 381 / 190.
-// quads: D and Bk are multiples of 4 (else one element, one position at a time; LPT is 1).
+// a part per wave every load touched a line per lane.  Rows x 4 heads x 64, us, that with 256 threads a workgroup / this, float32:
+// 3 rows over 128 tokens 7.5 / 6.5, 12 rows over 1000 30.0 / 13.7, 96 rows over 1000 55.0 / 34.1, 768 rows 253 / 115; bf16 768 rows
+// 241 / 138; FP8 64 rows over 128 10.1 / 8.4, 768 rows over 1000 168 / 106.
+// KU, VU: loads in flight.  An FP8 load is four conversions; eight of them in flight took 142 registers, and 1024 threads spilled
+// (FP8, the two figures above 11.6 and 186; 768 rows x 32 heads x 80 over 128 tokens 302 us, now 160).
+// LPT > 1: D and Bk are multiples of 4; LPT = 1: one element, one position at a time.
 template <typename T, typename KT, int NT, int LPT>
 __global__ void __launch_bounds__(NT) k_attn_generic(const T *__restrict__ q, const KT *__restrict__ pool,
                                                      const int32_t *__restrict__ bt, int max_blocks,
                                                      const int32_t *__restrict__ row_seq, const int32_t *__restrict__ row_kvlen,
                                                      T *__restrict__ out, int Hq, int Hkv, int D, int Bk, float scale,
-                                                     float k_scale, float v_scale, int parts, int quads) {
+                                                     float k_scale, float v_scale, int parts, int pl) {
+    constexpr bool quads = LPT > 1;
+    constexpr int KU = sizeof(KT) == 1 ? 2 : 8, VU = sizeof(KT) == 1 ? 4 : 8;
     __shared__ __attribute__((aligned(16))) float sc[1024];
     __shared__ size_t soff[1024];  // where a position's V elements are, within its head
     __shared__ float sum[NT];
@@ -516,7 +521,7 @@ __global__ void __launch_bounds__(NT) k_attn_generic(const T *__restrict__ q, co
     const int32_t *btr = bt + (size_t)s * max_blocks;
     for (int i = threadIdx.x; i < D; i += NT) qs[i] = Elem<T>::ld(q + ((size_t)row * Hq + h) * D + i);
     __syncthreads();
-    const int width = NT / parts, pl = parts >= 4 ? 4 : 1;  // parts, and so width, are powers of two
+    const int width = NT / parts;  // all three are powers of two
     const int part = threadIdx.x % pl + pl * (threadIdx.x / (pl * width)), d = threadIdx.x / pl % width;
     const int sub = threadIdx.x % LPT;
     size_t head_stride = (size_t)2 * Bk * D, blk_stride = (size_t)Hkv * head_stride;
@@ -531,8 +536,8 @@ __global__ void __launch_bounds__(NT) k_attn_generic(const T *__restrict__ q, co
             const size_t off = (size_t)btr[tok / Bk] * blk_stride;
             const KT *kr = head + off + (size_t)in_blk * D;
             float dot = 0.f;
-            if (LPT > 1 || quads) {
-#pragma unroll 8
+            if constexpr (quads) {
+#pragma unroll KU
                 for (int i = 4 * sub; i < D; i += 4 * LPT) {
                     float kv[4];
                     KVElem4<KT>::ld(kr + i, k_scale, kv);
@@ -568,8 +573,8 @@ __global__ void __launch_bounds__(NT) k_attn_generic(const T *__restrict__ q, co
         if (d < D) {
             float a = acc * alpha;
             const KT *vd = head + (size_t)Bk * D + (size_t)d * Bk;
-            if (quads) {
-#pragma unroll 8
+            if constexpr (quads) {
+#pragma unroll VU
                 for (int t = 4 * part; t + 3 < cnt; t += 4 * parts) {
                     float v[4];
                     KVElem4<KT>::ld(vd + soff[t], v_scale, v);
@@ -598,9 +603,10 @@ __global__ void __launch_bounds__(NT) k_attn_generic(const T *__restrict__ q, co
     }
 }
 
-// Workgroups up to which each gets a CU, and so 1024 threads.  Rows x 4 heads x 64 in float32, us with 256 / 1024 threads:
-// 48 workgroups over 1000 tokens 22.6 / 13.7, 192 over 128 tokens 6.8 / 6.7 and over 1000 28.8 / 17.6; 384 9.0 / 13.3 and
-// 34.1 / 33.3, 768 11.1 / 20.4 and 47.6 / 54.1.
+// Workgroups up to which each gets a CU, and so 1024 threads.  Rows x 4 heads x 64, us with 256 / 1024 threads, float32: 12
+// workgroups over 1000 tokens 20.7 / 13.7, 256 over 128 tokens 8.6 / 8.6 and over 1000 29.6 / 18.4, 260 8.4 / 12.8 and 37.4 / 37.8; bf16 256
+// 9.5 / 8.5 and 28.8 / 15.2, 260 9.2 / 12.8 and 45.1 / 34.3, 768 10.2 / 18.3 and 49.8 / 51.0; FP8 256 9.6 / 8.4 and 29.8 / 15.2, 260 9.2 / 12.1 and
+// 40.4 / 30.7, 768 10.4 / 16.9 and 50.1 / 48.7.
 constexpr int kGenericWide = 256;
 
 hipError_t launch_attn_generic(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
@@ -613,9 +619,10 @@ hipError_t launch_attn_generic(const Dims &dm, const void *q, const void *pool, 
         constexpr int NT = decltype(nt)::value, LPT = decltype(lpt)::value;
         int parts = 1;
         while (parts < 32 && NT / (2 * parts) >= dm.D) parts *= 2;
+        const int pl = std::min(parts, LPT == 1 || dm.Bk % 16 == 0 ? 4 : dm.Bk % 8 == 0 ? 2 : 1);  // quads of a block
         DISPATCH_TK(dm.bf16, dm.kv8, hipLaunchKernelGGL((k_attn_generic<T, KT, NT, LPT>), grid, dim3(NT), sizeof(float) * dm.D, st, (const T *)q,
                                                         (const KT *)pool, bt, max_blocks, rm.row_seq, rm.row_kvlen, (T *)out, dm.Hq, dm.Hkv,
-                                                        dm.D, dm.Bk, scale, dm.k_scale, dm.v_scale, parts, quads));
+                                                        dm.D, dm.Bk, scale, dm.k_scale, dm.v_scale, parts, pl));
         return hipGetLastError();
     };
     constexpr std::integral_constant<int, 1> one;
