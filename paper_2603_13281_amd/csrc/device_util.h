@@ -62,6 +62,27 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// Sums N values over the wave's 64 lanes (N a power of two up to 64): in each step a lane keeps half of its values and
+// sends the other half, so N - 1 + log2(64 / N) exchanges do what N sums of 6 would.  Lane l ends with the sum of
+// value l / (64 / N).  By recursion: as a loop over halves the values went through scratch memory where a kernel sums 64.
+template <int N, int H = N / 2, int O = 32>
+__device__ __forceinline__ float wave_sums(float (&v)[N], int lane) {
+    if constexpr (O > 0) {
+        const bool hi = lane & O;
+        if constexpr (H > 0) {
+#pragma unroll
+            for (int i = 0; i < H; ++i) {
+                const float keep = hi ? v[i + H] : v[i], send = hi ? v[i] : v[i + H];
+                v[i] = keep + __shfl_xor(send, O, 64);
+            }
+        } else {
+            v[0] += __shfl_xor(v[0], O, 64);
+        }
+        return wave_sums<N, H / 2, O / 2>(v, lane);
+    }
+    return v[0];
+}
+
 // Block-wide reductions for blocks of up to 1024 threads; `red` is a shared float[16].
 // Every thread gets the result.
 __device__ __forceinline__ float block_sum(float v, float *red) {

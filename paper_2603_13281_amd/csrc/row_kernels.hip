@@ -35,34 +35,15 @@ __device__ __forceinline__ void unpack8(uint4 v, float (&f)[8]) {
 // vector instructions per 8 products, and 6 exchanges per accumulator to sum it over the wave.  They take the two-way
 // bf16 dot product (fp32 sums; x and A as stored) and sum all accumulators together: 316 rows, 2 x 16 accumulators,
 // with the split-K sums of the projection before it 23.3 -> 18.3 us.  With 16 or fewer the same change was slower (12.5 -> 15.5 us
-// for the norm and one target: the loop lives from loads that the compiler then no longer keeps in flight).
+// for the norm and one target: the loop lives from loads that the compiler then no longer keeps in flight).  The joint sums of 64 accumulators
+// (two targets of rank 32), written as a loop, went through scratch memory: sums, norm, gate and up of 324 rows of 5120 with the norm before Q 84.9
+// us, by the recursion of wave_sums 53.8.
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float dot8(uint4 a, uint4 b, float c) {
     c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a.x), __builtin_bit_cast(bf16x2, b.x), c, false);
     c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a.y), __builtin_bit_cast(bf16x2, b.y), c, false);
     c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a.z), __builtin_bit_cast(bf16x2, b.z), c, false);
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a.w), __builtin_bit_cast(bf16x2, b.w), c, false);
-}
-
-// Sums N values over the wave's 64 lanes (N a power of two, 2 to 64): in each step a lane keeps half of its values and
-// sends the other half, so N - 1 + log2(64 / N) exchanges do what N sums of 6 would.  Lane l ends with the sum of
-// value l / (64 / N).
-template <int N>
-__device__ __forceinline__ float wave_sums(float (&v)[N], int lane) {
-    int o = 32;
-#pragma unroll
-    for (int n = N; n > 1; n >>= 1, o >>= 1) {
-        const bool hi = lane & o;
-#pragma unroll
-        for (int i = 0; i < n / 2; ++i) {
-            const float keep = hi ? v[i + n / 2] : v[i], send = hi ? v[i] : v[i + n / 2];
-            v[i] = keep + __shfl_xor(send, o, 64);
-        }
-    }
-    float s = v[0];
-#pragma unroll
-    for (; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    return s;
 }
 
 // Where a row comes from.

@@ -45,24 +45,6 @@ template <typename T> struct Vec1 {
 template <typename V, typename T> __device__ __forceinline__ typename V::Raw ld_raw(const T *p) { return *(const typename V::Raw *)p; }
 template <typename V, typename T> __device__ __forceinline__ void ld_vec(const T *p, float (&f)[V::N]) { V::un(ld_raw<V>(p), f); }
 
-// Sums over the wave's lanes of NV values each (a power of two up to 64): lane l gets that of value l / (64 / NV).  A lane hands
-// half of what it has to its partner and goes on with the other half, NV - 1 + log2(64 / NV) exchanges instead of 6 NV.
-template <int NV, int N = NV / 2, int O = 32>
-__device__ __forceinline__ float wave_sums(float (&v)[NV]) {
-    if constexpr (O > 0) {
-        const bool upper = threadIdx.x & O;
-        if constexpr (N > 0) {
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const float keep = upper ? v[i + N] : v[i], give = upper ? v[i] : v[i + N];
-                v[i] = keep + __shfl_xor(give, O, 64);
-            }
-        } else v[0] += __shfl_xor(v[0], O, 64);
-        return wave_sums<NV, N / 2, O / 2>(v);
-    }
-    return v[0];
-}
-
 // One workgroup per row: y = rmsnorm(x) * wn (NORM), and for a decoder row t[target][row][0..r) = scale * A[model] y (or
 // x) for up to two targets; a wave takes every fourth of the targets * r outputs.
 template <typename T, typename V, bool NORM>
@@ -184,7 +166,7 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(SkinnyArgs a) {
         k += 64 * V::N;
         if (k < a.K) load();
     }
-    float sum = wave_sums(acc), up = 0.f;
+    float sum = wave_sums(acc, lane), up = 0.f;
     if (dual) up = __shfl_xor(sum, 32, 64) + delta[1];  // the upper half of the lanes holds the up projection
     sum += delta[0];
     if (!first) return;
