@@ -21,7 +21,8 @@
  *    larger one, and a call that finds its buffer still in use by the call
  *    made 16 calls earlier blocks the HOST until that call's metadata copy has
  *    run (back-pressure: at most 16 such calls of one context are in flight).
- *    Metadata of up to 960 ints goes on as kernel arguments: nothing to wait for.
+ *    Metadata of up to 960 ints goes on as kernel arguments and leaves its buffer at once; such a call waits
+ *    only where the buffer whose turn it is still belongs to a larger call.
  *    icarus_attn_shared_kv_static uses neither the ring nor a workspace.
  *  - "host" / "device" after a pointer says where the memory lives.
  *  - Small integer metadata (lengths, row lists) is passed as HOST arrays so it
@@ -253,14 +254,14 @@ typedef struct icarus_gemm_args {
     const void *x, *w[3], *t, *b[2], *resid;
     void *y, *partials;
     int32_t rows, k, n[3], n_segs, fused, models, rank;
-    int32_t tile_rows, tile_cols, staged, slices; /* as icarus_gemm_choice names them */
+    int32_t tile_rows, tile_cols, staged, slices; /* as icarus_gemm_choice names them (staged: the mark) */
 } icarus_gemm_args;
 icarus_status icarus_gemm(const icarus_gemm_args *args, void *stream);
 
 /* The choice of such a launch, host only: a GEMM of `rows` rows over K = k against n_segs stacked weight matrices of n_seg[.] rows
  * (host, at most 3; fused != 0: the gate/up pair of n_seg[0] rows each), adapter_cols = n_models * rank (a multiple of 8; 0: no
  * adapters), at most max_slices slices of K, which a later kernel sums on the way if taken != 0.  choice (host): rows and weight
- * rows of a tile, a mark (1 for 192 and 160 rows by 256, else 0), slices. */
+ * rows of a tile, a mark (1 for 192 and 160 rows by 256, else 0: part of the tile's name, the sizes alone tell them apart), slices. */
 icarus_status icarus_gemm_choice(int32_t rows, int32_t k, const int32_t *n_seg /*host*/, int32_t n_segs, int32_t fused, int32_t adapter_cols,
                                  int32_t max_slices, int32_t taken, int32_t *choice /*host [4]*/);
 

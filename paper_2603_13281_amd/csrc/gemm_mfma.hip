@@ -324,9 +324,10 @@ hipError_t launch_cfg(GemmArgs g, hipStream_t st) {
 // others k_gemm_quad (192 x 128: gemm_quad.hip may take lower tiles, and see launch_gemm_mfma).  first_us: what a workgroup takes apart from its slabs (start, first slab, epilogue); slab_us: a slab
 // with every CU busy, for each of the per_cu workgroups that share one.  The figures are a fit to 5000 timings on
 // this GPU (80-4337 rows x the projections of a Llama-3-8B- and a Qwen3-32B-shaped layer x every tile x 1-12 slices; the
-// fit is 7-11 % off on average), see gemm_plan and gemm_row_tile.  They are of a kernel before k_gemm_quad, which is 5-16 % faster
-// in every one of its tiles: what they are for, the order of the choices, holds (144, 316, 512 and 753 rows of the four
-// projections, every tile and slice count timed anew: the choice is the fastest of these tiles or within 5 %).
+// fit is 7-11 % off on average), see gemm_plan and gemm_row_tile.  They are of the kernels before k_gemm_quad, and
+// count one 192 x 128 workgroup to a CU where two now fit.  What they are for, the order of the choices, holds (144, 316, 512 and 753 rows of
+// the four projections, every tile and slice count timed anew: the choice is the fastest of these tiles or within 5 %); as times
+// they are up to 16 % high.
 struct TileShape { int bm, bn, per_cu; float first_us, slab_us; };
 constexpr TileShape kTileShape[TILE_KINDS] = {
     {0, 0, 0, 0.f, 0.f},

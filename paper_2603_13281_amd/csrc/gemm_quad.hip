@@ -117,7 +117,7 @@ __global__ void __launch_bounds__(128 * WAVES_N, WAVES_N == 4 ? 1 : 2) k_gemm_qu
         return min(row0 + hr / per * WM + h * (16 * MT0) + hr % per, row_end - 1);
     };
     auto w_row = [&](int h, int hr) { return min(n0 + (dual ? hr : hr / (WN / 2) * WN + h * (WN / 2) + hr % (WN / 2)), n_lim - 1); };
-    // unit i of this wave in a half of X: w + 8 i, and of the four units left over by an odd number of row tiles one for each
+    // unit i of this wave in a half of X: w + NW i, and of the four units left over by an odd number of row tiles one for each
     // of waves 0-3 (first half) or 4-7 (second half; 0-3 again where only that half has them)
     auto x_unit = [&](int h, int i) { return i < (h ? LDX1 : LDX0) ? w + NW * i : NW * i + (w & 3); };
     auto x_has = [&](int h) { return h ? kOdd1 && (kOdd0 ? w >= 4 : w < 4) : kOdd0 && w < 4; };

@@ -446,7 +446,8 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
         // pieces run at a time, each next one on the first CU that is free; a piece costs its tokens and
         // kPieceTokens on top (prologue, Q loads, output), and if any group is cut, the partial results cost a merge
         // launch and their way through memory.  With every CU at work a token takes up to a third longer, the more query
-        // tiles a group fills: *busy is what the CUs' mean load comes to then.
+        // tiles a group fills: *busy is what the CUs' mean load comes to then.  Fitted to k_attn_prefill_short; k_attn_prefill takes up to
+        // 8 % less per token and somewhat more per piece.
         const int cus = std::max(1, ctx->attn_wgs / Hkv);
         auto cost = [&](int64_t *busy) {
             constexpr int64_t kPieceTokens = 160, kMergeTokens = 160, kSlotTokens = 8;

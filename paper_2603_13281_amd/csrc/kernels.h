@@ -176,8 +176,9 @@ int gemm_row_tile(const int *off, int n_groups);
 int gemm_tile_rows(int tile);
 int gemm_tile_cols(int tile);
 int gemm_grouped_splits(const GemmArgs &g, int max_splits, bool takes_slices);
-bool gemm_tile_marked(int tile);  // the mark of 192 and 160 rows by 256 in icarus_gemm_choice and icarus_gemm
-// Tiles of gemm_quad.hip (256, 192 or 160 rows by 256); launch_gemm_mfma takes this path for them.  g.K_ext and g.k_per_split are set.
+bool gemm_tile_marked(int tile);  // the mark of 192 and 160 rows by 256 in icarus_gemm_choice and icarus_gemm: part of their name, chooses nothing
+// Tiles of gemm_quad.hip: 256, 192 or 160 rows by 256, and 192 (or 160 or 128, where as many hold the rows) by 128; launch_gemm_mfma takes this
+// path for them.  g.K_ext and g.k_per_split are set.
 constexpr int kQuadMaxK = 1 << 23;  // a row's offset within its tile is kept in 32 bits of bytes
 hipError_t launch_gemm_quad(const GemmArgs &g, hipStream_t st);
 // Sum split-K partials P[splits][R][N] (fp32) and apply the epilogue `epi` into Y.

@@ -36,8 +36,8 @@ __device__ __forceinline__ void unpack8(uint4 v, float (&f)[8]) {
 // bf16 dot product (fp32 sums; x and A as stored) and sum all accumulators together: 316 rows, 2 x 16 accumulators,
 // with the split-K sums of the projection before it 23.3 -> 18.3 us.  With 16 or fewer the same change was slower (12.5 -> 15.5 us
 // for the norm and one target: the loop lives from loads that the compiler then no longer keeps in flight).  The joint sums of 64 accumulators
-// (two targets of rank 32), written as a loop, went through scratch memory: sums, norm, gate and up of 324 rows of 5120 with the norm before Q 84.9
-// us, by the recursion of wave_sums 53.8.
+// (two targets of rank 32) went through scratch memory as a loop: both norms of 324 rows of 5120 took 84.9 us, with the recursion of
+// wave_sums 53.8.
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float dot8(uint4 a, uint4 b, float c) {
     c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a.x), __builtin_bit_cast(bf16x2, b.x), c, false);
@@ -354,8 +354,10 @@ RowArgs shrink_args(const Dims &dm, const void *A0, const void *A1, const RowMet
 // The workgroups of a launch go to the 8 XCDs in turn.  The rows that have an adapter are dealt to them in runs of the same
 // model, so that an XCD's L2 holds the adapters of one or two models instead of all of them (A of one projection is 0.1-0.5 MB a
 // model at rank 16, 1.6 MB for 25600 columns at rank 32, beside an L2 of 4 MB), and evenly, so that no CU has two of them while
-// another has none; rows without one, which cost less, follow.  316 rows of 8 models, 4096 and 14336 columns: 12.7 -> 10.6 us
-// (norm and Q), 13.9 -> 12.1 (merge and O), 18.0 -> 14.7 (sums, norm, gate and up), 18.0 -> 16.1 (down); 144 rows, 25600 columns 28.6 -> 24.7.
+// another has none; rows without one, which cost less, follow.  All row kernels of a call (norms, merge, shrinks) in the order they have /
+// in this one, us, 8 models active: 4096 and 14336 columns, rank 16, 108 rows 50.5 / 46.0, 252 57.4 / 55.3, 288 59.0 / 50.6, 324 63.9 / 61.6, 576
+// 89.2 / 72.5, 1152 124 / 109; 5120 to 25600 columns, rank 32, 108 rows 72.8 / 63.9, 252 94.4 / 89.8, 288 118 / 93.0, 324 124 / 112, 576 157 / 131.
+// It is most where the rows with an adapter just fill the CUs, one or two to each; the merge alone gains up to 3 us or nothing.
 // A row's own loads then wait for its entry: 64 rows 7.5 -> 7.7, 9.7 -> 10.1 us, hence from 97 rows on.
 constexpr int kRowOrderMin = 97;
 constexpr int kRowOrderMaxModel = 0x7ffe;  // an entry has 15 bits for model + 1

@@ -142,6 +142,21 @@ def test_full_192_row_tiles_with_many_adapter_columns(rows, k):
         _check(binding.gemm(x, w, (192, 128, False), slices, t=t, b=b), torch.cat([q, v], 1), eps * torch.cat([qs, vs], 1) + 1e-30, (rows, k, slices))
 
 
+@pytest.mark.parametrize("k", [2 ** 23, 2 ** 23 + 64])
+@pytest.mark.parametrize("tile,rows", [((192, 128, False), 192), ((160, 256, True), 160)], ids=["192x128", "160x256"])
+def test_rows_gigabytes_apart(tile, rows, k):
+    # K = 2^23: the last row of a tile is more than 2^31 bytes behind its first, within the 32 bits that k_gemm_quad keeps; one slab
+    # more and the launch goes to the kernel with 64-bit row addresses.  A few columns of small whole numbers: exact in any order.
+    print("case: rows gigabytes apart", tile, rows, k, flush=True)
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    cols = torch.tensor([0, 63, 64, k // 12, k // 2 - 1, k // 2, k - 65, k - 64, k - 1], device="cuda:0")
+    x, w = (torch.zeros((n, k), dtype=torch.bfloat16, device="cuda:0") for n in (rows, 8))
+    xs, ws = (torch.randint(-8, 9, (n, len(cols)), generator=gen, device="cuda:0").to(torch.bfloat16) for n in (rows, 8))
+    x[:, cols], w[:, cols] = xs, ws
+    got = binding.gemm(x, [w], tile, 12)
+    assert torch.equal(got.double(), xs.double() @ ws.double().T)
+
+
 def test_gemm_refuses_what_the_kernels_do_not_take():
     x, w = _draw((4, 128), 1), _draw((16, 128), 2)
     for kw in (dict(tile=(96, 128, False)), dict(tile=(256, 256, True)), dict(tile=TILES[0], slices=13), dict(tile=TILES[0], slices=0)):
