@@ -77,11 +77,12 @@ def _bare(shape):
 
 @pytest.mark.parametrize("shape", [synth.LLAMA_SMALL, synth.QWEN_SMALL], ids=lambda s: s.name)
 @pytest.mark.parametrize("kind", ["normal", "slope", "step"])
-def test_both_prefill_kernels_give_the_same_bits(shape, kind):
+@pytest.mark.parametrize("longest", [470, 1200])
+def test_both_prefill_kernels_give_the_same_bits(shape, kind, longest):
     # Walks of up to 1280 tokens go to the kernel for short pieces, unless a longer one is in the call: the same chunks
     # with another chunk beside them, over 100 tokens and over 2004.
-    print("case: same bits", shape.name, kind, flush=True)
-    pre, chunk = PRE[:-1] + [1200], CHUNK + [3]
+    print("case: same bits", shape.name, kind, longest, flush=True)
+    pre, chunk = [min(n, longest) for n in PRE[:-1]] + [longest], CHUNK + [3]
     shape, base = _bare(shape)
     x = synth.make_hidden(shape, sum(chunk), seed=3, tag=5) / 16
     out = []
