@@ -89,7 +89,7 @@ def test_both_prefill_kernels_give_the_same_bits(shape, kind, longest):
     for last in (100, 2004):
         batch = synth.make_batch(shape, pre + [last], [0] * len(chunk), seed=3, headroom=max(chunk))
         pool = filled_batch(shape, batch, seed=3) if kind == "normal" else _pool(shape, batch, kind, 1000.0, pre)
-        mark_unwritten(shape, batch, pool, 0.0)
+        mark_unwritten(shape, batch, pool, np.nan)                     # positions past the context must not leak
         layer = make_layer(shape, base, None, batch.num_blocks)
         layer.set_attn_piece_limit(4096)
         out.append(layer.prefill_kv(dev(pool_to_device_layout(pool), True), torch.from_numpy(batch.block_tables).cuda(), pre + [last], chunk, dev(x, True)))
