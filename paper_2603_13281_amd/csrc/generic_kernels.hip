@@ -497,19 +497,18 @@ hipError_t launch_rope_append_tiles(const Dims &dm, const float *qkv, int ldq, i
 // tokens side by side, so a quad is one load, and neighbouring threads take the quads of a block's row (pl of them, up to four).
 // Latency-bound at the sizes this kernel is for, and next by the lines that its loads touch: with a thread per position and
 // a part per wave every load touched a line per lane.  Rows x 4 heads x 64, us, that with 256 threads a workgroup / this, float32:
-// 3 rows over 128 tokens 7.5 / 6.5, 12 rows over 1000 30.0 / 13.7, 96 rows over 1000 55.0 / 34.1, 768 rows 253 / 115; bf16 768 rows
-// 241 / 138; FP8 64 rows over 128 10.1 / 8.4, 768 rows over 1000 168 / 106.
-// KU, VU: loads in flight.  An FP8 load is four conversions; eight of them in flight took 142 registers, and 1024 threads spilled
-// (FP8, the two figures above 11.6 and 186; 768 rows x 32 heads x 80 over 128 tokens 302 us, now 160).
-// LPT > 1: D and Bk are multiples of 4; LPT = 1: one element, one position at a time.
-template <typename T, typename KT, int NT, int LPT>
+// 3 rows over 128 tokens 9.4 / 8.4, 12 rows over 1000 28.7 / 13.0, 768 rows 253 / 93; bf16 768 rows 240 / 93; FP8 64 rows over 128 10.1 / 8.6,
+// 768 rows over 1000 169 / 106.
+// KU, VU: loads in flight.  With eight the workgroups in flight were fewer (109-144 registers, now 74-82) and 1024 threads spilled for an FP8
+// cache, whose load is four conversions: 768 rows float32 115, bf16 138, FP8 186 us.
+// quads: D and Bk are multiples of 4; else one element, one position at a time.
+template <typename T, typename KT, int NT, int LPT, bool quads>
 __global__ void __launch_bounds__(NT) k_attn_generic(const T *__restrict__ q, const KT *__restrict__ pool,
                                                      const int32_t *__restrict__ bt, int max_blocks,
                                                      const int32_t *__restrict__ row_seq, const int32_t *__restrict__ row_kvlen,
                                                      T *__restrict__ out, int Hq, int Hkv, int D, int Bk, float scale,
                                                      float k_scale, float v_scale, int parts, int pl) {
-    constexpr bool quads = LPT > 1;
-    constexpr int KU = sizeof(KT) == 1 ? 2 : 8, VU = sizeof(KT) == 1 ? 4 : 8;
+    constexpr int KU = sizeof(KT) == 1 ? 2 : 4, VU = 4;
     __shared__ __attribute__((aligned(16))) float sc[1024];
     __shared__ size_t soff[1024];  // where a position's V elements are, within its head
     __shared__ float sum[NT];
@@ -603,7 +602,7 @@ __global__ void __launch_bounds__(NT) k_attn_generic(const T *__restrict__ q, co
     }
 }
 
-// Workgroups up to which each gets a CU, and so 1024 threads.  Rows x 4 heads x 64, us with 256 / 1024 threads, float32: 12
+// Workgroups up to which each gets a CU, and so 1024 threads (512 where D < 64).  Rows x 4 heads x 64, us with 256 / 1024 threads, float32: 12
 // workgroups over 1000 tokens 20.7 / 13.7, 256 over 128 tokens 8.6 / 8.6 and over 1000 29.6 / 18.4, 260 8.4 / 12.8 and 37.4 / 37.8; bf16 256
 // 9.5 / 8.5 and 28.8 / 15.2, 260 9.2 / 12.8 and 45.1 / 34.3, 768 10.2 / 18.3 and 49.8 / 51.0; FP8 256 9.6 / 8.4 and 29.8 / 15.2, 260 9.2 / 12.1 and
 // 40.4 / 30.7, 768 10.4 / 16.9 and 50.1 / 48.7.
@@ -613,24 +612,32 @@ hipError_t launch_attn_generic(const Dims &dm, const void *q, const void *pool, 
                                const RowMeta &rm, void *out, int R, hipStream_t st) {
     if (R <= 0) return hipSuccess;
     float scale = 1.0f / sqrtf((float)dm.D);
-    const int quads = dm.D % 4 == 0 && dm.Bk % 4 == 0;
     dim3 grid(dm.Hq, R);
-    auto launch = [&](auto nt, auto lpt) {
+    auto launch = [&](auto nt, auto lpt, auto by_quads) {
         constexpr int NT = decltype(nt)::value, LPT = decltype(lpt)::value;
+        constexpr bool quads = decltype(by_quads)::value;
         int parts = 1;
         while (parts < 32 && NT / (2 * parts) >= dm.D) parts *= 2;
-        const int pl = std::min(parts, LPT == 1 || dm.Bk % 16 == 0 ? 4 : dm.Bk % 8 == 0 ? 2 : 1);  // quads of a block
-        DISPATCH_TK(dm.bf16, dm.kv8, hipLaunchKernelGGL((k_attn_generic<T, KT, NT, LPT>), grid, dim3(NT), sizeof(float) * dm.D, st, (const T *)q,
+        const int pl = std::min(parts, !quads || dm.Bk % 16 == 0 ? 4 : dm.Bk % 8 == 0 ? 2 : 1);  // quads of a block
+        DISPATCH_TK(dm.bf16, dm.kv8, hipLaunchKernelGGL((k_attn_generic<T, KT, NT, LPT, quads>), grid, dim3(NT), sizeof(float) * dm.D, st, (const T *)q,
                                                         (const KT *)pool, bt, max_blocks, rm.row_seq, rm.row_kvlen, (T *)out, dm.Hq, dm.Hkv,
                                                         dm.D, dm.Bk, scale, dm.k_scale, dm.v_scale, parts, pl));
         return hipGetLastError();
     };
     constexpr std::integral_constant<int, 1> one;
+    constexpr std::integral_constant<int, 2> two;
     constexpr std::integral_constant<int, 4> four;
-    if (!quads) return launch(std::integral_constant<int, 256>(), one);
+    constexpr std::integral_constant<int, 256> few;
+    constexpr std::true_type by_quads;
+    if (dm.D % 4 || dm.Bk % 4) return launch(few, one, std::false_type());
+    // A position's address costs each of its threads two divisions, so a short row has fewer of them; and 1024 threads need more rounds to
+    // meet than a short row takes.  bf16, us, one thread a position and 256 a workgroup at first / four and 1024 / this: D = 32, 12 rows x
+    // 8 heads over 128 tokens 7.8 / 8.5 / 7.5, 768 rows over 1000 154 / 171 / 97; D = 16 the same 7.1 / 8.5 / 7.2 and 67 / 129 / 57; D = 48
+    // 9.0 / 8.6 / 7.8 and 302 / 243 / 156; D = 60, 768 rows x 4 heads 225 / 149 / 119 (float32 241 / 120 / 136).
     const bool wide = (int64_t)dm.Hq * R <= kGenericWide;
-    if (wide) return launch(std::integral_constant<int, 1024>(), four);
-    return launch(std::integral_constant<int, 256>(), four);
+    if (dm.D < 32) return wide ? launch(std::integral_constant<int, 512>(), one, by_quads) : launch(few, one, by_quads);
+    if (dm.D < 64) return wide ? launch(std::integral_constant<int, 512>(), two, by_quads) : launch(few, two, by_quads);
+    return wide ? launch(std::integral_constant<int, 1024>(), four, by_quads) : launch(few, four, by_quads);
 }
 
 }  // namespace icarus

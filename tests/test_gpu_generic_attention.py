@@ -38,7 +38,7 @@ def test_edges(D, Bk, rows):
 
 @pytest.mark.parametrize("rows", [1, 6], ids=["wide", "narrow"])
 @pytest.mark.parametrize("bf16,fp8", [(True, False), (True, True), (False, True)], ids=["bf16", "bf16-fp8", "fp32-fp8"])
-@pytest.mark.parametrize("D,Bk", [(64, 16), (80, 8), (40, 4), (30, 6)])
+@pytest.mark.parametrize("D,Bk", [(64, 16), (80, 8), (40, 4), (32, 16), (28, 8), (8, 16), (30, 6)])
 def test_edges_of_the_narrow_types(D, Bk, bf16, fp8, rows):
     print("case: vector attention, head size", D, "block size", Bk, "rows", rows, "bf16", bf16, "fp8", fp8, flush=True)
     shape = synth.TINY.replace(head_dim=D, block_size=Bk, d_model=4 * D, n_kv_heads=2, bf16=bf16)
