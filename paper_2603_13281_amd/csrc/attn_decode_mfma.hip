@@ -1079,11 +1079,8 @@ __global__ void __launch_bounds__(64 * kPrefillWaves) k_attn_prefill(const bf16_
 }
 
 // The same attention in eight waves of two query tiles, one phase after the other, two waves a SIMD: the kernel for the
-// FP8 cache, whose codes pass through registers that k_attn_prefill does not have, and for pieces of up to kShortPiece tokens, where
-// a wave's first and last groups, which nothing hides, count for more than what the pipeline hides of the others.  us here / there,
-// whole walks: 32 chunks of 64 rows, 32 query heads, over 480 tokens 36.0 / 38.1, 900 50.4 / 52.1, 1200 60.5 / 60.8, 1700 76.3 / 75.8, 4000
-// 149 / 143; 8 chunks of 256 rows, 64 heads, over 900 95.6 / 101, 1200 115 / 116, 1700 150 / 142, 7000 473 / 445.
-constexpr int kShortWaves = 8, kShortNT = 2, kShortPiece = 1280;
+// FP8 cache, whose codes pass through registers that k_attn_prefill does not have, and see attn_prefill_pipelined.
+constexpr int kShortWaves = 8, kShortNT = 2;
 static_assert(kShortWaves * kShortNT == kPrefillWaves * kPrefillNT, "the plan's groups fit both");
 
 // compute_group for a group that sits in LDS as fragments (src[i * 64]: K fragments i = 0..7, then
@@ -1419,6 +1416,15 @@ int attn_prefill_round() { return kRoundGroups * kGrp; }
 
 int attn_prefill_group_queries() { return kPrefillWaves * kPrefillNT * 16; }  // stacked queries one prefill workgroup holds
 
+// In pieces of up to some length a wave's first and last groups, which nothing hides, count for more than what the pipeline of
+// k_attn_prefill hides of the others; and a token group that is not full leaves whole waves of it idle, of four tiles each, where
+// eight waves are idle in twos.  Eight waves / four, us, whole walks and cut ones, by the longest piece: groups full to 97 % and more, 1088
+// tokens 49.8 / 51.0, 1408 63.0 / 61.9, 1792 78.2 / 75.7, 2750 101 / 96, 8250 277 / 252, 14064 486 / 441; less full (400 rows in groups
+// of 64 or 32), 1400 51.0 / 53.7, 2900 90.3 / 93.0, 3900 115.8 / 116.6, 5400 168 / 164, 14400 415 / 402.
+bool attn_prefill_pipelined(int longest, int64_t queries, int64_t groups) {
+    return longest > (100 * queries >= 97 * groups * attn_prefill_group_queries() ? 1280 : 5120);
+}
+
 bool attn_prefill_mfma_supported(const Dims &dm, int g_max) {
     return dm.bf16 && dm.D == kD && dm.Bk == kBk && g_max >= 1 && g_max <= attn_prefill_group_queries();
 }
@@ -1436,7 +1442,7 @@ hipError_t launch_attn_prefill_mfma(const Dims &dm, const void *q, const void *p
         set = e == hipSuccess;
         return e;
     };
-    if (!dm.kv8 && pl.chunk > kShortPiece) {
+    if (!dm.kv8 && pl.pipelined) {
         static bool set = false;
         const hipError_t e = allow_lds(k_attn_prefill, set);
         if (e != hipSuccess) return e;

@@ -550,11 +550,14 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
             pl->item_direct = pl->item_part + n_items;
             hp->ints += 2 * (size_t)S + 4 * n_items;
         }
+        int64_t queries = 0;
+        for (int s : order) queries += (int64_t)seq_rows[s] * g;
         pl->n_seq = S;
         pl->n_items = (int)n_items;
         pl->chunk = max_len;
         pl->g_max = g_max;
         pl->causal = 1;
+        pl->pipelined = attn_prefill_pipelined(max_len, queries, (int64_t)order.size());
         hp->has_split = any;
         hp->valid = true;
         return;

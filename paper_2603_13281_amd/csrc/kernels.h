@@ -113,6 +113,7 @@ struct AttnPlan {
     int n_seq;                         // S
     int n_items, n_wgs, chunk, g_max;  // n_wgs: shares; chunk: longest piece; g_max: largest stacked group (rows * Hq/Hkv)
     int causal;                  // 1: row t of a sequence attends to kv_len - (rows - 1 - t) tokens (prefill)
+    int pipelined;               // prefill: see attn_prefill_pipelined
 };
 // ICaRusLinear GEMM on matrix cores.  Y = X W^T (+ T Bcat^T), see gemm_mfma.hip.
 enum { GEMM_PLAIN = 0, GEMM_DUAL = 1 };          // DUAL: W[0] = gate, W[1] = up, Y = silu(gate) * up
@@ -216,6 +217,8 @@ hipError_t launch_merge_shrink(const Dims &dm, const float *part_o, const float 
 int attn_prefill_group_queries();
 int attn_prefill_max_ctx();  // longest piece, in tokens
 int attn_prefill_round();    // tokens of a round of the walk: pieces are cut between rounds
+// A call goes to the kernel for long pieces: its longest piece, its stacked queries per kv-head, their groups.
+bool attn_prefill_pipelined(int longest, int64_t queries, int64_t groups);
 bool attn_prefill_mfma_supported(const Dims &dm, int g_max);
 hipError_t launch_attn_prefill_mfma(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
                                     const AttnPlan &pl, void *out, float *part_o, float *part_ml, hipStream_t st);

@@ -13,7 +13,7 @@ from paper_2603_13281_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-PRE = [32, 64, 95, 127, 128, 129, 300, 513, 3000]
+PRE = [32, 64, 95, 127, 128, 129, 300, 513, 11000]
 CHUNK = [1, 16, 33, 64, 65, 70, 5, 40, 9]
 
 
@@ -39,7 +39,7 @@ def _pool(shape, batch, kind, reach, pre=PRE):
 @pytest.mark.parametrize("shape", [synth.LLAMA_SMALL, synth.QWEN_SMALL], ids=lambda s: s.name)
 @pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
 @pytest.mark.parametrize("kind", ["slope", "step"])
-@pytest.mark.parametrize("limit", [0, 128, 1408, 4096])  # 1408: pieces, 4096: whole walks, by the kernel for long pieces (more than 1280 tokens)
+@pytest.mark.parametrize("limit", [0, 128, 5504, 16384])  # 5504: pieces, 16384: whole walks, by the kernel for long pieces (more than 5120 tokens)
 def test_scores_far_from_the_reference(shape, fp8, kind, limit):
     print("case: far scores", shape.name, "fp8", fp8, kind, "pieces", limit, flush=True)
     base = synth.make_base(shape, seed=3, norm_ones=False)
@@ -79,19 +79,19 @@ def _bare(shape):
 @pytest.mark.parametrize("kind", ["normal", "slope", "step"])
 @pytest.mark.parametrize("longest", [470, 1200])
 def test_both_prefill_kernels_give_the_same_bits(shape, kind, longest):
-    # Walks of up to 1280 tokens go to the kernel for short pieces, unless a longer one is in the call: the same chunks
-    # with another chunk beside them, over 100 tokens and over 2004.
+    # Walks of up to 5120 tokens go to the kernel for short pieces, unless a longer one is in the call: the same chunks
+    # with another chunk beside them, over 100 tokens and over 6004.
     print("case: same bits", shape.name, kind, longest, flush=True)
     pre, chunk = [min(n, longest) for n in PRE[:-1]] + [longest], CHUNK + [3]
     shape, base = _bare(shape)
     x = synth.make_hidden(shape, sum(chunk), seed=3, tag=5) / 16
     out = []
-    for last in (100, 2004):
+    for last in (100, 6004):
         batch = synth.make_batch(shape, pre + [last], [0] * len(chunk), seed=3, headroom=max(chunk))
         pool = filled_batch(shape, batch, seed=3) if kind == "normal" else _pool(shape, batch, kind, 1000.0, pre)
         mark_unwritten(shape, batch, pool, np.nan)                     # positions past the context must not leak
         layer = make_layer(shape, base, None, batch.num_blocks)
-        layer.set_attn_piece_limit(4096)
+        layer.set_attn_piece_limit(8192)
         out.append(layer.prefill_kv(dev(pool_to_device_layout(pool), True), torch.from_numpy(batch.block_tables).cuda(), pre + [last], chunk, dev(x, True)))
     torch.cuda.synchronize()
     n = sum(CHUNK)
@@ -101,7 +101,7 @@ def test_both_prefill_kernels_give_the_same_bits(shape, kind, longest):
 @pytest.mark.parametrize("shape", [synth.LLAMA_SMALL, synth.QWEN_SMALL], ids=lambda s: s.name)
 @pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
 @pytest.mark.parametrize("kind", ["slope", "step"])
-@pytest.mark.parametrize("limit", [128, 1408, 4096])
+@pytest.mark.parametrize("limit", [128, 5504, 16384])
 def test_every_query_far_from_the_reference(shape, fp8, kind, limit):
     print("case: far scores by query", shape.name, "fp8", fp8, kind, "pieces", limit, flush=True)
     shape, base = _bare(shape)
