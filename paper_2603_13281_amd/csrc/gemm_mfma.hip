@@ -111,9 +111,11 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) k_gemm_mfma(GemmArgs g
     const int rmask = g.r - 1;
     const size_t model_stride = (size_t)g.n_seg[0] * g.r;  // elements between consecutive models' B
 
+    const int n_base = min(nk, max(0, (K_base - k_begin) / BK)), turn = gemm_turn(g, tile_n, n_base);
+    auto k_of = [&](int kt) { return k_begin + (kt < n_base ? gemm_slab(kt, turn, n_base) : kt) * BK; };
     // enqueue the loads of slab kt into ring stage `stage`
     auto issue = [&](int kt, int stage) {
-        const int k0 = k_begin + kt * BK;
+        const int k0 = k_of(kt);
         const uint32_t la = lds0 + stage * kStage + w * 1024;
         if (k0 < K_base) {  // slab inside the base weights (K is a multiple of the slab)
 #pragma unroll
@@ -203,14 +205,14 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) k_gemm_mfma(GemmArgs g
     // barrier is straight-line code: the first fragments of slab kt+1, then the pending MFMAs of slab
     // kt alternating with the loads of slab kt+NS, so that the matrix pipe is fed while the wave
     // issues its memory instructions.
-    const int n_steady = min(nk, max(0, (K_base - k_begin) / BK)) - NS;
+    const int n_steady = n_base - NS;
     for (; kt < n_steady; ++kt) {
         slab_head(stage);
         const int next = stage + 1 == NS ? 0 : stage + 1;
         wait_loads<(NS - 2) * NL>();
         __builtin_amdgcn_s_barrier();
         read_frags(next, 0, fa[0], fb[0]);
-        const int k0 = k_begin + (kt + NS) * BK;
+        const int k0 = k_begin + gemm_slab(kt + NS, turn, n_base) * BK;
         const uint32_t la = lds0 + stage * kStage + w * 1024;
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -345,6 +347,16 @@ int n_tiles_for(const GemmArgs &g, int bm, int bn) {
     for (int s = 0; s < g.nseg; ++s) n_tiles += (g.n_seg[s] + bn - 1) / bn;
     return m_tiles * n_tiles;
 }
+
+// Whether the workgroups of a launch take their slabs of the weights from different places along K (gemm_turn), column tile n from
+// slab n on.  Started all at the same one, they ask at any moment for the same few columns of every weight row; where the rows
+// are a multiple of 4 KB apart that is a few bits of the address, and what the memory channels make of it depends on where the
+// matrices lie.  Column tile n + 1 starts one slab behind n, so that an XCD's workgroups still pass over the same slabs of X within a few slabs'
+// time (starts a golden section apart were as good up to 64 rows but cost 316 rows, 14336 -> 4096 25 %).  us, same / different starts, weights
+// from HBM in 3-13 places: 4096 -> 2 x 14336, 9-64 rows 43.6-60 / 46.8-51, mean 53.4 / 47, 128 rows 58.6 / 54.5, 144 rows 61.2 / 58.5, 316 rows 82.5 / 78; LM head
+// 4096 -> 128256, 9 rows 196 / 177, 64 rows 221 / 198; 6144 -> 2 x 8192, 9 rows 56 / 51; 14336 -> 4096 and 4096 -> 4096 in slices equal; 576 and 753 rows equal (bound by
+// the matrix cores).  Rows 10 KB apart (5120 -> 2 x 25600) 107.6 / 109.7, 120.4 / 121.5.
+bool gemm_staggered(const GemmArgs &g) { return g.K % 2048 == 0 && g.R <= 384; }
 
 bool is_quad(int kind) { return kind >= TILE_192x128; }
 
@@ -533,6 +545,7 @@ hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st) {
     }
     g.K_ext = k_ext_of(g);
     g.k_per_split = ((g.K_ext + g.splits - 1) / g.splits + kKAlign - 1) / kKAlign * kKAlign;
+    g.stagger = gemm_staggered(g) ? gemm_inv(std::min(g.k_per_split, g.K) / kKAlign) : 0u;
     // Tiles of 192 rows by 128 that are needed in full (gemm_quad.hip has lower ones), with adapters: the slabs of adapter columns are
     // code that a workgroup of k_gemm_quad runs once, fetched as it goes (a form with fewer instructions per load but more of them in
     // all took 1.3 us longer still); four such slabs cost 1.3-2 us more there than in this kernel's loop, which only a long K earns back.  us with 8

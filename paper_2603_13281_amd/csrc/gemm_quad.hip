@@ -137,11 +137,13 @@ __global__ void __launch_bounds__(128 * WAVES_N, WAVES_N == 4 ? 1 : 2) k_gemm_qu
             wo[h][i] = (uint32_t)((w_row(h, p.hr) - n0) * (uint32_t)g.K + p.kc) * 2u;
         }
     }
+    const int turn = gemm_turn(g, tile_n, n_base);
     // part: 0, 1 the halves of X; 2, 3 those of W
     auto part_lds = [&](int P, int S) { return P >= 2 ? kBOff + S * kWStage + (P & 1) * (kWStage / 2) : S * kXStage + P * (32 * MT0 * kRow); };
     // load i of a part, of a slab of base weights
     auto load_one = [&](auto Part, auto Stage, int kt, int i) {
         constexpr int P = decltype(Part)::value, S = decltype(Stage)::value;
+        kt = gemm_slab(kt, turn, n_base);
         if constexpr (P < 2) {
             if (i < (P ? LDX1 : LDX0) || x_has(P)) dma16_at(xb + (size_t)kt * kRow, xo[P][i], lds0 + part_lds(P, S) + x_unit(P, i) * 1024);
         } else dma16_at((P & 1 ? wb1 : wb0) + (size_t)kt * kRow, wo[P & 1][i], lds0 + part_lds(P, S) + (w + NW * i) * 1024);

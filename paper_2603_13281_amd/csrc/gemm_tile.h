@@ -50,6 +50,13 @@ __device__ __forceinline__ BRow b_row(const GemmArgs &g, const bf16_t *W0, const
     return o;
 }
 
+// Slabs of base weights, n_base of them, are taken from slab `turn` on, around the end: tile_n modulo their number, or 0 (GemmArgs::stagger).
+__device__ __forceinline__ int gemm_turn(const GemmArgs &g, int tile_n, int n_base) { return (int)__umulhi((uint32_t)tile_n * g.stagger, (uint32_t)n_base); }
+__device__ __forceinline__ int gemm_slab(int kt, int turn, int n_base) {
+    const int at = kt + turn;
+    return at < n_base ? at : at - n_base;
+}
+
 // 256 bytes of zeros: the source of LDS-direct loads that must read as zeros (adapter columns a
 // row does not have, padding past the last adapter column).
 __device__ uint4 g_zero_page[16];

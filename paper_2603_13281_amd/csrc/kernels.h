@@ -138,6 +138,7 @@ struct GemmArgs {
     // rows at most).  Group 0 multiplies W[0] (DUAL: W[0], W[1]), group j > 0 Wg[.] + (j - 1) * wg_stride elements.
     const int32_t *row_tiles; int n_row_tiles;
     const bf16_raw *Wg[2]; size_t wg_stride;
+    uint32_t stagger;                                // gemm_inv of a slice's slabs of base weights, 0: every workgroup starts at the first one (gemm_staggered)
 };
 bool gemm_mfma_supported(const Dims &dm, int K);
 // fills the tile order from m_tiles, n_tiles and splits, for bm x bn tiles and per_cu workgroups to a CU
