@@ -27,6 +27,8 @@
 #include "device_util.h"
 #include "kernels.h"
 
+#include <type_traits>
+
 namespace icarus {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
@@ -182,36 +184,31 @@ __device__ __forceinline__ void compute_group(State<NT> &st, KVFrag &f, const bf
     }
 }
 
-// A wave's walk over its share of the chunk: groups first, first + stride, ... with N query tiles.
-// The first n_clean groups are valid for every query: they run in a loop with two register buffers,
-// loads issued one group ahead.  The few groups after them (a partial last group, the causal
-// stagger of a prefill chunk) are done with masks by the waves they fall to.
-template <int NT, int N>
-__device__ __forceinline__ void wave_walk(State<NT> &st, const bf16_t *__restrict__ pool, const int *__restrict__ blds,
-                                          int n_blk, int n_tok, int n_clean, const int (&stag)[NT], int first, int stride,
-                                          int c, int Hkv, const bf16x8 (&qr)[NT][kKS], const bf16x8 *__restrict__ qlds, float scale_log2, int lane) {
+// A wave's walk over its share of the chunk: groups first, first + stride, ... with N query tiles, two register buffers, loads
+// issued one group ahead; f0 holds group `first` (or is on its way) when the walk begins.  The first n_clean groups are valid for
+// every query; the last ones of the wave, a partial last group among them, are multiplied with masks.  What the loop loads it also
+// multiplies: loads that only repeat the last block would hold up the loads of the next piece.  (The loop's own loads are
+// unconditional: with a load under a condition the compiler no longer knows how many younger loads are in flight when a buffer
+// is consumed and waits for all of them, the prefetch included.)
+template <int NT, int N, typename Frag, typename Load, typename Compute>
+__device__ __forceinline__ void wave_walk(State<NT> &st, Frag &f0, int n_tok, int first, int stride, Load load, Compute compute) {
     const int n_grp = (n_tok + kGrp - 1) / kGrp;
-    auto blk_of = [&](int grp, int which) {
-        return __builtin_amdgcn_readfirstlane(blds[min(grp * 2 + which, n_blk - 1)]);
-    };
-    KVFrag f0, f1;
-    if (first < n_clean) load_group(f0, pool, blk_of(first, 0), blk_of(first, 1), c, Hkv, lane);
-    // The loads of the loop are unconditional (past the end blk_of repeats the chunk's last block and the
-    // data is dropped): with a load under a condition the compiler no longer knows how many younger loads
-    // are in flight when a buffer is consumed and waits for all of them, the prefetch included.
+    Frag f1;
+    int grp = first;
 #pragma nounroll
-    for (int grp = first; grp < n_clean; grp += 2 * stride) {
-        load_group(f1, pool, blk_of(grp + stride, 0), blk_of(grp + stride, 1), c, Hkv, lane);
-        compute_group<NT, N, false>(st, f0, qr, qlds, kGrp, stag, scale_log2, lane);
-        load_group(f0, pool, blk_of(grp + 2 * stride, 0), blk_of(grp + 2 * stride, 1), c, Hkv, lane);
-        if (grp + stride < n_clean) compute_group<NT, N, false>(st, f1, qr, qlds, kGrp, stag, scale_log2, lane);
+    for (; grp + 2 * stride < n_grp; grp += 2 * stride) {
+        load(f1, grp + stride);
+        compute(std::false_type(), f0, kGrp);
+        load(f0, grp + 2 * stride);
+        compute(std::false_type(), f1, kGrp);
     }
-#pragma nounroll
-    for (int grp = n_clean; grp < n_grp; ++grp) {
-        if (grp % stride != first) continue;
-        load_group(f0, pool, blk_of(grp, 0), blk_of(grp, 1), c, Hkv, lane);
-        compute_group<NT, N, true>(st, f0, qr, qlds, n_tok - grp * kGrp, stag, scale_log2, lane);
+    if (grp + stride < n_grp) {
+        load(f1, grp + stride);
+        compute(std::false_type(), f0, kGrp);
+        f0 = f1;
+        grp += stride;
     }
+    if (grp < n_grp) compute(std::true_type(), f0, n_tok - grp * kGrp);
 }
 
 // ---- FP8 (E4M3) cache: 1-byte codes, value = code * scale (one scale for K, one for V) ----------------
@@ -335,32 +332,6 @@ __device__ __forceinline__ void compute_group8(State<NT> &st, const KVRaw8 &f, c
         }
 #pragma unroll
         for (int qt = 0; qt < N; ++qt) st.o[dt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, pb[qt], st.o[dt][qt], 0, 0, 0);
-    }
-}
-
-// wave_walk over an FP8 cache: the two register buffers hold raw codes (48 registers each).
-template <int NT, int N>
-__device__ __forceinline__ void wave_walk8(State<NT> &st, const uint8_t *__restrict__ pool, const int *__restrict__ blds,
-                                           int n_blk, int n_tok, int n_clean, const int (&stag)[NT], int first, int stride,
-                                           int c, int Hkv, const bf16x8 (&qr)[NT][kKS], const bf16x8 *__restrict__ qlds, float scale_log2, int lane) {
-    const int n_grp = (n_tok + kGrp - 1) / kGrp;
-    auto blk_of = [&](int grp, int which) {
-        return __builtin_amdgcn_readfirstlane(blds[min(grp * 2 + which, n_blk - 1)]);
-    };
-    KVRaw8 f0, f1;
-    if (first < n_clean) load_group8(f0, pool, blk_of(first, 0), blk_of(first, 1), c, Hkv, lane);
-#pragma nounroll
-    for (int grp = first; grp < n_clean; grp += 2 * stride) {  // unconditional loads, see wave_walk
-        load_group8(f1, pool, blk_of(grp + stride, 0), blk_of(grp + stride, 1), c, Hkv, lane);
-        compute_group8<NT, N, false>(st, f0, qr, qlds, kGrp, stag, scale_log2, lane);
-        load_group8(f0, pool, blk_of(grp + 2 * stride, 0), blk_of(grp + 2 * stride, 1), c, Hkv, lane);
-        if (grp + stride < n_clean) compute_group8<NT, N, false>(st, f1, qr, qlds, kGrp, stag, scale_log2, lane);
-    }
-#pragma nounroll
-    for (int grp = n_clean; grp < n_grp; ++grp) {
-        if (grp % stride != first) continue;
-        load_group8(f0, pool, blk_of(grp, 0), blk_of(grp, 1), c, Hkv, lane);
-        compute_group8<NT, N, true>(st, f0, qr, qlds, n_tok - grp * kGrp, stag, scale_log2, lane);
     }
 }
 
@@ -530,6 +501,73 @@ __device__ __forceinline__ void store_to_lds(const State<NT> &st, float *__restr
     }
 }
 
+// The four waves' states of a piece, each over its own groups, put together: every wave leaves its state in LDS (image_store) and, after a
+// barrier, each takes a quarter of the head dimension (image_finish): d tiles 2w, 2w + 1 of all queries.
+template <int NT>
+struct Image {
+    static constexpr int kO = kDT * NT * 64, kBytes = kO * 16 + NT * 64 * 8;  // f32x4 [dt][qt][lane], float2 (max, sum) [qt][lane]
+};
+template <int NT>
+__device__ __forceinline__ void image_store(const State<NT> &st, char *__restrict__ img, int lane) {
+    f32x4 *o = (f32x4 *)img;
+    float2 *ml = (float2 *)(img + Image<NT>::kO * 16);
+#pragma unroll
+    for (int qt = 0; qt < NT; ++qt) {
+        ml[qt * 64 + lane] = make_float2(st.m[qt], st.l[qt]);
+#pragma unroll
+        for (int dt = 0; dt < kDT; ++dt) o[(dt * NT + qt) * 64 + lane] = st.o[dt][qt];
+    }
+}
+template <int NT, typename ReadDone>
+__device__ __forceinline__ void image_finish(const char *__restrict__ imgs, int w, int G, int g, int row0, int c, int Hq, int Hkv, int direct, int slot,
+                                             int g_max, float v_scale, bf16_t *__restrict__ out, float *__restrict__ part_o,
+                                             float *__restrict__ part_ml, int lane, ReadDone read_done) {
+    const int m = lane & 15, q = lane >> 4;
+    f32x4 o[NT][2];
+    float mn[NT], l[NT];
+#pragma unroll
+    for (int qt = 0; qt < NT; ++qt) {
+        float2 ml[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) ml[k] = ((const float2 *)(imgs + k * Image<NT>::kBytes + Image<NT>::kO * 16))[qt * 64 + lane];
+        mn[qt] = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));
+        l[qt] = 0.f;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) o[qt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float a = ml[k].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[k].x - mn[qt]);  // a wave without groups
+            l[qt] += a * ml[k].y;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f32x4 v = ((const f32x4 *)(imgs + k * Image<NT>::kBytes))[((2 * w + h) * NT + qt) * 64 + lane];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[qt][h][i] += a * v[i];
+            }
+        }
+    }
+    read_done();
+#pragma unroll
+    for (int qt = 0; qt < NT; ++qt) {
+        l[qt] += __shfl_xor(l[qt], 16, 64);
+        l[qt] += __shfl_xor(l[qt], 32, 64);
+        const int j = 16 * qt + m;
+        if (j >= G) continue;
+        if (direct) {
+            const float inv = v_scale / l[qt];
+            bf16_t *op = out + ((size_t)(row0 + j / g) * Hq + c * g + j % g) * kD + 32 * w + 4 * q;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                *(uint2 *)(op + 16 * h) = make_uint2(pack_bf16(o[qt][h][0] * inv, o[qt][h][1] * inv), pack_bf16(o[qt][h][2] * inv, o[qt][h][3] * inv));
+        } else {
+            const size_t pj = ((size_t)slot * Hkv + c) * g_max + j;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) *(f32x4 *)(part_o + pj * kD + 32 * w + 16 * h + 4 * q) = o[qt][h] * v_scale;
+            if (w == 0 && q == 0) *(float2 *)(part_ml + pj * 2) = make_float2(mn[qt], l[qt]);
+        }
+    }
+}
+
 // Write tiles [0, n) of st as the call's query tiles qt0 .. qt0+n-1: the final output when the
 // sequence has a single chunk, else this chunk's partial result.
 template <int NT>
@@ -567,10 +605,124 @@ __device__ __forceinline__ void finish(State<NT> &st, int qt0, int n, int G, int
     }
 }
 
-// NA: query tiles of waves 0,1 (of all four waves when NB == 0); NB: query tiles of waves 2,3.
-// KV8: the pool holds FP8 codes (scale_log2 then includes the K scale, v_scale multiplies the output).
-template <int NA, int NB, bool KV8 = false>
-__global__ void __launch_bounds__(256) k_attn_decode(const bf16_t *__restrict__ qg, const void *__restrict__ pool_v,
+// 4-byte LDS-direct load, as dma16
+__device__ __forceinline__ void dma4(const void *g, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_base), "v"(g) : "memory");
+}
+__device__ uint4 g_zero_query;  // source of Q fragments past a sequence's last query
+
+// A piece as its workgroups read it (AttnPlan::pieces).
+struct Piece {
+    int row0, rows, bt_row, begin, n_tok, slot;
+    bool direct, last;  // last: of its share
+    __device__ __forceinline__ Piece(const int32_t *p)
+        : row0(p[0] & 0xffff), rows(p[0] >> 16), bt_row(p[1]), begin(p[2]), n_tok(p[3] & kPieceTokens), slot(p[4]), direct(p[3] & kPieceDirect), last(p[3] & kPieceLast) {}
+};
+
+// Up to three query tiles: every wave holds all of them and takes every fourth group of the piece.  KV8: the pool holds FP8 codes
+// (scale_log2 then includes the K scale, v_scale multiplies the output).
+//
+// A workgroup walks the pieces of its share one after the other, and between two of them nothing of it would be under way: the next piece's
+// numbers, its Q and block ids, its first keys and values each wait for the one before.  So the Q and ids of the next piece are requested (LDS-direct,
+// into the other of two buffers) before this one is walked, and its first groups as soon as the waves' states are in LDS: the merge
+// runs under them.  A merge of two halvings through single floats, and each piece from nothing, took, us before / now: 16 sequences of
+// 500-8192 tokens, 72 k in all 60.3 / 57.0 (5.2 TB/s), one of 4096 14.5 / 12.0, 32 of 1024-8192 114 / 112, 64 of 1024-16384 418 / 416.5: long walks
+// are held by what HBM gives (5.6 TB/s of permuted blocks, where plain reads get 6.1).  Two workgroups of one query tile to a CU: no gain (112.6).
+template <int NT, bool KV8>
+__global__ void __launch_bounds__(256) k_attn_decode(const bf16_t *__restrict__ qg, const void *__restrict__ pool_v, const int32_t *__restrict__ bt,
+                                                     int max_blocks, AttnPlan pl, bf16_t *__restrict__ out, float *__restrict__ part_o,
+                                                     float *__restrict__ part_ml, int Hq, int Hkv, float scale_log2, float v_scale) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    // LDS: the waves' states | two buffers of Q fragments [qt][ks][lane] | two of block ids
+    constexpr int kQBytes = NT * kKS * 1024, kQAt = 4 * Image<NT>::kBytes, kIdsAt = kQAt + 2 * kQBytes;
+    static_assert(kQAt % 1024 == 0 || Image<NT>::kBytes % 512 == 0, "16-byte aligned");
+    const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)smem;
+    const int ids_bytes = ((pl.chunk + kBk - 1) / kBk * 4 + 255) & ~255;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = Hq / Hkv, m = lane & 15, q = lane >> 4;
+    // the Hkv workgroups of a share (one per kv-head, on different XCDs) walk the same blocks at about the same time
+    const int share = blockIdx.x / Hkv, c = blockIdx.x % Hkv;
+    Piece p(pl.pieces + 5 * share);
+    int next = pl.share_next[share];
+    // query j = 16qt + m  ->  row row0 + j / g, head c*g + j % g; wave w brings k-step w: d = 32 w + 8 q (bf16 cache),
+    // d = 64 (w / 2) + 16 q + 8 (w % 2) (FP8 cache, see KVRaw8)
+    auto stage = [&](const Piece &p, int buf) {
+        const int d0 = KV8 ? 64 * (w >> 1) + 16 * q + 8 * (w & 1) : 8 * q + 32 * w;
+#pragma unroll
+        for (int qt = 0; qt < NT; ++qt) {
+            const int j = 16 * qt + m;
+            const bf16_t *qp = qg + ((size_t)(p.row0 + j / g) * Hq + c * g + j % g) * kD + d0;
+            dma16(j < p.rows * g ? (const void *)qp : (const void *)&g_zero_query, lds0 + kQAt + buf * kQBytes + (qt * kKS + w) * 1024);
+        }
+        const int32_t *ids = bt + (size_t)p.bt_row * max_blocks + p.begin / kBk;
+        const int n_blk = (p.n_tok + kBk - 1) / kBk;
+        for (int i = 64 * w; i < n_blk; i += 256) dma4(ids + min(i + lane, n_blk - 1), lds0 + kIdsAt + buf * ids_bytes + i * 4);
+    };
+    typedef typename std::conditional<KV8, KVRaw8, KVFrag>::type Frag;
+    auto load = [&](Frag &f, const Piece &p, int buf, int grp) {
+        const int *ids = (const int *)(smem + kIdsAt + buf * ids_bytes);
+        const int n_blk = (p.n_tok + kBk - 1) / kBk;
+        const int b0 = __builtin_amdgcn_readfirstlane(ids[min(2 * grp, n_blk - 1)]), b1 = __builtin_amdgcn_readfirstlane(ids[min(2 * grp + 1, n_blk - 1)]);
+        if constexpr (KV8) load_group8(f, (const uint8_t *)pool_v, b0, b1, c, Hkv, lane);
+        else load_group(f, (const bf16_t *)pool_v, b0, b1, c, Hkv, lane);
+    };
+    // this wave's loads into LDS have landed and its LDS accesses are done; then those of all waves
+    auto meet = [] { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    stage(p, 0);
+    meet();
+    Frag f0;
+    load(f0, p, 0, w);
+    for (int buf = 0;; buf ^= 1) {
+        const Piece nx(pl.pieces + 5 * (p.last ? share : next));
+        const bf16x8 *qlds = (const bf16x8 *)(smem + kQAt + buf * kQBytes);
+        // the wave's Q fragments, see kQInRegs
+        bf16x8 qr[NT][kKS];
+        if constexpr (kQInRegs<NT>) {
+#pragma unroll
+            for (int qt = 0; qt < NT; ++qt)
+#pragma unroll
+                for (int ks = 0; ks < kKS; ++ks) qr[qt][ks] = qlds[(qt * kKS + ks) * 64 + lane];
+        }
+        if (!p.last) stage(nx, buf ^ 1);
+        State<NT> st;
+        int stag[NT];  // every stacked query of a decode step sits at the same position
+#pragma unroll
+        for (int qt = 0; qt < NT; ++qt) {
+            st.m[qt] = -INFINITY;
+            st.l[qt] = 0.f;
+            stag[qt] = 0;
+#pragma unroll
+            for (int dt = 0; dt < kDT; ++dt) st.o[dt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        // the launch is sized for the largest stacked group of the call; a sequence with fewer
+        // streams multiplies only the query tiles it has
+        auto walk = [&](auto tiles) {
+            constexpr int N = decltype(tiles)::value;
+            auto compute = [&](auto kind, Frag &f, int left) {
+                constexpr bool tail = decltype(kind)::value;
+                if constexpr (KV8) compute_group8<NT, N, tail>(st, f, qr, qlds, left, stag, scale_log2, lane);
+                else compute_group<NT, N, tail>(st, f, qr, qlds, left, stag, scale_log2, lane);
+            };
+            wave_walk<NT, N>(st, f0, p.n_tok, w, 4, [&](Frag &f, int grp) { load(f, p, buf, grp); }, compute);
+        };
+        const int n_act = (p.rows * g + 15) >> 4;
+        if (NT >= 3 && n_act >= 3) walk(std::integral_constant<int, NT>());
+        else if (NT >= 2 && n_act == 2) walk(std::integral_constant<int, (NT >= 2 ? 2 : 1)>());
+        else walk(std::integral_constant<int, 1>());
+        image_store<NT>(st, smem + w * Image<NT>::kBytes, lane);
+        meet();
+        if (!p.last) load(f0, nx, buf ^ 1, w);
+        image_finish<NT>(smem, w, p.rows * g, g, p.row0, c, Hq, Hkv, p.direct, p.slot, pl.g_max, v_scale, out, part_o, part_ml, lane,
+                         [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); });  // the states' LDS is free again
+        if (p.last) break;
+        p = nx;
+        next = next + 1;
+    }
+}
+
+// Four and five query tiles: NA tiles of waves 0,1, NB of waves 2,3.
+template <int NA, int NB, bool KV8>
+__global__ void __launch_bounds__(256) k_attn_decode_pairs(const bf16_t *__restrict__ qg, const void *__restrict__ pool_v,
                                                      const int32_t *__restrict__ bt, int max_blocks, AttnPlan pl,
                                                      bf16_t *__restrict__ out, float *__restrict__ part_o,
                                                      float *__restrict__ part_ml, int Hq, int Hkv, float scale_log2,
@@ -585,20 +737,18 @@ __global__ void __launch_bounds__(256) k_attn_decode(const bf16_t *__restrict__ 
   // the pieces of this workgroup's share, one after the other; the Hkv workgroups of a share (one per
   // kv-head, on different XCDs) walk the same blocks at about the same time
   const int share = blockIdx.x / Hkv, c = blockIdx.x % Hkv;
-  for (int item = pl.wg_first[share]; item < pl.wg_first[share + 1]; ++item) {
-    const int s = pl.item_seq[item];
-    const int tok_begin = pl.item_begin[item];
-    const int tok_end = tok_begin + pl.item_len[item];
-    const int row0 = pl.seq_row0[s], T = pl.seq_rows[s];
-    const int G = T * g;
-    const int32_t *btr = bt + (size_t)pl.seq_bt[s] * max_blocks;
+  for (int item = share, next = pl.share_next[share];; item = next++) {
+    const Piece p(pl.pieces + 5 * item);
+    const int tok_begin = p.begin, n_tok = p.n_tok;
+    const int row0 = p.row0;
+    const int G = p.rows * g;
+    const int32_t *btr = bt + (size_t)p.bt_row * max_blocks;
 
     // Q fragments (B operands) go to LDS once, as [qt][ks][lane]; wave w stages k-step w.
     // query j = 16qt + m  ->  row row0 + j / g, head c*g + j % g; rows past G are zero.
     // LDS: [merge images | KV ring] [Q fragments] [block ids]; the merge images reuse the ring.
-    constexpr size_t kHead = NB ? kRingBytes : (size_t)2 * kImg * sizeof(float);
-    static_assert(!NB || kRingBytes >= (size_t)2 * kImg * sizeof(float), "merge images must fit the ring");
-    bf16x8 *qlds = (bf16x8 *)((char *)lds + kHead);
+    static_assert(kRingBytes >= (size_t)2 * kImg * sizeof(float), "merge images must fit the ring");
+    bf16x8 *qlds = (bf16x8 *)((char *)lds + kRingBytes);
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) {
         int j = 16 * qt + m;
@@ -610,14 +760,13 @@ __global__ void __launch_bounds__(256) k_attn_decode(const bf16_t *__restrict__ 
     // The chunk's block ids go to LDS too: a lookup in the loop is then an LDS read, not a global
     // load whose wait would also drain the KV loads in flight.
     int *blds = (int *)(qlds + NQT * kKS * 64);
-    const int n_tok = tok_end - tok_begin;
     const int n_blk = (n_tok + kBk - 1) / kBk;
     for (int i = threadIdx.x; i < n_blk; i += 256) blds[i] = btr[tok_begin / kBk + i];
     __syncthreads();
     // the wave's own Q fragments, see kQInRegs (waves 2, 3 of a launch with NB tiles hold tiles NA .. NA + NB - 1)
     bf16x8 qr[NA][kKS];
     if constexpr (kQInRegs<NA>) {
-        const bool second = NB && (w >> 1);
+        const bool second = w >> 1;
         const bf16x8 *qsrc = qlds + (second ? NA * kKS * 64 : 0) + lane;
         const int nq = second ? NB : NA;
 #pragma unroll
@@ -634,81 +783,44 @@ __global__ void __launch_bounds__(256) k_attn_decode(const bf16_t *__restrict__ 
 #pragma unroll
         for (int dt = 0; dt < kDT; ++dt) st.o[dt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    const int direct = pl.item_direct[item];
-    const int slot = pl.item_part[item];
+    const int direct = p.direct, slot = p.slot;
     // every stacked query of a decode step sits at the same position: all whole groups need no mask
     const int n_clean = n_tok / kGrp;
     int stag[NA];
 #pragma unroll
     for (int qt = 0; qt < NA; ++qt) stag[qt] = 0;
 
-    if constexpr (NB == 0) {
-        // the launch is sized for the largest stacked group of the call; a sequence with fewer
-        // streams multiplies only the query tiles it has
-        const int n_act = (G + 15) >> 4;
-        if constexpr (KV8) {
-            const uint8_t *pool8 = (const uint8_t *)pool_v;
-            if (NA >= 3 && n_act >= 3)
-                wave_walk8<NA, NA>(st, pool8, blds, n_blk, n_tok, n_clean, stag, w, 4, c, Hkv, qr, qlds, scale_log2, lane);
-            else if (NA >= 2 && n_act == 2)
-                wave_walk8<NA, (NA >= 2 ? 2 : 1)>(st, pool8, blds, n_blk, n_tok, n_clean, stag, w, 4, c, Hkv, qr, qlds, scale_log2, lane);
-            else
-                wave_walk8<NA, 1>(st, pool8, blds, n_blk, n_tok, n_clean, stag, w, 4, c, Hkv, qr, qlds, scale_log2, lane);
-#pragma unroll
-            for (int qt = 0; qt < NA; ++qt)
-#pragma unroll
-                for (int dt = 0; dt < kDT; ++dt) {
-                    st.o[dt][qt][0] *= v_scale; st.o[dt][qt][1] *= v_scale; st.o[dt][qt][2] *= v_scale; st.o[dt][qt][3] *= v_scale;
-                }
-        } else if (NA >= 3 && n_act >= 3)
-            wave_walk<NA, NA>(st, pool, blds, n_blk, n_tok, n_clean, stag, w, 4, c, Hkv, qr, qlds, scale_log2, lane);
-        else if (NA >= 2 && n_act == 2)
-            wave_walk<NA, (NA >= 2 ? 2 : 1)>(st, pool, blds, n_blk, n_tok, n_clean, stag, w, 4, c, Hkv, qr, qlds, scale_log2, lane);
+    const int role = w >> 1, half = w & 1;  // role: which query tiles; half: which groups
+    bf16x8 *ring = (bf16x8 *)lds;
+    if constexpr (KV8) {  // codes are expanded on the way into the ring: through registers
+        const uint8_t *pool8 = (const uint8_t *)pool_v;
+        if (role == 0)
+            shared_walk8<NA, NA>(st, pool8, blds, n_blk, n_tok, n_clean, stag, w, half, c, Hkv, ring, qr, qlds, scale_log2, lane);
         else
-            wave_walk<NA, 1>(st, pool, blds, n_blk, n_tok, n_clean, stag, w, 4, c, Hkv, qr, qlds, scale_log2, lane);
-        // tree merge of the four waves through LDS: (2,3) -> (0,1), then 1 -> 0
-        if (w >= 2) store_to_lds<NA>(st, lds + (w - 2) * kImg, lane);
-        __syncthreads();
-        if (w < 2) merge_from_lds<NA>(st, lds + w * kImg, lane);
-        __syncthreads();
-        if (w == 1) store_to_lds<NA>(st, lds, lane);
-        __syncthreads();
-        if (w == 0) {
-            merge_from_lds<NA>(st, lds, lane);
-            finish<NA>(st, 0, NA, G, g, row0, c, Hq, Hkv, direct, slot, pl.g_max, out, part_o, part_ml, lane);
-        }
+            shared_walk8<NA, NB>(st, pool8, blds, n_blk, n_tok, n_clean, stag, w, half, c, Hkv, ring, qr, qlds,
+                                 scale_log2, lane);
+    } else if (role == 0) {
+        shared_walk_dma<NA, NA>(st, pool, blds, n_blk, n_tok, n_clean, stag, w, half, c, Hkv, ring, qr, qlds, scale_log2, lane);
     } else {
-        const int role = w >> 1, half = w & 1;  // role: which query tiles; half: which groups
-        bf16x8 *ring = (bf16x8 *)lds;
-        if constexpr (KV8) {  // codes are expanded on the way into the ring: through registers
-            const uint8_t *pool8 = (const uint8_t *)pool_v;
-            if (role == 0)
-                shared_walk8<NA, NA>(st, pool8, blds, n_blk, n_tok, n_clean, stag, w, half, c, Hkv, ring, qr, qlds, scale_log2, lane);
-            else
-                shared_walk8<NA, NB>(st, pool8, blds, n_blk, n_tok, n_clean, stag, w, half, c, Hkv, ring, qr, qlds,
-                                     scale_log2, lane);
-        } else if (role == 0) {
-            shared_walk_dma<NA, NA>(st, pool, blds, n_blk, n_tok, n_clean, stag, w, half, c, Hkv, ring, qr, qlds, scale_log2, lane);
-        } else {
-            shared_walk_dma<NA, NB>(st, pool, blds, n_blk, n_tok, n_clean, stag, w, half, c, Hkv, ring, qr, qlds,
-                                    scale_log2, lane);
-        }
-        if constexpr (KV8) {
-#pragma unroll
-            for (int qt = 0; qt < NA; ++qt)
-#pragma unroll
-                for (int dt = 0; dt < kDT; ++dt) {
-                    st.o[dt][qt][0] *= v_scale; st.o[dt][qt][1] *= v_scale; st.o[dt][qt][2] *= v_scale; st.o[dt][qt][3] *= v_scale;
-                }
-        }
-        // each pair merges its two halves through its own LDS image
-        if (half == 1) store_to_lds<NA>(st, lds + role * kImg, lane);
-        __syncthreads();
-        if (half == 0) {
-            merge_from_lds<NA>(st, lds + role * kImg, lane);
-            finish<NA>(st, role ? NA : 0, role ? NB : NA, G, g, row0, c, Hq, Hkv, direct, slot, pl.g_max, out, part_o, part_ml, lane);
-        }
+        shared_walk_dma<NA, NB>(st, pool, blds, n_blk, n_tok, n_clean, stag, w, half, c, Hkv, ring, qr, qlds,
+                                scale_log2, lane);
     }
+    if constexpr (KV8) {
+#pragma unroll
+        for (int qt = 0; qt < NA; ++qt)
+#pragma unroll
+            for (int dt = 0; dt < kDT; ++dt) {
+                st.o[dt][qt][0] *= v_scale; st.o[dt][qt][1] *= v_scale; st.o[dt][qt][2] *= v_scale; st.o[dt][qt][3] *= v_scale;
+            }
+    }
+    // each pair merges its two halves through its own LDS image
+    if (half == 1) store_to_lds<NA>(st, lds + role * kImg, lane);
+    __syncthreads();
+    if (half == 0) {
+        merge_from_lds<NA>(st, lds + role * kImg, lane);
+        finish<NA>(st, role ? NA : 0, role ? NB : NA, G, g, row0, c, Hq, Hkv, direct, slot, pl.g_max, out, part_o, part_ml, lane);
+    }
+    if (p.last) break;
     __syncthreads();  // LDS (Q fragments, block ids, merge images) is reused by the next piece
   }
 }
@@ -1385,17 +1497,20 @@ __global__ void __launch_bounds__(256) k_attn_merge(const float *__restrict__ pa
 template <int NA, int NB, bool KV8 = false>
 hipError_t launch_one(const void *q, const void *pool, const int32_t *bt, int max_blocks, const AttnPlan &pl, void *out,
                       float *part_o, float *part_ml, int Hq, int Hkv, float scale_log2, float v_scale, hipStream_t st) {
-    constexpr int kImg = kDT * NA * 4 * 64 + 2 * NA * 64;
-    // merge images + Q fragments + the chunk's block ids (chunk <= kAttnMaxChunk tokens)
-    size_t shm = (NB ? kRingBytes : (size_t)2 * kImg * sizeof(float)) + (size_t)(NA + NB) * kKS * 64 * 16 +
-                 (size_t)(kAttnMaxChunk / kBk) * 4;
+    // block ids of pieces of up to kAttnMaxChunk tokens
+    constexpr int kIds = (kAttnMaxChunk / kBk) * 4;
+    constexpr size_t shm = NB ? kRingBytes + (size_t)(NA + NB) * kKS * 1024 + kIds : 4 * (size_t)Image<NA>::kBytes + 2 * ((size_t)NA * kKS * 1024 + kIds);
+    const auto kernel = [] {
+        if constexpr (NB > 0) return k_attn_decode_pairs<NA, NB, KV8>;
+        else return k_attn_decode<NA, KV8>;
+    }();
     static bool attr_set = false;  // per instantiation
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_attn_decode<NA, NB, KV8>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((k_attn_decode<NA, NB, KV8>), dim3(pl.n_wgs * Hkv), dim3(256), shm, st, (const bf16_t *)q, pool, bt, max_blocks, pl,
+    hipLaunchKernelGGL(kernel, dim3(pl.n_wgs * Hkv), dim3(256), shm, st, (const bf16_t *)q, pool, bt, max_blocks, pl,
                        (bf16_t *)out, part_o, part_ml, Hq, Hkv, scale_log2, v_scale);
     return hipGetLastError();
 }

@@ -81,9 +81,11 @@ struct icarus_ctx {
     int attn_chunk_override = 0;  // longest attention piece in tokens; 0 = automatic (icarus_set_attn_piece_limit)
     int attn_wgs = 256;           // workgroups of the decode attention: Hkv per equal share of the work
     // cost model of the decode attention plan, from per-workgroup timings: a cached token costs
-    // attn_weight_base + attn_weight_tile * (16-query tiles of its sequence), a piece as much as
-    // attn_piece_tokens tokens on top
-    int attn_weight_base = 128, attn_weight_tile = 7, attn_piece_tokens = 768;
+    // attn_weight_base + attn_weight_tile * (16-query tiles of its sequence), a piece as much as attn_piece_tokens tokens on top: 384,
+    // over an FP8 cache, whose tokens cost half, 768.  Attention alone, us, at 768 / 512 / 384 / 256 tokens: 16 sequences of 500-8192 58.2 / 58.0 / 57.0 /
+    // 56.0, 64 of 1024-16384 420 / 416.8 / 416.5 / 417.7, one of 4096 12.7 / 12.1 / 12.0 / 12.3, 32 of 1024-8192 113.7 / 112.1 / 112.0 / 110.4; FP8,
+    // 64 of 1024-16384 193.3 / 193.3 / 193.7 / 195.6.
+    int attn_weight_base = 128, attn_weight_tile = 7, attn_piece_tokens = 384;
     char err[512];
     StageSlot slots[kSlots];
     int next_slot = 0;
@@ -182,8 +184,7 @@ WsLayout ws_layout(const icarus_ctx *ctx, size_t rows, size_t seqs, size_t max_c
     if (max_ctx > walk && attn_prefill_mfma_supported(ctx->dm, 1))
         forced_items = (rows / prefill_group_rows(c) + seqs) * ((max_ctx + walk - 1) / walk);
     w.max_items = std::max(decode_items, forced_items);
-    // metadata: 4 row arrays and the attention plan (5 arrays per piece, the shares' first pieces, 6 arrays
-    // per plan sequence); a prefill call has up to `rows` plan sequences, max_items pieces if any is cut, and an array
+    // metadata: 4 row arrays and the attention plan (5 ints per piece, one per share, up to 6 per plan sequence); a prefill call has up to `rows` plan sequences, max_items pieces if any is cut, and an array
     // of row tiles, one per row at most (where a decode call keeps the regrouping of its rows)
     w.meta_ints = 4 * rows + 5 * std::max(rows, w.max_items) + (size_t)ctx->attn_wgs + 6 * std::max(rows, seqs) + 64 +
                   rows + seqs +  // + what a layer stack stages with the call: prompt tokens, last row of each sequence
@@ -613,58 +614,43 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
     int n_wgs = fill(lo, true);
     const size_t n_items = pieces.size();
     if (n_items > max_items) return;
-    int32_t *item_seq = m + at, *item_begin = item_seq + n_items, *item_len = item_begin + n_items,
-            *item_part = item_len + n_items, *item_direct = item_part + n_items, *wg_first = item_direct + n_items,
-            *seq_kvlen = wg_first + n_wgs + 1, *row0 = seq_kvlen + S, *rows = row0 + S, *sbt = rows + S, *part0 = sbt + S,
-            *nparts = part0 + S;
+    // A share's first piece is piece `share`, where its workgroups find it without looking anything up; its others follow those of all
+    // shares, one after the other.
+    int32_t *rec = m + at, *share_next = rec + 5 * n_items, *row0 = share_next + n_wgs, *part0 = row0 + S, *nparts = part0 + S;
     for (int s = 0; s < S; ++s) {
-        seq_kvlen[s] = kv_lens[s];
         row0[s] = seq_row0[s];
-        rows[s] = seq_rows[s];
-        sbt[s] = seq_bt ? seq_bt[s] : s;
         part0[s] = 0;
         nparts[s] = 0;
     }
-    int max_len = 0;
     for (size_t i = 0; i < n_items; ++i) {  // pieces of one sequence are consecutive
+        if (nparts[pieces[i].s] == 0) part0[pieces[i].s] = (int32_t)i;
+        ++nparts[pieces[i].s];
+    }
+    int max_len = 0, at_rest = n_wgs;
+    for (size_t i = 0; i < n_items; ++i) {  // and in share order
         const Piece &e = pieces[i];
-        if (nparts[e.s] == 0) part0[e.s] = (int32_t)i;
-        ++nparts[e.s];
-        item_seq[i] = e.s;
-        item_begin[i] = e.begin;
-        item_len[i] = e.len;
-        item_part[i] = (int32_t)i;
+        const bool first = i == 0 || pieces[i - 1].wg != e.wg, last = i + 1 == n_items || pieces[i + 1].wg != e.wg;
+        if (first) share_next[e.wg] = at_rest;
+        int32_t *r = rec + 5 * (size_t)(first ? e.wg : at_rest++);
+        r[0] = seq_row0[e.s] | seq_rows[e.s] << 16;
+        r[1] = seq_bt ? seq_bt[e.s] : e.s;
+        r[2] = e.begin;
+        r[3] = e.len | (nparts[e.s] == 1 ? kPieceDirect : 0) | (last ? kPieceLast : 0);
+        r[4] = (int32_t)i;
+        if (nparts[e.s] > 1) hp->has_split = true;
         max_len = std::max(max_len, (int)e.len);
     }
-    for (size_t i = 0; i < n_items; ++i) {
-        item_direct[i] = nparts[pieces[i].s] == 1;
-        if (nparts[pieces[i].s] > 1) hp->has_split = true;
-    }
-    {   // first piece of each share (pieces are in share order)
-        size_t i = 0;
-        for (int b = 0; b <= n_wgs; ++b) {
-            while (i < n_items && pieces[i].wg < b) ++i;
-            wg_first[b] = (int32_t)i;
-        }
-    }
-    pl->item_seq = d;
-    pl->item_begin = d + n_items;
-    pl->item_len = d + 2 * n_items;
-    pl->item_part = d + 3 * n_items;
-    pl->item_direct = d + 4 * n_items;
-    pl->wg_first = d + 5 * n_items;
-    pl->seq_kvlen = pl->wg_first + n_wgs + 1;
-    pl->seq_row0 = pl->seq_kvlen + S;
-    pl->seq_rows = pl->seq_row0 + S;
-    pl->seq_bt = pl->seq_rows + S;
-    pl->seq_part0 = pl->seq_bt + S;
+    pl->pieces = d;
+    pl->share_next = d + 5 * n_items;
+    pl->seq_row0 = pl->share_next + n_wgs;
+    pl->seq_part0 = pl->seq_row0 + S;
     pl->seq_nparts = pl->seq_part0 + S;
     pl->n_items = (int)n_items;
     pl->n_wgs = n_wgs;
     pl->chunk = max_len;
     pl->g_max = g_max;
     pl->causal = 0;
-    hp->ints = 5 * n_items + (size_t)n_wgs + 1 + 6 * (size_t)S;
+    hp->ints = 5 * n_items + (size_t)n_wgs + 3 * (size_t)S;
     hp->valid = n_items > 0;
 }
 
@@ -1386,6 +1372,7 @@ icarus_status icarus_create(const icarus_layer_config *cfg, const icarus_base_we
     dm.d = c.d_model; dm.Hq = c.n_q_heads; dm.Hkv = c.n_kv_heads; dm.D = c.head_dim; dm.F = c.d_ffn; dm.Bk = c.block_size;
     dm.M = c.n_models; dm.r = c.lora_rank; dm.bf16 = c.dtype == ICARUS_BF16; dm.qk_norm = c.qk_norm != 0;
     dm.theta = c.rope_theta; dm.eps = (float)c.rms_eps; dm.lora_scale = (float)c.lora_scale;
+    if (c.kv_dtype == ICARUS_KV_FP8_E4M3) ctx->attn_piece_tokens = 768;
     dm.kv8 = c.kv_dtype == ICARUS_KV_FP8_E4M3; dm.k_scale = dm.kv8 ? (float)c.k_scale : 1.f; dm.v_scale = dm.kv8 ? (float)c.v_scale : 1.f;
     *out = ctx;
     return ICARUS_OK;

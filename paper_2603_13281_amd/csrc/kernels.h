@@ -91,19 +91,21 @@ hipError_t launch_bench_mfma(float *out, int waves, int iters, hipStream_t st);
 // Host-built plan of the attention kernels.  All arrays are device int32.
 // Decode (causal = 0): the call's work -- the cached tokens of every sequence -- is laid on one line
 // and cut into n_wgs equal shares; share b is walked by Hkv workgroups (one per kv-head), each over
-// the pieces [wg_first[b], wg_first[b+1]), a piece being a token range of one sequence.  Piece
+// piece b and the pieces from share_next[b] on up to one that is marked last, a piece being a token range of one sequence.  Piece
 // boundaries are multiples of 32 tokens.  A sequence cut into several pieces leaves one partial
-// result per piece and kv-head.
+// result per piece and kv-head.  Arrays: pieces, share_next, and of the sequences row0, part0, nparts.
 // Prefill (causal = 1): one workgroup per piece and kv-head; a piece is the whole walk of a token group, or a part of
 // it that leaves a partial result (launch_attn_merge combines them).  Inner boundaries on whole rounds of the walk.
 // Without any cut walk the arrays of parts are null: item_begin, _len, _part, _direct, seq_part0, _nparts.
+constexpr int kPieceDirect = 1 << 30, kPieceLast = 1 << 29, kPieceTokens = kPieceLast - 1;  // direct: the piece is its whole sequence; last: of its share
 struct AttnPlan {
     const int32_t *item_seq;     // [n_items] plan sequence of the piece
     const int32_t *item_begin;   // [n_items] first token of the piece
     const int32_t *item_len;     // [n_items] tokens of the piece
     const int32_t *item_part;    // [n_items] partial-result slot of the piece
     const int32_t *item_direct;  // [n_items] 1: the piece is its whole sequence: write the final output
-    const int32_t *wg_first;     // [n_wgs + 1] first piece of each share (decode)
+    const int32_t *pieces;       // decode: [n_items][5] first row | rows << 16, row of the block table, first token, tokens | kPieceDirect | kPieceLast, partial-result slot
+    const int32_t *share_next;   // decode: [n_wgs] second piece of each share
     const int32_t *seq_kvlen;    // [S] tokens to attend to
     const int32_t *seq_row0;     // [S] first row of the sequence
     const int32_t *seq_rows;     // [S] rows (stacked streams) of the sequence
