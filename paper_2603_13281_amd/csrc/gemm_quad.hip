@@ -137,13 +137,16 @@ __global__ void __launch_bounds__(128 * WAVES_N, WAVES_N == 4 ? 1 : 2) k_gemm_qu
             wo[h][i] = (uint32_t)((w_row(h, p.hr) - n0) * (uint32_t)g.K + p.kc) * 2u;
         }
     }
-    const int turn = gemm_turn(g, tile_n, n_base);
+    // different starts along K (gemm_turn): not in 256 x 256 tiles, whose launches are bound by the matrix cores (they took 0.4 % for the three scalar
+    // instructions a slab)
+    constexpr bool kTurns = MT0 + MT1 < 8;
+    const int turn = kTurns ? gemm_turn(g, tile_n, n_base) : 0;
+    auto place_of = [&](int kt) { return kTurns ? gemm_slab(kt, turn, n_base) : kt; };
     // part: 0, 1 the halves of X; 2, 3 those of W
     auto part_lds = [&](int P, int S) { return P >= 2 ? kBOff + S * kWStage + (P & 1) * (kWStage / 2) : S * kXStage + P * (32 * MT0 * kRow); };
-    // load i of a part, of a slab of base weights
+    // load i of a part, of the slab of base weights at place kt along K (gemm_slab)
     auto load_one = [&](auto Part, auto Stage, int kt, int i) {
         constexpr int P = decltype(Part)::value, S = decltype(Stage)::value;
-        kt = gemm_slab(kt, turn, n_base);
         if constexpr (P < 2) {
             if (i < (P ? LDX1 : LDX0) || x_has(P)) dma16_at(xb + (size_t)kt * kRow, xo[P][i], lds0 + part_lds(P, S) + x_unit(P, i) * 1024);
         } else dma16_at((P & 1 ? wb1 : wb0) + (size_t)kt * kRow, wo[P & 1][i], lds0 + part_lds(P, S) + (w + NW * i) * 1024);
@@ -154,7 +157,7 @@ __global__ void __launch_bounds__(128 * WAVES_N, WAVES_N == 4 ? 1 : 2) k_gemm_qu
         constexpr int P = decltype(Part)::value, S = decltype(Stage)::value;
         if (kt < n_base) {
 #pragma unroll
-            for (int i = 0; i < n_loads(P); ++i) load_one(Part, Stage, kt, i);
+            for (int i = 0; i < n_loads(P); ++i) load_one(Part, Stage, place_of(kt), i);
             return;
         }
         const int mr = g.M_models * g.r;
@@ -203,8 +206,8 @@ __global__ void __launch_bounds__(128 * WAVES_N, WAVES_N == 4 ? 1 : 2) k_gemm_qu
     };
     auto n_frags = [](int P) { return KS * (P >= 2 ? NT : P ? MT1 : MT0); };
     // One phase: quadrant (A, B) of the wave tile over the 64 columns of the slab; meanwhile part RD is read from
-    // stage RS and part LP of slab lk requested into stage LS.
-    auto phase = [&](auto A, auto B, auto RD, auto RS, auto LP, auto LS, auto hot, int lk) {
+    // stage RS and part LP of slab lk (at its place along K) requested into stage LS.
+    auto phase = [&](auto A, auto B, auto RD, auto RS, auto LP, auto LS, auto hot, int lk, int at) {
         constexpr int a = decltype(A)::value, b = decltype(B)::value, MT = a ? MT1 : MT0, kMul = MT * NT * KS;
         constexpr int rn = kMul / 2, l0 = kMul / 2, nl = n_loads(decltype(LP)::value), nrd = n_frags(decltype(RD)::value);
 #pragma unroll
@@ -219,7 +222,7 @@ __global__ void __launch_bounds__(128 * WAVES_N, WAVES_N == 4 ? 1 : 2) k_gemm_qu
             if constexpr (decltype(hot)::value) {
 #pragma unroll
                 for (int l = 0; l < nl; ++l)
-                    if (l0 + l * (kMul - l0) / nl == m) load_one(LP, LS, lk, l);
+                    if (l0 + l * (kMul - l0) / nl == m) load_one(LP, LS, at, l);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -251,14 +254,15 @@ __global__ void __launch_bounds__(128 * WAVES_N, WAVES_N == 4 ? 1 : 2) k_gemm_qu
             constexpr bool H = decltype(hot)::value;
             constexpr Int<decltype(S)::value> F; constexpr Int<1 - F.value> L, N;  // N: the next slab's stage
             constexpr Int<F.value + 2> WF; constexpr Int<L.value + 2> WL;
+            const int at = place_of(kt + 2);
             const bool there1 = H || kt + 1 < nk, there2 = H || kt + 2 < nk;
-            phase(I0, F, WL, S, I0, S, hot, kt + 2);
-            phase(I0, L, I1, S, WF, S, hot, kt + 2);
+            phase(I0, F, WL, S, I0, S, hot, kt + 2, at);
+            phase(I0, L, I1, S, WF, S, hot, kt + 2, at);
             if (there2) sync(Int<kSlab>());
             else if (there1) sync(Int<kPair1>());
             else sync(I0);
-            phase(I1, L, I0, N, WL, S, hot, kt + 2);
-            phase(I1, F, WL, N, I1, S, hot, kt + 2);
+            phase(I1, L, I0, N, WL, S, hot, kt + 2, at);
+            phase(I1, F, WL, N, I1, S, hot, kt + 2, at);
             if (there2) sync(Int<kSlab>());
             else sync(I0);
             ++kt;
