@@ -720,10 +720,18 @@ icarus_status run_gemm(icarus_ctx *ctx, char *ws, const WsLayout &L, int phase, 
     return ICARUS_OK;
 }
 
+// Rows of a prefill call that leave its last layer.
+struct RowSubset {
+    const int32_t *rows;  // device [n]
+    int n;
+    void *x;              // room for n rows of d_model: their residual
+};
+
 icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const RowMeta &rm, const HostPlan *hp, int R,
                              bool use_lora, bool kv_only, int slot_by_row, void *pool, const int32_t *bt, int max_blocks,
                              const void *x_in, void *x_out, int64_t *slot_out, hipStream_t st, int in_splits = 0,
-                             int *out_splits = nullptr) {
+                             int *out_splits = nullptr, const RowSubset *last = nullptr) {
+    // last != null (prefill): only these rows leave the layer, one after the other in x_out; of the others K and V are all that is asked for.
     // in_splits > 0 (layer stack): the input rows are still in pieces -- the previous layer's down projection left
     // `in_splits` split-K slices in the workspace and its residual in z -- and are formed (and stored to x_in) by
     // this layer's first row kernel.  out_splits != null: this layer may leave its own output the same way.
@@ -778,7 +786,13 @@ icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const
     }
     if (kv_only) return ICARUS_OK;
     bool merge_left = false;
-    LORA_TRY(run_decode_attention(ctx, ws, L, rm, hp, q, pool, bt, max_blocks, attn, R, st, &merge_left));
+    LORA_TRY(run_decode_attention(ctx, ws, L, rm, hp, q, pool, bt, max_blocks, attn, R, st, last ? nullptr : &merge_left));
+    if (last) {  // q is read by nothing after the attention: it takes the chosen rows of its output
+        PHASE(ctx, st, ICARUS_PH_ELEMWISE, launch_gather_rows(attn, last->rows, q, last->n, qd * 2, st, x_in, last->x, d * 2));
+        attn = q;
+        x_in = last->x;
+        R = last->n;
+    }
     {   // O projection (ICaRusLinear) + residual; its shrink also merges the attention partials of cut sequences
         GemmArgs g{};
         g.X = attn; g.ldx = qd; g.R = R; g.K = qd;
@@ -981,7 +995,8 @@ bool layer_takes_slices(icarus_ctx *ctx, bool use_lora) {
 // rows: x_in [R, d].  use_lora: decoder rows get adapter deltas.  kv_only: stop after the append.
 icarus_status run_layer(icarus_ctx *ctx, char *ws, const WsLayout &L, const RowMeta &rm, const HostPlan *hp, int R, bool use_lora, bool kv_only,
                         int slot_by_row, void *pool, const int32_t *bt, int max_blocks, const void *x_in, void *x_out,
-                        int64_t *slot_out, hipStream_t st, const FullPlan *fp = nullptr, int in_splits = 0, int *out_splits = nullptr) {
+                        int64_t *slot_out, hipStream_t st, const FullPlan *fp = nullptr, int in_splits = 0, int *out_splits = nullptr,
+                        const RowSubset *last = nullptr) {
     if (out_splits) *out_splits = 0;
     if (use_lora && !kv_only && ctx->full_set) {  // decoder rows with private weights
         if (!fp || !layer_mfma_supported(ctx)) return fail(ctx, ICARUS_ERR_UNSUPPORTED, "private decoder weights need the matrix-core path");
@@ -991,8 +1006,9 @@ icarus_status run_layer(icarus_ctx *ctx, char *ws, const WsLayout &L, const RowM
         bool lg = use_lora && has_lora(ctx, ICARUS_PROJ_GATE), lu = use_lora && has_lora(ctx, ICARUS_PROJ_UP);
         if (lg == lu)
             return run_layer_mfma(ctx, ws, L, rm, hp, R, use_lora, kv_only, slot_by_row, pool, bt, max_blocks, x_in, x_out, slot_out, st,
-                                  in_splits, out_splits);
+                                  in_splits, out_splits, last);
     }
+    if (last) return fail(ctx, ICARUS_ERR_UNSUPPORTED, "a subset of rows needs the matrix-core path");
     if (in_splits > 0) return fail(ctx, ICARUS_ERR_UNSUPPORTED, "input rows in pieces need the matrix-core path");
     if (R <= kSkinnyRows)
         return run_layer_skinny(ctx, ws, L, rm, hp, R, use_lora, kv_only, slot_by_row, pool, bt, max_blocks, x_in, x_out, slot_out, st);
@@ -1270,28 +1286,34 @@ icarus_status run_stack(icarus_stack *st, char *ws, const StackLayout &SL, const
     // A layer whose down projection was split over K leaves its slices (and the residual) in the workspace when the
     // next layer can form its input rows from them: the separate reduction launch between two layers is saved.
     int pending = 0;
+    char *xg = ws + SL.xn, *xn = xg + (size_t)n_head * row_bytes;
+    // Of a prompt's rows only the last of each chunk goes to the LM head, and the caches want K and V alone: what follows the attention of
+    // the last layer is run for those rows only (4337 rows in 4 chunks, 4 layers: 6609 -> 5418 us).  With fewer than kLastRowsGain rows
+    // less, the projections, bound by their weights (O, gate/up and down of 4096 and 14336 columns: 77 us for 9 rows, 84 for 64), gain less than the 3 us of the larger gather.
+    constexpr int kLastRowsGain = 32;
+    const RowSubset last{head_rows, n_head, xg};
+    const bool subset = head_rows && !decode && R - n_head >= kLastRowsGain && layer_mfma_supported(st->layers.back());
     for (size_t l = 0; l < st->layers.size(); ++l) {
         int left = 0;
-        // the last layer may do the same when every row goes to the LM head as it is: the final norm sums the slices
-        const bool head_takes_slices = !head_rows && n_head == R && layer_mfma_supported(c0) && gemm_mfma_supported(dm, dm.d);
+        // the last layer may do the same when all its rows go to the LM head as they are: the final norm sums the slices
+        const bool head_takes_slices = (subset || (!head_rows && n_head == R)) && layer_mfma_supported(c0) && gemm_mfma_supported(dm, dm.d);
         const bool may_defer = l + 1 < st->layers.size() ? layer_takes_slices(st->layers[l + 1], decode) : head_takes_slices;
         icarus_status rc = run_layer(st->layers[l], ws, pr.L, pr.rm, &pr.hp, R, decode, false, decode ? 0 : 1, kv_pools[l], bt, max_blocks,
-                                     xa, xb, nullptr, s, &pr.fp, pending, may_defer ? &left : nullptr);
+                                     xa, xb, nullptr, s, &pr.fp, pending, may_defer ? &left : nullptr, subset && l + 1 == st->layers.size() ? &last : nullptr);
         if (rc) return stack_fail(st, rc, st->layers[l]->err);
         pending = left;
         std::swap(xa, xb);
     }
     // final norm + LM head on the chosen rows, greedy token
-    char *xg = ws + SL.xn, *xn = xg + (size_t)n_head * row_bytes;
     const void *xh = xa;
-    if (head_rows) {
+    if (head_rows && !subset) {
         STACK_TRY(launch_gather_rows(xa, head_rows, xg, n_head, row_bytes, s));
         xh = xg;
     }
     float *lg = logits ? logits : (float *)(ws + SL.logits);
     if (layer_mfma_supported(c0) && gemm_mfma_supported(dm, dm.d)) {
         if (pending > 0)  // the last layer left its output in pieces (only when head_takes_slices)
-            STACK_TRY(launch_sum_norm_shrink(dm, (const float *)(ws + pr.L.gemm_part), pending, (size_t)R * dm.d, ws + pr.L.z, xa, st->final_norm,
+            STACK_TRY(launch_sum_norm_shrink(dm, (const float *)(ws + pr.L.gemm_part), pending, (size_t)n_head * dm.d, ws + pr.L.z, xa, st->final_norm,
                                              xn, n_head, dm.d, nullptr, nullptr, pr.rm, nullptr, s));
         else
             STACK_TRY(launch_norm_shrink(dm, xh, st->final_norm, xn, n_head, dm.d, nullptr, nullptr, pr.rm, nullptr, nullptr, 0, s));

@@ -235,8 +235,9 @@ hipError_t launch_attn_merge(const Dims &dm, const float *part_o, const float *p
 // ---- layer stack helpers (index work) ----------------------------------------------------------
 // x[row, :] = embed[tok[idx ? idx[row] : row], :]   (rows of row_bytes bytes, a multiple of 16)
 hipError_t launch_embed_rows(const void *embed, const int32_t *tok, const int32_t *idx, void *x, int R, int row_bytes, hipStream_t st);
-// out[i, :] = x[rows[i], :]
-hipError_t launch_gather_rows(const void *x, const int32_t *rows, void *out, int n, int row_bytes, hipStream_t st);
+// out[i, :] = x[rows[i], :], and out2[i, :] = x2[rows[i], :] if there is an x2
+hipError_t launch_gather_rows(const void *x, const int32_t *rows, void *out, int n, int row_bytes, hipStream_t st, const void *x2 = nullptr,
+                              void *out2 = nullptr, int row_bytes2 = 0);
 // token[row] = first index of the largest of logits[row, 0..V)
 // scratch: argmax_scratch_bytes(R) bytes of device memory, 8-byte aligned (partial results)
 size_t argmax_scratch_bytes(int R);

@@ -17,9 +17,11 @@ __global__ void __launch_bounds__(256) k_embed_rows(const uint4 *__restrict__ em
     for (int i = threadIdx.x; i < row_vec; i += 256) dst[i] = src[i];
 }
 
-// out[i, :] = x[rows[i], :]
+// out[i, :] = x[rows[i], :]; a second row of workgroups does the same for x2
 __global__ void __launch_bounds__(256) k_gather_rows(const uint4 *__restrict__ x, const int32_t *__restrict__ rows,
-                                                     uint4 *__restrict__ out, int row_vec) {
+                                                     uint4 *__restrict__ out, int row_vec, const uint4 *__restrict__ x2,
+                                                     uint4 *__restrict__ out2, int row_vec2) {
+    if (blockIdx.y) { x = x2; out = out2; row_vec = row_vec2; }
     const uint4 *src = x + (size_t)rows[blockIdx.x] * row_vec;
     uint4 *dst = out + (size_t)blockIdx.x * row_vec;
     for (int i = threadIdx.x; i < row_vec; i += 256) dst[i] = src[i];
@@ -87,9 +89,11 @@ hipError_t launch_embed_rows(const void *embed, const int32_t *tok, const int32_
     return hipGetLastError();
 }
 
-hipError_t launch_gather_rows(const void *x, const int32_t *rows, void *out, int n, int row_bytes, hipStream_t st) {
+hipError_t launch_gather_rows(const void *x, const int32_t *rows, void *out, int n, int row_bytes, hipStream_t st, const void *x2, void *out2,
+                              int row_bytes2) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gather_rows, dim3(n), dim3(256), 0, st, (const uint4 *)x, rows, (uint4 *)out, row_bytes / 16);
+    hipLaunchKernelGGL(k_gather_rows, dim3(n, x2 ? 2 : 1), dim3(256), 0, st, (const uint4 *)x, rows, (uint4 *)out, row_bytes / 16,
+                       (const uint4 *)x2, (uint4 *)out2, row_bytes2 / 16);
     return hipGetLastError();
 }
 

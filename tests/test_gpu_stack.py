@@ -92,6 +92,33 @@ def test_stack_prefill_then_greedy_decode(kind):
         ctx = ctx + 1
 
 
+@pytest.mark.parametrize("prompt_lens", [(20, 13), (20, 14), (1, 33), (300,)])
+@pytest.mark.parametrize("n_layers", [1, 2])
+def test_prompt_whose_last_layer_keeps_one_row_of_each_chunk(prompt_lens, n_layers):
+    """From 32 rows more than chunks on the last layer's projections run for the chunks' last rows alone: both sides of that line, a
+    chunk of one row, and a single layer (which is the first one too) against the oracle."""
+    from gpu_util import pool_from_device_layout
+    from paper_2603_13281_amd import synth
+    shape, vocab, tol = synth.QWEN_SMALL, 512, 2e-2
+    lens = np.array(prompt_lens, np.int32)
+    S = len(lens)
+    max_blocks = int(lens.max() + 8) // shape.block_size + 1
+    num_blocks = S * max_blocks
+    rng = np.random.default_rng(5)
+    wts, orc, stack, pools = _build(shape, n_layers, vocab, num_blocks, seed=3)
+    opools = orc.new_pools()
+    bt = rng.permutation(num_blocks).reshape(S, max_blocks).astype(np.int32)
+    tokens = rng.integers(0, vocab, size=int(lens.sum())).astype(np.int32)
+    zeros = np.zeros(S, np.int32)
+    nxt, lg = stack.prefill(pools, torch.from_numpy(bt).to("cuda:0"), zeros, lens, tokens, want_logits=True)
+    want_lg, _ = orc.prefill(opools, bt, zeros, lens, tokens)
+    torch.cuda.synchronize()
+    _check_tokens(nxt.cpu().numpy(), lg.cpu().numpy().astype(np.float64), want_lg, tol, f"{prompt_lens}")
+    for l in range(n_layers):  # every row's K and V are in the cache, those of rows that do not leave the last layer too
+        got, want = pool_from_device_layout(pools[l].float().cpu().numpy(), shape.block_size, shape.head_dim), opools[l]
+        assert np.linalg.norm(got - want) <= 1e-2 * np.linalg.norm(want)
+
+
 def test_stack_rejects_bad_arguments():
     from paper_2603_13281_amd import binding, synth
     shape = synth.TINY
