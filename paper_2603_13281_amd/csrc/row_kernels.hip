@@ -23,6 +23,11 @@ constexpr int kRowThreads = 512;  // threads per row: 8 waves share the K range 
 // 16: 316 rows 16.1 -> 12.8, 360 rows 18.7 -> 16.4; 25600 columns, rank 32, 144 rows 24.7 -> 19.4; with norm or sums 316 rows 10.6 -> 12.7,
 // 14.7 -> 19.0, merge 12.1 -> 14.1.
 constexpr int kRowMaxWorkgroups = 512, kRowMaxWorkgroupsPlain = 1024;
+// Down to two accumulators each: what a workgroup takes is its rows of A, which one CU fetches at some 50 GB/s, and the chain of their
+// groups.  Workgroups of 8 / 4 / 2 accumulators, us, rank 16: 9 rows, norm of 4096 8.2 / 6.2 / 5.2, merge 11.7 / 10.5 / 9.6, sums and norm
+// (32 accumulators) 9.0 / 7.3 / 6.2, 14336 columns 9.2 / 6.4 / 5.2; 64 rows, norm 7.0 / 5.4 / 5.1, merge 8.0 / 7.3 / 7.3, 14336 columns 8.8 / 6.5 / 6.3.
+// Parts that each sum the slices stop at one workgroup to a CU: 64 rows in 128 / 256 / 512 workgroups 9.1 / 7.3 / 8.8, 256 / 512 9.5 / 10.2.
+constexpr int kRowMinAcc = 2, kRowMaxWorkgroupsSums = 256;
 
 __device__ __forceinline__ void unpack8(uint4 v, float (&f)[8]) {
     f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
@@ -317,20 +322,22 @@ __global__ void __launch_bounds__(kRowThreads, NACC == 64 ? 2 : 4) k_row(RowArgs
 }
 
 // nacc: the row's accumulators (targets * r).  With few rows they are split over several workgroups per row
-// (each computes 8 or more of them against its share of the adapter rows and forms the row for itself), so
+// (each computes two or more of them against its share of the adapter rows and forms the row for itself), so
 // that a handful of rows still spreads over the chip and a thread's chain of dependent load groups gets shorter.
 template <int SRC, bool NORM>
 hipError_t launch_row(int nacc, int R, const RowMeta &rm, hipStream_t st, const RowArgs &a) {
     const bool ordered = nacc > 0 && rm.order;
     int parts = 1;
     const int most = SRC == SRC_PLAIN && !NORM ? kRowMaxWorkgroupsPlain : kRowMaxWorkgroups;
-    while (nacc / (2 * parts) >= 8 && R * 2 * parts <= most) parts *= 2;
+    while (nacc / (2 * parts) >= kRowMinAcc && R * 2 * parts <= (SRC == SRC_SLICES && nacc / (2 * parts) < 8 ? kRowMaxWorkgroupsSums : most)) parts *= 2;
     nacc /= parts;
 #define ICARUS_ROW(N)                                                                                                          \
     if (ordered) hipLaunchKernelGGL((k_row<SRC, NORM, N, (N > 0)>), dim3(rm.n_order, parts), dim3(kRowThreads), 0, st, a);      \
     else hipLaunchKernelGGL((k_row<SRC, NORM, N, false>), dim3(R, parts), dim3(kRowThreads), 0, st, a)
     switch (nacc) {
     case 0: ICARUS_ROW(0); break;
+    case 2: ICARUS_ROW(2); break;
+    case 4: ICARUS_ROW(4); break;
     case 8: ICARUS_ROW(8); break;
     case 16: ICARUS_ROW(16); break;
     case 32: ICARUS_ROW(32); break;

@@ -42,3 +42,10 @@ def test_every_row_once(shape, kind, n_seq):
                             np.asarray(model, np.int32), dev(x, True))
     torch.cuda.synchronize()
     assert_close(host(got), want, 2e-2, "x_out")
+
+
+@pytest.mark.parametrize("shape", [synth.LLAMA_SMALL, synth.QWEN_SMALL], ids=lambda s: s.name)
+@pytest.mark.parametrize("n_seq", [1, 4, 5, 8, 9, 16, 17, 32, 33])
+def test_few_rows_split_over_workgroups(shape, n_seq):
+    """2 n_seq rows: an adapter's products are split over 16, 8, 4 or 2 workgroups a row, fewer for more rows; both sides of each line."""
+    test_every_row_once(shape, "one model", n_seq)
