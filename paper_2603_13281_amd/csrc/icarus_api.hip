@@ -418,30 +418,39 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
         });
         // Cut every sequence's walk into parts of at most `most` tokens, whole rounds of the walk each: part p of a
         // group is tokens [p len, (p + 1) len) with the same len for all groups of a sequence; a last part shorter
-        // than a round joins the one before it.
-        struct Cut { int32_t s, begin, len, n; };
-        std::vector<Cut> cuts;
+        // than a round joins the one before it.  Or, with what equal parts would leave idle in the last round of CUs: parts of `most`
+        // tokens and then, when all of those are under way, the groups' remainders, longest first.  Either way the groups
+        // of a sequence are cut at the same tokens, so that those which run side by side read the same part of its cache.  753 rows over
+        // 2500-8200 tokens, us, attention + merge: equal parts 124 + 13.5, with remainders 111 + 10.3; one line of all walks cut into a share
+        // per CU, by the model the shortest of the three, 127 + 11.
+        struct Cut { int32_t s, begin, len, part, n; };
+        std::vector<Cut> cuts, rest;
         const int round = attn_prefill_round(), max_piece = attn_prefill_max_ctx();
         int cut_to = 0;  // what `cuts` holds
-        auto cut = [&](int most) {
-            if (most == cut_to) return;
+        bool cut_tails = false;
+        auto cut = [&](int most, bool tails) {
+            if (most == cut_to && tails == cut_tails) return;
             cut_to = most;
+            cut_tails = tails;
             cuts.clear();
+            rest.clear();
             for (size_t i = 0; i < order.size();) {
                 const int bt_row = seq_bt ? seq_bt[order[i]] : order[i];
                 size_t e = i;
                 while (e < order.size() && (seq_bt ? seq_bt[order[e]] : order[e]) == bt_row) ++e;
                 const int64_t top = longest[bt_row], k = (top + most - 1) / most;
-                const int len = (int)(((top + k - 1) / k + round - 1) / round * round);
+                const int len = tails ? most : (int)(((top + k - 1) / k + round - 1) / round * round);
                 for (int p = 0; p < k; ++p)
                     for (size_t o = i; o < e; ++o) {
                         const int s = order[o], kv = kv_lens[s];
                         int n = std::max(1, (kv - (round - 1) + len - 1) / len);  // parts of this group
                         if (kv - (n - 1) * len > max_piece) ++n;
-                        if (p < n) cuts.push_back({s, p * len, p + 1 < n ? len : kv - p * len, n});
+                        if (p < n) (tails && p > 0 && p + 1 == n ? rest : cuts).push_back({s, p * len, p + 1 < n ? len : kv - p * len, p, n});
                     }
                 i = e;
             }
+            std::stable_sort(rest.begin(), rest.end(), [](const Cut &a, const Cut &b) { return a.len > b.len; });
+            cuts.insert(cuts.end(), rest.begin(), rest.end());
         };
         // Model of a launch, in tokens walked by one workgroup: the kernel gives a CU one workgroup, so attn_wgs / Hkv
         // pieces run at a time, each next one on the first CU that is free; a piece costs its tokens and
@@ -450,21 +459,32 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
         // tiles a group fills: *busy is what the CUs' mean load comes to then.  Fitted to k_attn_prefill_short; k_attn_prefill takes up to
         // 8 % less per token and somewhat more per piece.
         const int cus = std::max(1, ctx->attn_wgs / Hkv);
-        auto cost = [&](int64_t *busy) {
+        std::vector<int64_t> free_at;  // min-heap of finishing times
+        auto cost = [&](int64_t at_most, int64_t *busy) {  // INT64_MAX: at_most at least, however the pieces fall, and so for smaller ones
             constexpr int64_t kPieceTokens = 160, kMergeTokens = 160, kSlotTokens = 8;
-            std::vector<int64_t> free_at((size_t)cus, 0);  // min-heap of finishing times
-            int64_t end = 0, sum = 0;
-            size_t slots = 0;
+            int64_t plain = 0, filled = 0, slots = 0;
             for (const Cut &c : cuts) {
-                std::pop_heap(free_at.begin(), free_at.end(), std::greater<int64_t>());
-                free_at.back() += c.len + kPieceTokens;
-                end = std::max(end, free_at.back());
-                std::push_heap(free_at.begin(), free_at.end(), std::greater<int64_t>());
-                sum += (c.len + kPieceTokens) * (100 + 35 * seq_rows[c.s] * g / attn_prefill_group_queries()) / 100;
+                plain += c.len + kPieceTokens;
+                filled += (c.len + kPieceTokens) * seq_rows[c.s];
                 slots += c.n > 1;
             }
-            const int64_t merge = slots ? kMergeTokens + kSlotTokens * (int64_t)slots : 0;
-            *busy = sum / cus + merge;
+            const int64_t merge = slots ? kMergeTokens + kSlotTokens * slots : 0;
+            *busy = (100 * plain + 35 * g * filled / attn_prefill_group_queries()) / 100 / cus + merge;
+            if (plain / cus + merge >= at_most) return INT64_MAX;
+            free_at.assign((size_t)cus, 0);
+            int64_t end = 0;
+            for (const Cut &c : cuts) {
+                const int64_t t = free_at[0] + c.len + kPieceTokens;
+                int at = 0;  // the heap's first goes down to its new place
+                for (int k = 1; k < cus; k = 2 * at + 1) {
+                    k += k + 1 < cus && free_at[k + 1] < free_at[k];
+                    if (free_at[k] >= t) break;
+                    free_at[at] = free_at[k];
+                    at = k;
+                }
+                free_at[at] = t;
+                end = std::max(end, t);
+            }
             return end + merge;
         };
         auto fits = [&]() {
@@ -473,32 +493,38 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
             return cuts.size() <= std::max(max_items, order.size()) && slots * (size_t)g_max <= max_partial;
         };
         int best_most = max_piece;
+        bool best_tails = false;
         if (ctx->attn_chunk_override > 0) {
             best_most = std::min(max_piece, std::max(round, ctx->attn_chunk_override / round * round));
         } else {
-            cut(max_piece);
+            cut(max_piece, false);
             // Enough pieces for several per CU need no cutting: the last ones end within a piece of each other.
             if (cuts.size() < (size_t)8 * cus) {
-                int64_t busy = 0, whole = cost(&busy), best = fits() ? whole : INT64_MAX, work = 0;
+                int64_t busy = 0, whole = cost(INT64_MAX, &busy), best = fits() ? whole : INT64_MAX, work = 0;
                 if (best == whole) best = whole * 9 / 10;  // see below
                 for (int s : order) work += kv_lens[s];
                 // one piece per CU, or up to five; lengths in between because a sequence's parts are of one length
-                for (int pct : {200, 150, 125, 105, 90, 78, 68, 60, 52, 45, 38, 32, 26, 20}) {
+                for (int pct : {200, 150, 125, 112, 105, 90, 78, 68, 60, 52, 45, 38, 32, 26, 20}) {
                     const int most = (int)std::min<int64_t>(max_piece, std::max<int64_t>(2 * round, work * pct / (100 * (int64_t)cus)));
-                    cut(most);
-                    if (!fits()) continue;
-                    // A modelled gain of less than a tenth is none: 520 rows over 64-600 tokens, 32 heads on 8 kv-heads, were
-                    // 2 % of a small layer slower cut, two chunks of 300 rows over 500 tokens 3 %; 2000 rows over 64 tokens, which
-                    // keep every CU busy, 3 % for a modelled fifth.
-                    const int64_t c = cost(&busy);
-                    if (c < best && (best_most != max_piece || busy < best)) { best = c; best_most = most; }
-                    if (most == 2 * round) break;
+                    bool dearer = false;
+                    for (bool tails : {false, true}) {
+                        const int len = tails ? (most + round / 2) / round * round : most;
+                        cut(len, tails);
+                        if (!fits()) continue;
+                        // A modelled gain of less than a tenth is none: 520 rows over 64-600 tokens, 32 heads on 8 kv-heads, were
+                        // 2 % of a small layer slower cut, two chunks of 300 rows over 500 tokens 3 %; 2000 rows over 64 tokens, which
+                        // keep every CU busy, 3 % for a modelled fifth.
+                        const int64_t c = cost(best, &busy);
+                        if (c < best && (best_most != max_piece || busy < best)) { best = c; best_most = len; best_tails = tails; }
+                        dearer = dearer || c == INT64_MAX;
+                    }
+                    if (dearer || most == 2 * round) break;
                 }
             }
         }
-        cut(best_most);
+        cut(best_most, best_tails);
         if (!fits()) {
-            cut(max_piece);
+            cut(max_piece, false);
             if (!fits()) return;
         }
         // The arrays of parts are staged only if there are any: with them the copy of a call of hundreds of whole walks grows
@@ -535,13 +561,12 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
                 part0[s] = slot;
                 if (nparts[s] > 1) slot += nparts[s];
             }
-            std::vector<int32_t> used((size_t)S, 0);
             for (size_t i = 0; i < n_items; ++i) {
                 const Cut &c = cuts[i];
                 item_begin[i] = c.begin;
                 item_len[i] = c.len;
                 item_direct[i] = c.n == 1;
-                item_part[i] = part0[c.s] + used[c.s]++;
+                item_part[i] = part0[c.s] + c.part;
             }
             pl->seq_part0 = pl->seq_bt + S;
             pl->seq_nparts = pl->seq_part0 + S;

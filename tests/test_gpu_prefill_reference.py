@@ -138,3 +138,30 @@ def test_every_query_far_from_the_reference(shape, fp8, kind, limit):
     # that rest, whose share the rounding of q may double, and probabilities, attention and (both sides) residual sum rounded to bf16
     bound = 2.0 ** -7 * np.abs(attn).max(-1, keepdims=True) + 2.0 ** -8 * np.abs(want)
     assert (np.abs(got - want) <= bound)[decided].all(), np.argwhere(~(np.abs(got - want) <= bound).all(-1) & decided)[:8]
+
+
+@pytest.mark.parametrize("ctx,chunk", [([2531, 3671], [841, 802]), ([316, 3859, 3623, 1796], [463, 642, 800, 805])], ids=["two", "four"])
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
+def test_walks_cut_with_remainders(ctx, chunk, fp8):
+    """A plan of equal parts and remainders against whole walks of the same calls."""
+    print("case: remainders", ctx, chunk, "fp8", fp8, flush=True)
+    shape = synth.LLAMA_SMALL
+    base = synth.make_base(shape, seed=3, norm_ones=False)
+    batch = synth.make_batch(shape, ctx, [0] * len(ctx), seed=3, headroom=max(chunk))
+    layer = make_layer(shape, base, None, batch.num_blocks, **(dict(kv_fp8=True, k_scale=0.02, v_scale=0.02) if fp8 else {}))
+    pool = torch.randn(layer.cfg.pool_shape(), generator=torch.Generator().manual_seed(1)).clamp(-4, 4)
+    pool = (pool / 0.02).to(torch.float8_e4m3fn).view(torch.uint8).cuda() if fp8 else pool.to(torch.bfloat16).cuda()
+    pieces = layer.prefill_plan(ctx, chunk)
+    assert (np.diff(pieces[:, 3][pieces[:, 4] >= 0]) < 0).sum() > 3  # remainders of several lengths
+    x = dev(synth.make_hidden(shape, sum(chunk), seed=3, tag=5), True)
+    bt = torch.from_numpy(batch.block_tables).cuda()
+    out = []
+    for limit in (0, 16384):
+        layer.set_attn_piece_limit(limit)
+        p = pool.clone()
+        out.append((host(layer.prefill_kv(p, bt, ctx, chunk, x)), p))
+    torch.cuda.synchronize()
+    (a, pa), (b, pb) = out
+    assert torch.equal(pa, pb)
+    # attention outputs that differ in the last bit of float32 sums round to neighbouring bf16 values, half of 2^-8 apart at most
+    assert np.linalg.norm(a - b) <= 2 ** -8 * np.linalg.norm(b)

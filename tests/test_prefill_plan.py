@@ -74,3 +74,18 @@ def test_a_shorter_call_needs_no_more_workspace():
     assert small <= at < past
     assert layer.workspace_bytes(9, 1, WALK + 4000) - layer.workspace_bytes(9, 1, WALK) < 1 << 24
     layer.close()
+
+
+@pytest.mark.parametrize("ctx,chunk", [([2522, 6657, 8161, 4188], [113, 345, 72, 223]), ([3366, 3809], [568, 469]), ([1933, 1832, 2744], [24, 89, 426])],
+                         ids=lambda v: "+".join(map(str, v)))
+def test_remainders_of_walks_follow_their_equal_parts(ctx, chunk):
+    layer = _layer(4, 8)
+    _check(layer, 4, ctx, chunk)
+    pieces = layer.prefill_plan(ctx, chunk)
+    cut = [p for p in pieces if (pieces[:, 0] == p[0]).sum() > 1]
+    last = {p[0]: max(q[2] for q in cut if q[0] == p[0]) for p in cut}
+    tail = [i for i, p in enumerate(pieces) if p[0] in last and p[2] == last[p[0]]]
+    assert tail == list(range(len(pieces) - len(tail), len(pieces)))  # after all others,
+    assert all(pieces[a][3] >= pieces[b][3] for a, b in zip(tail, tail[1:]))  # longest first
+    assert len({p[3] for i, p in enumerate(pieces) if p[0] in last and i not in tail}) == 1
+    layer.close()
