@@ -83,6 +83,13 @@ __device__ __forceinline__ float wave_sums(float (&v)[N], int lane) {
     return v[0];
 }
 
+// One rotated pair.  Which product is rounded before the sum is written out: a cache entry must not depend on which
+// of the kernels that append wrote it, and left to the compiler they came out differently.
+__device__ __forceinline__ void rotate_pair(float a, float b, float cs, float sn, float *ra, float *rb) {
+    *ra = __builtin_fmaf(a, cs, -(b * sn));
+    *rb = __builtin_fmaf(a, sn, b * cs);
+}
+
 // Block-wide reductions for blocks of up to 1024 threads; `red` is a shared float[16].
 // Every thread gets the result.
 __device__ __forceinline__ float block_sum(float v, float *red) {

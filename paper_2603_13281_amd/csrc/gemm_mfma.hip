@@ -563,6 +563,18 @@ hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st) {
     }
 }
 
+bool gemm_qkv_fused(const GemmArgs &g, GemmPlan plan) {
+    return plan.splits == 1 && is_quad(plan.tile) && std::max(g.K, g.ldx) <= kQuadMaxK && g.nseg == 3 && !g.T && !g.row_tiles;
+}
+hipError_t launch_gemm_qkv(GemmArgs g, const QkvStore &e, hipStream_t st) {
+    if (g.R <= 0) return hipSuccess;
+    if (g.K % kKAlign || !gemm_qkv_fused(g, {g.tile, g.splits})) return hipErrorInvalidValue;
+    g.slice_rows = g.R;
+    g.K_ext = g.k_per_split = g.K;
+    g.stagger = gemm_staggered(g) ? gemm_inv(g.K / kKAlign) : 0u;
+    return launch_gemm_quad_qkv(g, e, st);
+}
+
 hipError_t launch_splitk_reduce(const float *P, int splits, int R, int N, int epi, void *Y, int ldy, const void *resid,
                                 int ldr, hipStream_t st) {
     size_t quads = (size_t)R * N / 4;

@@ -51,8 +51,155 @@ struct QuadShape {
     static constexpr int kXStage = BM * BK * 2, kWStage = BN * BK * 2, kLds = 2 * (kXStage + kWStage);  // LDS: two stages of X, two of W
 };
 
-template <int MT0, int MT1, int WAVES_N, bool GROUPED>
-__global__ void __launch_bounds__(128 * WAVES_N, WAVES_N == 4 ? 1 : 2) k_gemm_quad(GemmArgs g) {
+// Epilogue of the QKV projection: a head is the columns of two neighbouring waves, which meet in LDS 32 rows at a time.  Of a q or k
+// head each wave takes half of those rows, a lane eight pairs of one; the sums of the QK-norm run in the order of
+// k_rope_append_tile.  Of a v head a wave takes its own columns, a lane one of them, and whole pieces of eight tokens of the transposed
+// plane go out at once.
+// The projections used to go out and in again in float32 (403 MB of 16384 rows each way) around a kernel of its own.  Projection + append, us,
+// before / now with the table of the rows' angles: 16384 rows, 48 heads 640 + 136 / 594 + 8 (256 x 256), 753 rows 53.6 + 13.2 / 57.2 + 4.9, 512
+// rows of 80 heads 67.9 + 12.2 / 68.2 + 4.8 (192 x 128).  The angles are fetched a group ahead: where they were asked for, 753 rows took
+// 64 us.
+template <int TM, int BN>
+__device__ __forceinline__ void store_qkv_tile(const GemmArgs &g, const QkvStore &e, const f32x4 (&acc)[TM][4], float *scratch, int w, int wn,
+                                               int tile_n, int wrow0, int row_end) {
+    constexpr int kEs = 64 + 8, kScr = 32 * kEs, kPlane = 16 * 128;
+    const int lane = threadIdx.x & 63, half = wn & 1;
+    const int t1 = tile_n - g.tiles_seg[0], t2 = t1 - g.tiles_seg[1];
+    const int seg = t1 < 0 ? 0 : t2 < 0 ? 1 : 2, t = t1 < 0 ? tile_n : t2 < 0 ? t1 : t2;
+    const int head = (t * BN + wn * 64) >> 7;
+    const bool there = head < (seg == 0 ? e.Hq : e.Hkv);
+    float *own = scratch + w * kScr;
+    const float *lo = scratch + (w - half) * kScr, *hi = lo + kScr;
+    const int c = lane & 7;  // the pairs of a lane: 8 c and the seven after it
+    // angles and slots of a group are requested while the one before it is stored
+    float cs[2][8], sn[2][8];
+    int64_t slot[2];
+    auto fetch = [&](int i) {
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+            const int row = min(wrow0 + 32 * i + (seg < 2 ? 16 * half + 8 * pass + (lane >> 3) : lane & 31), row_end - 1);
+            if (seg > 0) slot[pass] = e.slot[row];
+            if (seg < 2)
+#pragma unroll
+                for (int x = 0; x < 8; x += 4) {
+                    *(float4 *)(cs[pass] + x) = *(const float4 *)(e.cs + (size_t)row * 64 + 8 * c + x);
+                    *(float4 *)(sn[pass] + x) = *(const float4 *)(e.sn + (size_t)row * 64 + 8 * c + x);
+                }
+        }
+    };
+    fetch(0);
+    const bf16_t *nw = seg == 0 ? e.q_norm : seg == 1 ? e.k_norm : nullptr;
+    uint4 nlo = make_uint4(0u, 0u, 0u, 0u), nhi = nlo;
+    if (nw) { nlo = *(const uint4 *)(nw + 8 * c); nhi = *(const uint4 *)(nw + 64 + 8 * c); }
+    auto element = [](uint4 v, int x) {
+        const uint32_t u = x < 2 ? v.x : x < 4 ? v.y : x < 6 ? v.z : v.w;
+        return __uint_as_float(x & 1 ? u & 0xffff0000u : u << 16);
+    };
+#pragma unroll
+    for (int i = 0; i < (TM + 1) / 2; ++i) {
+        const int first = wrow0 + 32 * i, n = min(min(32, (TM - 2 * i) * 16), row_end - first);
+        if (i > 0) __syncthreads();
+#pragma unroll
+        for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (2 * i + ii < TM) own[(ii * 16 + (lane >> 4) * 4 + r) * kEs + j * 16 + (lane & 15)] = acc[2 * i + ii][j][r];
+        __syncthreads();
+        if (!there) continue;
+        if (seg < 2) {
+            float ra[2][8], rb[2][8];
+#pragma unroll
+            for (int pass = 0; pass < 2; ++pass) {
+                const int rr = 16 * half + 8 * pass + (lane >> 3);
+                float a[8], b[8];
+#pragma unroll
+                for (int x = 0; x < 8; x += 4) {
+                    *(float4 *)(a + x) = *(const float4 *)(lo + rr * kEs + 8 * c + x);
+                    *(float4 *)(b + x) = *(const float4 *)(hi + rr * kEs + 8 * c + x);
+                }
+                if (nw) {
+                    float p[8];
+#pragma unroll
+                    for (int x = 0; x < 8; ++x) {
+                        p[x] = __builtin_fmaf(b[x], b[x], a[x] * a[x]);
+#pragma unroll
+                        for (int o = 4; o > 0; o >>= 1) p[x] += __shfl_xor(p[x], o, 64);
+                    }
+                    const float inv = rsqrtf((((p[0] + p[4]) + (p[2] + p[6])) + ((p[1] + p[5]) + (p[3] + p[7]))) / 128.f + e.eps);
+#pragma unroll
+                    for (int x = 0; x < 8; ++x) {
+                        a[x] = a[x] * inv * element(nlo, x);
+                        b[x] = b[x] * inv * element(nhi, x);
+                    }
+                }
+#pragma unroll
+                for (int x = 0; x < 8; ++x) rotate_pair(a[x], b[x], cs[pass][x], sn[pass][x], &ra[pass][x], &rb[pass][x]);
+            }
+            const int64_t at[2] = {slot[0], slot[1]};
+            if (i + 1 < (TM + 1) / 2) fetch(i + 1);
+#pragma unroll
+            for (int pass = 0; pass < 2; ++pass) {
+                const int rr = 16 * half + 8 * pass + (lane >> 3), row = first + rr;
+                if (rr >= n) continue;
+                auto pack = [](const float (&v)[8]) { return make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])); };
+                auto pack8 = [&](const float (&v)[8]) {
+                    uint32_t u[2] = {0u, 0u};
+#pragma unroll
+                    for (int x = 0; x < 8; ++x) u[x >> 2] |= f32_to_fp8(v[x] / e.k_scale) << (8 * (x & 3));
+                    return make_uint2(u[0], u[1]);
+                };
+                if (seg == 0) {
+                    bf16_t *dst = e.q + ((size_t)row * e.Hq + head) * 128 + 8 * c;
+                    *(uint4 *)dst = pack(ra[pass]);
+                    *(uint4 *)(dst + 64) = pack(rb[pass]);
+                } else {
+                    const size_t dst = ((size_t)(at[pass] >> 4) * e.Hkv + head) * 2 * kPlane + (size_t)(at[pass] & 15) * 128 + 8 * c;
+                    if (e.kv8) {
+                        *(uint2 *)((uint8_t *)e.pool + dst) = pack8(ra[pass]);
+                        *(uint2 *)((uint8_t *)e.pool + dst + 64) = pack8(rb[pass]);
+                    } else {
+                        *(uint4 *)((bf16_t *)e.pool + dst) = pack(ra[pass]);
+                        *(uint4 *)((bf16_t *)e.pool + dst + 64) = pack(rb[pass]);
+                    }
+                }
+            }
+        } else {
+            const int d = half * 64 + lane, slot_lo = (int)slot[0], slot_hi = (int)(slot[0] >> 32);
+            auto slot_of = [&](int r) { return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane(slot_hi, r) << 32 | (uint32_t)__builtin_amdgcn_readlane(slot_lo, r)); };
+            if (i + 1 < (TM + 1) / 2) fetch(i + 1);
+            for (int r = 0; r < n;) {
+                const int64_t first_slot = slot_of(r);
+                const size_t dst = (((size_t)(first_slot >> 4) * e.Hkv + head) * 2 + 1) * kPlane + (size_t)d * 16 + (size_t)(first_slot & 15);
+                if (!(first_slot & 7) && r + 8 <= n && slot_of(r + 7) == first_slot + 7) {  // a sequence's rows follow one another: the six between lie between
+                    float v[8];
+#pragma unroll
+                    for (int x = 0; x < 8; ++x) v[x] = own[(r + x) * kEs + lane];
+                    if (e.kv8) {
+                        uint32_t u[2] = {0u, 0u};
+#pragma unroll
+                        for (int x = 0; x < 8; ++x) u[x >> 2] |= f32_to_fp8(v[x] / e.v_scale) << (8 * (x & 3));
+                        *(uint2 *)((uint8_t *)e.pool + dst) = make_uint2(u[0], u[1]);
+                    } else {
+                        *(uint4 *)((bf16_t *)e.pool + dst) =
+                            make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
+                    }
+                    r += 8;
+                } else {
+                    const float v = own[r * kEs + lane];
+                    if (e.kv8) ((uint8_t *)e.pool)[dst] = (uint8_t)f32_to_fp8(v / e.v_scale);
+                    else ((bf16_t *)e.pool)[dst] = f32_to_bf16(v);
+                    ++r;
+                }
+            }
+        }
+    }
+}
+
+// e: the epilogue's arguments where it is that of the QKV projection (QKV), else null
+template <int MT0, int MT1, int WAVES_N, bool GROUPED, bool QKV>
+__device__ __forceinline__ void quad_tile(const GemmArgs &g, const QkvStore *e) {
     using Shape = QuadShape<MT0, MT1, WAVES_N>;
     constexpr int NW = 2 * WAVES_N, BM = Shape::BM, BN = Shape::BN, BK = Shape::BK;
     constexpr int WM = BM / 2, WN = 64, NT = 2, KS = BK / 32;
@@ -278,11 +425,20 @@ __global__ void __launch_bounds__(128 * WAVES_N, WAVES_N == 4 ? 1 : 2) k_gemm_qu
     }
     __syncthreads();  // every wave has left the K loop: the stages are the epilogue's scratch
     static_assert(NW * 32 * (WN + 8) * 4 <= Shape::kLds, "epilogue scratch must fit the stages");
-    store_wave_tile<16, MT0 + MT1, 2 * NT, BN>(g, acc, (float *)smem + w * 32 * (WN + 8), tile_n, kz, row0 + wm * WM, row_end, wn);
+    if constexpr (QKV) store_qkv_tile<MT0 + MT1, BN>(g, *e, acc, (float *)smem, w, wn, tile_n, row0 + wm * WM, row_end);
+    else store_wave_tile<16, MT0 + MT1, 2 * NT, BN>(g, acc, (float *)smem + w * 32 * (WN + 8), tile_n, kz, row0 + wm * WM, row_end, wn);
 }
 
 template <int MT0, int MT1, int WAVES_N, bool GROUPED>
-hipError_t launch_quad(GemmArgs g, hipStream_t st) {
+__global__ void __launch_bounds__(128 * WAVES_N, WAVES_N == 4 ? 1 : 2) k_gemm_quad(GemmArgs g) { quad_tile<MT0, MT1, WAVES_N, GROUPED, false>(g, nullptr); }
+
+template <int MT0, int MT1, int WAVES_N>
+__global__ void __launch_bounds__(128 * WAVES_N, WAVES_N == 4 ? 1 : 2) k_gemm_quad_qkv(GemmArgs g, QkvStore e) {
+    quad_tile<MT0, MT1, WAVES_N, false, true>(g, &e);
+}
+
+template <int MT0, int MT1, int WAVES_N, bool GROUPED>
+hipError_t launch_quad(GemmArgs g, hipStream_t st, const QkvStore *e = nullptr) {
     using Shape = QuadShape<MT0, MT1, WAVES_N>;
     constexpr int BM = Shape::BM, BN = Shape::BN;
     g.m_tiles = GROUPED ? g.n_row_tiles : (g.R + BM - 1) / BM;
@@ -296,33 +452,47 @@ hipError_t launch_quad(GemmArgs g, hipStream_t st) {
         }
     }
     gemm_set_panels(&g, BM, BN, WAVES_N == 4 ? 1 : 2);
+    dim3 grid(gemm_grid(g));
+    if constexpr (!GROUPED)
+        if (e) {
+            static bool qkv_set = false;
+            if (!qkv_set) {
+                hipError_t rc = hipFuncSetAttribute((const void *)k_gemm_quad_qkv<MT0, MT1, WAVES_N>, hipFuncAttributeMaxDynamicSharedMemorySize, Shape::kLds);
+                if (rc != hipSuccess) return rc;
+                qkv_set = true;
+            }
+            hipLaunchKernelGGL((k_gemm_quad_qkv<MT0, MT1, WAVES_N>), grid, dim3(128 * WAVES_N), Shape::kLds, st, g, *e);
+            return hipGetLastError();
+        }
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_gemm_quad<MT0, MT1, WAVES_N, GROUPED>, hipFuncAttributeMaxDynamicSharedMemorySize, Shape::kLds);
-        if (e != hipSuccess) return e;
+        hipError_t rc = hipFuncSetAttribute((const void *)k_gemm_quad<MT0, MT1, WAVES_N, GROUPED>, hipFuncAttributeMaxDynamicSharedMemorySize, Shape::kLds);
+        if (rc != hipSuccess) return rc;
         attr_set = true;
     }
-    dim3 grid(gemm_grid(g));
     hipLaunchKernelGGL((k_gemm_quad<MT0, MT1, WAVES_N, GROUPED>), grid, dim3(128 * WAVES_N), Shape::kLds, st, g);
     return hipGetLastError();
 }
 
-}  // namespace
-hipError_t launch_gemm_quad(const GemmArgs &g, hipStream_t st) {
+hipError_t launch_any(const GemmArgs &g, const QkvStore *e, hipStream_t st) {
     switch (g.tile) {
     case TILE_192x128: {
         if (g.row_tiles) return launch_quad<3, 3, 2, true>(g, st);
         // As many lower tiles, if they hold the rows: no MFMAs for padding (316 rows in tiles of 192 / 160: 14336 -> 4096 in 4
         // slices 54.4 / 53.5 us, 4096 -> 4096 28.5 / 26.7; 144 rows, 8192 -> 5120 in 6 slices 34.4 / 32.2)
         const int tiles = (g.R + 191) / 192;
-        if (g.R <= 128 * tiles) return launch_quad<2, 2, 2, false>(g, st);
-        return g.R <= 160 * tiles ? launch_quad<3, 2, 2, false>(g, st) : launch_quad<3, 3, 2, false>(g, st);
+        if (g.R <= 128 * tiles) return launch_quad<2, 2, 2, false>(g, st, e);
+        return g.R <= 160 * tiles ? launch_quad<3, 2, 2, false>(g, st, e) : launch_quad<3, 3, 2, false>(g, st, e);
     }
-    case TILE_256x256: return g.row_tiles ? launch_quad<4, 4, 4, true>(g, st) : launch_quad<4, 4, 4, false>(g, st);
-    case TILE_192x256: return launch_quad<3, 3, 4, false>(g, st);
-    case TILE_160x256: return launch_quad<3, 2, 4, false>(g, st);
+    case TILE_256x256: return g.row_tiles ? launch_quad<4, 4, 4, true>(g, st) : launch_quad<4, 4, 4, false>(g, st, e);
+    case TILE_192x256: return launch_quad<3, 3, 4, false>(g, st, e);
+    case TILE_160x256: return launch_quad<3, 2, 4, false>(g, st, e);
     default: return hipErrorInvalidValue;
     }
 }
+
+}  // namespace
+hipError_t launch_gemm_quad(const GemmArgs &g, hipStream_t st) { return launch_any(g, nullptr, st); }
+hipError_t launch_gemm_quad_qkv(const GemmArgs &g, const QkvStore &e, hipStream_t st) { return launch_any(g, &e, st); }
 
 }  // namespace icarus

@@ -174,13 +174,6 @@ hipError_t launch_silu_mul(const Dims &dm, const float *gate, const float *up, v
 // GEMM, `slice` floats apart) that are summed here.  Angles are computed in double, once per
 // row: pos * theta^(-2i/D).
 
-// One rotated pair.  Which product is rounded before the sum is written out: a cache entry must not depend on which
-// of the two kernels below wrote it, and left to the compiler the two came out differently.
-__device__ __forceinline__ void rotate_pair(float a, float b, float cs, float sn, float *ra, float *rb) {
-    *ra = __builtin_fmaf(a, cs, -(b * sn));
-    *rb = __builtin_fmaf(a, sn, b * cs);
-}
-
 template <typename T, typename KT>
 __global__ void __launch_bounds__(256) k_rope_append(const float *__restrict__ qkv, int ldq, int splits, size_t slice,
                                                      const int32_t *__restrict__ row_seq,
@@ -489,6 +482,30 @@ hipError_t launch_rope_append_tiles(const Dims &dm, const float *qkv, int ldq, i
         return hipGetLastError();
     };
     return dm.kv8 ? launch(fp8_t()) : launch(bf16_t());
+}
+
+// What the fused form of the above (gemm_quad.hip) needs of each row: cosines and sines of its 64 angles, and its slot.
+__global__ void __launch_bounds__(256) k_rope_table(const int32_t *__restrict__ row_seq, const int32_t *__restrict__ row_pos,
+                                                    const int32_t *__restrict__ bt, int max_blocks, int R, double log2_theta,
+                                                    float *__restrict__ cs, float *__restrict__ sn, int64_t *__restrict__ slot) {
+    constexpr int D = 128, half = 64, Bk = 16;
+    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), i = threadIdx.x & 63;
+    if (row >= R) return;
+    const int pos = row_pos[row];
+    const double ang = (double)pos * exp2(-(2.0 * (double)i / (double)D) * log2_theta);
+    double sn_d, cs_d;
+    sincos(ang, &sn_d, &cs_d);
+    cs[(size_t)row * half + i] = (float)cs_d;
+    sn[(size_t)row * half + i] = (float)sn_d;
+    if (i == 0) slot[row] = (int64_t)bt[(size_t)row_seq[row] * max_blocks + pos / Bk] * Bk + pos % Bk;
+}
+
+hipError_t launch_rope_table(const Dims &dm, const RowMeta &rm, const int32_t *bt, int max_blocks, int R, float *cs, float *sn, int64_t *slot,
+                             hipStream_t st) {
+    if (R <= 0) return hipSuccess;
+    if (dm.D != 128 || dm.Bk != 16) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_rope_table, dim3((R + 3) / 4), dim3(256), 0, st, rm.row_seq, rm.row_pos, bt, max_blocks, R, log2(dm.theta), cs, sn, slot);
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ attention (one block per row and query head)

@@ -714,17 +714,24 @@ bool layer_mfma_supported(const icarus_ctx *ctx) {
            gemm_mfma_supported(ctx->dm, c.d_ffn) && shrink_ok;
 }
 
+int outputs(const GemmArgs &g) {
+    int n = 0;
+    for (int s = 0; s < g.nseg; ++s) n += g.n_seg[s];
+    return n;
+}
+GemmPlan plan_gemm(const GemmArgs &g, const WsLayout &L, bool takes_slices) {
+    return gemm_plan(g, (int)std::max<size_t>(1, std::min<size_t>(kGemmMaxSplits, L.gemm_part_bytes / ((size_t)g.R * outputs(g) * 4))), takes_slices);
+}
+
 // One plain ICaRusLinear GEMM.  Where its grid would leave most of the chip idle (few rows and a
 // narrow output), K is split over several workgroups into fp32 partials [splits][R][N]; a second
 // small kernel sums them and applies the epilogue, unless the caller takes the slices as they are
 // (deferred_splits: set to the number of slices left in the workspace, 0 if the output is final).
 icarus_status run_gemm(icarus_ctx *ctx, char *ws, const WsLayout &L, int phase, GemmArgs g, hipStream_t st,
                        int *deferred_splits = nullptr) {
-    int n_total = 0;
-    for (int s = 0; s < g.nseg; ++s) n_total += g.n_seg[s];
+    const int n_total = outputs(g);
     const bool takes_slices = deferred_splits && n_total == g.ldy;
-    const int max_splits = (int)std::max<size_t>(1, std::min<size_t>(kGemmMaxSplits, L.gemm_part_bytes / ((size_t)g.R * n_total * 4)));
-    const GemmPlan plan = gemm_plan(g, max_splits, takes_slices);
+    const GemmPlan plan = plan_gemm(g, L, takes_slices);
     const int splits = plan.splits;
     g.tile = plan.tile;
     if (deferred_splits) *deferred_splits = 0;
@@ -755,7 +762,8 @@ struct RowSubset {
 icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const RowMeta &rm, const HostPlan *hp, int R,
                              bool use_lora, bool kv_only, int slot_by_row, void *pool, const int32_t *bt, int max_blocks,
                              const void *x_in, void *x_out, int64_t *slot_out, hipStream_t st, int in_splits = 0,
-                             int *out_splits = nullptr, const RowSubset *last = nullptr) {
+                             int *out_splits = nullptr, const RowSubset *last = nullptr, bool rope_ready = false) {
+    // rope_ready (layer stack): a layer of this call before left the rows' angles and slots where this one would put them.
     // last != null (prefill): only these rows leave the layer, one after the other in x_out; of the others K and V are all that is asked for.
     // in_splits > 0 (layer stack): the input rows are still in pieces -- the previous layer's down projection left
     // `in_splits` split-K slices in the workspace and its residual in z -- and are formed (and stored to x_in) by
@@ -783,6 +791,7 @@ icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const
                                                           nullptr, rm, T, nullptr, 0, st));
     }
     int qkv_splits = 0, o_splits = 0;
+    bool appended = false;
     {   // Q (ICaRusLinear) and the encoder's K, V in one GEMM over [W_q; W_k; W_v]
         GemmArgs g{};
         g.X = xn; g.ldx = d; g.R = R; g.K = d;
@@ -796,9 +805,24 @@ icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const
             g.W[2] = W(ICARUS_PROJ_V); g.n_seg[2] = kvd; g.nseg = 3;
             g.Y = qkv; g.ldy = ldq;
         }
-        LORA_TRY(run_gemm(ctx, ws, L, ICARUS_PH_GEMM_QKV, g, st, &qkv_splits));
+        // A prefill call whose projection is a whole launch in tiles of k_gemm_quad writes q and the cache from there: the fp32 projections
+        // (403 MB of 16384 rows, out and in again) stay in the registers they are summed in.
+        if (slot_by_row && !kv_only && !lq && dm.D == 128 && dm.Bk == 16) {
+            const GemmPlan plan = plan_gemm(g, L, true);
+            if (gemm_qkv_fused(g, plan)) {
+                float *cs = qkv, *sn = cs + (size_t)R * 64;  // where the projections would be
+                int64_t *slot = slot_out ? slot_out : (int64_t *)(sn + (size_t)R * 64);
+                if (!rope_ready) PHASE(ctx, st, ICARUS_PH_ROPE_APPEND, launch_rope_table(dm, rm, bt, max_blocks, R, cs, sn, slot, st));
+                g.tile = plan.tile;
+                const QkvStore e{cs, sn, slot, q, pool, dm.qk_norm ? (const bf16_raw *)ctx->base.q_norm : nullptr,
+                                 dm.qk_norm ? (const bf16_raw *)ctx->base.k_norm : nullptr, dm.Hq, dm.Hkv, dm.kv8, dm.eps, dm.k_scale, dm.v_scale};
+                PHASE(ctx, st, ICARUS_PH_GEMM_QKV, launch_gemm_qkv(g, e, st));
+                appended = true;
+            }
+        }
+        if (!appended) LORA_TRY(run_gemm(ctx, ws, L, ICARUS_PH_GEMM_QKV, g, st, &qkv_splits));
     }
-    {   // split-K slices of the projection, if any were left, are summed by the RoPE kernel
+    if (!appended) {   // split-K slices of the projection, if any were left, are summed by the RoPE kernel
         const float *src = qkv_splits ? (const float *)(ws + L.gemm_part) : qkv;
         const size_t slice = (size_t)R * ldq;
         if (rm.n_rope_tiles > 0 && rope_tiles_supported(dm, ldq, slice))
@@ -1021,7 +1045,7 @@ bool layer_takes_slices(icarus_ctx *ctx, bool use_lora) {
 icarus_status run_layer(icarus_ctx *ctx, char *ws, const WsLayout &L, const RowMeta &rm, const HostPlan *hp, int R, bool use_lora, bool kv_only,
                         int slot_by_row, void *pool, const int32_t *bt, int max_blocks, const void *x_in, void *x_out,
                         int64_t *slot_out, hipStream_t st, const FullPlan *fp = nullptr, int in_splits = 0, int *out_splits = nullptr,
-                        const RowSubset *last = nullptr) {
+                        const RowSubset *last = nullptr, bool rope_ready = false) {
     if (out_splits) *out_splits = 0;
     if (use_lora && !kv_only && ctx->full_set) {  // decoder rows with private weights
         if (!fp || !layer_mfma_supported(ctx)) return fail(ctx, ICARUS_ERR_UNSUPPORTED, "private decoder weights need the matrix-core path");
@@ -1031,7 +1055,7 @@ icarus_status run_layer(icarus_ctx *ctx, char *ws, const WsLayout &L, const RowM
         bool lg = use_lora && has_lora(ctx, ICARUS_PROJ_GATE), lu = use_lora && has_lora(ctx, ICARUS_PROJ_UP);
         if (lg == lu)
             return run_layer_mfma(ctx, ws, L, rm, hp, R, use_lora, kv_only, slot_by_row, pool, bt, max_blocks, x_in, x_out, slot_out, st,
-                                  in_splits, out_splits, last);
+                                  in_splits, out_splits, last, rope_ready);
     }
     if (last) return fail(ctx, ICARUS_ERR_UNSUPPORTED, "a subset of rows needs the matrix-core path");
     if (in_splits > 0) return fail(ctx, ICARUS_ERR_UNSUPPORTED, "input rows in pieces need the matrix-core path");
@@ -1324,7 +1348,7 @@ icarus_status run_stack(icarus_stack *st, char *ws, const StackLayout &SL, const
         const bool head_takes_slices = (subset || (!head_rows && n_head == R)) && layer_mfma_supported(c0) && gemm_mfma_supported(dm, dm.d);
         const bool may_defer = l + 1 < st->layers.size() ? layer_takes_slices(st->layers[l + 1], decode) : head_takes_slices;
         icarus_status rc = run_layer(st->layers[l], ws, pr.L, pr.rm, &pr.hp, R, decode, false, decode ? 0 : 1, kv_pools[l], bt, max_blocks,
-                                     xa, xb, nullptr, s, &pr.fp, pending, may_defer ? &left : nullptr, subset && l + 1 == st->layers.size() ? &last : nullptr);
+                                     xa, xb, nullptr, s, &pr.fp, pending, may_defer ? &left : nullptr, subset && l + 1 == st->layers.size() ? &last : nullptr, l > 0);
         if (rc) return stack_fail(st, rc, st->layers[l]->err);
         pending = left;
         std::swap(xa, xb);

@@ -60,6 +60,9 @@ bool rope_tiles_pay(const Dims &dm, int rows, int n_tiles);
 hipError_t launch_rope_append_tiles(const Dims &dm, const float *qkv, int ldq, int splits, size_t slice, const RowMeta &rm,
                                     const int32_t *tiles, int n_tiles, bool kv_only, const int32_t *bt, int max_blocks, void *pool,
                                     void *q_out, int64_t *slot_out, const void *q_norm, const void *k_norm, hipStream_t st);
+// Cosines and sines [R][64] of the rows' angles and their slots [R], for launch_gemm_qkv.
+hipError_t launch_rope_table(const Dims &dm, const RowMeta &rm, const int32_t *bt, int max_blocks, int R, float *cs, float *sn, int64_t *slot,
+                             hipStream_t st);
 // out[row, h, :] = softmax(q[row,h,:] K^T / sqrt(D)) V over positions 0..row_kvlen[row]-1 of row_seq[row]
 hipError_t launch_attn_generic(const Dims &dm, const void *q, const void *pool, const int32_t *bt, int max_blocks,
                                const RowMeta &rm, void *out, int R, hipStream_t st);
@@ -171,6 +174,17 @@ __device__ __forceinline__ bool tile_of_workgroup(const GemmArgs &g, int *tile_m
     return tile_at(g, blockIdx.x, blockIdx.y, tile_m, tile_n, kz);
 }
 hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st);
+// QKV projection of encoder rows (head_dim 128, blocks of 16, no adapters) that normalises and rotates in its epilogue and writes q and
+// the cache itself; a whole launch in tiles of k_gemm_quad (gemm_qkv_fused).
+struct QkvStore {
+    const float *cs, *sn; const int64_t *slot;   // of each row, see launch_rope_table
+    bf16_raw *q; void *pool;
+    const bf16_raw *q_norm, *k_norm;             // null: no QK-norm
+    int Hq, Hkv, kv8; float eps, k_scale, v_scale;
+};
+bool gemm_qkv_fused(const GemmArgs &g, struct GemmPlan plan);
+hipError_t launch_gemm_qkv(GemmArgs g, const QkvStore &e, hipStream_t st);
+hipError_t launch_gemm_quad_qkv(const GemmArgs &g, const QkvStore &e, hipStream_t st);
 // How a GEMM is run: tile kind and split-K slices, at most max_splits (1 where K cannot be split: DUAL).  takes_slices: a
 // later kernel of the caller reads the slices as they are, no reduction is launched for them.
 struct GemmPlan { int tile, splits; };
