@@ -992,20 +992,8 @@ icarus_status run_layer_skinny(icarus_ctx *ctx, char *ws, const WsLayout &L, con
     auto lo = [&](int p) { return use_lora && has_lora(ctx, p); };
     auto A = [&](int p) { return lo(p) ? ctx->lora.A[p] : nullptr; };
     auto B = [&](int p) { return lo(p) ? ctx->lora.B[p] : nullptr; };
-    auto gemm = [&](int phase, int mode, const void *X, int K, int p0, int n0, int p1, int n1, int p2, int n2, const void *resid, void *Y,
-                    int ldy) -> icarus_status {
-        SkinnyGemm g{};
-        g.X = X; g.ldx = K; g.R = R; g.K = K; g.mode = mode; g.resid = resid; g.Y = Y; g.ldy = ldy;
-        const int p[3] = {p0, p1, p2}, n[3] = {n0, n1, n2};
-        for (int s = 0; s < 3; ++s)
-            if (p[s] >= 0) { g.W[s] = ctx->base.w[p[s]]; g.n[s] = n[s]; }
-        g.B[0] = B(p0); g.B[1] = mode == SKINNY_DUAL ? B(p1) : nullptr; g.t = t; g.row_model = rm.row_model;
-        PHASE(ctx, st, phase, launch_gemm_skinny(dm, g, st));
-        return ICARUS_OK;
-    };
     // norm + shrink of the projections that read the normalised rows: a target without an adapter leaves its half of t unused
-    auto row = [&](int phase, const void *x, int K, const void *wn, void *y, int p0, int p1) -> icarus_status {
-        const void *A0 = p0 >= 0 ? A(p0) : nullptr, *A1 = p1 >= 0 ? A(p1) : nullptr;
+    auto row = [&](int phase, const void *x, int K, const void *wn, void *y, const void *A0, const void *A1) -> icarus_status {
         if (!A0 && A1) {  // the second target alone: its t is the second half
             PHASE(ctx, st, phase, launch_row_generic(dm, x, K, K, wn, y, nullptr, nullptr, rm.row_model, t, R, st));
             PHASE(ctx, st, ICARUS_PH_LORA, launch_row_generic(dm, y, K, K, nullptr, nullptr, A1, nullptr, rm.row_model, t + (size_t)R * dm.r, R, st));
@@ -1014,21 +1002,39 @@ icarus_status run_layer_skinny(icarus_ctx *ctx, char *ws, const WsLayout &L, con
         PHASE(ctx, st, phase, launch_row_generic(dm, x, K, K, wn, y, A0, A1, rm.row_model, t, R, st));
         return ICARUS_OK;
     };
-    LORA_TRY(row(ICARUS_PH_NORM, x_in, d, ctx->base.norm_attn, xn, kv_only ? -1 : ICARUS_PROJ_Q, -1));
+    auto gemm = [&](int phase, int mode, const void *X, int K, int p0, int n0, int p1, int n1, int p2, int n2, const void *resid, void *Y,
+                    int ldy, const void *wn) -> icarus_status {
+        // The projection and, before it or in the same launch, what its rows still need: their norm and the shrink of its adapters
+        SkinnyGemm g{};
+        g.X = X; g.ldx = K; g.R = R; g.K = K; g.mode = mode; g.resid = resid; g.Y = Y; g.ldy = ldy;
+        const int p[3] = {p0, p1, p2}, n[3] = {n0, n1, n2};
+        for (int s = 0; s < 3; ++s)
+            if (p[s] >= 0) { g.W[s] = ctx->base.w[p[s]]; g.n[s] = n[s]; }
+        g.B[0] = B(p0); g.B[1] = mode == SKINNY_DUAL ? B(p1) : nullptr; g.t = t; g.row_model = rm.row_model;
+        const void *A0 = A(p0), *A1 = mode == SKINNY_DUAL ? A(p1) : nullptr;
+        if (mode == SKINNY_F32 && p2 < 0) A0 = nullptr;  // K and V alone
+        if (A0 || A1 || wn) {
+            g.wn = wn; g.A[0] = A0; g.A[1] = A1;
+            if (!skinny_takes_rows(dm, g)) {
+                g.wn = g.A[0] = g.A[1] = nullptr;
+                LORA_TRY(row(wn ? ICARUS_PH_NORM : ICARUS_PH_LORA, X, K, wn, wn ? xn : nullptr, A0, A1));
+                if (wn) g.X = xn;
+            }
+        }
+        PHASE(ctx, st, phase, launch_gemm_skinny(dm, g, st));
+        return ICARUS_OK;
+    };
     if (kv_only)  // K and V carry no adapter
-        LORA_TRY(gemm(ICARUS_PH_GEMM_QKV, SKINNY_F32, xn, d, ICARUS_PROJ_K, kvd, ICARUS_PROJ_V, kvd, -1, 0, nullptr, qkv + qd, ldq));
+        LORA_TRY(gemm(ICARUS_PH_GEMM_QKV, SKINNY_F32, x_in, d, ICARUS_PROJ_K, kvd, ICARUS_PROJ_V, kvd, -1, 0, nullptr, qkv + qd, ldq, ctx->base.norm_attn));
     else
-        LORA_TRY(gemm(ICARUS_PH_GEMM_QKV, SKINNY_F32, xn, d, ICARUS_PROJ_Q, qd, ICARUS_PROJ_K, kvd, ICARUS_PROJ_V, kvd, nullptr, qkv, ldq));
+        LORA_TRY(gemm(ICARUS_PH_GEMM_QKV, SKINNY_F32, x_in, d, ICARUS_PROJ_Q, qd, ICARUS_PROJ_K, kvd, ICARUS_PROJ_V, kvd, nullptr, qkv, ldq, ctx->base.norm_attn));
     PHASE(ctx, st, ICARUS_PH_ROPE_APPEND, launch_rope_append(dm, qkv, ldq, 1, 0, rm, bt, max_blocks, pool, q, slot_out, slot_by_row,
                                                              ctx->base.q_norm, ctx->base.k_norm, R, st));
     if (kv_only) return ICARUS_OK;
     LORA_TRY(run_decode_attention(ctx, ws, L, rm, hp, q, pool, bt, max_blocks, attn, R, st));
-    if (lo(ICARUS_PROJ_O)) LORA_TRY(row(ICARUS_PH_LORA, attn, qd, nullptr, nullptr, ICARUS_PROJ_O, -1));
-    LORA_TRY(gemm(ICARUS_PH_GEMM_O, SKINNY_RESID, attn, qd, ICARUS_PROJ_O, d, -1, 0, -1, 0, x_in, z, d));
-    LORA_TRY(row(ICARUS_PH_NORM, z, d, ctx->base.norm_ffn, xn, ICARUS_PROJ_GATE, ICARUS_PROJ_UP));
-    LORA_TRY(gemm(ICARUS_PH_GEMM_GATEUP, SKINNY_DUAL, xn, d, ICARUS_PROJ_GATE, F, ICARUS_PROJ_UP, F, -1, 0, nullptr, h, F));
-    if (lo(ICARUS_PROJ_DOWN)) LORA_TRY(row(ICARUS_PH_LORA, h, F, nullptr, nullptr, ICARUS_PROJ_DOWN, -1));
-    LORA_TRY(gemm(ICARUS_PH_GEMM_DOWN, SKINNY_RESID, h, F, ICARUS_PROJ_DOWN, d, -1, 0, -1, 0, z, x_out, d));
+    LORA_TRY(gemm(ICARUS_PH_GEMM_O, SKINNY_RESID, attn, qd, ICARUS_PROJ_O, d, -1, 0, -1, 0, x_in, z, d, nullptr));
+    LORA_TRY(gemm(ICARUS_PH_GEMM_GATEUP, SKINNY_DUAL, z, d, ICARUS_PROJ_GATE, F, ICARUS_PROJ_UP, F, -1, 0, nullptr, h, F, ctx->base.norm_ffn));
+    LORA_TRY(gemm(ICARUS_PH_GEMM_DOWN, SKINNY_RESID, h, F, ICARUS_PROJ_DOWN, d, -1, 0, -1, 0, z, x_out, d, nullptr));
     return ICARUS_OK;
 }
 

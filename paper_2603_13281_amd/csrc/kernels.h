@@ -77,7 +77,11 @@ struct SkinnyGemm {
     const int32_t *row_model;
     const void *resid; void *Y; int ldy;      // SKINNY_RESID: resid has the stride of Y
     int mode;
+    // In place of launch_row_generic before it, where skinny_takes_rows (else both null): the rows are rmsnorm(X) * wn (not of
+    // SKINNY_RESID), and t = lora_scale * A[model(row)] x of the targets that B names
+    const void *wn, *A[2];
 };
+bool skinny_takes_rows(const Dims &dm, const SkinnyGemm &g);
 hipError_t launch_gemm_skinny(const Dims &dm, const SkinnyGemm &g, hipStream_t st);
 // y = rmsnorm(x) * wn (wn != null) and, with A0, t[target][row][0..r) = lora_scale * A_target[model(row)] (y or x)
 hipError_t launch_row_generic(const Dims &dm, const void *x, int ldx, int K, const void *wn, void *y, const void *A0, const void *A1,

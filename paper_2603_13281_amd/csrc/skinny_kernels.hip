@@ -96,15 +96,23 @@ struct SkinnyArgs {
     const void *B[2]; const float *t; int r; // adapter of the first segment (DUAL: gate, up), t from k_row_generic; null: none
     const int32_t *row_model;
     const void *resid; void *Y; int ldy;     // SKINNY_F32: float Y; else storage Y (SKINNY_RESID: + resid, same stride)
+    const void *wn; float eps;               // NORM: the rows are rmsnorm(X) * wn
+    const void *A[2]; float scale;           // SHRINK: t = scale * A[model] x, computed here
 };
 
-template <typename T, typename V, int RM, int MODE>
+// The row kernel's work in the projection that reads its rows, where that is little: a launch of its own takes 2.4-3.2 us and the next
+// one's start.  NORM: every wave sums the squares of the rows that it multiplies anyway, and scales its sums.  SHRINK: wave w multiplies row w
+// with the up to eight rows of its model's A, in every workgroup, and the products meet in LDS.
+constexpr int kShrinkRank = 8;
+template <typename T, typename V, int RM, int MODE, bool NORM = false, bool SHRINK = false>
 __global__ void __launch_bounds__(256) k_gemm_skinny(SkinnyArgs a) {
     constexpr bool dual = MODE == SKINNY_DUAL;
+    constexpr int ND = dual ? 2 : 1;  // targets with adapters
+    __shared__ float ts[SHRINK ? ND * 4 * kShrinkRank : 1];
     constexpr int NO = dual ? kCols / 2 : kCols;  // output columns of a wave
     const int lane = threadIdx.x & 63, N = a.n_end[dual ? 0 : 2];
     const int n0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * NO;
-    if (n0 >= N) return;
+    if (!SHRINK && n0 >= N) return;
     const T *wrow[kCols];
 #pragma unroll
     for (int c = 0; c < kCols; ++c) {
@@ -120,11 +128,30 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(SkinnyArgs a) {
     constexpr int kShare = 64 / (kCols * RM);
     const int c = lane / kShare / RM, row = lane / kShare % RM, n = n0 + c;
     const bool mine = c < NO && row < a.R && n < N, first = mine && lane % kShare == 0;
-    const int j = mine && a.t && n < a.n_end[0] ? a.row_model[row] : -1;
+    const int j = mine && (SHRINK || a.t) && n < a.n_end[0] ? a.row_model[row] : -1;
     const T *X = (const T *)a.X;
     int k = lane * V::N;
-    typename V::Raw wv[kCols], xv[RM];
+    typename V::Raw wv[kCols], xv[RM], gv, av[ND][kShrinkRank], dv;
+    // SHRINK: this wave's row and its model's A; without one the products are those of a weight row, and dropped
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int model = SHRINK && wave < a.R ? a.row_model[wave] : -1;
+    const T *drow = X + (size_t)min(wave, a.R - 1) * a.ldx, *A[ND];
+    int astep[ND];
+#pragma unroll
+    for (int d = 0; d < ND; ++d) {
+        const bool has = SHRINK && model >= 0 && a.A[d];
+        A[d] = has ? (const T *)a.A[d] + (size_t)model * a.r * a.K : wrow[0];
+        astep[d] = has ? a.K : 0;
+    }
     auto load = [&] {
+        if constexpr (NORM) gv = ld_raw<V>((const T *)a.wn + k);
+        if constexpr (SHRINK) {
+#pragma unroll
+            for (int d = 0; d < ND; ++d)
+#pragma unroll
+                for (int i = 0; i < kShrinkRank; ++i) av[d][i] = ld_raw<V>(A[d] + (size_t)min(i, a.r - 1) * astep[d] + k);
+            dv = ld_raw<V>(drow + k);
+        }
 #pragma unroll
         for (int i = 0; i < kCols; ++i) wv[i] = ld_raw<V>(wrow[i] + k);
 #pragma unroll
@@ -134,7 +161,14 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(SkinnyArgs a) {
     // what is added to the sum is fetched beneath the first pieces
     float res = 0.f, delta[2] = {0.f, 0.f};
     if (MODE == SKINNY_RESID && first) res = Elem<T>::ld((const T *)a.resid + (size_t)row * a.ldy + n);
-    if (j >= 0) {
+    float bv[2][kShrinkRank];
+    if constexpr (SHRINK) {
+#pragma unroll
+        for (int d = 0; d < ND; ++d)
+#pragma unroll
+            for (int i = 0; i < kShrinkRank; ++i)
+                bv[d][i] = a.B[d] ? Elem<T>::ld((const T *)a.B[d] + ((size_t)max(j, 0) * a.n_end[0] + min(n, a.n_end[0] - 1)) * a.r + min(i, a.r - 1)) : 0.f;
+    } else if (j >= 0) {
 #pragma unroll
         for (int d = 0; d < (dual ? 2 : 1); ++d) {
             const T *b = (const T *)a.B[d];
@@ -150,11 +184,38 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(SkinnyArgs a) {
     float acc[kCols * RM];
 #pragma unroll
     for (int i = 0; i < kCols * RM; ++i) acc[i] = 0.f;
+    float ss[RM], dot[ND * kShrinkRank];
+#pragma unroll
+    for (int m = 0; m < RM; ++m) ss[m] = 0.f;
+#pragma unroll
+    for (int i = 0; i < ND * kShrinkRank; ++i) dot[i] = 0.f;
     while (k < a.K) {
+        float gf[V::N];
+        if constexpr (NORM) V::un(gv, gf);
+        if constexpr (SHRINK) {
+            float xf[V::N];
+            V::un(dv, xf);
+#pragma unroll
+            for (int e = 0; e < V::N; ++e) xf[e] = NORM ? xf[e] * gf[e] : xf[e];
+#pragma unroll
+            for (int i = 0; i < ND * kShrinkRank; ++i) {
+                float af[V::N];
+                V::un(av[i / kShrinkRank][i % kShrinkRank], af);
+#pragma unroll
+                for (int e = 0; e < V::N; ++e) dot[i] += af[e] * xf[e];
+            }
+        }
 #pragma unroll
         for (int m = 0; m < RM; ++m) {
             float xf[V::N];
             V::un(xv[m], xf);
+            if constexpr (NORM) {
+#pragma unroll
+                for (int e = 0; e < V::N; ++e) {
+                    ss[m] += xf[e] * xf[e];
+                    xf[e] *= gf[e];
+                }
+            }
 #pragma unroll
             for (int i = 0; i < kCols; ++i) {
                 float wf[V::N];
@@ -166,7 +227,26 @@ __global__ void __launch_bounds__(256) k_gemm_skinny(SkinnyArgs a) {
         k += 64 * V::N;
         if (k < a.K) load();
     }
-    float sum = wave_sums(acc, lane), up = 0.f;
+    float sum = wave_sums(acc, lane), up = 0.f, inv = 1.f;
+    if constexpr (NORM) {
+        inv = rsqrtf(wave_sums(ss, lane) / (float)a.K + a.eps);  // of row lane / (64 / RM)
+        sum *= __shfl(inv, row * (64 / RM), 64);
+    }
+    if constexpr (SHRINK) {
+        constexpr int kLanes = 64 / (ND * kShrinkRank);  // that hold the sum of one product
+        const int d = lane / kLanes / kShrinkRank, i = lane / kLanes % kShrinkRank;
+        float v = wave_sums(dot, lane) * a.scale;
+        if constexpr (NORM) v *= __shfl(inv, wave * (64 / RM), 64);
+        if (lane % kLanes == 0) ts[(d * 4 + wave) * kShrinkRank + i] = v;
+        __syncthreads();
+        if (j >= 0) {
+#pragma unroll
+            for (int d = 0; d < ND; ++d)
+#pragma unroll
+                for (int x = 0; x < kShrinkRank; ++x)
+                    if (x < a.r && a.A[d]) delta[d] += bv[d][x] * ts[(d * 4 + row) * kShrinkRank + x];
+        }
+    }
     if (dual) up = __shfl_xor(sum, 32, 64) + delta[1];  // the upper half of the lanes holds the up projection
     sum += delta[0];
     if (!first) return;
@@ -203,6 +283,23 @@ hipError_t launch_row_generic(const Dims &dm, const void *x, int ldx, int K, con
     });
 }
 
+// float32 rows of whole 16-byte pieces (in bf16 the projection reads the normalised rows as rounded), with adapters up to four of them, a
+// wave each.  Beyond some width what every workgroup does again outweighs the launch, the sooner the more rows there are.  A layer step with
+// adapters on q and o, FFN 2.7 times as wide, us, row kernels / fused: 3 rows, 256 columns 46.5 / 36.0, 512 45.1 / 35.1, 1024 52.4 / 43.3, 2048
+// 88.7 / 73.0; 12 rows (norm alone) 46.4 / 42.9, 52.1 / 50.3, 72.8 / 75.5, 117 / 125.
+constexpr int kFusedColumns = 2048, kFusedColumnsMoreRows = 512;
+bool skinny_takes_rows(const Dims &dm, const SkinnyGemm &g) {
+    const bool shrink = g.A[0] || g.A[1];
+    if (dm.bf16 || g.K > (g.R <= 4 ? kFusedColumns : kFusedColumnsMoreRows) || !whole_pieces(dm, g.K) || !whole_pieces(dm, g.ldx) || !aligned16(g.X) || (g.wn && !aligned16(g.wn))) return false;
+    for (int s = 0; s < 3; ++s)
+        if (g.W[s] && !aligned16(g.W[s])) return false;
+    if ((g.mode == SKINNY_RESID) != !g.wn) return false;
+    if (!shrink) return g.wn != nullptr;
+    for (int d = 0; d < 2; ++d)
+        if (g.A[d] && !aligned16(g.A[d])) return false;
+    return g.R <= 4 && dm.r <= kShrinkRank;
+}
+
 hipError_t launch_gemm_skinny(const Dims &dm, const SkinnyGemm &g, hipStream_t st) {
     if (g.R <= 0) return hipSuccess;
     if (g.R > kSkinnyRows) return hipErrorInvalidValue;
@@ -217,11 +314,32 @@ hipError_t launch_gemm_skinny(const Dims &dm, const SkinnyGemm &g, hipStream_t s
         if (!dual) end += g.n[s];
         a.n_end[s] = dual ? g.n[0] : end;
     }
-    a.B[0] = g.B[0]; a.B[1] = g.B[1]; a.t = (g.B[0] || g.B[1]) ? g.t : nullptr; a.r = dm.r; a.row_model = g.row_model;
+    a.B[0] = g.B[0]; a.B[1] = g.B[1]; a.t = !g.A[0] && !g.A[1] && (g.B[0] || g.B[1]) ? g.t : nullptr; a.r = dm.r; a.row_model = g.row_model;
     a.resid = g.resid; a.Y = g.Y; a.ldy = g.ldy;
+    a.wn = g.wn; a.eps = dm.eps; a.A[0] = g.A[0]; a.A[1] = g.A[1]; a.scale = dm.lora_scale;
+    const bool shrink = g.A[0] || g.A[1];
     const int N = a.n_end[dual ? 0 : 2], per_wg = 4 * (dual ? kCols / 2 : kCols);
     if (N <= 0) return hipSuccess;
     const dim3 grid((N + per_wg - 1) / per_wg);
+    if (g.wn || shrink) {
+        if (!skinny_takes_rows(dm, g) || !vec) return hipErrorInvalidValue;
+        auto rows = [&](auto rm, auto with_shrink) {
+            constexpr int RM = decltype(rm)::value;
+            constexpr bool SH = decltype(with_shrink)::value;
+            switch (g.mode) {
+            case SKINNY_F32: hipLaunchKernelGGL((k_gemm_skinny<float, Vec16<float>, RM, SKINNY_F32, true, SH>), grid, dim3(256), 0, st, a); break;
+            case SKINNY_RESID:
+                if constexpr (SH) hipLaunchKernelGGL((k_gemm_skinny<float, Vec16<float>, RM, SKINNY_RESID, false, true>), grid, dim3(256), 0, st, a);
+                break;
+            default: hipLaunchKernelGGL((k_gemm_skinny<float, Vec16<float>, RM, SKINNY_DUAL, true, SH>), grid, dim3(256), 0, st, a); break;
+            }
+            return hipGetLastError();
+        };
+        if (shrink) return rows(std::integral_constant<int, 4>(), std::true_type());
+        if (g.R <= 4) return rows(std::integral_constant<int, 4>(), std::false_type());
+        if (g.R <= 8) return rows(std::integral_constant<int, 8>(), std::false_type());
+        return rows(std::integral_constant<int, 16>(), std::false_type());
+    }
     return with_type(dm.bf16, vec, [&](auto tt, auto vv) {
         typedef decltype(tt) T;
         typedef decltype(vv) V;

@@ -1,0 +1,39 @@
+"""Steps of a few float32 rows: norm and adapter shrink inside the projections (up to four rows, rank 8, 2048 columns; the norm alone up to 512
+columns) and in row kernels before them, on both sides of each line, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import dev, host, make_layer, pool_to_device_layout
+from helpers import assert_close, filled_batch, oracle_config
+from paper_2603_13281_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+MASKS = {"none": 0, "all": 0b1111001, "gate": 0b0010000, "up": 0b0100000, "q-down": 0b1000001}  # bits in the order of synth.PROJ: q k v o gate up down
+
+
+@pytest.mark.parametrize("mask", MASKS)
+@pytest.mark.parametrize("rank", [1, 8, 9])
+@pytest.mark.parametrize("width", [256, 516, 2052, 250])
+@pytest.mark.parametrize("active", [[[0], [1]], [[], [], [1, 0]], [[0, 1], [1], []]], ids=["4 rows", "5 rows", "6 rows"])
+def test_few_rows(mask, rank, width, active):
+    print("case: few rows", mask, rank, width, len(active), flush=True)
+    shape = synth.TINY.replace(d_model=width, d_ffn=108, lora_rank=rank, lora_target_mask=MASKS[mask])
+    base, lora = synth.make_base(shape, seed=6, norm_ones=False), synth.make_lora(shape, seed=6)
+    lens = [9, 40, 17][:len(active)]
+    batch = synth.make_batch(shape, lens, [0] * len(lens), seed=6)
+    pool = filled_batch(shape, batch, seed=6)
+    seq, model = [], []
+    for s, act in enumerate(active):
+        seq += [s] * (1 + len(act))
+        model += [-1] + act
+    x = synth.make_hidden(shape, len(seq), seed=6)
+    want_pool = pool.copy()
+    want, _ = oracle.Oracle(oracle_config(shape, batch.num_blocks), base, lora).decode_step(want_pool, batch.block_tables, lens, seq, model, x)
+    layer = make_layer(shape, base, lora, batch.num_blocks)
+    got = layer.decode_step(dev(pool_to_device_layout(pool), False), torch.from_numpy(batch.block_tables).cuda(), lens, np.asarray(seq, np.int32),
+                            np.asarray(model, np.int32), dev(x, False))
+    torch.cuda.synchronize()
+    assert_close(host(got), want, 1e-5, "x_out")
