@@ -360,6 +360,12 @@ bool gemm_staggered(const GemmArgs &g) { return g.K % 2048 == 0 && g.R <= 384; }
 
 bool is_quad(int kind) { return kind >= TILE_192x128; }
 
+// Launches of gemm_quad.hip: 128 x 128 tiles too where there is more than one row tile.  A single one waits for its weights and takes the deeper
+// ring of k_gemm_mfma, as do groups of rows.
+bool in_quadrants(const GemmArgs &g, int tile) {
+    return std::max(g.K, g.ldx) <= kQuadMaxK && (is_quad(tile) || (tile == TILE_128 && g.R > 128 && !g.row_tiles));
+}
+
 int k_ext_of(const GemmArgs &g) {
     if (g.mode == GEMM_DUAL) return g.K + (g.T ? 2 * g.M_models * g.r : 0);
     return g.K + ((g.T && g.B[0]) ? g.M_models * g.r : 0);
@@ -555,7 +561,7 @@ hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st) {
     const int cols = g.K_ext - g.K;
     if (g.tile == TILE_192x128 && !g.row_tiles && g.mode == GEMM_PLAIN && g.R > 160 * ((g.R + 191) / 192) && cols >= 256 && g.K <= 64 * cols)
         return launch_cfg<192, 128, 64, 3, 2, 2>(g, st);
-    if (is_quad(g.tile)) return launch_gemm_quad(g, st);
+    if (in_quadrants(g, g.tile)) return launch_gemm_quad(g, st);
     switch (g.tile) {
     case TILE_64x128: return g.row_tiles ? launch_cfg<64, 128, 64, 3, 2, 2, true>(g, st) : launch_cfg<64, 128, 64, 3, 2, 2>(g, st);
     case TILE_128: return g.row_tiles ? launch_cfg<128, 128, 64, 4, 2, 2, true>(g, st) : launch_cfg<128, 128, 64, 4, 2, 2>(g, st);
@@ -564,7 +570,7 @@ hipError_t launch_gemm_mfma(GemmArgs g, hipStream_t st) {
 }
 
 bool gemm_qkv_fused(const GemmArgs &g, GemmPlan plan) {
-    return plan.splits == 1 && is_quad(plan.tile) && std::max(g.K, g.ldx) <= kQuadMaxK && g.nseg == 3 && !g.T && !g.row_tiles;
+    return plan.splits == 1 && in_quadrants(g, plan.tile) && g.nseg == 3 && !g.T && !g.row_tiles;
 }
 hipError_t launch_gemm_qkv(GemmArgs g, const QkvStore &e, hipStream_t st) {
     if (g.R <= 0) return hipSuccess;

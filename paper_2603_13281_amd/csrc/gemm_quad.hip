@@ -45,10 +45,12 @@ __device__ __forceinline__ void dma16_at(const void *base, uint32_t off, uint32_
 template <int V> struct Int { static constexpr int value = V; };
 
 // MT0, MT1: 16-row tiles of a wave in the two halves of its rows
-template <int MT0, int MT1, int WAVES_N>
+template <int MT0, int MT1, int WAVES_N, int WAVES_M>
 struct QuadShape {
-    static constexpr int BM = 32 * (MT0 + MT1), BN = 64 * WAVES_N, BK = 64;
-    static constexpr int kXStage = BM * BK * 2, kWStage = BN * BK * 2, kLds = 2 * (kXStage + kWStage);  // LDS: two stages of X, two of W
+    static constexpr int BM = 16 * WAVES_M * (MT0 + MT1), BN = 64 * WAVES_N, BK = 64;
+    static constexpr int kXStage = BM * BK * 2, kWStage = BN * BK * 2, kStages = 2 * (kXStage + kWStage);  // LDS: two stages of X, two of W,
+    static constexpr int kScratch = WAVES_M * WAVES_N * 32 * 72 * 4;                                          // then the epilogue's scratch
+    static constexpr int kLds = kStages > kScratch ? kStages : kScratch;
 };
 
 // Epilogue of the QKV projection: a head is the columns of two neighbouring waves, which meet in LDS 32 rows at a time.  Of a q or k
@@ -198,15 +200,15 @@ __device__ __forceinline__ void store_qkv_tile(const GemmArgs &g, const QkvStore
 }
 
 // e: the epilogue's arguments where it is that of the QKV projection (QKV), else null
-template <int MT0, int MT1, int WAVES_N, bool GROUPED, bool QKV>
+template <int MT0, int MT1, int WAVES_N, int WAVES_M, bool GROUPED, bool QKV>
 __device__ __forceinline__ void quad_tile(const GemmArgs &g, const QkvStore *e) {
-    using Shape = QuadShape<MT0, MT1, WAVES_N>;
-    constexpr int NW = 2 * WAVES_N, BM = Shape::BM, BN = Shape::BN, BK = Shape::BK;
-    constexpr int WM = BM / 2, WN = 64, NT = 2, KS = BK / 32;
+    using Shape = QuadShape<MT0, MT1, WAVES_N, WAVES_M>;
+    constexpr int NW = WAVES_M * WAVES_N, BM = Shape::BM, BN = Shape::BN, BK = Shape::BK;
+    constexpr int WM = BM / WAVES_M, WN = 64, NT = 2, KS = BK / 32;
     constexpr int kRow = BK * 2;                          // bytes of a tile row in LDS
     constexpr int kXStage = Shape::kXStage, kWStage = Shape::kWStage, kBOff = 2 * kXStage;
-    constexpr int LDW = 2, LDX0 = 4 * MT0 / NW, LDX1 = 4 * MT1 / NW;        // loads of a wave for a half of W, for the halves of X;
-    constexpr bool kOdd0 = 4 * MT0 % NW != 0, kOdd1 = 4 * MT1 % NW != 0;    // an odd number of row tiles leaves four units over
+    constexpr int LDW = 4 / WAVES_M, LDX0 = 2 * MT0 / WAVES_N, LDX1 = 2 * MT1 / WAVES_N;        // loads of a wave for a half of W, for the halves of X;
+    constexpr bool kOdd0 = 2 * MT0 % WAVES_N != 0, kOdd1 = 2 * MT1 % WAVES_N != 0;    // an odd number of row tiles leaves four units over
     constexpr int kPair0 = LDW + LDX0, kPair1 = LDW + LDX1;                   // loads of a wave in the first, the second two phases of a slab: at least
     constexpr int kSlab = kPair0 + kPair1 + (kOdd0 && kOdd1 ? 1 : 0);
     extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -290,7 +292,7 @@ __device__ __forceinline__ void quad_tile(const GemmArgs &g, const QkvStore *e) 
     const int turn = kTurns ? gemm_turn(g, tile_n, n_base) : 0;
     auto place_of = [&](int kt) { return kTurns ? gemm_slab(kt, turn, n_base) : kt; };
     // part: 0, 1 the halves of X; 2, 3 those of W
-    auto part_lds = [&](int P, int S) { return P >= 2 ? kBOff + S * kWStage + (P & 1) * (kWStage / 2) : S * kXStage + P * (32 * MT0 * kRow); };
+    auto part_lds = [&](int P, int S) { return P >= 2 ? kBOff + S * kWStage + (P & 1) * (kWStage / 2) : S * kXStage + P * (16 * WAVES_M * MT0 * kRow); };
     // load i of a part, of the slab of base weights at place kt along K (gemm_slab)
     auto load_one = [&](auto Part, auto Stage, int kt, int i) {
         constexpr int P = decltype(Part)::value, S = decltype(Stage)::value;
@@ -424,22 +426,24 @@ __device__ __forceinline__ void quad_tile(const GemmArgs &g, const QkvStore *e) 
         }
     }
     __syncthreads();  // every wave has left the K loop: the stages are the epilogue's scratch
-    static_assert(NW * 32 * (WN + 8) * 4 <= Shape::kLds, "epilogue scratch must fit the stages");
+    static_assert(NW * 32 * (WN + 8) * 4 <= Shape::kLds, "epilogue scratch must fit");
     if constexpr (QKV) store_qkv_tile<MT0 + MT1, BN>(g, *e, acc, (float *)smem, w, wn, tile_n, row0 + wm * WM, row_end);
     else store_wave_tile<16, MT0 + MT1, 2 * NT, BN>(g, acc, (float *)smem + w * 32 * (WN + 8), tile_n, kz, row0 + wm * WM, row_end, wn);
 }
 
-template <int MT0, int MT1, int WAVES_N, bool GROUPED>
-__global__ void __launch_bounds__(128 * WAVES_N, WAVES_N == 4 ? 1 : 2) k_gemm_quad(GemmArgs g) { quad_tile<MT0, MT1, WAVES_N, GROUPED, false>(g, nullptr); }
-
-template <int MT0, int MT1, int WAVES_N>
-__global__ void __launch_bounds__(128 * WAVES_N, WAVES_N == 4 ? 1 : 2) k_gemm_quad_qkv(GemmArgs g, QkvStore e) {
-    quad_tile<MT0, MT1, WAVES_N, false, true>(g, &e);
+template <int MT0, int MT1, int WAVES_N, int WAVES_M, bool GROUPED>
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, WAVES_M * WAVES_N == 8 ? 1 : 2) k_gemm_quad(GemmArgs g) {
+    quad_tile<MT0, MT1, WAVES_N, WAVES_M, GROUPED, false>(g, nullptr);
 }
 
-template <int MT0, int MT1, int WAVES_N, bool GROUPED>
+template <int MT0, int MT1, int WAVES_N, int WAVES_M>
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, WAVES_M * WAVES_N == 8 ? 1 : 2) k_gemm_quad_qkv(GemmArgs g, QkvStore e) {
+    quad_tile<MT0, MT1, WAVES_N, WAVES_M, false, true>(g, &e);
+}
+
+template <int MT0, int MT1, int WAVES_N, bool GROUPED, int WAVES_M = 2>
 hipError_t launch_quad(GemmArgs g, hipStream_t st, const QkvStore *e = nullptr) {
-    using Shape = QuadShape<MT0, MT1, WAVES_N>;
+    using Shape = QuadShape<MT0, MT1, WAVES_N, WAVES_M>;
     constexpr int BM = Shape::BM, BN = Shape::BN;
     g.m_tiles = GROUPED ? g.n_row_tiles : (g.R + BM - 1) / BM;
     g.n_tiles = 0;
@@ -451,27 +455,34 @@ hipError_t launch_quad(GemmArgs g, hipStream_t st, const QkvStore *e = nullptr) 
             g.n_tiles += g.tiles_seg[s];
         }
     }
-    gemm_set_panels(&g, BM, BN, WAVES_N == 4 ? 1 : 2);
+    gemm_set_panels(&g, BM, BN, WAVES_M * WAVES_N == 8 ? 1 : 2);
     dim3 grid(gemm_grid(g));
     if constexpr (!GROUPED)
         if (e) {
             static bool qkv_set = false;
             if (!qkv_set) {
-                hipError_t rc = hipFuncSetAttribute((const void *)k_gemm_quad_qkv<MT0, MT1, WAVES_N>, hipFuncAttributeMaxDynamicSharedMemorySize, Shape::kLds);
+                hipError_t rc = hipFuncSetAttribute((const void *)k_gemm_quad_qkv<MT0, MT1, WAVES_N, WAVES_M>, hipFuncAttributeMaxDynamicSharedMemorySize, Shape::kLds);
                 if (rc != hipSuccess) return rc;
                 qkv_set = true;
             }
-            hipLaunchKernelGGL((k_gemm_quad_qkv<MT0, MT1, WAVES_N>), grid, dim3(128 * WAVES_N), Shape::kLds, st, g, *e);
+            hipLaunchKernelGGL((k_gemm_quad_qkv<MT0, MT1, WAVES_N, WAVES_M>), grid, dim3(64 * WAVES_M * WAVES_N), Shape::kLds, st, g, *e);
             return hipGetLastError();
         }
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t rc = hipFuncSetAttribute((const void *)k_gemm_quad<MT0, MT1, WAVES_N, GROUPED>, hipFuncAttributeMaxDynamicSharedMemorySize, Shape::kLds);
+        hipError_t rc = hipFuncSetAttribute((const void *)k_gemm_quad<MT0, MT1, WAVES_N, WAVES_M, GROUPED>, hipFuncAttributeMaxDynamicSharedMemorySize, Shape::kLds);
         if (rc != hipSuccess) return rc;
         attr_set = true;
     }
-    hipLaunchKernelGGL((k_gemm_quad<MT0, MT1, WAVES_N, GROUPED>), grid, dim3(128 * WAVES_N), Shape::kLds, st, g);
+    hipLaunchKernelGGL((k_gemm_quad<MT0, MT1, WAVES_N, WAVES_M, GROUPED>), grid, dim3(64 * WAVES_M * WAVES_N), Shape::kLds, st, g);
     return hipGetLastError();
+}
+
+int gemm_col_tiles(const GemmArgs &g, int bn) {
+    if (g.mode == GEMM_DUAL) return (2 * g.n_seg[0] + bn - 1) / bn;
+    int n = 0;
+    for (int s = 0; s < g.nseg; ++s) n += (g.n_seg[s] + bn - 1) / bn;
+    return n;
 }
 
 hipError_t launch_any(const GemmArgs &g, const QkvStore *e, hipStream_t st) {
@@ -481,10 +492,20 @@ hipError_t launch_any(const GemmArgs &g, const QkvStore *e, hipStream_t st) {
         // As many lower tiles, if they hold the rows: no MFMAs for padding (316 rows in tiles of 192 / 160: 14336 -> 4096 in 4
         // slices 54.4 / 53.5 us, 4096 -> 4096 28.5 / 26.7; 144 rows, 8192 -> 5120 in 6 slices 34.4 / 32.2)
         const int tiles = (g.R + 191) / 192;
+        // Eight waves in place of four where a workgroup has its CU to itself: two waves a SIMD, each half as high, hide each other's
+        // reads and barriers for a third more of those reads.  us: QKV of 753 rows (192 workgroups) 58.4 / 54.6, of 512 rows x 10240 (240) 68.7 / 67.3,
+        // 360 rows, 4096 -> 4096 in 4 slices 24.6 / 22.7, 14336 -> 4096 53.7 / 52.7.
+        const int cols = gemm_col_tiles(g, 128);
+        if (tiles * cols * g.splits <= 256) {
+            if (g.R <= 128 * tiles) return launch_quad<1, 1, 2, false, 4>(g, st, e);
+            if (g.R > 160 * tiles) return launch_quad<2, 1, 2, false, 4>(g, st, e);
+        }
         if (g.R <= 128 * tiles) return launch_quad<2, 2, 2, false>(g, st, e);
         return g.R <= 160 * tiles ? launch_quad<3, 2, 2, false>(g, st, e) : launch_quad<3, 3, 2, false>(g, st, e);
     }
     case TILE_256x256: return g.row_tiles ? launch_quad<4, 4, 4, true>(g, st) : launch_quad<4, 4, 4, false>(g, st, e);
+    // 753 rows, 4096 -> 4096, in k_gemm_mfma / here with four waves / with eight 45.7 / 45.5 / 43.1 us
+    case TILE_128: return launch_quad<1, 1, 2, false, 4>(g, st, e);
     case TILE_192x256: return launch_quad<3, 3, 4, false>(g, st, e);
     case TILE_160x256: return launch_quad<3, 2, 4, false>(g, st, e);
     default: return hipErrorInvalidValue;

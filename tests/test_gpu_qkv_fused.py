@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = {"plain": synth.LLAMA8B.replace(d_ffn=512), "norms": synth.QWEN32B.replace(d_ffn=512)}
 # rows -> the projection's tile; chunks whose rows begin and end anywhere in a block of 16 tokens, in a tile and in a group of 32 rows
-CASES = [("plain", 700, (192, 128)), ("plain", 780, (192, 128)), ("plain", 1003, (160, 256)), ("plain", 1701, (192, 256)), ("plain", 2011, (256, 256)),
+CASES = [("plain", 500, (128, 128)), ("norms", 300, (128, 128)), ("plain", 700, (192, 128)), ("plain", 780, (192, 128)), ("plain", 1003, (160, 256)), ("plain", 1701, (192, 256)), ("plain", 2011, (256, 256)),
          ("norms", 400, (192, 128)), ("norms", 601, (160, 256)), ("norms", 1001, (192, 256)), ("norms", 1203, (256, 256))]
 
 
