@@ -322,8 +322,8 @@ hipError_t launch_cfg(GemmArgs g, hipStream_t st) {
 }
 
 // Tile shapes: rows x weight rows of a workgroup, all with 64-wide K slabs (32-wide slabs ask for every 128-byte line of
-// a weight row twice, half each time, and stream at about 60 % of the rate).  The first two are k_gemm_mfma, the
-// others k_gemm_quad (192 x 128: gemm_quad.hip may take lower tiles, and see launch_gemm_mfma).  first_us: what a workgroup takes apart from its slabs (start, first slab, epilogue); slab_us: a slab
+// a weight row twice, half each time, and stream at about 60 % of the rate).  The first two are k_gemm_mfma (128 x 128 of more than
+// one row tile: k_gemm_quad, see in_quadrants), the others k_gemm_quad (192 x 128: gemm_quad.hip may take lower tiles, and see launch_gemm_mfma).  first_us: what a workgroup takes apart from its slabs (start, first slab, epilogue); slab_us: a slab
 // with every CU busy, for each of the per_cu workgroups that share one.  The figures are a fit to 5000 timings on
 // this GPU (80-4337 rows x the projections of a Llama-3-8B- and a Qwen3-32B-shaped layer x every tile x 1-12 slices; the
 // fit is 7-11 % off on average), see gemm_plan and gemm_row_tile.  They are of the kernels before k_gemm_quad, and

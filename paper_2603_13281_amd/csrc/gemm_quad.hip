@@ -1,9 +1,10 @@
 // ICaRusLinear (see gemm_mfma.hip) for more than 128 rows: tiles of 256 weight rows x 256, 192 or 160 stacked rows, for the
-// projections of a prefill chunk and the wide ones of a decode batch, and of 128 x 192, 160 or 128 for the narrow ones.
+// projections of a prefill chunk and the wide ones of a decode batch, and of 128 x 192, 160 or 128 for the narrow ones.  Below: the
+// epilogue of the QKV projection, which appends to the cache.
 //
-// Bound: the matrix cores, and the power they draw.  Eight waves sit 2 x 4 over a wide tile, four 2 x 2 over a narrow one, which
-// leaves room for a second workgroup on its CU; a wave owns (BM / 2) x 64 outputs in
-// 16x16x32 bf16 MFMAs.  K advances 64 columns (whole 128-byte lines of every row) at a time through two LDS stages filled by
+// Bound: the matrix cores, and the power they draw.  Eight waves sit 2 x 4 over a wide tile; over a narrow one four sit 2 x 2, which
+// leaves room for a second workgroup on its CU, or eight 4 x 2 where there is none (see launch_any); a wave owns (BM / 2) x 64 outputs, or
+// (BM / 4) x 64, in 16x16x32 bf16 MFMAs.  K advances 64 columns (whole 128-byte lines of every row) at a time through two LDS stages filled by
 // LDS-direct loads.  What a slab's loads get is time: with the fragments read K step by K step, as in gemm_mfma.hip, every
 // part of a stage is in use until the last step, and a load has three quarters of a slab to arrive; measured at 16384 x 28672 x
 // 4096 the 256 x 256 loop waited for its loads more than for anything else (matrix pipe busy 64 % of the cycles).  Here a wave

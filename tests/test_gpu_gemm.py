@@ -128,6 +128,18 @@ def test_lower_tiles_where_as_many_hold_the_rows(rows):
     _check(binding.gemm(x, w, (192, 128, False), fused=True), silu * u, bound, (rows, "fused"))
 
 
+@pytest.mark.parametrize("rows", [384, 576])
+@pytest.mark.parametrize("cols", [85, 86])
+def test_narrow_tiles_by_eight_waves_and_by_four(rows, cols):
+    # three row tiles of 128 or 192: up to 256 workgroups have a CU to themselves and eight waves, more share one with four each
+    print("case: waves of a narrow tile", rows, cols, flush=True)
+    k, n, models, rank = 64 * 9, 128 * cols - 56, 3, 16
+    x, w = _draw((rows, k), 1), _draw((n, k), 10, 0.05)
+    t, b = _adapters(rows, n, models, rank, 1, 20)
+    want, size = _product(x, w, t, b[0])
+    _check(binding.gemm(x, [w], (192, 128, False), t=t, b=b), want, (k + models * rank + 16) * 2.0 ** -23 * size + 1e-30, (rows, cols))
+
+
 @pytest.mark.parametrize("rows", [160, 161, 192, 193, 320, 321, 384, 480, 481])
 @pytest.mark.parametrize("k", [64 * 9, 64 * 257])
 def test_full_192_row_tiles_with_many_adapter_columns(rows, k):
