@@ -762,8 +762,9 @@ struct RowSubset {
 icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const RowMeta &rm, const HostPlan *hp, int R,
                              bool use_lora, bool kv_only, int slot_by_row, void *pool, const int32_t *bt, int max_blocks,
                              const void *x_in, void *x_out, int64_t *slot_out, hipStream_t st, int in_splits = 0,
-                             int *out_splits = nullptr, const RowSubset *last = nullptr, bool rope_ready = false) {
-    // rope_ready (layer stack): a layer of this call before left the rows' angles and slots where this one would put them.
+                             int *out_splits = nullptr, const RowSubset *last = nullptr, bool *rope_table = nullptr) {
+    // rope_table (layer stack): in, whether a layer of this call before left the rows' angles and slots where this one would put them; out,
+    // whether they are there now.  The other paths put projections in that place.
     // last != null (prefill): only these rows leave the layer, one after the other in x_out; of the others K and V are all that is asked for.
     // in_splits > 0 (layer stack): the input rows are still in pieces -- the previous layer's down projection left
     // `in_splits` split-K slices in the workspace and its residual in z -- and are formed (and stored to x_in) by
@@ -791,6 +792,7 @@ icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const
                                                           nullptr, rm, T, nullptr, 0, st));
     }
     int qkv_splits = 0, o_splits = 0;
+    const bool rope_ready = rope_table && *rope_table;
     bool appended = false;
     {   // Q (ICaRusLinear) and the encoder's K, V in one GEMM over [W_q; W_k; W_v]
         GemmArgs g{};
@@ -820,6 +822,7 @@ icarus_status run_layer_mfma(icarus_ctx *ctx, char *ws, const WsLayout &L, const
                 appended = true;
             }
         }
+        if (rope_table) *rope_table = appended;
         if (!appended) LORA_TRY(run_gemm(ctx, ws, L, ICARUS_PH_GEMM_QKV, g, st, &qkv_splits));
     }
     if (!appended) {   // split-K slices of the projection, if any were left, are summed by the RoPE kernel
@@ -1051,18 +1054,20 @@ bool layer_takes_slices(icarus_ctx *ctx, bool use_lora) {
 icarus_status run_layer(icarus_ctx *ctx, char *ws, const WsLayout &L, const RowMeta &rm, const HostPlan *hp, int R, bool use_lora, bool kv_only,
                         int slot_by_row, void *pool, const int32_t *bt, int max_blocks, const void *x_in, void *x_out,
                         int64_t *slot_out, hipStream_t st, const FullPlan *fp = nullptr, int in_splits = 0, int *out_splits = nullptr,
-                        const RowSubset *last = nullptr, bool rope_ready = false) {
+                        const RowSubset *last = nullptr, bool *rope_table = nullptr) {
     if (out_splits) *out_splits = 0;
     if (use_lora && !kv_only && ctx->full_set) {  // decoder rows with private weights
         if (!fp || !layer_mfma_supported(ctx)) return fail(ctx, ICARUS_ERR_UNSUPPORTED, "private decoder weights need the matrix-core path");
+        if (rope_table) *rope_table = false;
         return run_layer_full(ctx, ws, L, rm, hp, *fp, R, slot_by_row, pool, bt, max_blocks, x_in, x_out, slot_out, st);
     }
     if (layer_mfma_supported(ctx)) {
         bool lg = use_lora && has_lora(ctx, ICARUS_PROJ_GATE), lu = use_lora && has_lora(ctx, ICARUS_PROJ_UP);
         if (lg == lu)
             return run_layer_mfma(ctx, ws, L, rm, hp, R, use_lora, kv_only, slot_by_row, pool, bt, max_blocks, x_in, x_out, slot_out, st,
-                                  in_splits, out_splits, last, rope_ready);
+                                  in_splits, out_splits, last, rope_table);
     }
+    if (rope_table) *rope_table = false;
     if (last) return fail(ctx, ICARUS_ERR_UNSUPPORTED, "a subset of rows needs the matrix-core path");
     if (in_splits > 0) return fail(ctx, ICARUS_ERR_UNSUPPORTED, "input rows in pieces need the matrix-core path");
     if (R <= kSkinnyRows)
@@ -1341,6 +1346,7 @@ icarus_status run_stack(icarus_stack *st, char *ws, const StackLayout &SL, const
     // A layer whose down projection was split over K leaves its slices (and the residual) in the workspace when the
     // next layer can form its input rows from them: the separate reduction launch between two layers is saved.
     int pending = 0;
+    bool rope_table = false;  // a layer's kernel mode decides what it leaves: only the layer itself knows (run_layer_mfma)
     char *xg = ws + SL.xn, *xn = xg + (size_t)n_head * row_bytes;
     // Of a prompt's rows only the last of each chunk goes to the LM head, and the caches want K and V alone: what follows the attention of
     // the last layer is run for those rows only (4337 rows in 4 chunks, 4 layers: 6609 -> 5418 us).  With fewer than kLastRowsGain rows
@@ -1354,7 +1360,7 @@ icarus_status run_stack(icarus_stack *st, char *ws, const StackLayout &SL, const
         const bool head_takes_slices = (subset || (!head_rows && n_head == R)) && layer_mfma_supported(c0) && gemm_mfma_supported(dm, dm.d);
         const bool may_defer = l + 1 < st->layers.size() ? layer_takes_slices(st->layers[l + 1], decode) : head_takes_slices;
         icarus_status rc = run_layer(st->layers[l], ws, pr.L, pr.rm, &pr.hp, R, decode, false, decode ? 0 : 1, kv_pools[l], bt, max_blocks,
-                                     xa, xb, nullptr, s, &pr.fp, pending, may_defer ? &left : nullptr, subset && l + 1 == st->layers.size() ? &last : nullptr, l > 0);
+                                     xa, xb, nullptr, s, &pr.fp, pending, may_defer ? &left : nullptr, subset && l + 1 == st->layers.size() ? &last : nullptr, &rope_table);
         if (rc) return stack_fail(st, rc, st->layers[l]->err);
         pending = left;
         std::swap(xa, xb);

@@ -119,6 +119,40 @@ def test_prompt_whose_last_layer_keeps_one_row_of_each_chunk(prompt_lens, n_laye
         assert np.linalg.norm(got - want) <= 1e-2 * np.linalg.norm(want)
 
 
+@pytest.mark.parametrize("modes", [(0, 1, 0), (1, 0, 0), (0, 0, 1), (1, 0, 1, 0)], ids=lambda m: "".join(map(str, m)))
+@pytest.mark.parametrize("kind", ["norms", "fp8"])
+def test_prompt_through_layers_of_different_kernel_modes(kind, modes):
+    """Rows enough for the projection that appends by itself; its table of angles and slots stands where the layers of mode 1 put their
+    projections, so a layer may take it over from the one before it only if that one left it."""
+    from gpu_util import fp8_pool_to_float, pool_from_device_layout
+    from paper_2603_13281_amd import binding, synth
+    print("case: kernel modes", kind, modes, flush=True)
+    shape, vocab, tol = synth.QWEN_SMALL if kind == "norms" else synth.LLAMA_SMALL, 512, 2e-2
+    scales = (0.02, 0.02) if kind == "fp8" else None
+    lens = np.array([149, 151], np.int32)
+    qd, kvd = shape.n_q_heads * 128, shape.n_kv_heads * 128
+    tile = binding.gemm_choice(int(lens.sum()), shape.d_model, [qd, kvd, kvd], taken=True)
+    assert tile[0] >= 128 and tile[3] == 1, tile  # several row tiles, one slice: the fused form
+    S, max_blocks = len(lens), int(lens.max()) // shape.block_size + 1
+    wts, orc, stack, pools = _build(shape, len(modes), vocab, S * max_blocks, seed=9, kv_scales=scales)
+    opools = orc.new_pools()
+    rng = np.random.default_rng(9)
+    bt = rng.permutation(S * max_blocks).reshape(S, max_blocks).astype(np.int32)
+    tokens = rng.integers(0, vocab, size=int(lens.sum())).astype(np.int32)
+    zeros = np.zeros(S, np.int32)
+    for layer, mode in zip(stack.layers, modes):
+        layer.set_kernel_mode(mode)
+    nxt, lg = stack.prefill(pools, torch.from_numpy(bt).to("cuda:0"), zeros, lens, tokens, want_logits=True)
+    want_lg, _ = orc.prefill(opools, bt, zeros, lens, tokens)
+    torch.cuda.synchronize()
+    _check_tokens(nxt.cpu().numpy(), lg.cpu().numpy().astype(np.float64), want_lg, tol, f"modes {modes}")
+    for l, want in enumerate(opools):
+        got = fp8_pool_to_float(pools[l], *scales) if scales else pools[l].float().cpu().numpy()
+        got = pool_from_device_layout(got, shape.block_size, shape.head_dim)
+        # FP8: a code rounds to its neighbour, 2^-3 of its size away at most, for no more than one value in four
+        assert np.linalg.norm(got - want) <= (2.0 ** -4 if scales else 1e-2) * np.linalg.norm(want), l
+
+
 def test_stack_rejects_bad_arguments():
     from paper_2603_13281_amd import binding, synth
     shape = synth.TINY
