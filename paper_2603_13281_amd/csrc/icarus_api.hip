@@ -85,7 +85,7 @@ struct icarus_ctx {
     // over an FP8 cache, whose tokens cost half, 768.  Attention alone, us, at 768 / 512 / 384 / 256 tokens: 16 sequences of 500-8192 58.2 / 58.0 / 57.0 /
     // 56.0, 64 of 1024-16384 420 / 416.8 / 416.5 / 417.7, one of 4096 12.7 / 12.1 / 12.0 / 12.3, 32 of 1024-8192 113.7 / 112.1 / 112.0 / 110.4; FP8,
     // 64 of 1024-16384 193.3 / 193.3 / 193.7 / 195.6.
-    int attn_weight_base = 128, attn_weight_tile = 7, attn_piece_tokens = 384;
+    int attn_weight_base = 128, attn_weight_tile = 7, attn_piece_tokens = 384;  // FP8: kDearPieceTokens
     char err[512];
     StageSlot slots[kSlots];
     int next_slot = 0;
@@ -150,6 +150,7 @@ struct FullPlan {
     int n_row_tiles = 0, tile = 0;       // tile: kind of the grouped GEMMs
 };
 
+constexpr int kDearPieceTokens = 768;  // icarus_ctx::attn_piece_tokens of an FP8 cache
 constexpr int kAttnTargetWgs = 1280;  // decode attention: sizing bound for pieces and partial results
 constexpr int kAttnMaxChunk = 16384;  // tokens per attention chunk, at most (block ids of a chunk sit in LDS)
 constexpr int kAttnGMax = 80;         // largest stacked query group the MFMA attention covers
@@ -371,11 +372,12 @@ struct HostPlan {
 // Prefill (causal): seq_bt gives the block-table row of each plan sequence (a group of consecutive
 // chunk tokens; row t attends to kv_len - (rows-1-t) tokens).  A few groups over long contexts would
 // leave most of the chip idle: then each walk is cut into pieces, see below.
+// piece_tokens: cost of a decode piece in tokens; 0: the context's.
 // max_items: pieces the staging buffer and the workspace are sized for; max_partial: stacked queries
 // (per kv-head, over all pieces of cut walks) that the workspace's partial results hold.
 void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t *dmeta, int S, const int32_t *kv_lens,
                      const int32_t *seq_row0, const int32_t *seq_rows, const int32_t *seq_bt, bool causal, size_t max_items,
-                     size_t max_partial, HostPlan *hp) {
+                     size_t max_partial, HostPlan *hp, int piece_tokens = 0) {
     AttnPlan *pl = &hp->pl;
     *pl = AttnPlan{};
     hp->valid = false;
@@ -592,7 +594,8 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
     auto weight = [&](int s) {  // cost of one cached token
         return (int64_t)(ctx->attn_weight_base + ctx->attn_weight_tile * ((seq_rows[s] * g + 15) / 16));
     };
-    auto piece_cost = [&](int s) { return (int64_t)ctx->attn_piece_tokens * weight(s); };  // fixed cost of starting a piece
+    if (piece_tokens == 0) piece_tokens = ctx->attn_piece_tokens;
+    auto piece_cost = [&](int s) { return (int64_t)piece_tokens * weight(s); };  // fixed cost of starting a piece
     int64_t total = 0, tokens = 0;
     for (int s = 0; s < S; ++s)
         if (seq_rows[s] > 0) {
@@ -607,7 +610,7 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
     // Shares are filled in order up to a target cost T (tokens x weight + a fixed cost per piece); a share closes when
     // what is left of its target would not pay for another piece.  T is the smallest target with which max_wgs shares
     // take everything (bisection: the fill is monotone in T), so that no share, the last included, exceeds it.
-    const int min_piece = std::max(64, ctx->attn_piece_tokens);  // a shorter piece is not worth its fixed cost
+    const int min_piece = std::max(64, piece_tokens);  // a shorter piece is not worth its fixed cost
     auto fill = [&](int64_t T, bool emit) {
         int wg = 0;
         int64_t room = T;
@@ -1455,7 +1458,7 @@ icarus_status icarus_create(const icarus_layer_config *cfg, const icarus_base_we
     dm.d = c.d_model; dm.Hq = c.n_q_heads; dm.Hkv = c.n_kv_heads; dm.D = c.head_dim; dm.F = c.d_ffn; dm.Bk = c.block_size;
     dm.M = c.n_models; dm.r = c.lora_rank; dm.bf16 = c.dtype == ICARUS_BF16; dm.qk_norm = c.qk_norm != 0;
     dm.theta = c.rope_theta; dm.eps = (float)c.rms_eps; dm.lora_scale = (float)c.lora_scale;
-    if (c.kv_dtype == ICARUS_KV_FP8_E4M3) ctx->attn_piece_tokens = 768;
+    if (c.kv_dtype == ICARUS_KV_FP8_E4M3) ctx->attn_piece_tokens = kDearPieceTokens;
     dm.kv8 = c.kv_dtype == ICARUS_KV_FP8_E4M3; dm.k_scale = dm.kv8 ? (float)c.k_scale : 1.f; dm.v_scale = dm.kv8 ? (float)c.v_scale : 1.f;
     *out = ctx;
     return ICARUS_OK;
@@ -1794,14 +1797,26 @@ static icarus_status attn_shared_kv_impl(icarus_ctx *ctx, const void *q, const v
     if (use_static) L.meta = 0;  // the static scratch starts with the metadata
     const int32_t *dmeta = (const int32_t *)(ws + L.meta);
     HostPlan hp;
-    build_attn_plan(ctx, m, (size_t)4 * R, dmeta, S, kv_lens, row0.data(), rows.data(), nullptr, false, L.max_items, L.max_partial, &hp);
-    const size_t used = (size_t)4 * R + hp.ints;
-    if (use_static) {
-        // what THIS call needs, from its own plan: metadata, then the partial results of its pieces
+    // what THIS call needs of the static array, from its own plan: metadata, then the partial results of its pieces
+    size_t used, part_o, part_ml, need;
+    auto plan = [&](int piece_tokens) {
+        build_attn_plan(ctx, m, (size_t)4 * R, dmeta, S, kv_lens, row0.data(), rows.data(), nullptr, false, L.max_items, L.max_partial, &hp, piece_tokens);
         const size_t pj = hp.valid ? (size_t)hp.pl.n_items * c.n_kv_heads * hp.pl.g_max : 0;
-        L.part_o = align_up(used * 4, 256);
-        L.part_ml = align_up(L.part_o + pj * c.head_dim * 4, 256);
-        const size_t need = L.part_ml + pj * 2 * 4;
+        used = (size_t)4 * R + hp.ints;
+        part_o = align_up(used * 4, 256);
+        part_ml = align_up(part_o + pj * c.head_dim * 4, 256);
+        need = part_ml + pj * 2 * 4;
+    };
+    plan(0);
+    // Cheap pieces are more pieces, up to a tenth more of some hundred sequences: a call that they take past the array is planned with
+    // dear ones.  With a workspace too, for the same bits from both entry points.
+    if (need > kStaticScratchBytes && ctx->attn_piece_tokens < kDearPieceTokens) {
+        plan(kDearPieceTokens);
+        if (need > kStaticScratchBytes) plan(0);
+    }
+    if (use_static) {
+        L.part_o = part_o;
+        L.part_ml = part_ml;
         if (need > kStaticScratchBytes)
             return fail(ctx, ICARUS_ERR_CAPACITY, "this call needs %zu bytes of scratch, the static array holds %zu", need, kStaticScratchBytes);
         rc = stage_by_kernarg(ctx, m, used, (int32_t *)ws, st);

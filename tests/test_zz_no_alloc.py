@@ -67,3 +67,11 @@ def test_static_attention_refuses_what_does_not_fit():
         layer.attn_shared_kv_static(q, pool, torch.from_numpy(batch.block_tables).cuda(), [L] * S, row_seq, torch.empty_like(q))
     assert e.value.status_name == "CAPACITY", str(e.value)
     layer.close()
+
+
+def test_static_attention_takes_calls_whose_cheapest_plan_does_not_fit():
+    # 376 sequences, one of them with 20 rows (a partial result is 2 kv-heads x 80 stacked queries x 130 floats): 410 pieces at a cost of 384
+    # tokens each need 34.1 MB, 378 at a cost of 768 need 31.5 MB; the array holds 33.6 MB
+    from paper_2603_13281_amd import synth
+    lens = np.random.default_rng([376, 1]).integers(100, 900, 376)
+    _case(synth.LLAMA_SMALL.replace(n_models=20), lens.tolist(), [20] + [1] * 375, seed=34, limit=0)
