@@ -171,11 +171,14 @@ __device__ __forceinline__ void store_qkv_tile(const GemmArgs &g, const QkvStore
         } else {
             const int d = half * 64 + lane, slot_lo = (int)slot[0], slot_hi = (int)(slot[0] >> 32);
             auto slot_of = [&](int r) { return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane(slot_hi, r) << 32 | (uint32_t)__builtin_amdgcn_readlane(slot_lo, r)); };
+            // bit r: row r + 1 has the slot after row r's (entries of a call may share a block, with rows of others between theirs)
+            const int lo_after = __shfl_down(slot_lo, 1, 64), hi_after = __shfl_down(slot_hi, 1, 64);
+            const uint64_t in_line = __ballot(hi_after == slot_hi && lo_after == slot_lo + 1);
             if (i + 1 < (TM + 1) / 2) fetch(i + 1);
             for (int r = 0; r < n;) {
                 const int64_t first_slot = slot_of(r);
                 const size_t dst = (((size_t)(first_slot >> 4) * e.Hkv + head) * 2 + 1) * kPlane + (size_t)d * 16 + (size_t)(first_slot & 15);
-                if (!(first_slot & 7) && r + 8 <= n && slot_of(r + 7) == first_slot + 7) {  // a sequence's rows follow one another: the six between lie between
+                if (!(first_slot & 7) && r + 8 <= n && (in_line >> r & 0x7f) == 0x7f) {
                     float v[8];
 #pragma unroll
                     for (int x = 0; x < 8; ++x) v[x] = own[(r + x) * kEs + lane];

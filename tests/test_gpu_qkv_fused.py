@@ -59,3 +59,34 @@ def test_projection_that_appends(kind, rows, tile, fp8):
     assert not off[untouched].any()
     want = host(torch.cat(want))
     assert np.linalg.norm(got - want) <= 1e-2 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16", "fp8"])
+def test_entries_of_one_call_that_append_to_one_block(fp8):
+    """Token 8 and tokens 12-15 of one block from two entries of the call with another conversation's three rows between them: eight rows,
+    of which the first and the last alone are where eight tokens in line would be."""
+    print("case: fused append, shared block", "fp8", fp8, flush=True)
+    shape = SHAPES["plain"]
+    chunk, ctx = np.int32([1, 3, 4, 492]), np.int32([8, 5, 12, 0])
+    rows = int(chunk.sum())
+    kvd = shape.n_kv_heads * 128
+    assert binding.gemm_choice(rows, shape.d_model, [shape.n_q_heads * 128, kvd, kvd], taken=True) == (128, 128, False, 1)
+    base = synth.make_base(shape, seed=4, norm_ones=False)
+    batch = synth.make_batch(shape, list(ctx), [0] * len(ctx), seed=4, headroom=int(chunk.max()))
+    layer = make_layer(shape, base, None, batch.num_blocks, **(dict(kv_fp8=True, k_scale=0.02, v_scale=0.02) if fp8 else {}))
+    tables = batch.block_tables.copy()
+    tables[2] = tables[0]
+    bt = torch.from_numpy(tables).cuda()
+    pool = torch.zeros(layer.cfg.pool_shape(), dtype=layer.cfg.pool_dtype, device="cuda")
+    x = dev(synth.make_hidden(shape, rows, seed=4, tag=5), True)
+    fused, parts, row = pool.clone(), pool.clone(), 0
+    layer.prefill_kv(fused, bt, ctx, chunk, x)
+    for s, n in enumerate(chunk):
+        for t in range(0, int(n), 128):
+            m = min(128, int(n) - t)
+            layer.prefill_kv(parts, bt[s:s + 1].clone(), ctx[s:s + 1] + np.int32(t), np.int32([m]), x[row + t:row + t + m])
+        row += int(n)
+    torch.cuda.synchronize()
+    a, b = _bits(fused, layer), _bits(parts, layer)
+    # the products are summed in another order: some entries round to the neighbouring value, 2^-8 (FP8: 2^-3) of their own size apart
+    assert (np.abs(a - b) <= (0.13 if fp8 else 0.008) * np.abs(b) + 0.02 * 2.0 ** -8).all()
