@@ -287,9 +287,15 @@ hipError_t launch_row_generic(const Dims &dm, const void *x, int ldx, int K, con
 // wave each.  Beyond some width what every workgroup does again outweighs the launch, the sooner the more rows there are.  A layer step with
 // adapters on q and o, FFN 2.7 times as wide, us, row kernels / fused: 3 rows, 256 columns 46.5 / 36.0, 512 45.1 / 35.1, 1024 52.4 / 43.3, 2048
 // 88.7 / 73.0; 12 rows (norm alone) 46.4 / 42.9, 52.1 / 50.3, 72.8 / 75.5, 117 / 125.
+// Nine rows and more take the form of 16, whose norm costs it the registers of a second wave on its SIMD (256 instead of 240): beyond a wave to each of the
+// 1024 SIMDs, 4096 rows of weights, it loses.  12 rows of 256 / 512 columns, us, row kernel / fused: gate and up of 2 x 2048 49.4 / 47.6 and 52.1 / 50.9,
+// 2 x 2560 54.4 / 54.8 and 57.0 / 59.4, 2 x 4096 57.6 / 58.7 and 62.3 / 64.9, 2 x 8192 78.0 / 83.2 and 83.9 / 91.2, 2 x 32768 194 / 226 and 206 / 247; q, k and v
+// (gate and up fused in both) of 4096 52.5 / 49.5 and 55 / 52.7, 6144 60.5 / 61.4 and 63.5 / 66.2.  Up to eight rows the fused form is the faster one at all of these.
 constexpr int kFusedColumns = 2048, kFusedColumnsMoreRows = 512;
+constexpr int kFusedRowsAnyWidth = 8, kFusedWeightRows = 4 * 1024;
 bool skinny_takes_rows(const Dims &dm, const SkinnyGemm &g) {
     const bool shrink = g.A[0] || g.A[1];
+    if (g.R > kFusedRowsAnyWidth && g.n[0] + g.n[1] + g.n[2] > kFusedWeightRows) return false;
     if (dm.bf16 || g.K > (g.R <= 4 ? kFusedColumns : kFusedColumnsMoreRows) || !whole_pieces(dm, g.K) || !whole_pieces(dm, g.ldx) || !aligned16(g.X) || (g.wn && !aligned16(g.wn))) return false;
     for (int s = 0; s < 3; ++s)
         if (g.W[s] && !aligned16(g.W[s])) return false;

@@ -14,15 +14,9 @@ pytestmark = pytest.mark.gpu
 MASKS = {"none": 0, "all": 0b1111001, "gate": 0b0010000, "up": 0b0100000, "q-down": 0b1000001}  # bits in the order of synth.PROJ: q k v o gate up down
 
 
-@pytest.mark.parametrize("mask", MASKS)
-@pytest.mark.parametrize("rank", [1, 8, 9])
-@pytest.mark.parametrize("width", [256, 516, 2052, 250])
-@pytest.mark.parametrize("active", [[[0], [1]], [[], [], [1, 0]], [[0, 1], [1], []]], ids=["4 rows", "5 rows", "6 rows"])
-def test_few_rows(mask, rank, width, active):
-    print("case: few rows", mask, rank, width, len(active), flush=True)
-    shape = synth.TINY.replace(d_model=width, d_ffn=108, lora_rank=rank, lora_target_mask=MASKS[mask])
+def _step(shape, active):
     base, lora = synth.make_base(shape, seed=6, norm_ones=False), synth.make_lora(shape, seed=6)
-    lens = [9, 40, 17][:len(active)]
+    lens = [9, 40, 17, 5, 33, 16, 2, 64, 12][:len(active)]
     batch = synth.make_batch(shape, lens, [0] * len(lens), seed=6)
     pool = filled_batch(shape, batch, seed=6)
     seq, model = [], []
@@ -37,3 +31,21 @@ def test_few_rows(mask, rank, width, active):
                             np.asarray(model, np.int32), dev(x, False))
     torch.cuda.synchronize()
     assert_close(host(got), want, 1e-5, "x_out")
+
+
+@pytest.mark.parametrize("mask", MASKS)
+@pytest.mark.parametrize("rank", [1, 8, 9])
+@pytest.mark.parametrize("width", [256, 516, 2052, 250])
+@pytest.mark.parametrize("active", [[[0], [1]], [[], [], [1, 0]], [[0, 1], [1], []]], ids=["4 rows", "5 rows", "6 rows"])
+def test_few_rows(mask, rank, width, active):
+    print("case: few rows", mask, rank, width, len(active), flush=True)
+    _step(synth.TINY.replace(d_model=width, d_ffn=108, lora_rank=rank, lora_target_mask=MASKS[mask]), active)
+
+
+@pytest.mark.parametrize("heads,ffn", [(4, 2048), (4, 2052), (60, 108), (62, 108)], ids=["gate-up", "wider", "qkv", "qkv wider"])
+@pytest.mark.parametrize("rows", [8, 9, 16])
+def test_norm_of_nine_rows_and_more_before_wide_outputs(rows, heads, ffn):
+    """From nine rows on the norm goes into projections of up to 4096 weight rows (gate and up, or q, k and v without an adapter on q) alone."""
+    print("case: norm", rows, heads, ffn, flush=True)
+    shape = synth.TINY.replace(n_q_heads=heads, n_kv_heads=4 if heads == 4 else 2, d_ffn=ffn, lora_target_mask=MASKS["none"] if heads > 4 else MASKS["all"])
+    _step(shape, [[0]] * (rows - 8) + [[]] * (16 - rows))
