@@ -203,8 +203,8 @@ __device__ __forceinline__ void store_qkv_tile(const GemmArgs &g, const QkvStore
     }
 }
 
-// e: the epilogue's arguments where it is that of the QKV projection (QKV), else null
-template <int MT0, int MT1, int WAVES_N, int WAVES_M, bool GROUPED, bool QKV>
+// e: the epilogue's arguments where it is that of the QKV projection (QKV), else null.  TURN: workgroups may start at different places along K (gemm_turn).
+template <int MT0, int MT1, int WAVES_N, int WAVES_M, bool GROUPED, bool QKV, bool TURN>
 __device__ __forceinline__ void quad_tile(const GemmArgs &g, const QkvStore *e) {
     using Shape = QuadShape<MT0, MT1, WAVES_N, WAVES_M>;
     constexpr int NW = WAVES_M * WAVES_N, BM = Shape::BM, BN = Shape::BN, BK = Shape::BK;
@@ -290,11 +290,8 @@ __device__ __forceinline__ void quad_tile(const GemmArgs &g, const QkvStore *e) 
             wo[h][i] = (uint32_t)((w_row(h, p.hr) - n0) * (uint32_t)g.K + p.kc) * 2u;
         }
     }
-    // different starts along K (gemm_turn): not in 256 x 256 tiles, whose launches are bound by the matrix cores (they took 0.4 % for the three scalar
-    // instructions a slab)
-    constexpr bool kTurns = MT0 + MT1 < 8;
-    const int turn = kTurns ? gemm_turn(g, tile_n, n_base) : 0;
-    auto place_of = [&](int kt) { return kTurns ? gemm_slab(kt, turn, n_base) : kt; };
+    const int turn = TURN ? gemm_turn(g, tile_n, n_base) : 0;
+    auto place_of = [&](int kt) { return TURN ? gemm_slab(kt, turn, n_base) : kt; };
     // part: 0, 1 the halves of X; 2, 3 those of W
     auto part_lds = [&](int P, int S) { return P >= 2 ? kBOff + S * kWStage + (P & 1) * (kWStage / 2) : S * kXStage + P * (16 * WAVES_M * MT0 * kRow); };
     // load i of a part, of the slab of base weights at place kt along K (gemm_slab)
@@ -435,17 +432,22 @@ __device__ __forceinline__ void quad_tile(const GemmArgs &g, const QkvStore *e) 
     else store_wave_tile<16, MT0 + MT1, 2 * NT, BN>(g, acc, (float *)smem + w * 32 * (WN + 8), tile_n, kz, row0 + wm * WM, row_end, wn);
 }
 
-template <int MT0, int MT1, int WAVES_N, int WAVES_M, bool GROUPED>
+// 256 x 256 tiles turn in an instance of their own: launches bound by the matrix cores took 0.4 % for the three scalar instructions a slab, but those
+// of 193-256 rows wait for their weights.  us, same / different starts: LM head 4096 -> 128256, 193 rows 264 / 249, 256 rows 282 / 260; gate and
+// up 8192 -> 2 x 28672, 193 rows 210 / 207, 224 rows 225 / 212, 256 rows 227 / 217 (means of two GPUs, 2-8 % each).
+constexpr bool turns(int row_tiles) { return row_tiles < 8; }
+
+template <int MT0, int MT1, int WAVES_N, int WAVES_M, bool GROUPED, bool TURN>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, WAVES_M * WAVES_N == 8 ? 1 : 2) k_gemm_quad(GemmArgs g) {
-    quad_tile<MT0, MT1, WAVES_N, WAVES_M, GROUPED, false>(g, nullptr);
+    quad_tile<MT0, MT1, WAVES_N, WAVES_M, GROUPED, false, TURN>(g, nullptr);
 }
 
 template <int MT0, int MT1, int WAVES_N, int WAVES_M>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, WAVES_M * WAVES_N == 8 ? 1 : 2) k_gemm_quad_qkv(GemmArgs g, QkvStore e) {
-    quad_tile<MT0, MT1, WAVES_N, WAVES_M, false, true>(g, &e);
+    quad_tile<MT0, MT1, WAVES_N, WAVES_M, false, true, turns(MT0 + MT1)>(g, &e);
 }
 
-template <int MT0, int MT1, int WAVES_N, bool GROUPED, int WAVES_M = 2>
+template <int MT0, int MT1, int WAVES_N, bool GROUPED, int WAVES_M = 2, bool TURN = turns(MT0 + MT1)>
 hipError_t launch_quad(GemmArgs g, hipStream_t st, const QkvStore *e = nullptr) {
     using Shape = QuadShape<MT0, MT1, WAVES_N, WAVES_M>;
     constexpr int BM = Shape::BM, BN = Shape::BN;
@@ -474,11 +476,11 @@ hipError_t launch_quad(GemmArgs g, hipStream_t st, const QkvStore *e = nullptr) 
         }
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t rc = hipFuncSetAttribute((const void *)k_gemm_quad<MT0, MT1, WAVES_N, WAVES_M, GROUPED>, hipFuncAttributeMaxDynamicSharedMemorySize, Shape::kLds);
+        hipError_t rc = hipFuncSetAttribute((const void *)k_gemm_quad<MT0, MT1, WAVES_N, WAVES_M, GROUPED, TURN>, hipFuncAttributeMaxDynamicSharedMemorySize, Shape::kLds);
         if (rc != hipSuccess) return rc;
         attr_set = true;
     }
-    hipLaunchKernelGGL((k_gemm_quad<MT0, MT1, WAVES_N, WAVES_M, GROUPED>), grid, dim3(64 * WAVES_M * WAVES_N), Shape::kLds, st, g);
+    hipLaunchKernelGGL((k_gemm_quad<MT0, MT1, WAVES_N, WAVES_M, GROUPED, TURN>), grid, dim3(64 * WAVES_M * WAVES_N), Shape::kLds, st, g);
     return hipGetLastError();
 }
 
@@ -507,7 +509,9 @@ hipError_t launch_any(const GemmArgs &g, const QkvStore *e, hipStream_t st) {
         if (g.R <= 128 * tiles) return launch_quad<2, 2, 2, false>(g, st, e);
         return g.R <= 160 * tiles ? launch_quad<3, 2, 2, false>(g, st, e) : launch_quad<3, 3, 2, false>(g, st, e);
     }
-    case TILE_256x256: return g.row_tiles ? launch_quad<4, 4, 4, true>(g, st) : launch_quad<4, 4, 4, false>(g, st, e);
+    case TILE_256x256:
+        if (g.row_tiles) return launch_quad<4, 4, 4, true>(g, st);
+        return g.stagger && !e ? launch_quad<4, 4, 4, false, 2, true>(g, st) : launch_quad<4, 4, 4, false>(g, st, e);
     // 753 rows, 4096 -> 4096, in k_gemm_mfma / here with four waves / with eight 45.7 / 45.5 / 43.1 us
     case TILE_128: return launch_quad<1, 1, 2, false, 4>(g, st, e);
     case TILE_192x256: return launch_quad<3, 3, 4, false>(g, st, e);

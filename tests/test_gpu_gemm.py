@@ -140,6 +140,27 @@ def test_narrow_tiles_by_eight_waves_and_by_four(rows, cols):
     _check(binding.gemm(x, [w], (192, 128, False), t=t, b=b), want, (k + models * rank + 16) * 2.0 ** -23 * size + 1e-30, (rows, cols))
 
 
+@pytest.mark.parametrize("tile", TILES, ids=lambda t: f"{t[0]}x{t[1]}" + ("r" if t[2] else ""))
+@pytest.mark.parametrize("rows", [100, 200, 384, 385])
+@pytest.mark.parametrize("models", [0, 8])
+def test_column_tiles_that_start_at_different_places_along_k(tile, rows, models):
+    # K a multiple of 2048, up to 384 rows: column tile n starts at slab n modulo their number -- 34 column tiles (fused: 67) on 32 slabs, on three
+    # slices of 11 and 10, and on twelve of three slabs, of which with adapters one ends in and one is nothing but adapter columns and without one is empty
+    print("case: turn", tile, rows, models, flush=True)
+    k, n, rank = 2048, 33 * tile[1] + 8, 32
+    x, w = _draw((rows, k), 1), [_draw((n, k), 10 + i, 0.05) for i in range(2)]
+    t, b = _adapters(rows, n, models, rank, 2, 20) if models else (None, None)
+    half = (lambda s: t[:, s * models * rank:(s + 1) * models * rank].contiguous()) if models else (lambda s: None)
+    (g, gs), (u, us) = (_product(x, w[s], half(s), b[s] if models else None) for s in range(2))
+    eps = (k + models * rank + 16) * 2.0 ** -23
+    for slices in (1, 3, 12):
+        got = binding.gemm(x, w[:1], tile, slices, t=half(0), b=b[:1] if models else None)
+        _check(got, g, eps * gs + 1e-30, (tile, rows, models, slices))
+    silu = g * torch.sigmoid(g)
+    bound = 1.1 * eps * gs * u.abs() + eps * us * silu.abs() + (2.0 ** -8 + (2 + g.abs()) * 2.0 ** -21) * (silu * u).abs() + 2.0 ** -100
+    _check(binding.gemm(x, w, tile, fused=True, t=t, b=b), silu * u, bound, (tile, rows, models, "fused"))
+
+
 @pytest.mark.parametrize("rows", [160, 161, 192, 193, 320, 321, 384, 480, 481])
 @pytest.mark.parametrize("k", [64 * 9, 64 * 257])
 def test_full_192_row_tiles_with_many_adapter_columns(rows, k):
