@@ -128,16 +128,23 @@ def test_lower_tiles_where_as_many_hold_the_rows(rows):
     _check(binding.gemm(x, w, (192, 128, False), fused=True), silu * u, bound, (rows, "fused"))
 
 
-@pytest.mark.parametrize("rows", [384, 576])
-@pytest.mark.parametrize("cols", [85, 86])
-def test_narrow_tiles_by_eight_waves_and_by_four(rows, cols):
-    # three row tiles of 128 or 192: up to 256 workgroups have a CU to themselves and eight waves, more share one with four each
-    print("case: waves of a narrow tile", rows, cols, flush=True)
-    k, n, models, rank = 64 * 9, 128 * cols - 56, 3, 16
-    x, w = _draw((rows, k), 1), _draw((n, k), 10, 0.05)
-    t, b = _adapters(rows, n, models, rank, 1, 20)
-    want, size = _product(x, w, t, b[0])
-    _check(binding.gemm(x, [w], (192, 128, False), t=t, b=b), want, (k + models * rank + 16) * 2.0 ** -23 * size + 1e-30, (rows, cols))
+@pytest.mark.parametrize("fused", [False, True], ids=["plain", "fused"])
+@pytest.mark.parametrize("rows,cols", [(250, 128), (250, 129), (576, 85), (576, 86)])
+def test_narrow_tiles_by_eight_waves_and_by_four(rows, cols, fused):
+    # 192 x 128 tiles, two of 128 rows or three of 192: up to 256 workgroups have a CU to themselves and eight waves, more share one with four each
+    print("case: waves of a narrow tile", rows, cols, fused, flush=True)
+    k, n, models, rank = 64 * 9, (64 if fused else 128) * cols - 24, 3, 16
+    x, w = _draw((rows, k), 1), [_draw((n, k), 10 + i, 0.05) for i in range(1 + fused)]
+    t, b = _adapters(rows, n, models, rank, 1 + fused, 20)
+    eps = (k + models * rank + 16) * 2.0 ** -23
+    got = binding.gemm(x, w, (192, 128, False), fused=fused, t=t, b=b)
+    parts = [_product(x, w[s], t[:, s * models * rank:(s + 1) * models * rank], b[s]) for s in range(1 + fused)]
+    if not fused:
+        return _check(got, parts[0][0], eps * parts[0][1] + 1e-30, (rows, cols))
+    (g, gs), (u, us) = parts
+    silu = g * torch.sigmoid(g)
+    bound = 1.1 * eps * gs * u.abs() + eps * us * silu.abs() + (2.0 ** -8 + (2 + g.abs()) * 2.0 ** -21) * (silu * u).abs() + 2.0 ** -100
+    _check(got, silu * u, bound, (rows, cols, "fused"))
 
 
 @pytest.mark.parametrize("tile", TILES, ids=lambda t: f"{t[0]}x{t[1]}" + ("r" if t[2] else ""))

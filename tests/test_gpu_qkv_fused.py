@@ -9,10 +9,12 @@ from paper_2603_13281_amd import binding, synth
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = {"plain": synth.LLAMA8B.replace(d_ffn=512), "norms": synth.QWEN32B.replace(d_ffn=512)}
-# rows -> the projection's tile; chunks whose rows begin and end anywhere in a block of 16 tokens, in a tile and in a group of 32 rows
+SHAPES = {"plain": synth.LLAMA8B.replace(d_ffn=512), "norms": synth.QWEN32B.replace(d_ffn=512),
+          "ungrouped": synth.LLAMA8B.replace(d_model=512, n_q_heads=16, n_kv_heads=16, d_ffn=512)}
+# rows -> the projection's tile; chunks whose rows begin and end anywhere in a block of 16 tokens, in a tile and in a group of 32 rows.  192 x 128: full
+# tiles of up to 256 workgroups (eight waves) and of more (four), and tiles of 160 rows (four)
 CASES = [("plain", 500, (128, 128)), ("norms", 300, (128, 128)), ("plain", 700, (192, 128)), ("plain", 780, (192, 128)), ("plain", 1003, (160, 256)), ("plain", 1701, (192, 256)), ("plain", 2011, (256, 256)),
-         ("norms", 400, (192, 128)), ("norms", 601, (160, 256)), ("norms", 1001, (192, 256)), ("norms", 1203, (256, 256))]
+         ("norms", 400, (192, 128)), ("norms", 601, (160, 256)), ("norms", 1001, (192, 256)), ("norms", 1203, (256, 256)), ("ungrouped", 2700, (192, 128))]
 
 
 def _bits(pool, layer):
