@@ -434,7 +434,9 @@ __device__ __forceinline__ void quad_tile(const GemmArgs &g, const QkvStore *e) 
 
 // 256 x 256 tiles turn in an instance of their own: launches bound by the matrix cores took 0.4 % for the three scalar instructions a slab, but those
 // of 193-256 rows wait for their weights.  us, same / different starts: LM head 4096 -> 128256, 193 rows 264 / 249, 256 rows 282 / 260; gate and
-// up 8192 -> 2 x 28672, 193 rows 210 / 207, 224 rows 225 / 212, 256 rows 227 / 217 (means of two GPUs, 2-8 % each).
+// up 8192 -> 2 x 28672, 193 rows 210 / 207, 224 rows 225 / 212, 256 rows 227 / 217 (means of two GPUs, 2-8 % each);
+// a token step of one layer and that head, 194 rows 536 / 507, 230 rows 566 / 536.
+// Not in slices of K: 8192 -> 10240 in 6, 220 rows 45.6 / 57.7, 256 rows 47.5 / 57.
 constexpr bool turns(int row_tiles) { return row_tiles < 8; }
 
 template <int MT0, int MT1, int WAVES_N, int WAVES_M, bool GROUPED, bool TURN>
@@ -511,7 +513,7 @@ hipError_t launch_any(const GemmArgs &g, const QkvStore *e, hipStream_t st) {
     }
     case TILE_256x256:
         if (g.row_tiles) return launch_quad<4, 4, 4, true>(g, st);
-        return g.stagger && !e ? launch_quad<4, 4, 4, false, 2, true>(g, st) : launch_quad<4, 4, 4, false>(g, st, e);
+        return g.stagger && g.splits == 1 && !e ? launch_quad<4, 4, 4, false, 2, true>(g, st) : launch_quad<4, 4, 4, false>(g, st, e);
     // 753 rows, 4096 -> 4096, in k_gemm_mfma / here with four waves / with eight 45.7 / 45.5 / 43.1 us
     case TILE_128: return launch_quad<1, 1, 2, false, 4>(g, st, e);
     case TILE_192x256: return launch_quad<3, 3, 4, false>(g, st, e);
