@@ -455,13 +455,18 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
             cuts.insert(cuts.end(), rest.begin(), rest.end());
         };
         // Model of a launch, in tokens walked by one workgroup: the kernel gives a CU one workgroup, so attn_wgs / Hkv
-        // pieces run at a time, each next one on the first CU that is free; a piece costs its tokens and
+        // pieces run at a time.  Workgroups are dealt to the XCDs and, within one, to its four shader engines of 8 CUs in turn, whoever is
+        // free: piece i waits for the first free CU of its own engine, of which the kv-heads leave cus / 8 in turn.  (Modelled as going to any free CU, a
+        // few short remainders behind a full round of equal parts seemed to cost nothing; they ran after it: attention + merge, us, equal parts / those:
+        // 632 rows over 9000 tokens 120 / 134, 300 over 14000 93 / 106, 5 x 317 over 9000 with 4 kv-heads 153 / 185.  The ratio of two plans of one call is
+        // 4 % off on average over 37 calls, that of a common pool was 8 %.)  A piece costs its tokens and
         // kPieceTokens on top (prologue, Q loads, output), and if any group is cut, the partial results cost a merge
         // launch and their way through memory.  With every CU at work a token takes up to a third longer, the more query
         // tiles a group fills: *busy is what the CUs' mean load comes to then.  Fitted to k_attn_prefill_short; k_attn_prefill takes up to
         // 8 % less per token and somewhat more per piece.
         const int cus = std::max(1, ctx->attn_wgs / Hkv);
-        std::vector<int64_t> free_at;  // min-heap of finishing times
+        const int engines = std::max(1, cus / 8), per_engine = cus / engines;
+        std::vector<int64_t> free_at;  // per engine a min-heap of finishing times
         auto cost = [&](int64_t at_most, int64_t *busy) {  // INT64_MAX: at_most at least, however the pieces fall, and so for smaller ones
             constexpr int64_t kPieceTokens = 160, kMergeTokens = 160, kSlotTokens = 8;
             int64_t plain = 0, filled = 0, slots = 0;
@@ -475,16 +480,17 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
             if (plain / cus + merge >= at_most) return INT64_MAX;
             free_at.assign((size_t)cus, 0);
             int64_t end = 0;
-            for (const Cut &c : cuts) {
-                const int64_t t = free_at[0] + c.len + kPieceTokens;
+            for (size_t i = 0; i < cuts.size(); ++i) {
+                int64_t *h = free_at.data() + i % engines * per_engine;
+                const int64_t t = h[0] + cuts[i].len + kPieceTokens;
                 int at = 0;  // the heap's first goes down to its new place
-                for (int k = 1; k < cus; k = 2 * at + 1) {
-                    k += k + 1 < cus && free_at[k + 1] < free_at[k];
-                    if (free_at[k] >= t) break;
-                    free_at[at] = free_at[k];
+                for (int k = 1; k < per_engine; k = 2 * at + 1) {
+                    k += k + 1 < per_engine && h[k + 1] < h[k];
+                    if (h[k] >= t) break;
+                    h[at] = h[k];
                     at = k;
                 }
-                free_at[at] = t;
+                h[at] = t;
                 end = std::max(end, t);
             }
             return end + merge;
@@ -504,6 +510,7 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
             if (cuts.size() < (size_t)8 * cus) {
                 int64_t busy = 0, whole = cost(INT64_MAX, &busy), best = fits() ? whole : INT64_MAX, work = 0;
                 if (best == whole) best = whole * 9 / 10;  // see below
+                size_t best_pieces = cuts.size();
                 for (int s : order) work += kv_lens[s];
                 // one piece per CU, or up to five; lengths in between because a sequence's parts are of one length
                 for (int pct : {200, 150, 125, 112, 105, 90, 78, 68, 60, 52, 45, 38, 32, 26, 20}) {
@@ -516,8 +523,12 @@ void build_attn_plan(const icarus_ctx *ctx, int32_t *m, size_t at, const int32_t
                         // A modelled gain of less than a tenth is none: 520 rows over 64-600 tokens, 32 heads on 8 kv-heads, were
                         // 2 % of a small layer slower cut, two chunks of 300 rows over 500 tokens 3 %; 2000 rows over 64 tokens, which
                         // keep every CU busy, 3 % for a modelled fifth.
-                        const int64_t c = cost(best, &busy);
-                        if (c < best && (best_most != max_piece || busy < best)) { best = c; best_most = len; best_tails = tails; }
+                        // Remainders that open a second round of CUs have to gain a twentieth over parts that need only one: where the model gave
+                        // them 3-4 % (1273 rows over 5000 tokens, 4 kv-heads; 2 x 300 over 3000-4000) they lost 5-8.
+                        const int64_t modelled = cost(best, &busy);
+                        const bool second = tails && best_pieces <= (size_t)cus && cuts.size() > (size_t)cus;
+                        const int64_t c = second && modelled != INT64_MAX ? modelled + modelled / 20 : modelled;
+                        if (c < best && (best_most != max_piece || busy < best)) { best = modelled; best_most = len; best_tails = tails; best_pieces = cuts.size(); }
                         dearer = dearer || c == INT64_MAX;
                     }
                     if (dearer || most == 2 * round) break;

@@ -89,3 +89,35 @@ def test_remainders_of_walks_follow_their_equal_parts(ctx, chunk):
     assert all(pieces[a][3] >= pieces[b][3] for a, b in zip(tail, tail[1:]))  # longest first
     assert len({p[3] for i, p in enumerate(pieces) if p[0] in last and i not in tail}) == 1
     layer.close()
+
+
+@pytest.mark.parametrize("n_kv,ctx,chunk", [(8, [9000], [632]), (8, [14000], [300]), (8, [24000], [300]), (4, [9000] * 5, [317] * 5), (4, [24000], [326])],
+                         ids=lambda v: "+".join(map(str, v)) if isinstance(v, list) else str(v))
+def test_no_short_remainders_behind_a_full_round_of_equal_parts(n_kv, ctx, chunk):
+    """Pieces are dealt to the engines of 8 CUs in turn, whoever is free: what is dealt to an engine after eight of its CUs have a long piece waits for
+    one of them.  The call's longest engine is no longer than with equal parts of the shortest length that still makes whole rounds of CUs."""
+    layer = _layer(4, n_kv)
+    _check(layer, 4, ctx, chunk)
+    pieces, engines = layer.prefill_plan(ctx, chunk), 32 // n_kv
+    cus = 8 * engines
+    assert any((pieces[:, 4] >= 0))
+
+    def longest(lens):
+        free, end = np.zeros((engines, 8), np.int64), 0
+        for i, n in enumerate(lens):
+            h = free[i % engines]
+            k = int(h.argmin())
+            h[k] += n + 160
+            end = max(end, int(h[k]))
+        return end
+
+    groups = sum(-(-n // 64) for n in chunk)
+    best = None
+    for rounds in (1, 2, 3, 4):
+        parts = rounds * cus // groups
+        if parts:
+            top = max(c + n for c, n in zip(ctx, chunk))
+            n = -(-top // parts // 128) * 128 + 128
+            best = min(best or 1 << 60, rounds * (n + 160))
+    assert longest(pieces[:, 3]) <= best
+    layer.close()
