@@ -327,9 +327,10 @@ hipError_t launch_cfg(GemmArgs g, hipStream_t st) {
 // with every CU busy, for each of the per_cu workgroups that share one.  The figures are a fit to 5000 timings on
 // this GPU (80-4337 rows x the projections of a Llama-3-8B- and a Qwen3-32B-shaped layer x every tile x 1-12 slices; the
 // fit is 7-11 % off on average), see gemm_plan and gemm_row_tile.  They are of the kernels before k_gemm_quad, and
-// count one 192 x 128 workgroup to a CU where two now fit.  What they are for, the order of the choices, holds (144, 316, 512 and 753 rows of
-// the four projections, every tile and slice count timed anew: the choice is the fastest of these tiles or within 5 %); as times
-// they are up to 16 % high.
+// count one 192 x 128 workgroup to a CU where two now fit.  What they are for, the order of the choices, holds for the present ones (144-1100 rows,
+// 12 counts, of the four projections of both layers, every tile and slice count timed anew with weights from HBM: the choice is 1.6 % from the fastest on
+// average and within 5 % in 87 of 96; 250 rows, 5120 -> 10240 55.9 us where three slices of 160 x 256 take 39.6 + their sums, 512 rows, 14336 -> 4096 74.5
+// and 8 of 256 x 256 55.6 + sums); as times they are up to 16 % high.
 struct TileShape { int bm, bn, per_cu; float first_us, slab_us; };
 constexpr TileShape kTileShape[TILE_KINDS] = {
     {0, 0, 0, 0.f, 0.f},
@@ -355,7 +356,8 @@ int n_tiles_for(const GemmArgs &g, int bm, int bn) {
 // time (starts a golden section apart were as good up to 64 rows but cost 316 rows, 14336 -> 4096 25 %).  us, same / different starts, weights
 // from HBM in 3-13 places: 4096 -> 2 x 14336, 9-64 rows 43.6-60 / 46.8-51, mean 53.4 / 47, 128 rows 58.6 / 54.5, 144 rows 61.2 / 58.5, 316 rows 82.5 / 78; LM head
 // 4096 -> 128256, 9 rows 196 / 177, 64 rows 221 / 198; 6144 -> 2 x 8192, 9 rows 56 / 51; 14336 -> 4096 and 4096 -> 4096 in slices equal; 576 and 753 rows equal (bound by
-// the matrix cores).  Rows 10 KB apart (5120 -> 2 x 25600) 107.6 / 109.7, 120.4 / 121.5.
+// the matrix cores).  Rows 10 KB apart (5120 -> 2 x 25600) 107.6 / 109.7, 120.4 / 121.5.  Groups of rows with weights of their own, steps of 9-360 rows: 4096 columns within
+// the runs' 3 %, 2048 columns, 330 rows 279 / 268.
 bool gemm_staggered(const GemmArgs &g) { return g.K % 2048 == 0 && g.R <= 384; }
 
 bool is_quad(int kind) { return kind >= TILE_192x128; }

@@ -502,7 +502,10 @@ hipError_t launch_any(const GemmArgs &g, const QkvStore *e, hipStream_t st) {
         const int tiles = (g.R + 191) / 192;
         // Eight waves in place of four where a workgroup has its CU to itself: two waves a SIMD, each half as high, hide each other's
         // reads and barriers for a third more of those reads.  us: QKV of 753 rows (192 workgroups) 58.4 / 54.6, of 512 rows x 10240 (240) 68.7 / 67.3,
-        // 360 rows, 4096 -> 4096 in 4 slices 24.6 / 22.7, 14336 -> 4096 53.7 / 52.7.
+        // 360 rows, 4096 -> 4096 in 4 slices 24.6 / 22.7, 14336 -> 4096 53.7 / 52.7.  In layers of four widths (2048-5120), weights from HBM, 135-1100 rows,
+        // prefill and decode with 8 adapters: 91 launches of 192-row tiles 3835 / 3741 us together, single ones up to 4 % either way (in a loop of one
+        // launch some are: 384 rows, 8192 -> 5120 in 3 slices 39.2 / 40.2).  129-160 rows a tile keep four waves of 160; eight of 192 took 1-3 %
+        // longer: prefill of 140 rows 180 / 184.5, 158 rows 183 / 190.5, 318 rows 246 / 249.5, decode of 261 and 288 rows 269 / 272.5, 272 / 275.
         const int cols = gemm_col_tiles(g, 128);
         if (tiles * cols * g.splits <= 256) {
             if (g.R <= 128 * tiles) return launch_quad<1, 1, 2, false, 4>(g, st, e);
@@ -514,7 +517,7 @@ hipError_t launch_any(const GemmArgs &g, const QkvStore *e, hipStream_t st) {
     case TILE_256x256:
         if (g.row_tiles) return launch_quad<4, 4, 4, true>(g, st);
         return g.stagger && g.splits == 1 && !e ? launch_quad<4, 4, 4, false, 2, true>(g, st) : launch_quad<4, 4, 4, false>(g, st, e);
-    // 753 rows, 4096 -> 4096, in k_gemm_mfma / here with four waves / with eight 45.7 / 45.5 / 43.1 us
+    // 753 rows, 4096 -> 4096, in k_gemm_mfma / here with four waves / with eight 45.7 / 45.5 / 43.1 us; the 286 launches of the layers above 7574 / 7589 / 7349
     case TILE_128: return launch_quad<1, 1, 2, false, 4>(g, st, e);
     case TILE_192x256: return launch_quad<3, 3, 4, false>(g, st, e);
     case TILE_160x256: return launch_quad<3, 2, 4, false>(g, st, e);
